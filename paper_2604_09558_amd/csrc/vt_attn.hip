@@ -24,6 +24,10 @@
 //                   block inside its registers (v_perm_b32) and feeds it as the A operand;
 //                   the contraction index is permuted identically for P, which the softmax
 //                   already holds in exactly that layout.
+// Head dims 128 and 64 (a template argument): a tile of 64-wide heads is half as many bytes, eight
+// lanes read a K row and a lane's piece of a V row is 8 bytes.  Serving 16 sequences of 2368 paged
+// keys of 64-wide heads (77.7 MB): 18.0 us = 4.3 TB/s, against 10.8 ms when only 128 was planned
+// and every element went through the generic evaluator below.
 // The workgroup that finishes last for a (b, g) merges the splits' partial results (a ticket
 // counter per (b, g) in the workspace; no second launch, no spinning).
 #include <hip/hip_runtime.h>
@@ -51,7 +55,6 @@ VT_PROF_DECLARE(attn)
 
 namespace {
 
-constexpr int kD = 128;          // head dim
 constexpr int kTile = 32;        // context rows per wave step
 constexpr int kMaxAttnPieces = 4;
 constexpr int kMaxSegs = 8;
@@ -100,7 +103,7 @@ struct AttnParams {
   int32_t n_seg;
   const char* q_ptr;
   int64_t q_sb, q_sh;    // bytes
-  int32_t B, Hkv, G, S, n_splits, rows_per_split;
+  int32_t B, Hkv, G, S, D, n_splits, rows_per_split;
   float scale_log2;      // softmax scale * log2(e)
   uint32_t* tickets;     // [B, Hkv], zero between launches
   float* ws_ml;          // [B, Hkv, n_splits, G, 2]
@@ -148,6 +151,18 @@ __device__ __forceinline__ Regs16 load16(const char* base, uint32_t off) {
   Regs16 r;
   r.w[0] = t[0]; r.w[1] = t[1]; r.w[2] = t[2]; r.w[3] = t[3];
   return r;
+}
+
+// A lane's piece of one V row: NE consecutive columns.
+template <int NE>
+struct VReg {
+  uint32_t w[NE / 2];
+};
+template <int NE>
+__device__ __forceinline__ VReg<NE> load_v(const char* base, uint32_t off) {
+  typedef unsigned int uvec __attribute__((ext_vector_type(NE / 2)));
+  const uvec t = __builtin_nontemporal_load(reinterpret_cast<const uvec*>(base + off));
+  return __builtin_bit_cast(VReg<NE>, t);
 }
 
 // The 32-row tiles of a split [t_begin, t_end) are taken one after the other.  A tile lies in one
@@ -270,12 +285,21 @@ __device__ __forceinline__ void walk_advance(const AttnParams& P, TileWalk& w, i
   if (w.seg < P.n_seg) walk_fetch(P, w, b, g);
 }
 
-template <typename T, int WAVES, int OCC>
+// D = head dim (64 or 128).
+template <typename T, int D, int WAVES, int OCC>
 __global__ void __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(OCC, OCC)))
 k_decode_attn(const AttnParams P) {
   typedef Mfma<T> M;
   typedef typename M::vec opvec;
-  __shared__ uint4 lds[WAVES][kTile * 16];   // per wave: 32 rows x 16 chunks of 16 bytes, swizzled
+  constexpr int kD = D;
+  constexpr int LPR = kD / 8;                // lanes (and 16-byte chunks) per K row
+  constexpr int KL = kTile * LPR / 64;       // K loads per tile
+  constexpr int NE = kD / 16;                // columns of V per lane: 16 or 8 bytes of a row
+  // 64-wide heads: the probabilities enter the product as a sum of two 16-bit numbers (their fp32
+  // value to 2^-16 or better).  The matrix pipes idle here either way: the second product is free
+  // and the result carries one rounding, its own.
+  constexpr bool kSplitP = kD == 64;
+  __shared__ uint4 lds[WAVES][kTile * LPR];  // per wave: 32 rows of LPR chunks of 16 bytes, swizzled
   __shared__ float red_ml[WAVES * 16 * 2];   // [WAVES][16][2]
   __shared__ uint32_t ticket_sh;
 
@@ -294,12 +318,12 @@ k_decode_attn(const AttnParams P) {
   const int t_end = min(P.S, t_begin + P.rows_per_split);
   const float c = P.scale_log2;
 
-  // Q^T operand: lane (head l16, k-group lg) holds 8 consecutive d for each of the 4 k-steps
-  opvec qreg[4];
+  // Q^T operand: lane (head l16, k-group lg) holds 8 consecutive d for each of the kD / 32 k-steps
+  opvec qreg[kD / 32];
   {
     const char* qp = P.q_ptr + b * P.q_sb + (int64_t)(g * P.G + l16) * P.q_sh;
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) {
+    for (int kk = 0; kk < kD / 32; ++kk) {
       uint4 raw = make_uint4(0, 0, 0, 0);
       if (l16 < P.G) raw = *reinterpret_cast<const uint4*>(qp + (kk * 32 + lg * 8) * 2);
       qreg[kk] = __builtin_bit_cast(opvec, raw);
@@ -308,31 +332,34 @@ k_decode_attn(const AttnParams P) {
 
   float m_ref = -1.0e30f;   // reference maximum (log2 domain) of head l16, identical in the 4 lane groups
   float l_run = 0.0f;       // this lane's share of the denominator, relative to m_ref
-  f32x4 acc[8];
+  f32x4 acc[NE];
 #pragma unroll
-  for (int e = 0; e < 8; ++e) acc[e] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int e = 0; e < NE; ++e) acc[e] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-  // Loads of one tile.  K: instruction j covers rows 4j..4j+3 (16 lanes per 256-byte row);
-  // V: instruction j is contraction slot j of the lane group, row (j>>2)*16 + lg*4 + (j&3).
+  // Loads of one tile.  K: 16 bytes per lane, LPR lanes per row, instruction j covers RPL rows
+  // from RPL * j; V: 2 * NE bytes per lane, 16 lanes per row, instruction j is contraction slot j of the lane group, row (j>>2)*16 + lg*4 + (j&3).
   // In a full tile the address is a wave-uniform base per instruction plus ONE per-lane
   // offset; a partial tile (last of a segment) clamps its rows onto the last valid one.
-  Regs16 kst[8], vst[8];
+  constexpr int RPL = 64 / LPR;
+  const int k_r = lane / LPR, k_c = lane % LPR;       // this lane's row of an instruction and chunk of the row
+  Regs16 kst[KL];
+  VReg<NE> vst[8];
   auto issue_k = [&](const TileWalk& tp) {
     const uint32_t st = tp.k_st;
     const char* kb = tp.k + (int64_t)(tp.r0 - tp.t_lo) * st;
     if (tp.r0 + kTile <= tp.end && tp.seg2 < 0) {
-      const uint32_t off = lg * st + l16 * 16;
+      const uint32_t off = k_r * st + k_c * 16;
 #pragma unroll
-      for (int j = 0; j < 8; ++j) kst[j] = load16(kb + (size_t)(4 * j) * st, off);
+      for (int j = 0; j < KL; ++j) kst[j] = load16(kb + (size_t)(RPL * j) * st, off);
     } else {
       // a short tile (rows past its end repeat the last valid one) or one that continues in the
       // next segment: per-lane row addresses
       const int span = tp.end - 1 - tp.r0, ncut = tp.cut - tp.r0;
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int rr = min(4 * j + lg, span);
+      for (int j = 0; j < KL; ++j) {
+        const int rr = min(RPL * j + k_r, span);
         const bool in2 = rr >= ncut;
-        kst[j] = load16(in2 ? tp.k2 : kb, (in2 ? (uint32_t)(rr - ncut) * tp.k2_st : (uint32_t)rr * st) + l16 * 16);
+        kst[j] = load16(in2 ? tp.k2 : kb, (in2 ? (uint32_t)(rr - ncut) * tp.k2_st : (uint32_t)rr * st) + k_c * 16);
       }
     }
   };
@@ -340,16 +367,16 @@ k_decode_attn(const AttnParams P) {
     const uint32_t st = tp.v_st;
     const char* vb = tp.v + (int64_t)(tp.r0 - tp.t_lo) * st;
     if (tp.r0 + kTile <= tp.end && tp.seg2 < 0) {
-      const uint32_t off = lg * 4 * st + l16 * 16;
+      const uint32_t off = lg * 4 * st + l16 * (2 * NE);
 #pragma unroll
-      for (int j = 0; j < 8; ++j) vst[j] = load16(vb + (size_t)((j >> 2) * 16 + (j & 3)) * st, off);
+      for (int j = 0; j < 8; ++j) vst[j] = load_v<NE>(vb + (size_t)((j >> 2) * 16 + (j & 3)) * st, off);
     } else {
       const int span = tp.end - 1 - tp.r0, ncut = tp.cut - tp.r0;
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
         const int rr = min((j >> 2) * 16 + lg * 4 + (j & 3), span);
         const bool in2 = rr >= ncut;
-        vst[j] = load16(in2 ? tp.v2 : vb, (in2 ? (uint32_t)(rr - ncut) * tp.v2_st : (uint32_t)rr * st) + l16 * 16);
+        vst[j] = load_v<NE>(in2 ? tp.v2 : vb, (in2 ? (uint32_t)(rr - ncut) * tp.v2_st : (uint32_t)rr * st) + l16 * (2 * NE));
       }
     }
   };
@@ -374,24 +401,26 @@ k_decode_attn(const AttnParams P) {
     const bool partial = r0 + kTile > r_end;
     walk_advance(P, cur, WAVES, b, g, t_end);              // cur is now the next tile of this wave
     const bool more = cur.seg < P.n_seg;
-    // ---- stage K through LDS (swizzle: chunk c of row r sits at unit c ^ (r & 15))
+    // ---- stage K through LDS (swizzle: chunk c of row r sits at unit c ^ (r & 15), or, with two
+    // rows in the 256 bytes that 16 lanes read at once, at unit c ^ ((r >> 1) & 7))
+    auto key = [](int r) { return LPR == 16 ? r & 15 : (r >> 1) & 7; };
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      int r = 4 * j + lg;
-      my_lds[r * 16 + (l16 ^ (r & 15))] = make_uint4(kst[j].w[0], kst[j].w[1], kst[j].w[2], kst[j].w[3]);
+    for (int j = 0; j < KL; ++j) {
+      int r = RPL * j + k_r;
+      my_lds[r * LPR + (k_c ^ key(r))] = make_uint4(kst[j].w[0], kst[j].w[1], kst[j].w[2], kst[j].w[3]);
     }
     VT_PROF_ONCE(1);
     if (more) issue_k(cur);              // next tile's K is in flight during this tile's math
 
-    // ---- S^T = K . Q^T : two 16-row blocks, 4 k-steps each
+    // ---- S^T = K . Q^T : two 16-row blocks, kD / 32 k-steps each
     f32x4 s[2];
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
       s[u] = f32x4{0.f, 0.f, 0.f, 0.f};
       int r = u * 16 + l16;
 #pragma unroll
-      for (int kk = 0; kk < 4; ++kk) {
-        uint4 raw = my_lds[r * 16 + ((kk * 4 + lg) ^ l16)];
+      for (int kk = 0; kk < kD / 32; ++kk) {
+        uint4 raw = my_lds[r * LPR + ((kk * 4 + lg) ^ key(r))];
         s[u] = M::run(__builtin_bit_cast(opvec, raw), qreg[kk], s[u]);
       }
     }
@@ -416,7 +445,7 @@ k_decode_attn(const AttnParams P) {
       m_ref = mn;
       l_run *= alpha;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
+      for (int e = 0; e < NE; ++e) {
         acc[e][0] *= alpha; acc[e][1] *= alpha; acc[e][2] *= alpha; acc[e][3] *= alpha;
       }
     }
@@ -427,14 +456,22 @@ k_decode_attn(const AttnParams P) {
     uint4 praw = make_uint4(M::pack2(pv[0], pv[1]), M::pack2(pv[2], pv[3]), M::pack2(pv[4], pv[5]),
                             M::pack2(pv[6], pv[7]));
     const opvec pop = __builtin_bit_cast(opvec, praw);
-    // ---- O^T += V^T . P^T : transpose the lane's 8x8 block, one MFMA per column e
+    opvec plo = pop;                     // what rounding the probabilities to 16 bits left over
+    if constexpr (kSplitP) {
+      float d[8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
+      for (int j = 0; j < 8; ++j) d[j] = pv[j] - (float)pop[j];
+      plo = __builtin_bit_cast(opvec, make_uint4(M::pack2(d[0], d[1]), M::pack2(d[2], d[3]), M::pack2(d[4], d[5]), M::pack2(d[6], d[7])));
+    }
+    // ---- O^T += V^T . P^T : transpose the lane's 8 x NE block, one MFMA per column e
+#pragma unroll
+    for (int e = 0; e < NE; ++e) {
       const uint32_t sel = (e & 1) ? 0x07060302u : 0x05040100u;
       uint32_t w[4];
 #pragma unroll
       for (int u = 0; u < 4; ++u) w[u] = __builtin_amdgcn_perm(vst[2 * u + 1].w[e >> 1], vst[2 * u].w[e >> 1], sel);
       uint4 traw = make_uint4(w[0], w[1], w[2], w[3]);
+      if constexpr (kSplitP) acc[e] = M::run(__builtin_bit_cast(opvec, traw), plo, acc[e]);
       acc[e] = M::run(__builtin_bit_cast(opvec, traw), pop, acc[e]);
     }
     if (more) issue_v(cur);              // next tile's V: lands while the next K tile is being scored
@@ -457,13 +494,13 @@ k_decode_attn(const AttnParams P) {
   l_run += __shfl_xor(l_run, 32, 64);
   __syncthreads();                       // every wave is done with its K tile
   VT_PROF(2);
-  float* red_o = reinterpret_cast<float*>(&lds[0][0]);    // [WAVES][G][D] floats: at most the K tiles' 32 KB
+  float* red_o = reinterpret_cast<float*>(&lds[0][0]);    // [WAVES][G][D] floats: at most the K tiles' memory
   const int G = a_G;
   if (l16 < G) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e)
+    for (int e = 0; e < NE; ++e)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) red_o[(wave * G + l16) * kD + (lg * 4 + i) * 8 + e] = acc[e][i];
+      for (int i = 0; i < 4; ++i) red_o[(wave * G + l16) * kD + (lg * 4 + i) * NE + e] = acc[e][i];
     if (lg == 0) {
       red_ml[(wave * 16 + l16) * 2 + 0] = m_ref;
       red_ml[(wave * 16 + l16) * 2 + 1] = l_run;
@@ -519,7 +556,7 @@ k_decode_attn(const AttnParams P) {
   // partial outputs are requested in the same breath as (m, l), with 16-byte device-coherent
   // loads, so that the merge costs one memory round trip, not two.
   float* ml_sh = reinterpret_cast<float*>(&lds[0][0]);
-  const int idx0 = threadIdx.x * 4;                   // G * kD / 4 >= 32 threads are busy; the rest idle through
+  const int idx0 = threadIdx.x * 4;                   // G * kD / 4 threads are busy; the rest idle through
   const int h0 = min(idx0 / kD, G - 1), d0 = idx0 % kD;
   const int i_ml = threadIdx.x;                       // ns * G * 2 <= 256 * 32 ... a thread may own several
   float ml_first = 0.f;
@@ -848,7 +885,9 @@ int plan_operand(const vt_desc& d, const char* name, int64_t G, AttnOperand* out
   return VT_OK;
 }
 
-// About two workgroups per compute unit, and at least one 32-row tile per wave.
+// About two workgroups per compute unit, and at least one 32-row tile per wave.  (The 64-wide heads'
+// tiles are half as many bytes, but four workgroups per unit are no faster: 16 sequences x 8 kv
+// heads x 2368 keys 17.8 us with 4 splits and 19.1 with 8, 8 x 8 x 8192 keys 25.7 with 8, 28.2 with 16.)
 int choose_splits(int units, int S, int n_splits) {
   if (n_splits > 0) return n_splits;
   int max_splits = std::max(1, (S + 127) / 128);
@@ -917,7 +956,7 @@ static int plan_attention(const vt_desc* Q, const vt_desc* K, const vt_desc* V, 
   const int64_t B = K->shape[0], Hq = K->shape[1], S = K->shape[2], D = K->shape[3];
   if (Q->shape[0] != B || Q->shape[1] != Hq || Q->shape[2] != 1 || Q->shape[3] != D)
     return fail(VT_ERR_SHAPE, "vt_decode_attn: Q does not match K");
-  if (D != kD) return fail(VT_ERR_UNSUPPORTED, "vt_decode_attn: head dim must be 128");
+  if (D != 64 && D != 128) return fail(VT_ERR_UNSUPPORTED, "vt_decode_attn: head dim must be 64 or 128");
   if (B > 65535 || Hq > 65535 || S >= (1ll << 31)) return fail(VT_ERR_UNSUPPORTED, "vt_decode_attn: extents too large");
   if (n_splits < 0) return fail(VT_ERR_INVALID_ARG, "vt_decode_attn: n_splits < 0");
 
@@ -988,15 +1027,18 @@ static int plan_attention(const vt_desc* Q, const vt_desc* K, const vt_desc* V, 
     if ((uintptr_t)P.q_ptr % 16 || P.q_sb % 16 || P.q_sh % 16) return fail(VT_ERR_UNSUPPORTED, "Q: rows are not 16-byte aligned");
   }
   const int Hkv = (int)(Hq / G);
-  const int ns = choose_splits((int)B * Hkv, (int)S, n_splits);
+  int ns = choose_splits((int)B * Hkv, (int)S, n_splits);
+  if (n_splits == 0 && D == 64) ns = std::min(ns, (int)(kWaves * kTile * D / 4 / G));   // what the merge below has room for
   int rows = (int)((S + ns - 1) / ns);
   rows = (rows + kTile - 1) / kTile * kTile;
   const int ns_eff = (int)((S + rows - 1) / rows);
-  if ((int64_t)ns_eff * G * 2 > kWaves * kTile * 64) return fail(VT_ERR_UNSUPPORTED, "vt_decode_attn: too many splits");
+  // the merge keeps (m, l) of every split and head in the K tiles' memory
+  if ((int64_t)ns_eff * G * 2 > kWaves * kTile * D / 2) return fail(VT_ERR_UNSUPPORTED, "vt_decode_attn: too many splits");
   P.B = (int)B;
   P.Hkv = Hkv;
   P.G = (int)G;
   P.S = (int)S;
+  P.D = (int)D;
   P.n_splits = ns_eff;
   P.rows_per_split = rows;
   return VT_OK;
@@ -1026,7 +1068,11 @@ static int launch_attention(const vt_desc* Q, const vt_desc* K, const vt_desc* V
   if (!out || !workspace) return fail(VT_ERR_INVALID_ARG, std::string(who) + ": NULL argument");
   AttnParams P;
   int rc = plan_attention(Q, K, V, n_splits, P);
-  if (rc == VT_ERR_UNSUPPORTED) {
+  const size_t need = rc == VT_OK ? ticket_bytes(P.B, (int64_t)P.Hkv * P.G) + (size_t)P.B * P.Hkv * P.G * P.n_splits * ((size_t)P.D + 2) * sizeof(float) : 0;
+  // the generic kernel needs no workspace and no alignment of out: 64-wide heads keep it where
+  // those of the planned kernel are not given
+  const bool unplaced = rc == VT_OK && P.D != 128 && (workspace_bytes < need || (uintptr_t)workspace % 16 || (uintptr_t)out % 8);
+  if (rc == VT_ERR_UNSUPPORTED || unplaced) {
     // maps or a head dim the planned kernel does not take: the generic kernel, if the shapes allow
     const std::string why = vt_last_error();
     const int64_t B = K->shape[0], Hq = K->shape[1], S = K->shape[2], D = K->shape[3];
@@ -1044,7 +1090,6 @@ static int launch_attention(const vt_desc* Q, const vt_desc* K, const vt_desc* V
   if (rc != VT_OK) return rc;
   const int64_t B = P.B, Hq = (int64_t)P.Hkv * P.G;
   const int ns_eff = P.n_splits, Hkv = P.Hkv;
-  const size_t need = ticket_bytes(B, Hq) + (size_t)B * Hq * ns_eff * ((size_t)kD + 2) * sizeof(float);
   if (workspace_bytes < need)
     return fail(VT_ERR_INVALID_ARG, std::string(who) + ": workspace too small (" + std::to_string(need) + " bytes needed, " +
                                         std::to_string(workspace_bytes) + " available)");
@@ -1065,8 +1110,15 @@ static int launch_attention(const vt_desc* Q, const vt_desc* K, const vt_desc* V
   dim3 grid(ns_eff, Hkv, (unsigned)B);
   // compiled for three waves per SIMD (two workgroups of four waves per compute unit and room for
   // a third); the build for two measures the same on the benchmark's shape
-  if (Q->dtype == VT_BF16) hipLaunchKernelGGL((k_decode_attn<bf16_t, kWaves, 3>), grid, dim3(kWaves * 64), 0, st, P);
-  else hipLaunchKernelGGL((k_decode_attn<f16_t, kWaves, 3>), grid, dim3(kWaves * 64), 0, st, P);
+#define VT_ATTN(TT, DD, OCC) hipLaunchKernelGGL((k_decode_attn<TT, DD, kWaves, OCC>), grid, dim3(kWaves * 64), 0, st, P)
+  if (P.D == 64) {
+    if (Q->dtype == VT_BF16) VT_ATTN(bf16_t, 64, 4);
+    else VT_ATTN(f16_t, 64, 4);
+  } else {
+    if (Q->dtype == VT_BF16) VT_ATTN(bf16_t, 128, 3);
+    else VT_ATTN(f16_t, 128, 3);
+  }
+#undef VT_ATTN
   return check_launch(who);
 }
 

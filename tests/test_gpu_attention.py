@@ -249,3 +249,35 @@ def test_paged_kv_cache_full_size(gpu):
     mx = check(got, ref["out"])
     assert mx <= 2e-3, mx
     assert np.max(np.abs(tio.to_host_f64(res["lse"]) - ref["lse"])) <= 1e-3
+
+
+# 64-wide heads: the smallest contexts, edges of the 32-row tile, ragged splits, every group size class
+@pytest.mark.parametrize("B,Hkv,G,S,dtype,ns", [(1, 1, 4, 2, "bf16", 0), (2, 3, 1, 32, "f16", 0), (2, 2, 7, 33, "bf16", 0), (1, 2, 16, 130, "f16", 2),
+                                                (1, 1, 18, 95, "bf16", 1), (3, 2, 2, 777, "f16", 7), (2, 8, 4, 1025, "bf16", 0)])
+def test_heads_of_64(gpu, B, Hkv, G, S, dtype, ns):
+    """The probabilities keep their fp32 value (two 16-bit halves), so what separates the result from
+    the oracle is its own rounding (2^-9 or 2^-12 of it) and fp32 sums: twice that plus 1e-4."""
+    vt, tio, pipelines, torch = gpu
+    wl = workloads.c2_decode_attention(seed=1, B=B, Hkv=Hkv, G=G, S=S, D=64, dtype=dtype)
+    ref = run_workload(wl)
+    res = pipelines.run_decode_attention(tio.DeviceWorkload(wl), n_splits=ns)
+    p = res["pipeline"]
+    assert vt.binding.vt_decode_attn_plan(p.q, p.k, p.v, ns)["group_size"] == (9 if G == 18 else G)
+    eps = 2.0 ** -8 if dtype == "bf16" else 2.0 ** -11
+    for _ in range(2):
+        assert np.all(np.abs(tio.to_host_f64(p.out) - ref["out"]) <= eps * np.abs(ref["out"]) + 1e-4)
+        assert np.max(np.abs(tio.to_host_f64(p.lse) - ref["lse"])) <= 1e-4
+        # a workspace that holds no partial results: the generic kernel, which needs none
+        vt.vt_decode_attn(p.q, p.k, p.v, p.scale, p.out, p.ws, 16, ns, lse=p.lse)
+        torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("B,Hkv,G,P,page", [(2, 2, 4, 3, 32), (3, 1, 7, 2, 96)])
+def test_paged_heads_of_64(gpu, B, Hkv, G, P, page):
+    vt, tio, pipelines, torch = gpu
+    wl = workloads.paged_decode_attention(seed=11, B=B, Hkv=Hkv, G=G, pages_per_seq=P, page=page, D=64, poison_unused=True)
+    ref = run_workload(wl)["out"]
+    res = pipelines.run_decode_attention(tio.DeviceWorkload(wl))
+    p = res["pipeline"]
+    assert vt.binding.vt_decode_attn_plan(p.q, p.k, p.v)["paged_segments"] == 1
+    assert np.all(np.abs(tio.to_host_f64(p.out) - ref) <= 2.0 ** -8 * np.abs(ref) + 1e-4)
