@@ -227,7 +227,7 @@ int vt_gemm(const vt_desc* const* A, const vt_desc* const* B, void* const* C, in
  * runs on a generic kernel that applies the whole map per element: same result to rounding,
  * far slower, no context splits; vt_decode_attn_plan reports VT_ERR_UNSUPPORTED for such operands.
  * D = 64 also runs there when the workspace or the alignment of out is not what the planned kernel
- * needs (for D = 128 that is an error).
+ * needs (for D = 128 that is an error), so vt_decode_attn_plan reports VT_ERR_UNSUPPORTED for it too.
  * workspace: device pointer (16-byte aligned) of at least vt_decode_attn_workspace(...) bytes,
  * holding arrival counters and the per-split partial results, prepared once with
  * vt_decode_attn_workspace_init; the split that finishes last for a (batch, kv head) merges

@@ -1049,6 +1049,8 @@ int vt_decode_attn_plan(const vt_desc* Q, const vt_desc* K, const vt_desc* V, in
   AttnParams P;
   int rc = plan_attention(Q, K, V, n_splits, P);
   if (rc != VT_OK) return rc;
+  // 64-wide heads run planned or generic depending on the workspace and on out, which are not known here
+  if (P.D != 128) return fail(VT_ERR_UNSUPPORTED, "vt_decode_attn: head dim must be 128 to be planned in advance");
   if (group_size) *group_size = P.G;
   if (n_segments) *n_segments = P.n_seg;
   if (splits) *splits = P.n_splits;
