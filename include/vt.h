@@ -208,8 +208,9 @@ int vt_weighted_sum(const vt_desc* x, const vt_desc* y, const float* weights, vo
  * kernel that applies the whole map per element: same results, far slower.
  * prologue = VT_GEMM_LAYERNORM applies per-row LayerNorm (gamma 1, beta 0, eps) over K to A,
  * rounded to the operand dtype, before the product, inside the load stage (the normalised
- * tensor is never stored).  The fused kernel is built for K = 64 or 128, N <= 384 and contiguous
- * rows of A; other shapes and maps run on the generic kernel with the same prologue (far slower).
+ * tensor is never stored).  The fused kernels take contiguous, 16-byte aligned rows of A, K <= 1024
+ * and a row-major W, K and N multiples of 8 (K = 64 or 128 with N <= 384 keeps W in registers);
+ * other shapes and maps run on the generic kernel with the same prologue (far slower).
  * A, B, C are host arrays of n_groups pointers. */
 typedef enum { VT_GEMM_PLAIN = 0, VT_GEMM_LAYERNORM = 1 } vt_gemm_prologue;
 int vt_gemm(const vt_desc* const* A, const vt_desc* const* B, void* const* C, int n_groups,

@@ -613,6 +613,7 @@ int plan_b(const vt_desc& d, GemmGroup* g, int64_t* K, int64_t* N) {
 
 namespace vt {
 int ln_gemm_launch(const vt_desc& A, const vt_desc& B, void* C, int c_dtype, float eps, hipStream_t st);
+int ln_gemm_wide_launch(const vt_desc& A, const vt_desc& B, void* C, int c_dtype, float eps, hipStream_t st);
 }
 
 namespace vt {
@@ -692,7 +693,9 @@ extern "C" int vt_gemm(const vt_desc* const* A, const vt_desc* const* B, void* c
       if (!A[i] || !B[i] || !C[i]) return fail(VT_ERR_INVALID_ARG, "vt_gemm: NULL descriptor or output");
       if (A[i]->dtype != dt || B[i]->dtype != dt) return fail(VT_ERR_INVALID_ARG, "vt_gemm: mixed operand dtypes");
       int rc = ln_gemm_launch(*A[i], *B[i], C[i], c_dtype, eps, st);
-      // shapes or maps the fused kernel is not built for: the generic kernel with the same prologue
+      // K or N that the kernel with W in registers is not built for: the one that streams W; maps
+      // that neither takes: the generic kernel with the same prologue
+      if (rc == VT_ERR_UNSUPPORTED) rc = ln_gemm_wide_launch(*A[i], *B[i], C[i], c_dtype, eps, st);
       if (rc == VT_ERR_UNSUPPORTED) rc = launch_generic(*A[i], *B[i], C[i], c_dtype, true, eps, st);
       if (rc != VT_OK) return rc;
     }
