@@ -199,7 +199,8 @@ int vt_weighted_sum(const vt_desc* x, const vt_desc* y, const float* weights, vo
  * folded: [.., K] counts as rows x K), B[g] virtual [K, N]; f16 or bf16 operands, fp32
  * accumulation, C[g] dense [M_g, N] row-major device pointers of dtype c_dtype (same as the
  * operands, or VT_F32).  One launch covers all groups.
- * Operand forms: the tiled kernel (256 x 256 tiles) takes maps that separate into a row part plus
+ * Operand forms: the tiled kernels (256 x 256 tiles, smaller ones where those would leave compute
+ * units idle; the same bits) take maps that separate into a row part plus
  * a column part with runs of 8 contiguous, 16-byte aligned elements along K for A (rows through
  * any mixed-radix map or an index table: permuted, gathered, broadcast rows) and along N or
  * along K for B (a [K,N] weight, or an [N,K] weight seen through a Permute); an A that a Concat

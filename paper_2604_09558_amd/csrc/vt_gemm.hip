@@ -30,6 +30,7 @@
 #include <vector>
 
 #include "vt_gemm_common.h"
+#include "vt_gemm_params.h"
 #include "vt_profile.h"
 
 using namespace vt;
@@ -42,38 +43,8 @@ VT_PROF_DECLARE(gemm)
 namespace {
 
 constexpr int BM = 256, BN = 256, BK = 64;
-constexpr int kMaxGroups = 8;
-constexpr int kGroupRows = 8;      // tile rows walked together (L2 reuse of the B panel)
 constexpr int kBPitch = BN * 2 + 64;   // bytes between k-rows of the B tile in LDS
 constexpr int kMaxSteps = 1024;        // K steps whose offsets are tabulated in LDS (K <= 65536)
-
-struct GemmGroup {
-  const char* a;
-  const char* b;
-  char* c;
-  AxisMap<5> a_row;
-  AxisMap<3> a_col, b_row, b_col;
-  int32_t M, tile_begin, tiles_m;
-  int32_t k64;   // a K step of 64 never leaves the innermost K digit of A or of B: the step's offset is uniform
-  int32_t b_kmajor;   // B's contiguous axis is K (all groups of a launch agree)
-};
-
-struct GemmParams {
-  GemmGroup g[kMaxGroups];
-  int32_t n_groups, N, K, tiles_n, total_tiles, chunk, c_f32, pad;
-};
-
-// Output written through a map (producer-side store, Sec. 4.2): columns [col_lo, col_hi) of C
-// live in one physical tensor, element (m, n) at base + 2 * (row(m) + col(n - col_lo)).
-struct OutPiece {
-  char* base;
-  int32_t col_lo, col_hi;
-  AxisMap<3> row, col;
-};
-struct OutMap {
-  OutPiece p[4];
-  int32_t n, pad;
-};
 
 template <typename T, bool C_F32, bool K_TAIL, bool MAPPED, bool B_KMAJOR = false>
 __global__ void __launch_bounds__(256) k_gemm(const GemmParams P, const OutMap O) {
@@ -90,22 +61,9 @@ __global__ void __launch_bounds__(256) k_gemm(const GemmParams P, const OutMap O
 
   VT_PROF_BEGIN();
   VT_PROF(0);
-  // ---- which tile: XCD-contiguous bands, groups of kGroupRows tile rows
-  const int wg = blockIdx.x;
-  const int slot = wg >> 3;
-  const int idx = (wg & 7) * P.chunk + slot;
-  if (slot >= P.chunk || idx >= P.total_tiles) return;
-  int gi = 0;
-#pragma unroll
-  for (int i = 1; i < kMaxGroups; ++i)
-    if (i < P.n_groups && idx >= P.g[i].tile_begin) gi = i;
+  int gi, tm, tn;
+  if (!pick_tile(P, blockIdx.x, &gi, &tm, &tn)) return;
   const GemmGroup& G = P.g[gi];
-  const int local = idx - G.tile_begin;
-  const int width = kGroupRows * P.tiles_n;
-  const int first_m = (local / width) * kGroupRows;
-  const int gsz = min(G.tiles_m - first_m, kGroupRows);
-  const int tm = first_m + (local % width) % gsz;
-  const int tn = (local % width) / gsz;
 
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int wm = wave >> 1, wn = wave & 1;
@@ -614,6 +572,7 @@ int plan_b(const vt_desc& d, GemmGroup* g, int64_t* K, int64_t* N) {
 namespace vt {
 int ln_gemm_launch(const vt_desc& A, const vt_desc& B, void* C, int c_dtype, float eps, hipStream_t st);
 int ln_gemm_wide_launch(const vt_desc& A, const vt_desc& B, void* C, int c_dtype, float eps, hipStream_t st);
+int gemm_tile_launch(const gemm::GemmParams& P, const gemm::OutMap* O, int dtype, hipStream_t st);
 }
 
 namespace vt {
@@ -657,15 +616,13 @@ int gemm_store_launch(const vt_desc& A, const vt_desc& B, const vt_desc& Cd, hip
   O.n = (int32_t)ps.size();
   P.g[0].c = nullptr;
   P.g[0].M = (int32_t)M;
-  P.g[0].tiles_m = (int32_t)((M + BM - 1) / BM);
-  P.g[0].tile_begin = 0;
   P.g[0].k64 = P.g[0].a_col.radix[2].d % 64 == 0 && P.g[0].b_row.radix[2].d % 64 == 0;
   P.n_groups = 1;
   P.N = (int32_t)N;
   P.K = (int32_t)Ka;
-  P.tiles_n = (int32_t)((N + BN - 1) / BN);
-  P.total_tiles = P.g[0].tiles_m * P.tiles_n;
-  P.chunk = (P.total_tiles + 7) / 8;
+  rc = gemm_tile_launch(P, &O, dt, st);
+  if (rc != VT_ERR_UNSUPPORTED) return rc;
+  set_tiles(&P, BM, BN);
   dim3 grid(P.chunk * 8);
   const bool kt = Ka % BK != 0;
   if (dt == VT_BF16) {
@@ -737,7 +694,6 @@ extern "C" int vt_gemm(const vt_desc* const* A, const vt_desc* const* B, void* c
     GemmParams P;
     memset(&P, 0, sizeof(P));
     const int ng = (int)std::min<size_t>(kMaxGroups, units.size() - u0);
-    int tiles = 0;
     for (int i = 0; i < ng; ++i) {
       const vt_desc* a = A[units[u0 + i].group];
       const vt_desc* b = B[units[u0 + i].group];
@@ -758,19 +714,19 @@ extern "C" int vt_gemm(const vt_desc* const* A, const vt_desc* const* B, void* c
       if ((uintptr_t)c % 4) return fail(VT_ERR_INVALID_ARG, "vt_gemm: misaligned C");
       P.g[i].c = static_cast<char*>(c) + (size_t)row_begin * (size_t)N * (c_dtype == VT_F32 ? 4 : 2);
       P.g[i].M = (int32_t)M;
-      P.g[i].tiles_m = (int32_t)((M + BM - 1) / BM);
-      P.g[i].tile_begin = tiles;
       P.g[i].k64 = P.g[i].a_col.radix[2].d % 64 == 0 && P.g[i].b_row.radix[2].d % 64 == 0;
       if (P.g[i].b_kmajor != P.g[0].b_kmajor) return fail(VT_ERR_UNSUPPORTED, "vt_gemm: the groups of one call must store B the same way (all [K,N] or all [N,K])");
-      tiles += P.g[i].tiles_m * (int32_t)((N + BN - 1) / BN);
     }
     P.n_groups = ng;
     P.N = (int32_t)N;
     P.K = (int32_t)K;
-    P.tiles_n = (int32_t)((N + BN - 1) / BN);
-    P.total_tiles = tiles;
-    P.chunk = (tiles + 7) / 8;
     P.c_f32 = c_dtype == VT_F32;
+    {
+      const int rc = gemm_tile_launch(P, nullptr, dt, st);
+      if (rc == VT_OK) continue;
+      if (rc != VT_ERR_UNSUPPORTED) return rc;
+    }
+    set_tiles(&P, BM, BN);
     dim3 grid(P.chunk * 8);
     const bool kt = K % BK != 0;
     OutMap no_map;

@@ -1,0 +1,379 @@
+// Tiled GEMM for products that the 256 x 256 tiles of vt_gemm.hip would spread over too few compute
+// units: the same product, operand maps, order of accumulation (identical bits) and tile walk, with
+// smaller tiles and a deeper pipeline.  A short prompt or a decode batch's experts are bound by
+// pulling the operands into the compute units, not by the matrix cores: a unit draws some 55 GB/s
+// from L2 and 40 GB/s from HBM, so what counts is how many units share the work and how few bytes
+// each has to read (BM + BN per K step and tile).
+//
+// One workgroup of 4 waves computes a BM x BN tile of C in 32 x 32 matrix-core blocks
+// (v_mfma_f32_32x32x16).  K steps of 64 run through a ring of STAGES tiles in LDS; operands go from
+// global memory straight into it (global_load_lds_dwordx4: no registers, no store instructions),
+// STAGES steps ahead, one barrier per step; a step's fragments are read into registers during the
+// step before.  The lanes of a request land in the order of their numbers, so the swizzle that keeps
+// the fragment reads free of bank conflicts (4.3 million conflict cycles per launch without it, 6000
+// with it) is applied to what a lane asks for.  Waits count the requests by hand: a wave issues the
+// same number in every step and nothing else that goes through the vector memory counter.
+// Measured (f16/bf16, K = 4096): 333 x 4096 83 -> 26 us, 400 x 6144 91 -> 35 us, 1024 x 4096 90 -> 48 us.
+// A loop with the requests alone takes the same time, one without them half of it; rings twice as
+// deep, with the waves divided into readers of A and of B, measured no faster.
+#include <hip/hip_runtime.h>
+
+#include <cstring>
+#include <type_traits>
+
+#include "vt_gemm_common.h"
+#include "vt_gemm_params.h"
+
+using namespace vt;
+using namespace vt::gemm;
+
+namespace {
+
+constexpr int BK = 64;
+constexpr int kMaxSteps = 256;        // K <= 16384
+
+typedef __attribute__((address_space(3))) void* lptr_t;
+
+// N requests of 16 bytes per lane: lane l's bytes of request i, from base[i] + off[i], land at LDS byte
+// dst + 1024 i + 16 l.  (M0 holds the destination; it is saved and put back.)
+template <int N>
+__device__ __forceinline__ void request(const uint32_t* off, const char* const* base, uint32_t dst) {
+  uint32_t m0_saved;
+  if constexpr (N >= 2) {
+    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %5\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %3\n\t"
+                 "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %4\n\ts_nop 0\n\ts_mov_b32 m0, %0"
+                 : "=&s"(m0_saved) : "v"(off[0]), "v"(off[1]), "s"(base[0]), "s"(base[1]), "s"(dst) : "memory", "scc");
+    if constexpr (N > 2) request<N - 2>(off + 2, base + 2, dst + 2048);
+  } else {
+    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2\n\ts_nop 0\n\ts_mov_b32 m0, %0"
+                 : "=&s"(m0_saved) : "v"(off[0]), "s"(base[0]), "s"(dst) : "memory");
+  }
+}
+
+// The swizzle: chunk c (16 bytes) of a 128-byte row r lies at position c ^ row_key(r): the 16 rows of a
+// fragment read fall into different banks.  Chunk c of B's k-row k lies at c ^ k_key(k): so do the
+// four k-rows x 64 bytes that 32 lanes of a transposing read touch.
+__device__ __forceinline__ int row_key(int r) { return r >> 1 & 7; }
+template <int BN>
+__device__ __forceinline__ int k_key(int k) { return BN == 64 ? (k >> 1 & 1) << 2 : (k & 3) << 2; }
+
+template <typename T, bool C_F32, bool MAPPED, bool B_KMAJOR, int BM, int BN, int WM, int STAGES>
+__global__ void __launch_bounds__(256) k_gemm_tile(const GemmParams P, const OutMap O) {
+  typedef Mma<T> M_;
+  typedef typename M_::vec opvec;
+  constexpr int kABytes = BM * BK * 2, kStage = (BM + BN) * BK * 2;
+  constexpr int AI = BM / 32, BI = BN / 32;          // requests per wave and step (1 KB each)
+  constexpr int WN = 4 / WM;                         // the waves' grid
+  constexpr int MB = BM / (32 * WM), NB = BN / (32 * WN);   // 32 x 32 blocks per wave
+  static_assert(!MAPPED || 4 * BM * 8 <= STAGES * kStage, "the row offsets of the output fit the ring");
+  __shared__ __attribute__((aligned(1024))) char lds[STAGES * kStage];
+  // byte offsets of every K step along A's columns and B's rows (a step of 64 stays inside the
+  // innermost K digit of both), evaluated once: nothing in the K loop reads kernel arguments
+  __shared__ uint4 steps[kMaxSteps];
+
+  int gi, tm, tn;
+  if (!pick_tile(P, blockIdx.x, &gi, &tm, &tn)) return;
+  const GemmGroup& G = P.g[gi];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave / WN, wn = wave % WN;
+  const int l32 = lane & 31, lh = lane >> 5;
+  const int Mg = G.M, N = P.N, nk = P.K / BK;
+
+  // ---- stage 1 through the map.  A: 8 lanes per row of 64 k, 8 rows per request; B: BN / 8 lanes per
+  // k-row; B_KMAJOR: like A, rows are the columns n.  (32-bit offsets: checked on the host.)
+  const char* const a_base = G.a;
+  const char* const b_base = G.b;
+  const int r8 = lane >> 3, p8 = lane & 7;
+  uint32_t a_off[AI], b_off[BI];
+#pragma unroll
+  for (int i = 0; i < AI; ++i) {
+    const int r = (wave * AI + i) * 8 + r8;
+    const uint32_t m = (uint32_t)min(tm * BM + r, Mg - 1);
+    const int64_t ro = G.a_row.tdig >= 0 ? axis_off_table(G.a_row, m) : axis_off(G.a_row, m);
+    a_off[i] = (uint32_t)(ro * 2) + (uint32_t)((p8 ^ row_key(r)) * 16);
+  }
+  constexpr int LB = BN / 8, RB = 64 / LB;           // lanes per k-row of B, k-rows per request
+  const int64_t b_kstride = G.b_row.stride[2] * 2;
+  if (B_KMAJOR) {
+#pragma unroll
+    for (int i = 0; i < BI; ++i) {
+      const int r = (wave * BI + i) * 8 + r8;
+      b_off[i] = (uint32_t)(axis_off(G.b_col, (uint32_t)min(tn * BN + r, N - 1)) * 2) + (uint32_t)((p8 ^ row_key(r)) * 16);
+    }
+  } else {
+    const int kr = lane / LB;
+    const uint32_t n = (uint32_t)min(tn * BN + ((lane % LB) ^ k_key<BN>(kr)) * 8, N - 8);
+#pragma unroll
+    for (int i = 0; i < BI; ++i) b_off[i] = (uint32_t)(axis_off(G.b_col, n) * 2) + (uint32_t)(kr * b_kstride);
+  }
+  if ((int)threadIdx.x < nk) {
+    const uint32_t k = threadIdx.x * BK;
+    const uint64_t bo = (uint64_t)(axis_off(G.b_row, k) * 2);
+    steps[threadIdx.x] = make_uint4((uint32_t)(axis_off(G.a_col, k) * 2), (uint32_t)bo, (uint32_t)(bo >> 32), 0);
+  }
+  __syncthreads();
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(lptr_t)&lds[0];
+  auto issue = [&](const uint4& o, int slot) {
+    const uint32_t ao = __builtin_amdgcn_readfirstlane(o.x), b_lo = __builtin_amdgcn_readfirstlane(o.y),
+                   b_hi = __builtin_amdgcn_readfirstlane(o.z);
+    const char* const as = a_base + ao;
+    const char* const bs = b_base + (int64_t)(((uint64_t)b_hi << 32) | b_lo);
+    const uint32_t dst = lds0 + slot * kStage;
+    const char *sa[AI], *sb[BI];
+#pragma unroll
+    for (int i = 0; i < AI; ++i) sa[i] = as;
+#pragma unroll
+    for (int i = 0; i < BI; ++i) sb[i] = B_KMAJOR ? bs : bs + (wave * BI + i) * RB * b_kstride;
+    request<AI>(a_off, sa, dst + wave * AI * 1024);
+    request<BI>(b_off, sb, dst + kABytes + wave * BI * 1024);
+  };
+
+  // ---- fragment addresses in a stage (bytes), for k16 step 0
+  uint32_t a_frag[MB], b_frag[NB][2];
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb) {
+    const int r = (wm * MB + mb) * 32 + l32;
+    a_frag[mb] = r * 128 + ((lh ^ row_key(r)) * 16);    // chunk 2 ks + lh: XOR with 32 ks
+  }
+  const int lq = lane >> 4, ll = lane & 15;
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) {
+    if (B_KMAJOR) {
+      const int r = (wn * NB + nb) * 32 + l32;
+      b_frag[nb][0] = kABytes + r * 128 + ((lh ^ row_key(r)) * 16);
+      b_frag[nb][1] = 0;
+    } else {
+      // lane ll of a 16-lane group points at k-row (ll >> 2) (and 4 further), columns 4 (ll & 3) .. + 3;
+      // it receives the 4 consecutive k of column ll
+      const int chunk = (wn * NB + nb) * 4 + 2 * (lq & 1) + ((ll & 3) >> 1);
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int k = 8 * (lq >> 1) + (ll >> 2) + 4 * h;
+        b_frag[nb][h] = kABytes + k * (BN * 2) + ((chunk ^ k_key<BN>(k)) * 16) + (ll & 1) * 8;
+      }
+    }
+  }
+
+  f32x16 acc[MB][NB];
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+
+  // all fragments of one K step: read from LDS during the step before, so that neither the barrier
+  // nor the latency of the reads stands between two steps' products
+  struct Frags {
+    opvec a[BK / 16][MB], b[BK / 16][NB];
+  };
+  auto read_frags = [&](const char* st, Frags& f) {
+#pragma unroll
+    for (int ks = 0; ks < BK / 16; ++ks) {
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb) f.a[ks][mb] = __builtin_bit_cast(opvec, *reinterpret_cast<const uint4*>(st + (a_frag[mb] ^ (ks * 32))));
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) {
+        if (B_KMAJOR) {
+          f.b[ks][nb] = __builtin_bit_cast(opvec, *reinterpret_cast<const uint4*>(st + (b_frag[nb][0] ^ (ks * 32))));
+        } else {
+          typedef short s16x4 __attribute__((ext_vector_type(4)));
+          typedef __attribute__((address_space(3))) s16x4* lds_s16x4;
+          struct { s16x4 lo, hi; } v;
+          v.lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(st + b_frag[nb][0] + ks * 16 * (BN * 2)));
+          v.hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(st + b_frag[nb][1] + ks * 16 * (BN * 2)));
+          f.b[ks][nb] = __builtin_bit_cast(opvec, v);
+        }
+      }
+    }
+  };
+  auto multiply = [&](const Frags& f) {
+#pragma unroll
+    for (int ks = 0; ks < BK / 16; ++ks)
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = M_::run(f.a[ks][mb], f.b[ks][nb], acc[mb][nb]);
+  };
+  // What was loaded above (index tables) has to be out of the vector memory counter's way.  Requests past
+  // the last step repeat it (they hit the caches and land in stages that are not read again), so that
+  // every step issues the same number and the loop has no branches.
+  __builtin_amdgcn_s_waitcnt(0x0F70);                 // vmcnt(0)
+#pragma unroll
+  for (int s = 0; s < STAGES; ++s) issue(steps[min(s, nk - 1)], s);
+  constexpr int kFirst = (STAGES - 1) * (AI + BI);    // requests behind those of the first step,
+  constexpr int kBehind = (STAGES - 2) * (AI + BI);   // and in the loop behind those of the next one
+  static_assert(kFirst < 64, "vmcnt has 6 bits");
+  Frags f0, f1;
+  __builtin_amdgcn_s_waitcnt((kFirst & 15) | ((kFirst >> 4) << 14) | 0x0F70);
+  asm volatile("s_barrier" ::: "memory");
+  read_frags(lds, f0);
+  uint4 ahead = steps[min(STAGES, nk - 1)];
+  int slot = 0;                                       // the stage that step `it` came from: in registers, free to be filled
+  auto k_step = [&](int it, const Frags& cur, Frags& nxt) {
+    // this wave has its fragments of step `it`, and its requests of step it + 1 have landed; behind
+    // the barrier that holds for every wave
+    __builtin_amdgcn_s_waitcnt((kBehind & 15) | ((kBehind >> 4) << 14) | 0x0070);   // vmcnt(kBehind) lgkmcnt(0)
+    asm volatile("s_barrier" ::: "memory");
+    issue(ahead, slot);
+    slot = slot == STAGES - 1 ? 0 : slot + 1;
+    ahead = steps[min(it + STAGES + 1, nk - 1)];
+    read_frags(lds + slot * kStage, nxt);
+    multiply(cur);
+    // a product, two reads, a product, ...
+    constexpr int kMma = BK / 16 * MB * NB;
+#pragma unroll
+    for (int i = 0; i < kMma; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+    }
+  };
+  int it = 0;
+  for (; it + 1 < nk; it += 2) {
+    k_step(it, f0, f1);
+    k_step(it + 1, f1, f0);
+  }
+  if (it < nk) multiply(f0);
+  __builtin_amdgcn_s_waitcnt(0x0F70);                 // requests still target this workgroup's LDS
+
+  // ---- stage 3 (as in vt_gemm.hip): a lane holds column l32 of a block and rows 8 j + 4 lh + i
+  if (MAPPED) {
+    __syncthreads();
+    int64_t* rowoff = reinterpret_cast<int64_t*>(lds);               // [pieces][BM]
+    for (int pc = 0; pc < O.n; ++pc)
+      for (int r = threadIdx.x; r < BM; r += 256) rowoff[pc * BM + r] = axis_off(O.p[pc].row, (uint32_t)min(tm * BM + r, Mg - 1));
+    __syncthreads();
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+      const int col = tn * BN + (wn * NB + nb) * 32 + l32;
+      if (col >= N) continue;
+      int pc = 0;
+#pragma unroll
+      for (int i = 1; i < 4; ++i)
+        if (i < O.n && col >= O.p[i].col_lo) pc = i;
+      T* base = reinterpret_cast<T*>(O.p[pc].base) + axis_off(O.p[pc].col, (uint32_t)(col - O.p[pc].col_lo));
+      const int64_t* ro = rowoff + pc * BM;
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb) {
+        const int r0 = (wm * MB + mb) * 32 + lh * 4;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (tm * BM + r0 + 8 * j + i < Mg) base[ro[r0 + 8 * j + i]] = from_float<T>(acc[mb][nb][4 * j + i]);
+      }
+    }
+    return;
+  }
+  typedef typename std::conditional<C_F32, float, T>::type CT;
+  CT* cbase = reinterpret_cast<CT*>(G.c);
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+      const int col = tn * BN + (wn * NB + nb) * 32 + l32;
+      const int row0 = tm * BM + (wm * MB + mb) * 32 + lh * 4;
+      CT* cp = cbase + (size_t)row0 * N + col;
+      if (col < N) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (row0 + 8 * j + i < Mg) cp[(size_t)(8 * j + i) * N] = from_float<CT>(acc[mb][nb][4 * j + i]);
+      }
+    }
+}
+
+template <typename T, bool C_F32, bool MAPPED, bool B_KMAJOR>
+int launch_tile(GemmParams P, const OutMap& O, int bm, int bn, hipStream_t st) {
+  set_tiles(&P, bm, bn);
+  const dim3 grid(P.chunk * 8);
+#define VT_TILE(BM_, BN_, WM_, S_)                                                                                  \
+  if (bm == BM_ && bn == BN_) {                                                                                     \
+    hipLaunchKernelGGL((k_gemm_tile<T, C_F32, MAPPED, B_KMAJOR, BM_, BN_, WM_, S_>), grid, dim3(256), 0, st, P, O); \
+    return check_launch(MAPPED ? "vt_gemm_store" : "vt_gemm");                                                      \
+  }
+  VT_TILE(256, 128, 2, 3)
+  VT_TILE(128, 128, 2, 4)
+  VT_TILE(96, 128, 1, 5)
+  VT_TILE(64, 128, 2, 3)
+  VT_TILE(64, 64, 2, 4)
+#undef VT_TILE
+  return fail(VT_ERR_UNSUPPORTED, "vt_gemm: no such tile");
+}
+
+// The tile with the shortest time, by what one K step of 64 takes a compute unit (ns, measured at K = 4096
+// with every unit at work; a unit draws about 55 GB/s of operands whatever the depth of the ring, so the
+// smaller tiles are bound by their bytes) times the rounds of tiles.  64-row tiles run two to a unit.
+//   rows x columns of C (K = 4096): us on 256x256 / 256x128 / 128x128 / 96x128 / 64x128 / 64x64
+//   16 x 4096       88 / 60 / 37 / 33 / 32 / 23        333 x 4096    88 / 65 / 41 / 37 / 33 / 33
+//   400 x 6144     100 / 70 / 46 / 40 / 50 / 54       1024 x 4096    91 / 70 / 49 / 66 / 58 / 72
+//   2048 x 4096     93 / 80 / 90 / 103 / 106 / 126    4000 x 4096   121 / 147 / 166 / 188 / 184 / 225
+//   8 x about 50 x 14336 (grouped)                                  251 / 298 / 217 / 213 / 210 / 239
+// 0 x 0: the 256 x 256 kernel.
+void choose_tile(const GemmParams& P, int* bm, int* bn) {
+  static const int n_cu = [] {
+    int dev = 0, n = 256;
+    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) n = 256;
+    return n > 0 ? n : 256;
+  }();
+  static const struct {
+    int bm, bn, ns, ns_shared;     // a unit's time per step with one tile, and per tile with two at a time
+  } kTiles[] = {{256, 256, 1370, 0}, {256, 128, 1250, 0}, {128, 128, 750, 0}, {96, 128, 600, 0}, {64, 128, 500, 430}, {64, 64, 360, 270}};
+  int64_t best = 0;
+  for (const auto& t : kTiles) {
+    int64_t tiles = 0;
+    for (int i = 0; i < P.n_groups; ++i) tiles += ((int64_t)P.g[i].M + t.bm - 1) / t.bm * ((P.N + t.bn - 1) / t.bn);
+    const int64_t rounds = (tiles + n_cu - 1) / n_cu;
+    const int64_t cost = rounds > 1 && t.ns_shared ? rounds * t.ns_shared : rounds * t.ns;
+    if (best == 0 || cost < best) {
+      best = cost;
+      *bm = t.bm, *bn = t.bn;
+    }
+  }
+  if (*bm == 256 && *bn == 256) *bm = *bn = 0;
+}
+
+// bytes that an axis can span, or -1 for an index table on it
+template <int ND>
+int64_t axis_span(const AxisMap<ND>& a) {
+  if (a.table) return -1;
+  int64_t span = 0;
+  for (int i = 0; i < ND; ++i) span += (int64_t)(a.radix[i].d - 1) * a.stride[i] * 2;
+  return span;
+}
+
+}  // namespace
+
+namespace vt {
+
+// The product of P (operands planned, tiles not yet cut) on smaller tiles, or VT_ERR_UNSUPPORTED when
+// the 256 x 256 kernel is the better one or the only one.
+int gemm_tile_launch(const GemmParams& P, const OutMap* O, int dtype, hipStream_t st) {
+  const char* no = "vt_gemm: outside the small-tile kernel";
+  if (P.K % BK || P.K < BK || P.K > kMaxSteps * BK || P.N < 8) return fail(VT_ERR_UNSUPPORTED, no);
+  for (int i = 0; i < P.n_groups; ++i) {
+    const GemmGroup& g = P.g[i];
+    if (!g.k64 || g.b_kmajor != P.g[0].b_kmajor) return fail(VT_ERR_UNSUPPORTED, no);
+    // a lane's share of B's address is 32 bits
+    const int64_t span = axis_span(g.b_col) + (g.b_kmajor ? 128 : 8 * (g.b_row.stride[2] < 0 ? 1ll << 32 : g.b_row.stride[2]) * 2 + 16);
+    if (span >= (1ll << 32)) return fail(VT_ERR_UNSUPPORTED, no);
+  }
+  int bm = 0, bn = 0;
+  choose_tile(P, &bm, &bn);
+  if (!bm) return fail(VT_ERR_UNSUPPORTED, no);
+  OutMap none;
+  if (!O) memset(&none, 0, sizeof(none));
+  const bool km = P.g[0].b_kmajor != 0;
+#define VT_TILE_T(TT)                                                                            \
+  do {                                                                                           \
+    if (O) return launch_tile<TT, false, true, false>(P, *O, bm, bn, st);                        \
+    if (P.c_f32) return km ? launch_tile<TT, true, false, true>(P, none, bm, bn, st) : launch_tile<TT, true, false, false>(P, none, bm, bn, st); \
+    return km ? launch_tile<TT, false, false, true>(P, none, bm, bn, st) : launch_tile<TT, false, false, false>(P, none, bm, bn, st);            \
+  } while (0)
+  if (dtype == VT_BF16) VT_TILE_T(bf16_t);
+  else VT_TILE_T(f16_t);
+#undef VT_TILE_T
+}
+
+}  // namespace vt

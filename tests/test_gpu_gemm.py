@@ -220,6 +220,35 @@ def test_operand_stacked_by_a_concat_along_the_rows(gpu):
     assert torch.equal(p.out, m.out)
 
 
+# every tile shape of the small-tile kernel (64x64, 64x128, 96x128, 128x128, 256x128, then back to
+# 256x256), K of one step, of fewer steps than its ring holds, of an odd number; ragged rows and columns
+@pytest.mark.parametrize("M,K,N,dtype", [(1, 64, 8, "bf16"), (65, 192, 520, "f16"), (333, 320, 4088, "bf16"), (391, 448, 5992, "f16"),
+                                         (1000, 128, 4040, "bf16"), (2000, 704, 4000, "f16"), (2100, 64, 6088, "bf16")])
+def test_tile_shapes(gpu, M, K, N, dtype):
+    """Gathered rows of A (index table), W as [K,N] and as [N,K] through a Permute: the oracle's values to
+    one rounding (2^-8 / 2^-11) plus fp32 sums of K terms of about 0.05 (1e-4), equal bits for both
+    weights, the 16-bit result the fp32 one rounded once, nothing written behind the last row."""
+    vt, tio, pipelines, torch = gpu
+    rng = np.random.default_rng(31)
+    x = workloads.encode(rng.normal(size=(M + 7, K)).astype(np.float32), dtype)
+    w = workloads.encode((rng.normal(size=(K, N)) * 0.05).astype(np.float32), dtype)
+    tables = {"t": rng.integers(0, M + 7, size=M).astype(np.int32)}
+    chain = [("A", "index_select", ("X",), {"dim": 0, "index": "t"}), ("Bt", "permute", ("Wt",), {"perm": (1, 0)})]
+    src = {"X": x, "W": w, "Wt": np.ascontiguousarray(w.T)}
+    wl = workloads.Workload("tiles", dtype, src, chain, {"kind": "gemm", "a": "A", "b": "W"}, tables)
+    ref = run_workload(wl)["out"]
+    p = run(pipelines, tio, torch, wl)
+    eps = 2.0 ** -8 if dtype == "bf16" else 2.0 ** -11
+    assert np.all(np.abs(tio.to_host_f64(p.out) - ref) <= eps * np.abs(ref) + 1e-4)
+    wl.consumer = {"kind": "gemm", "a": "A", "b": "Bt"}
+    q = run(pipelines, tio, torch, wl)
+    assert torch.equal(p.out, q.out)
+    f32 = torch.full((M + 1, N), 7.0, device="cuda:0")
+    vt.vt_gemm(p.A, p.B, [f32], "f32")
+    torch.cuda.synchronize()
+    assert torch.equal(f32[:M].to(p.out.dtype), p.out) and bool((f32[M] == 7.0).all())
+
+
 @pytest.fixture(scope="module")
 def c5_full(gpu):
     """Config 5 at the benchmark's size, launched once as the benchmark launches it (8 experts in
