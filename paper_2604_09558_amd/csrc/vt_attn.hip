@@ -285,8 +285,8 @@ __device__ __forceinline__ void walk_advance(const AttnParams& P, TileWalk& w, i
   if (w.seg < P.n_seg) walk_fetch(P, w, b, g);
 }
 
-// D = head dim (64 or 128).
-template <typename T, int D, int WAVES, int OCC>
+// D = head dim (64 or 128).  MANY: more than eight splits, the merge below divides them among its threads.
+template <typename T, int D, bool MANY, int WAVES, int OCC>
 __global__ void __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(OCC, OCC)))
 k_decode_attn(const AttnParams P) {
   typedef Mfma<T> M;
@@ -556,55 +556,88 @@ k_decode_attn(const AttnParams P) {
   // partial outputs are requested in the same breath as (m, l), with 16-byte device-coherent
   // loads, so that the merge costs one memory round trip, not two.
   float* ml_sh = reinterpret_cast<float*>(&lds[0][0]);
-  const int idx0 = threadIdx.x * 4;                   // G * kD / 4 threads are busy; the rest idle through
+  // MANY: the threads that four columns each leave idle take a share of the splits: 2^lw threads per
+  // output, thread w merges splits w, w + 2^lw, ... (a long context of one sequence has 24 splits:
+  // three round trips become one or two), and the shares, parked behind the (m, l) in the K tiles'
+  // memory, are added in order.  (8 kv heads x 8192 keys in 32 splits: 16.5 -> 15.6 us, 1 x 8192 in 24:
+  // 13.2 -> 12.9; with lw a run-time value in the kernel for few splits that one lost 0.1 us.)
+  constexpr int kTileFloats = WAVES * kTile * LPR * 4, kShareFloats = 5 * WAVES * 64;
+  float* const part = ml_sh + (kTileFloats - kShareFloats);
+  int lw = 0;
+  if (MANY && ns * G * 2 <= kTileFloats - kShareFloats)
+    while ((G * kD / 4) << (lw + 1) <= WAVES * 64) ++lw;
+  const int way = MANY ? (int)threadIdx.x * (1 << lw) / (WAVES * 64) : 0;
+  const int col = MANY ? (int)threadIdx.x & ((WAVES * 64 >> lw) - 1) : (int)threadIdx.x;
+  const int idx0 = col * 4;                         // a thread with idx0 >= G * kD idles through
   const int h0 = min(idx0 / kD, G - 1), d0 = idx0 % kD;
-  const int i_ml = threadIdx.x;                       // ns * G * 2 <= 256 * 32 ... a thread may own several
+  const int i_ml = threadIdx.x;                     // ns * G * 2 <= 256 * 32 ... a thread may own several
   float ml_first = 0.f;
   if (i_ml < ns * G * 2) ml_first = ld(&a_ws_ml[u0 * G * 2 + i_ml]);
   u32x4_t v0[8];
   {
     const void* q[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) q[u] = &a_ws_o[((u0 + min(u, ns - 1)) * G + h0) * kD + d0];
+    for (int u = 0; u < 8; ++u) q[u] = &a_ws_o[((u0 + min(way + (u << lw), ns - 1)) * G + h0) * kD + d0];
     load_device_8xb128(q, v0);
   }
   VT_PROF(6);
   if (i_ml < ns * G * 2) ml_sh[i_ml] = ml_first;
   for (int i = i_ml + WAVES * 64; i < ns * G * 2; i += WAVES * 64) ml_sh[i] = ld(&a_ws_ml[u0 * G * 2 + i]);
   __syncthreads();
-  for (int idx = idx0; idx < G * kD; idx += WAVES * 64 * 4) {
-    const int h = idx / kD, d = idx - h * kD;
-    float mx = -1.0e30f;
-    for (int sp = 0; sp < ns; ++sp) mx = fmaxf(mx, ml_sh[(sp * G + h) * 2]);
-    float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
-    float l = 0.f;
-    for (int sp0 = 0; sp0 < ns; sp0 += 8) {
-      u32x4_t v[8];
-      if (idx == idx0 && sp0 == 0) {
-#pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = v0[u];
-      } else {
-        const void* q[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) q[u] = &a_ws_o[((u0 + min(sp0 + u, ns - 1)) * G + h) * kD + d];
-        load_device_8xb128(q, v);
-      }
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        if (sp0 + u < ns) {
-          const float sc = __builtin_amdgcn_exp2f(ml_sh[((sp0 + u) * G + h) * 2] - mx);
-          const float4 r = __builtin_bit_cast(float4, v[u]);
-          o.x += r.x * sc; o.y += r.y * sc; o.z += r.z * sc; o.w += r.w * sc;
-          l += ml_sh[((sp0 + u) * G + h) * 2 + 1] * sc;
-        }
-      }
-    }
-    const size_t hq = (size_t)bg * G + h;      // = b * Hq + g * G + h
+  auto finish = [&](float mx, float4 o, float l, int h, int d) {
+    const size_t hq = (size_t)bg * G + h;           // = b * Hq + g * G + h
     Vec<T, 4> r;
     r.v[0] = from_float<T>(o.x / l); r.v[1] = from_float<T>(o.y / l);
     r.v[2] = from_float<T>(o.z / l); r.v[3] = from_float<T>(o.w / l);
     *reinterpret_cast<Vec<T, 4>*>(&out[hq * kD + d]) = r;
     if (a_lse && d == 0) a_lse[hq] = (mx + log2f(l)) * 0.6931471805599453f;
+  };
+  float mx = -1.0e30f;
+  for (int idx = idx0; idx < G * kD; idx += WAVES * 64 * 4) {     // (one round if lw > 0)
+    const int h = idx / kD, d = idx - h * kD;
+    mx = -1.0e30f;
+    for (int sp = 0; sp < ns; ++sp) mx = fmaxf(mx, ml_sh[(sp * G + h) * 2]);
+    float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
+    float l = 0.f;
+    for (int sp0 = way; sp0 < ns; sp0 += 8 << lw) {
+      u32x4_t v[8];
+      if (idx == idx0 && sp0 == way) {
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = v0[u];
+      } else {
+        const void* q[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) q[u] = &a_ws_o[((u0 + min(sp0 + (u << lw), ns - 1)) * G + h) * kD + d];
+        load_device_8xb128(q, v);
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int sp = sp0 + (u << lw);
+        if (sp < ns) {
+          const float sc = __builtin_amdgcn_exp2f(ml_sh[(sp * G + h) * 2] - mx);
+          const float4 r = __builtin_bit_cast(float4, v[u]);
+          o.x += r.x * sc; o.y += r.y * sc; o.z += r.z * sc; o.w += r.w * sc;
+          l += ml_sh[(sp * G + h) * 2 + 1] * sc;
+        }
+      }
+    }
+    if (lw == 0) {
+      finish(mx, o, l, h, d);
+    } else {
+      static_assert(WAVES == 4, "256 threads");
+      const int t = threadIdx.x;
+      part[t] = o.x, part[256 + t] = o.y, part[512 + t] = o.z, part[768 + t] = o.w, part[1024 + t] = l;
+    }
+  }
+  if (lw > 0) {
+    __syncthreads();
+    if (way == 0 && idx0 < G * kD) {
+      float o[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
+      for (int w = 0; w < 1 << lw; ++w)
+#pragma unroll
+        for (int i = 0; i < 5; ++i) o[i] += part[256 * i + w * (WAVES * 64 >> lw) + col];
+      finish(mx, make_float4(o[0], o[1], o[2], o[3]), o[4], h0, d0);
+    }
   }
 #ifdef VT_PROFILE
   __builtin_amdgcn_s_waitcnt(0);
@@ -885,14 +918,28 @@ int plan_operand(const vt_desc& d, const char* name, int64_t G, AttnOperand* out
   return VT_OK;
 }
 
-// About two workgroups per compute unit, and at least one 32-row tile per wave.  (The 64-wide heads'
-// tiles are half as many bytes, but four workgroups per unit are no faster: 16 sequences x 8 kv
-// heads x 2368 keys 17.8 us with 4 splits and 19.1 with 8, 8 x 8 x 8192 keys 25.7 with 8, 28.2 with 16.)
-int choose_splits(int units, int S, int n_splits) {
+// At most this many splits: two workgroups per compute unit, and at least one 32-row tile per wave.
+// (The size of the workspace follows from it: it never falls when there are fewer units.)
+int most_splits(int units, int S, int n_splits) {
   if (n_splits > 0) return n_splits;
   int max_splits = std::max(1, (S + 127) / 128);
   int want = std::max(1, (512 + units - 1) / units);
   return std::min(want, max_splits);
+}
+
+// Two workgroups per compute unit (the 64-wide heads' tiles are half as many bytes, but four are no
+// faster: 16 sequences x 8 kv heads x 2368 keys 17.8 us with 4 splits and 19.1 with 8), or one, where
+// the units divide the chip almost evenly and there are few of them: every split costs its partial
+// results and a share of the merge.  More than 16 splits only while each keeps 352 rows.
+//   units x keys, us with 512 / units, 256 / units and this rule's splits (128-wide heads, 4 a group):
+//   8 x 8192  23.3 (64) 16.5 (32) 15.3 (24)     8 x 4096  14.2 (32) 14.2 (32) 11.8 (16)     1 x 8192  15.8 (64)  13.2 (24)
+//   16 x 4096 18.7 (32) 14.4 (16)               32 x 2048 14.7 (16) 12.0 (8)                32 x 8192 28.2 (16)  25.8 (8)
+//   64 x 4096 25.9 (8)  25.8 (4)                128 x 2048 25.8 (4) 25.8 (2)
+int choose_splits(int units, int S, int n_splits, int64_t D) {
+  if (n_splits > 0) return n_splits;
+  int ns = most_splits(units, S, 0);
+  if (D == 128 && units < 64 && 256 / units * units >= 230) ns = std::min(ns, 256 / units);
+  return std::min(ns, std::max(16, (S + 351) / 352));
 }
 
 constexpr int kWaves = 4;
@@ -933,7 +980,7 @@ size_t vt_decode_attn_workspace(int B, int Hq, int D, int S, int n_splits) {
   if (B < 1 || Hq < 1 || D < 1 || S < 1 || n_splits < 0) return 0;
   // an upper bound that does not need the grouping: the fewest kv heads (16 query heads each)
   // give the most splits
-  int ns = choose_splits(B * std::max(1, Hq / 16), S, n_splits);
+  int ns = most_splits(B * std::max(1, Hq / 16), S, n_splits);
   return ticket_bytes(B, Hq) + (size_t)B * Hq * ns * ((size_t)D + 2) * sizeof(float);
 }
 
@@ -1027,7 +1074,7 @@ static int plan_attention(const vt_desc* Q, const vt_desc* K, const vt_desc* V, 
     if ((uintptr_t)P.q_ptr % 16 || P.q_sb % 16 || P.q_sh % 16) return fail(VT_ERR_UNSUPPORTED, "Q: rows are not 16-byte aligned");
   }
   const int Hkv = (int)(Hq / G);
-  int ns = choose_splits((int)B * Hkv, (int)S, n_splits);
+  int ns = choose_splits((int)B * Hkv, (int)S, n_splits, D);
   if (n_splits == 0 && D == 64) ns = std::min(ns, (int)(kWaves * kTile * D / 4 / G));   // what the merge below has room for
   int rows = (int)((S + ns - 1) / ns);
   rows = (rows + kTile - 1) / kTile * kTile;
@@ -1112,7 +1159,11 @@ static int launch_attention(const vt_desc* Q, const vt_desc* K, const vt_desc* V
   dim3 grid(ns_eff, Hkv, (unsigned)B);
   // compiled for three waves per SIMD (two workgroups of four waves per compute unit and room for
   // a third); the build for two measures the same on the benchmark's shape
-#define VT_ATTN(TT, DD, OCC) hipLaunchKernelGGL((k_decode_attn<TT, DD, kWaves, OCC>), grid, dim3(kWaves * 64), 0, st, P)
+#define VT_ATTN(TT, DD, OCC)                                                                                          \
+  do {                                                                                                                \
+    if (ns_eff > 8) hipLaunchKernelGGL((k_decode_attn<TT, DD, true, kWaves, OCC>), grid, dim3(kWaves * 64), 0, st, P); \
+    else hipLaunchKernelGGL((k_decode_attn<TT, DD, false, kWaves, OCC>), grid, dim3(kWaves * 64), 0, st, P);          \
+  } while (0)
   if (P.D == 64) {
     if (Q->dtype == VT_BF16) VT_ATTN(bf16_t, 64, 4);
     else VT_ATTN(f16_t, 64, 4);

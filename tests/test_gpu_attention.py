@@ -281,3 +281,23 @@ def test_paged_heads_of_64(gpu, B, Hkv, G, P, page):
     p = res["pipeline"]
     assert p.ws.any()
     assert np.all(np.abs(tio.to_host_f64(p.out) - ref) <= 2.0 ** -8 * np.abs(ref) + 1e-4)
+
+
+# more than eight splits: each number of threads per output of the shared merge, a head count that
+# leaves threads idle, one that leaves none, split counts around multiples of eight, rounds with gaps
+@pytest.mark.parametrize("Hkv,G,D,S,ns", [(1, 1, 64, 1200, 9), (2, 1, 128, 2000, 17), (1, 4, 128, 1500, 24), (2, 7, 64, 1100, 33),
+                                          (1, 8, 128, 900, 12), (1, 16, 64, 700, 16)])
+def test_merge_of_many_splits(gpu, Hkv, G, D, S, ns):
+    vt, tio, pipelines, torch = gpu
+    wl = workloads.c2_decode_attention(seed=13, B=2, Hkv=Hkv, G=G, S=S, D=D)
+    ref = run_workload(wl)
+    res = pipelines.run_decode_attention(tio.DeviceWorkload(wl), n_splits=ns)
+    p = res["pipeline"]
+    first = p.out.clone()
+    # one rounding of the result (2^-9), and for D = 128 one of each probability, averaged: 2e-3 as at full size
+    assert np.max(np.abs(tio.to_host_f64(p.out) - ref["out"])) <= 2e-3
+    assert np.max(np.abs(tio.to_host_f64(p.lse) - ref["lse"])) <= 1e-3
+    for _ in range(3):
+        p.run()
+    torch.cuda.synchronize()
+    assert torch.equal(p.out, first)
