@@ -572,14 +572,15 @@ int plan_b(const vt_desc& d, GemmGroup* g, int64_t* K, int64_t* N) {
 namespace vt {
 int ln_gemm_launch(const vt_desc& A, const vt_desc& B, void* C, int c_dtype, float eps, hipStream_t st);
 int ln_gemm_wide_launch(const vt_desc& A, const vt_desc& B, void* C, int c_dtype, float eps, hipStream_t st);
-int gemm_tile_launch(const gemm::GemmParams& P, const gemm::OutMap* O, int dtype, hipStream_t st);
+int gemm_tile_launch(const gemm::GemmParams& P, const gemm::OutMap* O, int dtype, hipStream_t st, int64_t below_ns = 0);
 }
 
 namespace vt {
 
 // C = A . B with the result written through the output descriptor Cd (pieces split the columns;
 // the caller has checked that the map is one to one).  One group, operands' dtype for the output.
-int gemm_store_launch(const vt_desc& A, const vt_desc& B, const vt_desc& Cd, hipStream_t st) {
+// below_ns: VT_ERR_UNSUPPORTED unless small tiles are expected to take less than that (0: no limit).
+int gemm_store_launch(const vt_desc& A, const vt_desc& B, const vt_desc& Cd, int64_t below_ns, hipStream_t st) {
   const int dt = A.dtype;
   GemmParams P;
   memset(&P, 0, sizeof(P));
@@ -620,8 +621,8 @@ int gemm_store_launch(const vt_desc& A, const vt_desc& B, const vt_desc& Cd, hip
   P.n_groups = 1;
   P.N = (int32_t)N;
   P.K = (int32_t)Ka;
-  rc = gemm_tile_launch(P, &O, dt, st);
-  if (rc != VT_ERR_UNSUPPORTED) return rc;
+  rc = gemm_tile_launch(P, &O, dt, st, below_ns);
+  if (rc != VT_ERR_UNSUPPORTED || below_ns) return rc;
   set_tiles(&P, BM, BN);
   dim3 grid(P.chunk * 8);
   const bool kt = Ka % BK != 0;

@@ -33,7 +33,7 @@ VT_PROF_DECLARE(gemm_store)
 #define STORE_WG (blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z))
 
 namespace vt {
-int gemm_store_launch(const vt_desc& A, const vt_desc& B, const vt_desc& Cd, hipStream_t st);   // vt_gemm.hip
+int gemm_store_launch(const vt_desc& A, const vt_desc& B, const vt_desc& Cd, int64_t below_ns, hipStream_t st);   // vt_gemm.hip
 }
 
 namespace {
@@ -280,17 +280,22 @@ __global__ void k_zero_store_ws(uint32_t* p, size_t n) {
   if (i < n) p[i] = 0u;
 }
 
+int compute_units() {
+  static const int n_cu = [] {
+    int dev = 0, n = 256;
+    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) n = 256;
+    return n > 0 ? n : 256;
+  }();
+  return n_cu;
+}
+
 // Slices of K per block: as many as keep every workgroup on a compute unit of its own (one unit
 // draws only about 40 GB/s from memory, so the matrix has to be spread over all of them, and a
 // second workgroup on a unit would finish last; measured on the 4096 x 6144 projection, 48 column
 // blocks: 4 slices 14.75 us, 5: 14.5, 6: 16.7, 7: 16.6, 8: 15.9), at least one tile per wave, at
 // most 64.  The slices are whole tiles and need not be equal.
 int choose_k_splits(int64_t blocks, int64_t K) {
-  static const int n_cu = [] {
-    int dev = 0, n = 256;
-    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) n = 256;
-    return n > 0 ? n : 256;
-  }();
+  const int n_cu = compute_units();
   const int64_t max_splits = std::max<int64_t>(1, K / (kTileK * kWaves));
   return (int)std::min<int64_t>(std::min(std::max<int64_t>(1, n_cu / blocks), max_splits), 64);
 }
@@ -331,7 +336,7 @@ int vt_gemm_store(const vt_desc* A, const vt_desc* B, const vt_desc* C, void* wo
   if (rc0 != VT_OK) return rc0;
   // many rows: the tiled GEMM with the map applied in its store stage (this kernel would read B
   // once per 16 rows)
-  if (M > kTiledFrom) return gemm_store_launch(*A, *B, *C, (hipStream_t)stream);
+  if (M > kTiledFrom) return gemm_store_launch(*A, *B, *C, 0, (hipStream_t)stream);
 
   StoreParams P;
   memset(&P, 0, sizeof(P));
@@ -409,6 +414,15 @@ int vt_gemm_store(const vt_desc* A, const vt_desc* B, const vt_desc* C, void* wo
   P.k_per_split = kps;
   P.tickets = static_cast<uint32_t*>(workspace);
   P.partial = reinterpret_cast<float*>(static_cast<char*>(workspace) + ticket_area(rbs * cbs));
+  // Several blocks of 16 rows: this kernel reads B once for each of them, and takes the time its busiest
+  // compute unit needs to draw its share (40 GB/s, 6.5 us around it).  The tiled kernel takes over
+  // where it is expected to be faster (us here / there: 4096 x 6144 with 32 rows 24.4 / 27.5, 48 rows
+  // 35.3 / 29.0, 90 rows 64.5 / 27.0; 2048 x 3072 with 48 rows 12.7 / 14.3, 90 rows 20.3 / 14.5).
+  if (rbs > 1) {
+    const int64_t rounds = (rbs * cbs * ns_eff + compute_units() - 1) / compute_units();
+    rc = gemm_store_launch(*A, *B, *C, 6500 + rounds * kps * (kBN * 2) / 40, (hipStream_t)stream);
+    if (rc != VT_ERR_UNSUPPORTED) return rc;
+  }
   dim3 grid((unsigned)ns_eff, (unsigned)cbs, (unsigned)rbs);
   hipStream_t st = (hipStream_t)stream;
   if (A->dtype == VT_BF16) hipLaunchKernelGGL((k_gemm_store<bf16_t>), grid, dim3(kWaves * 64), 0, st, P);

@@ -310,8 +310,8 @@ int launch_tile(GemmParams P, const OutMap& O, int bm, int bn, hipStream_t st) {
 //   400 x 6144     100 / 70 / 46 / 40 / 50 / 54       1024 x 4096    91 / 70 / 49 / 66 / 58 / 72
 //   2048 x 4096     93 / 80 / 90 / 103 / 106 / 126    4000 x 4096   121 / 147 / 166 / 188 / 184 / 225
 //   8 x about 50 x 14336 (grouped)                                  251 / 298 / 217 / 213 / 210 / 239
-// 0 x 0: the 256 x 256 kernel.
-void choose_tile(const GemmParams& P, int* bm, int* bn) {
+// 0 x 0: the 256 x 256 kernel.  Returns the time of one K step in ns.
+int64_t choose_tile(const GemmParams& P, int* bm, int* bn) {
   static const int n_cu = [] {
     int dev = 0, n = 256;
     if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) n = 256;
@@ -332,6 +332,7 @@ void choose_tile(const GemmParams& P, int* bm, int* bn) {
     }
   }
   if (*bm == 256 && *bn == 256) *bm = *bn = 0;
+  return best;
 }
 
 // bytes that an axis can span, or -1 for an index table on it
@@ -348,8 +349,9 @@ int64_t axis_span(const AxisMap<ND>& a) {
 namespace vt {
 
 // The product of P (operands planned, tiles not yet cut) on smaller tiles, or VT_ERR_UNSUPPORTED when
-// the 256 x 256 kernel is the better one or the only one.
-int gemm_tile_launch(const GemmParams& P, const OutMap* O, int dtype, hipStream_t st) {
+// the 256 x 256 kernel is the better one or the only one, or when the estimate (3.5 us and the time of
+// the K steps) is not below below_ns (if that is not 0).
+int gemm_tile_launch(const GemmParams& P, const OutMap* O, int dtype, hipStream_t st, int64_t below_ns) {
   const char* no = "vt_gemm: outside the small-tile kernel";
   if (P.K % BK || P.K < BK || P.K > kMaxSteps * BK || P.N < 8) return fail(VT_ERR_UNSUPPORTED, no);
   for (int i = 0; i < P.n_groups; ++i) {
@@ -360,7 +362,8 @@ int gemm_tile_launch(const GemmParams& P, const OutMap* O, int dtype, hipStream_
     if (span >= (1ll << 32)) return fail(VT_ERR_UNSUPPORTED, no);
   }
   int bm = 0, bn = 0;
-  choose_tile(P, &bm, &bn);
+  const int64_t step_ns = choose_tile(P, &bm, &bn);
+  if (below_ns && 3500 + step_ns * (P.K / BK) >= below_ns) return fail(VT_ERR_UNSUPPORTED, no);
   if (!bm) return fail(VT_ERR_UNSUPPORTED, no);
   OutMap none;
   if (!O) memset(&none, 0, sizeof(none));

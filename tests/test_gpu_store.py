@@ -186,3 +186,17 @@ def test_decode_segment_full_size(gpu):
     got = tio.to_host_f64(p.out)
     err = np.abs(got - r2["out"])
     assert (err <= 1e-2 + 1e-2 * np.abs(r2["out"])).all(), err.max()
+
+
+@pytest.mark.parametrize("B,T", [(1, 33), (2, 45), (1, 128)])
+def test_a_few_row_blocks_of_a_wide_projection(gpu, B, T):
+    """33 to 128 rows of a projection wide enough that the small tiles take over from the kernel that
+    reads the weight once per 16 rows: stored values to one rounding and fp32 sums, everything else kept."""
+    vt, tio, pipelines, torch = gpu
+    wl = workloads.qkv_proj_store(seed=7, B=B, hidden=2048, Hq=32, Hkv=8, D=128, cap=160, pos=31, T=T)
+    ref = run_workload(wl)
+    dw = tio.DeviceWorkload(wl)
+    p = pipelines.GemmStore(dw)
+    p.run()
+    torch.cuda.synchronize()
+    compare_stored(tio, dw, wl, ref)
