@@ -123,3 +123,18 @@ def test_every_benchmark_chain_kind_replays_bitwise(gpu):
                 assert torch.equal(o, w), (wl.name, rep)
             v.run()                       # eager work between the replays
             torch.cuda.synchronize()
+
+
+def test_calls_go_to_the_current_stream(gpu):
+    """Without a stream argument a call is queued on torch's current stream, whichever thread or context set it."""
+    import threading
+    vt, torch = gpu[0], gpu[-1]
+    handle = lambda: vt.binding._stream(None).value or 0
+    side, seen = torch.cuda.Stream(), []
+    assert handle() == torch.cuda.default_stream().cuda_stream
+    with torch.cuda.stream(side):
+        assert handle() == side.cuda_stream
+        t = threading.Thread(target=lambda: seen.append(handle()))       # another thread has its own current stream
+        t.start()
+        t.join()
+    assert seen == [torch.cuda.default_stream().cuda_stream] and handle() == seen[0]
