@@ -26,7 +26,7 @@
 //                   already holds in exactly that layout.
 // Head dims 128 and 64 (a template argument): a tile of 64-wide heads is half as many bytes, eight
 // lanes read a K row and a lane's piece of a V row is 8 bytes.  Serving 16 sequences of 2368 paged
-// keys of 64-wide heads (77.7 MB): 18.0 us = 4.3 TB/s, against 10.8 ms when only 128 was planned
+// keys of 64-wide heads (77.7 MB): 17.6 us = 4.4 TB/s, against 10.8 ms when only 128 was planned
 // and every element went through the generic evaluator below.
 // The workgroup that finishes last for a (b, g) merges the splits' partial results (a ticket
 // counter per (b, g) in the workspace; no second launch, no spinning).
@@ -98,8 +98,13 @@ struct AttnSeg {
   int64_t k_sb, k_sh, v_sb, v_sh;   // bytes per batch / per stored head
   PagedOperand kp, vp;
 };
-struct AttnParams {
-  AttnSeg seg[kMaxSegs];
+// NS = segments there is room for: the arguments travel with every launch (and are read through the
+// scalar cache in front of the first load), and nearly every cache has one or two.
+template <int NS>
+struct AttnSegs {
+  AttnSeg seg[NS];
+};
+struct AttnArgs {
   int32_t n_seg;
   const char* q_ptr;
   int64_t q_sb, q_sh;    // bytes
@@ -111,6 +116,9 @@ struct AttnParams {
   void* out;             // [B, Hq, D]
   float* lse;            // [B, Hq] or NULL
 };
+template <int NS>
+struct AttnParamsT : AttnSegs<NS>, AttnArgs {};
+typedef AttnParamsT<kMaxSegs> AttnParams;
 
 template <typename T>
 struct Mfma;
@@ -211,14 +219,16 @@ __device__ __forceinline__ const char* paged_base(const PagedOperand& o, const c
 }
 
 // the tile at w.r0 moved: paged operands look their page up again
-__device__ __forceinline__ void walk_locate(const AttnParams& P, TileWalk& w, int b, int g) {
+template <int NS>
+__device__ __forceinline__ void walk_locate(const AttnParamsT<NS>& P, TileWalk& w, int b, int g) {
   const AttnSeg& sg = P.seg[w.seg];
   if (w.paged & 1) w.k = paged_base(sg.kp, sg.k, sg.k_st, b, g / sg.k_hdiv, w.r0 - sg.t_lo);
   if (w.paged & 2) w.v = paged_base(sg.vp, sg.v, sg.v_st, b, g / sg.v_hdiv, w.r0 - sg.t_lo);
 }
 
 // The tile that starts at row r0 of segment seg (r0 inside the segment and the split).
-__device__ __forceinline__ void walk_place(const AttnParams& P, TileWalk& w, int seg, int r0, int t_end) {
+template <int NS>
+__device__ __forceinline__ void walk_place(const AttnParamsT<NS>& P, TileWalk& w, int seg, int r0, int t_end) {
   w.seg = seg;
   w.r0 = r0;
   w.cut = 0x7fffffff;
@@ -238,7 +248,8 @@ __device__ __forceinline__ void walk_place(const AttnParams& P, TileWalk& w, int
 }
 
 // The tile after the current one; w.seg = P.n_seg when there is none.
-__device__ __forceinline__ void walk_next(const AttnParams& P, TileWalk& w, int t_end) {
+template <int NS>
+__device__ __forceinline__ void walk_next(const AttnParamsT<NS>& P, TileWalk& w, int t_end) {
   const int r0 = w.end;
   int seg = w.seg2 >= 0 ? w.seg2 : w.seg;
   while (seg < P.n_seg && r0 >= min(P.seg[seg].t_hi, t_end)) ++seg;
@@ -250,7 +261,8 @@ __device__ __forceinline__ void walk_next(const AttnParams& P, TileWalk& w, int 
 }
 
 // Row pointers and pitches of the tile that walk_place / walk_next chose.
-__device__ __forceinline__ void walk_fetch(const AttnParams& P, TileWalk& w, int b, int g) {
+template <int NS>
+__device__ __forceinline__ void walk_fetch(const AttnParamsT<NS>& P, TileWalk& w, int b, int g) {
   const AttnSeg& sg = P.seg[w.seg];
   w.k = sg.k + b * sg.k_sb + (g / sg.k_hdiv) * sg.k_sh;
   w.v = sg.v + b * sg.v_sb + (g / sg.v_hdiv) * sg.v_sh;
@@ -268,7 +280,8 @@ __device__ __forceinline__ void walk_fetch(const AttnParams& P, TileWalk& w, int
 }
 
 // n tiles forward (n >= 0), then the pointers of the tile reached
-__device__ __forceinline__ void walk_advance(const AttnParams& P, TileWalk& w, int n, int b, int g, int t_end) {
+template <int NS>
+__device__ __forceinline__ void walk_advance(const AttnParamsT<NS>& P, TileWalk& w, int n, int b, int g, int t_end) {
   if (w.seg >= P.n_seg) return;
   const bool fetched = n > 0 && w.k != nullptr;
   if (w.seg2 < 0 && w.r0 + kTile * (n + 1) <= w.seg_end) {
@@ -286,9 +299,9 @@ __device__ __forceinline__ void walk_advance(const AttnParams& P, TileWalk& w, i
 }
 
 // D = head dim (64 or 128).  MANY: more than eight splits, the merge below divides them among its threads.
-template <typename T, int D, bool MANY, int WAVES, int OCC>
+template <typename T, int D, bool MANY, int NS, int WAVES, int OCC>
 __global__ void __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(OCC, OCC)))
-k_decode_attn(const AttnParams P) {
+k_decode_attn(const AttnParamsT<NS> P) {
   typedef Mfma<T> M;
   typedef typename M::vec opvec;
   constexpr int kD = D;
@@ -306,9 +319,15 @@ k_decode_attn(const AttnParams P) {
   // the tile walk below reads the segment table with data-dependent indices: have its first lines
   // (three segments) and the scalars behind the table in the scalar cache before the chain of
   // dependent reads starts
-  static_assert(offsetof(AttnParams, n_seg) >= 1024 && offsetof(AttnParams, n_seg) / 64 * 64 + 68 <= sizeof(AttnParams),
-                "the warmed lines lie inside the arguments");
-  warm_kernarg_16_and_2(offsetof(AttnParams, n_seg) / 64 * 64);
+  typedef AttnParamsT<NS> Params;
+  constexpr int kScalars = sizeof(AttnSegs<NS>) / 64 * 64;
+  if constexpr (NS > 2) {
+    static_assert(NS <= 2 || (sizeof(AttnSegs<NS>) >= 1024 && kScalars + 68 <= sizeof(Params)), "the warmed lines lie inside the arguments");
+    warm_kernarg_16_and_2(kScalars);
+  } else {
+    static_assert(NS > 2 || 11 * 64 + 4 <= sizeof(Params), "the warmed lines lie inside the arguments");
+    warm_kernarg_12();
+  }
   VT_PROF_BEGIN();
   VT_PROF(0);
   const int split = blockIdx.x, g = blockIdx.y, b = blockIdx.z;
@@ -1159,10 +1178,23 @@ static int launch_attention(const vt_desc* Q, const vt_desc* K, const vt_desc* V
   dim3 grid(ns_eff, Hkv, (unsigned)B);
   // compiled for three waves per SIMD (two workgroups of four waves per compute unit and room for
   // a third); the build for two measures the same on the benchmark's shape
+  // (2 KB less with every launch: the call 6.5 -> 4.3 us of host time, the kernel 25.75 -> 25.55 us at
+  // 64 units x 4096 keys and 17.95 -> 17.63 us at 128 x 2368 paged keys of 64-wide heads)
+  AttnParamsT<2> P2;
+  const bool few = P.n_seg <= 2;
+  if (few) {
+    static_cast<AttnArgs&>(P2) = P;
+    for (int i = 0; i < 2; ++i) P2.seg[i] = P.seg[i];
+  }
+#define VT_ATTN_NS(TT, DD, MM, OCC)                                                                                   \
+  do {                                                                                                                \
+    if (few) hipLaunchKernelGGL((k_decode_attn<TT, DD, MM, 2, kWaves, OCC>), grid, dim3(kWaves * 64), 0, st, P2);     \
+    else hipLaunchKernelGGL((k_decode_attn<TT, DD, MM, kMaxSegs, kWaves, OCC>), grid, dim3(kWaves * 64), 0, st, P);   \
+  } while (0)
 #define VT_ATTN(TT, DD, OCC)                                                                                          \
   do {                                                                                                                \
-    if (ns_eff > 8) hipLaunchKernelGGL((k_decode_attn<TT, DD, true, kWaves, OCC>), grid, dim3(kWaves * 64), 0, st, P); \
-    else hipLaunchKernelGGL((k_decode_attn<TT, DD, false, kWaves, OCC>), grid, dim3(kWaves * 64), 0, st, P);          \
+    if (ns_eff > 8) VT_ATTN_NS(TT, DD, true, OCC);                                                                    \
+    else VT_ATTN_NS(TT, DD, false, OCC);                                                                              \
   } while (0)
   if (P.D == 64) {
     if (Q->dtype == VT_BF16) VT_ATTN(bf16_t, 64, 4);
@@ -1172,6 +1204,7 @@ static int launch_attention(const vt_desc* Q, const vt_desc* K, const vt_desc* V
     else VT_ATTN(f16_t, 128, 3);
   }
 #undef VT_ATTN
+#undef VT_ATTN_NS
   return check_launch(who);
 }
 

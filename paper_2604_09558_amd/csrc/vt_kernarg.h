@@ -65,6 +65,30 @@ __device__ __forceinline__ void warm_kernarg_8() {
       : "memory");
 }
 
+// lines 0..11 (bytes 0..767): 11 * 64 + 4 <= sizeof(arguments)
+__device__ __forceinline__ void warm_kernarg_12() {
+  typedef __attribute__((address_space(4))) const char* karg_t;
+  const uint64_t p = (uint64_t)(karg_t)__builtin_amdgcn_kernarg_segment_ptr();
+  uint32_t d[12];
+  asm volatile(
+      "s_load_dword %0, %12, 0x0\n\t"
+      "s_load_dword %1, %12, 0x40\n\t"
+      "s_load_dword %2, %12, 0x80\n\t"
+      "s_load_dword %3, %12, 0xc0\n\t"
+      "s_load_dword %4, %12, 0x100\n\t"
+      "s_load_dword %5, %12, 0x140\n\t"
+      "s_load_dword %6, %12, 0x180\n\t"
+      "s_load_dword %7, %12, 0x1c0\n\t"
+      "s_load_dword %8, %12, 0x200\n\t"
+      "s_load_dword %9, %12, 0x240\n\t"
+      "s_load_dword %10, %12, 0x280\n\t"
+      "s_load_dword %11, %12, 0x2c0\n\t"
+      "s_waitcnt lgkmcnt(0)"
+      : "=&s"(d[0]), "=&s"(d[1]), "=&s"(d[2]), "=&s"(d[3]), "=&s"(d[4]), "=&s"(d[5]), "=&s"(d[6]), "=&s"(d[7]), "=&s"(d[8]), "=&s"(d[9]), "=&s"(d[10]), "=&s"(d[11])
+      : "s"(p)
+      : "memory");
+}
+
 // lines 0..26 (bytes 0..1727): two block walks (26 * 64 + 4 <= sizeof(arguments))
 __device__ __forceinline__ void warm_kernarg_27() {
   typedef __attribute__((address_space(4))) const char* karg_t;
