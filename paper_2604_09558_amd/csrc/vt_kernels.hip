@@ -558,9 +558,16 @@ VT_PROF_DECLARE(add_rowsum)
 
 // WIDE: both operands keep blocks of at least 64 columns.  WALK: block addresses from the host's
 // segments (wx, wy) instead of the evaluator on X and Y.
+template <bool WALK>
+struct RowMaps {                                       // (2.6 KB that the segments make unnecessary)
+  DevDesc x, y;
+};
+template <>
+struct RowMaps<true> {};
+
 template <bool WIDE, bool WALK>
 __global__ void __launch_bounds__(256) k_add_rowsum_blocks(const RowWalk wx, const RowWalk wy, float* __restrict__ out, uint32_t R, uint32_t C,
-                                                           uint32_t bx, uint32_t by, const DevDesc X, const DevDesc Y) {
+                                                           uint32_t bx, uint32_t by, const RowMaps<WALK> M) {
   VT_PROF_BEGIN();
   VT_PROF(0);
   if (WALK) {
@@ -573,8 +580,8 @@ __global__ void __launch_bounds__(256) k_add_rowsum_blocks(const RowWalk wx, con
   const kernarg_walk_t kwalk = (kernarg_walk_t)__builtin_amdgcn_kernarg_segment_ptr();
   (void)wx, (void)wy;
   __shared__ DevDesc maps[2];                         // unused (and not allocated) with WALK
-  if (!WALK) {
-    const DevDesc* const src[2] = {&X, &Y};
+  if constexpr (!WALK) {
+    const DevDesc* const src[2] = {&M.x, &M.y};
     stage_maps(maps, src);
   }
   VT_PROF(1);
@@ -620,6 +627,72 @@ __global__ void __launch_bounds__(256) k_add_rowsum_blocks(const RowWalk wx, con
   if (lane == 0) out[row] = p;
   VT_PROF(4);
   VT_PROF_FLUSH(add_rowsum, blockIdx.x);
+}
+
+// The same sum, same order, for a few long rows: one workgroup of 16 waves per row.  A wave per row keeps
+// sixteen loads in flight and pays one memory latency per 512 columns, which is all there is when the
+// rows do not fill the chip; here every wave loads 512 columns of its own at once, the sums x + y of
+// 8192 columns meet in LDS, and the first wave adds them in ascending order.
+constexpr uint32_t kSplitWaves = 16;
+template <bool WIDE>
+__global__ void __launch_bounds__(kSplitWaves * 64) k_add_rowsum_split(const RowWalk wx, const RowWalk wy, float* __restrict__ out, uint32_t C,
+                                                                     uint32_t bx, uint32_t by) {
+  static_assert(2 * sizeof(RowWalk) + sizeof(float*) + 3 * sizeof(uint32_t) <= 512, "the walked arguments lie in the first eight lines");
+  warm_kernarg_8();
+  const kernarg_walk_t kwalk = (kernarg_walk_t)__builtin_amdgcn_kernarg_segment_ptr();
+  (void)wx, (void)wy;
+  __shared__ float t_sh[kSplitWaves * 8][64];
+  const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6, row = blockIdx.x;
+  float p = 0.0f;
+  for (uint32_t base = 0; base < C; base += kSplitWaves * 512) {
+    const uint32_t c0 = base + wave * 512;
+    if (c0 < C) {
+      float xv[8], yv[8];
+      BlockCursor cx, cy;
+      // 64 blocks of at least 8 columns are the wave's 512 and more; smaller ones are found per window
+      const bool once_x = WIDE || bx >= 3, once_y = WIDE || by >= 3;
+      if (once_x) cursor_walk(kwalk, row, C, bx, c0 >> bx, lane, cx);
+      if (once_y) cursor_walk(kwalk + 1, row, C, by, c0 >> by, lane, cy);
+#pragma unroll
+      for (uint32_t u = 0; u < 8; ++u) {
+        const uint32_t cw = c0 + 64 * u;
+        if (cw < C) {
+          if (WIDE) {                                  // C is a multiple of the blocks: the window is whole
+            xv[u] = cursor_read_window(cx, cw, lane, bx);
+            yv[u] = cursor_read_window(cy, cw, lane, by);
+          } else {
+            if (!once_x) cursor_walk(kwalk, row, C, bx, cw >> bx, lane, cx);
+            if (!once_y) cursor_walk(kwalk + 1, row, C, by, cw >> by, lane, cy);
+            const uint32_t col = min(cw + lane, C - 1);
+            xv[u] = cursor_read(cx, col, bx);
+            yv[u] = cursor_read(cy, col, by);
+          }
+        }
+      }
+#pragma unroll
+      for (uint32_t u = 0; u < 8; ++u)
+        if (c0 + 64 * u < C) t_sh[wave * 8 + u][lane] = xv[u] + yv[u];
+    }
+    __syncthreads();
+    if (wave == 0) {
+      const uint32_t cols = min(C - base, kSplitWaves * 512), whole = cols / 64;
+      uint32_t i = 0;
+      for (; i + 8 <= whole; i += 8) {
+        float t[8];
+#pragma unroll
+        for (uint32_t u = 0; u < 8; ++u) t[u] = t_sh[i + u][lane];
+#pragma unroll
+        for (uint32_t u = 0; u < 8; ++u) p = p + t[u];
+      }
+      for (; i < whole; ++i) p = p + t_sh[i][lane];
+      if (whole * 64 + lane < cols) p = p + t_sh[whole][lane];
+    }
+    if (base + kSplitWaves * 512 < C) __syncthreads();
+  }
+  if (wave != 0) return;
+#pragma unroll
+  for (int s = 32; s >= 1; s >>= 1) p = p + __shfl_xor(p, s, 64);
+  if (lane == 0) out[row] = p;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1018,12 +1091,29 @@ int vt_elementwise(int kind, const vt_desc* x, const vt_desc* y, float eps, void
     const bool walk = resolve_row_walk(*x, 1ll << bx, &wx) && resolve_row_walk(*y, 1ll << by, &wy);
     if (walk || (bx >= 4 && by >= 4)) {
       const bool wide = bx >= 6 && by >= 6;
-#define VT_ROWSUM(WIDE, WALK) \
-  hipLaunchKernelGGL((k_add_rowsum_blocks<WIDE, WALK>), grid, dim3(256), 0, st, wx, wy, (float*)out, R, C, bx, by, X, Y)
-      if (wide && walk) VT_ROWSUM(true, true);
-      else if (wide) VT_ROWSUM(true, false);
-      else if (walk) VT_ROWSUM(false, true);
-      else VT_ROWSUM(false, false);
+#define VT_ROWSUM(WIDE, WALK, MAPS) \
+  hipLaunchKernelGGL((k_add_rowsum_blocks<WIDE, WALK>), grid, dim3(256), 0, st, wx, wy, (float*)out, R, C, bx, by, MAPS)
+      // A workgroup per row while two of them per compute unit hold all rows (four for blocks of 8 to 32
+      // columns, whose addresses a wave hands round column by column), and rows longer than what a wave
+      // has in flight.  us, wave / workgroup per row: 16 x 5120 11.2 / 4.9, 512 x 5120 12.3 / 7.0, 512 x 768
+      // 6.0 / 4.7, 512 x 3592 in blocks of 8 20.5 / 6.6, but 768 x 768 6.1 / 7.0, 2048 x 5120 16.6 / 21.9
+      static const uint32_t n_cu = [] {
+        int dev = 0, n = 256;
+        if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) n = 256;
+        return (uint32_t)(n > 0 ? n : 256);
+      }();
+      if (walk && C > 512 && R <= (!wide && bx >= 3 && by >= 3 ? 4 : 2) * n_cu) {
+        if (wide) hipLaunchKernelGGL((k_add_rowsum_split<true>), dim3(R), dim3(kSplitWaves * 64), 0, st, wx, wy, (float*)out, C, bx, by);
+        else hipLaunchKernelGGL((k_add_rowsum_split<false>), dim3(R), dim3(kSplitWaves * 64), 0, st, wx, wy, (float*)out, C, bx, by);
+      } else if (walk) {
+        if (wide) VT_ROWSUM(true, true, RowMaps<true>());
+        else VT_ROWSUM(false, true, RowMaps<true>());
+      } else {
+        RowMaps<false> maps;
+        maps.x = X, maps.y = Y;
+        if (wide) VT_ROWSUM(true, false, maps);
+        else VT_ROWSUM(false, false, maps);
+      }
 #undef VT_ROWSUM
     } else hipLaunchKernelGGL(k_add_rowsum, grid, dim3(256), 0, st, X, Y, (float*)out, R, C);
     return check_launch("vt_elementwise(add_rowsum)");

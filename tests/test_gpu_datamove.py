@@ -468,3 +468,20 @@ def test_add_rowsum_at_a_memory_bound_size_bit_exact(gpu):
     lean.run()
     torch.cuda.synchronize()
     assert np.array_equal(bits(lean.consumer.out.cpu().numpy()), bits(ref))
+
+
+# a few long rows (a workgroup per row): blocks of 128, 8, 1 and 4 columns, a ragged last window, one
+# column more than one wave's share, rows longer than one round of the workgroup; and rows just too many
+@pytest.mark.parametrize("A,B,C0,ny", [(11, 5, 128, 64), (27, 3, 96, 1000), (7, 2, 75, 20), (8, 1, 64, 1), (70, 2, 128, 64), (90, 1, 96, 4),
+                                       (5, 600, 128, 64)])
+def test_add_rowsum_few_long_rows_bit_exact(gpu, A, B, C0, ny):
+    vt, tio, torch = gpu
+    wl = workloads.rowsum_chain_large(seed=2, A=A, B=B, C0=C0, ny=ny)
+    ref = run_workload(wl)["out"]
+    dw = tio.DeviceWorkload(wl)
+    v, z = dw.build("V"), dw.build("Z")
+    out = torch.full((B + 1,), 7.0, device="cuda:0")
+    vt.vt_elementwise(vt.EW_ADD_ROWSUM, v, z, 0.0, out)
+    torch.cuda.synchronize()
+    got = out.cpu().numpy()
+    assert np.array_equal(bits(got[:B]), bits(ref)) and got[B] == 7.0
