@@ -21,10 +21,18 @@ struct GemmGroup {
   int32_t b_kmajor;   // B's contiguous axis is K (all groups of a launch agree)
 };
 
-struct GemmParams {
-  GemmGroup g[kMaxGroups];
+// (NG = groups there is room for: the arguments are copied with every launch and read through the
+// scalar cache before a workgroup knows its tile)
+struct GemmSizes {
   int32_t n_groups, N, K, tiles_n, total_tiles, chunk, c_f32, pad;
 };
+template <int NG>
+struct GemmGroups {
+  GemmGroup g[NG];
+};
+template <int NG>
+struct GemmParamsT : GemmGroups<NG>, GemmSizes {};
+typedef GemmParamsT<kMaxGroups> GemmParams;
 
 // Output written through a map (producer-side store, Sec. 4.2): columns [col_lo, col_hi) of C
 // live in one physical tensor, element (m, n) at base + 2 * (row(m) + col(n - col_lo)).
@@ -37,16 +45,18 @@ struct OutMap {
   OutPiece p[4];
   int32_t n, pad;
 };
+struct NoMap {};
 
 // Which tile workgroup `wg` takes: each compute die (own L2; workgroups are dealt to them in turn)
 // works on a contiguous band of the list, walked in groups of kGroupRows tile rows.  False: none.
-__device__ __forceinline__ bool pick_tile(const GemmParams& P, int wg, int* group, int* tm, int* tn) {
+template <int NG>
+__device__ __forceinline__ bool pick_tile(const GemmParamsT<NG>& P, int wg, int* group, int* tm, int* tn) {
   const int slot = wg >> 3;
   const int idx = (wg & 7) * P.chunk + slot;
   if (slot >= P.chunk || idx >= P.total_tiles) return false;
   int gi = 0;
 #pragma unroll
-  for (int i = 1; i < kMaxGroups; ++i)
+  for (int i = 1; i < NG; ++i)
     if (i < P.n_groups && idx >= P.g[i].tile_begin) gi = i;
   const int local = idx - P.g[gi].tile_begin;
   const int width = kGroupRows * P.tiles_n;

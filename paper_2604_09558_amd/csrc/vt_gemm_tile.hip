@@ -57,8 +57,9 @@ __device__ __forceinline__ int row_key(int r) { return r >> 1 & 7; }
 template <int BN>
 __device__ __forceinline__ int k_key(int k) { return BN == 64 ? (k >> 1 & 1) << 2 : (k & 3) << 2; }
 
-template <typename T, bool C_F32, bool MAPPED, bool B_KMAJOR, int BM, int BN, int WM, int STAGES>
-__global__ void __launch_bounds__(256) k_gemm_tile(const GemmParams P, const OutMap O) {
+template <typename T, bool C_F32, bool MAPPED, bool B_KMAJOR, int NG, int BM, int BN, int WM, int STAGES>
+__global__ void __launch_bounds__(256)
+k_gemm_tile(const GemmParamsT<NG> P, const typename std::conditional<MAPPED, OutMap, NoMap>::type O) {
   typedef Mma<T> M_;
   typedef typename M_::vec opvec;
   constexpr int kABytes = BM * BK * 2, kStage = (BM + BN) * BK * 2;
@@ -237,7 +238,7 @@ __global__ void __launch_bounds__(256) k_gemm_tile(const GemmParams P, const Out
   __builtin_amdgcn_s_waitcnt(0x0F70);                 // requests still target this workgroup's LDS
 
   // ---- stage 3 (as in vt_gemm.hip): a lane holds column l32 of a block and rows 8 j + 4 lh + i
-  if (MAPPED) {
+  if constexpr (MAPPED) {
     __syncthreads();
     int64_t* rowoff = reinterpret_cast<int64_t*>(lds);               // [pieces][BM]
     for (int pc = 0; pc < O.n; ++pc)
@@ -284,13 +285,18 @@ __global__ void __launch_bounds__(256) k_gemm_tile(const GemmParams P, const Out
     }
 }
 
-template <typename T, bool C_F32, bool MAPPED, bool B_KMAJOR>
-int launch_tile(GemmParams P, const OutMap& O, int bm, int bn, hipStream_t st) {
-  set_tiles(&P, bm, bn);
+template <typename T, bool C_F32, bool MAPPED, bool B_KMAJOR, int NG = 1>
+int launch_tile(GemmParams P8, const typename std::conditional<MAPPED, OutMap, NoMap>::type& O, int bm, int bn, hipStream_t st) {
+  if constexpr (NG == 1 && !MAPPED)
+    if (P8.n_groups > 1) return launch_tile<T, C_F32, MAPPED, B_KMAJOR, kMaxGroups>(P8, O, bm, bn, st);
+  set_tiles(&P8, bm, bn);
+  GemmParamsT<NG> P;
+  static_cast<GemmSizes&>(P) = P8;
+  for (int i = 0; i < NG; ++i) P.g[i] = P8.g[i];
   const dim3 grid(P.chunk * 8);
 #define VT_TILE(BM_, BN_, WM_, S_)                                                                                  \
   if (bm == BM_ && bn == BN_) {                                                                                     \
-    hipLaunchKernelGGL((k_gemm_tile<T, C_F32, MAPPED, B_KMAJOR, BM_, BN_, WM_, S_>), grid, dim3(256), 0, st, P, O); \
+    hipLaunchKernelGGL((k_gemm_tile<T, C_F32, MAPPED, B_KMAJOR, NG, BM_, BN_, WM_, S_>), grid, dim3(256), 0, st, P, O); \
     return check_launch(MAPPED ? "vt_gemm_store" : "vt_gemm");                                                      \
   }
   VT_TILE(256, 128, 2, 3)
@@ -365,8 +371,7 @@ int gemm_tile_launch(const GemmParams& P, const OutMap* O, int dtype, hipStream_
   const int64_t step_ns = choose_tile(P, &bm, &bn);
   if (below_ns && 3500 + step_ns * (P.K / BK) >= below_ns) return fail(VT_ERR_UNSUPPORTED, no);
   if (!bm) return fail(VT_ERR_UNSUPPORTED, no);
-  OutMap none;
-  if (!O) memset(&none, 0, sizeof(none));
+  const NoMap none;
   const bool km = P.g[0].b_kmajor != 0;
 #define VT_TILE_T(TT)                                                                            \
   do {                                                                                           \
