@@ -223,13 +223,14 @@ int vt_gemm(const vt_desc* const* A, const vt_desc* const* B, void* const* C, in
  * Query heads whose K/V rows coincide (a broadcast digit in the map) share one read.
  * K and V may be split into pieces along the context (Concat), and a piece may reach its rows
  * through a page table: an index_select over a pool of pages of 32 k rows, in context order
- * after the usual reshape / permute (a paged KV cache); the kernel then looks up the page of
- * every 32-row tile.  Anything else that a descriptor can hold (another head dim up to 1024, more
+ * after the usual reshape / permute (a paged KV cache), or an index_select over the batch dim (one
+ * page or cache slot per sequence); the kernel then looks up the page of every 32-row tile.  Anything else that a descriptor can hold (another head dim up to 1024, more
  * index stages, tables elsewhere, rows that are not contiguous along D, pieces along other dims)
  * runs on a generic kernel that applies the whole map per element: same result to rounding,
  * far slower, no context splits; vt_decode_attn_plan reports VT_ERR_UNSUPPORTED for such operands.
- * D = 64 also runs there when the workspace or the alignment of out is not what the planned kernel
- * needs (for D = 128 that is an error), so vt_decode_attn_plan reports VT_ERR_UNSUPPORTED for it too.
+ * D = 64 and tables over the batch also run there when the workspace or the alignment of out is not
+ * what the planned kernel needs (otherwise that is an error), so vt_decode_attn_plan reports
+ * VT_ERR_UNSUPPORTED for them too.
  * workspace: device pointer (16-byte aligned) of at least vt_decode_attn_workspace(...) bytes,
  * holding arrival counters and the per-split partial results, prepared once with
  * vt_decode_attn_workspace_init; the split that finishes last for a (batch, kv head) merges

@@ -301,3 +301,43 @@ def test_merge_of_many_splits(gpu, Hkv, G, D, S, ns):
         p.run()
     torch.cuda.synchronize()
     assert torch.equal(p.out, first)
+
+
+@pytest.mark.parametrize("B,Hkv,G,D,page", [(3, 2, 4, 128, 64), (5, 1, 7, 64, 32), (2, 2, 1, 128, 128)])
+def test_one_page_per_sequence(gpu, B, Hkv, G, D, page):
+    """The table digit sits in the batch dim: planned, with the probabilities in two halves as the generic
+    kernel (which such maps ran on, and still do without a workspace) keeps them in fp32."""
+    vt, tio, pipelines, torch = gpu
+    wl = workloads.paged_decode_attention(seed=12, B=B, Hkv=Hkv, G=G, pages_per_seq=1, page=page, D=D, poison_unused=True)
+    ref = run_workload(wl)
+    p = pipelines.run_decode_attention(tio.DeviceWorkload(wl))["pipeline"]
+    assert p.ws.any()
+    for _ in range(2):
+        assert np.all(np.abs(tio.to_host_f64(p.out) - ref["out"]) <= 2.0 ** -8 * np.abs(ref["out"]) + 1e-4)
+        assert np.max(np.abs(tio.to_host_f64(p.lse) - ref["lse"])) <= 1e-4
+        vt.vt_decode_attn(p.q, p.k, p.v, p.scale, p.out, p.ws, 16, lse=p.lse)
+        torch.cuda.synchronize()
+
+
+def test_cache_slots_through_a_table_and_the_new_row(gpu):
+    """Each sequence's cache slot picked through a table over the batch, the new token's row appended."""
+    vt, tio, pipelines, torch = gpu
+    B, Hkv, G, S, D, slots = 3, 2, 4, 200, 128, 7
+    wl = workloads.c2_decode_attention(seed=14, B=B, Hkv=Hkv, G=G, S=S, D=D)
+    rng = np.random.default_rng(14)
+    table = rng.permutation(slots)[:B].astype(np.int32)
+    chain = []
+    for out, op, ins, p in wl.chain:
+        if op == "slice":                                   # [slots, ...] -> the sequences' slots, then the chain as it is
+            chain.append((ins[0] + "_sel", "index_select", ins, {"dim": 0, "index": "slot"}))
+            ins = (ins[0] + "_sel",)
+        chain.append((out, op, ins, p))
+    for name in ("Kcache", "Vcache"):
+        pool = np.full((slots,) + wl.sources[name].shape[1:], 0x7FC0, dtype=np.uint16)        # NaN where no sequence lives
+        pool[table] = wl.sources[name]
+        wl.sources[name] = pool
+    wl.chain, wl.index_tables = chain, {"slot": table}
+    ref = run_workload(wl)
+    p = pipelines.run_decode_attention(tio.DeviceWorkload(wl))["pipeline"]
+    assert np.isfinite(ref["out"]).all() and p.ws.any()
+    assert np.all(np.abs(tio.to_host_f64(p.out) - ref["out"]) <= 2.0 ** -8 * np.abs(ref["out"]) + 1e-4)
