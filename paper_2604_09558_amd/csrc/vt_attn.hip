@@ -26,7 +26,7 @@
 //                   already holds in exactly that layout.
 // Head dims 128 and 64 (a template argument): a tile of 64-wide heads is half as many bytes, eight
 // lanes read a K row and a lane's piece of a V row is 8 bytes.  Serving 16 sequences of 2368 paged
-// keys of 64-wide heads (77.7 MB): 17.6 us = 4.4 TB/s, against 10.8 ms when only 128 was planned
+// keys of 64-wide heads (77.7 MB): 18.3 us = 4.2 TB/s, against 10.8 ms when only 128 was planned
 // and every element went through the generic evaluator below.
 // The workgroup that finishes last for a (b, g) merges the splits' partial results (a ticket
 // counter per (b, g) in the workspace; no second launch, no spinning).
@@ -128,6 +128,8 @@ template <>
 struct Mfma<bf16_t> {
   typedef bf16x8 vec;
   static constexpr float kThreshold = 16.0f;   // p <= 2^16: far inside the bf16 exponent range
+  static constexpr uint16_t kInf = 0x7F80;
+  static constexpr float kTiny = 0x1p-126f;    // the smallest weight that keeps an infinity one
   static __device__ __forceinline__ f32x4 run(vec a, vec b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
   }
@@ -140,6 +142,8 @@ template <>
 struct Mfma<f16_t> {
   typedef f16x8 vec;
   static constexpr float kThreshold = 0.0f;    // keep p <= 1 (f16 tops out at 65504)
+  static constexpr uint16_t kInf = 0x7C00;
+  static constexpr float kTiny = 0x1p-24f;
   static __device__ __forceinline__ f32x4 run(vec a, vec b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
   }
@@ -477,13 +481,39 @@ k_decode_attn(const AttnParamsT<NS> P) {
     l_run += ((pv[0] + pv[1]) + (pv[2] + pv[3])) + ((pv[4] + pv[5]) + (pv[6] + pv[7]));
     uint4 praw = make_uint4(M::pack2(pv[0], pv[1]), M::pack2(pv[2], pv[3]), M::pack2(pv[4], pv[5]),
                             M::pack2(pv[6], pv[7]));
-    const opvec pop = __builtin_bit_cast(opvec, praw);
+    opvec pop = __builtin_bit_cast(opvec, praw);
     opvec plo = pop;                     // what rounding the probabilities to 16 bits left over
     if constexpr (kSplitP) {
       float d[8];
 #pragma unroll
       for (int j = 0; j < 8; ++j) d[j] = pv[j] - (float)pop[j];
       plo = __builtin_bit_cast(opvec, make_uint4(M::pack2(d[0], d[1]), M::pack2(d[2], d[3]), M::pack2(d[4], d[5]), M::pack2(d[6], d[7])));
+      // Infinities in V stay infinities, as with fp32 probabilities: the rows that a short tile repeats are
+      // cleared (their weight is zero), and in a tile that holds an infinity no half is zero or negative.
+      // (0.25 us of 18.9 at 128 units x 2368 paged keys of 64-wide heads; leaving the second product out of
+      // such tiles instead put a branch before every product: 1 us)
+      if (partial) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+          if (r0 + (j >> 2) * 16 + lg * 4 + (j & 3) >= r_end)
+#pragma unroll
+            for (int i = 0; i < NE / 2; ++i) vst[j].w[i] = 0;
+      }
+      typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+      u16x2 big = {0, 0};
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+#pragma unroll
+        for (int i = 0; i < NE / 2; ++i) big = __builtin_elementwise_max(big, __builtin_bit_cast(u16x2, vst[j].w[i] & 0x7FFF7FFFu));
+      if (__builtin_amdgcn_ballot_w64(big[0] >= M::kInf || big[1] >= M::kInf) != 0) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          d[j] = pv[j] > 0.f ? M::kTiny : 0.f;
+          pv[j] = pv[j] > 0.f ? fmaxf(pv[j], M::kTiny) : pv[j];
+        }
+        pop = __builtin_bit_cast(opvec, make_uint4(M::pack2(pv[0], pv[1]), M::pack2(pv[2], pv[3]), M::pack2(pv[4], pv[5]), M::pack2(pv[6], pv[7])));
+        plo = __builtin_bit_cast(opvec, make_uint4(M::pack2(d[0], d[1]), M::pack2(d[2], d[3]), M::pack2(d[4], d[5]), M::pack2(d[6], d[7])));
+      }
     }
     // ---- O^T += V^T . P^T : transpose the lane's 8 x NE block, one MFMA per column e
 #pragma unroll
@@ -960,7 +990,7 @@ int most_splits(int units, int S, int n_splits) {
 }
 
 // Two workgroups per compute unit (the 64-wide heads' tiles are half as many bytes, but four are no
-// faster: 16 sequences x 8 kv heads x 2368 keys 17.8 us with 4 splits and 19.1 with 8), or one, where
+// faster: 16 sequences x 8 kv heads x 2368 keys 18.3 us with 4 splits and 1.3 more with 8), or one, where
 // the units divide the chip almost evenly and there are few of them: every split costs its partial
 // results and a share of the merge.  More than 16 splits only while each keeps 352 rows.
 //   units x keys, us with 512 / units, 256 / units and this rule's splits (128-wide heads, 4 a group):
@@ -1037,7 +1067,8 @@ static int plan_attention(const vt_desc* Q, const vt_desc* K, const vt_desc* V, 
     return fail(VT_ERR_SHAPE, "vt_decode_attn: Q does not match K");
   if (D != 64 && D != 128) return fail(VT_ERR_UNSUPPORTED, "vt_decode_attn: head dim must be 64 or 128");
   if (B > 65535 || Hq > 65535 || S >= (1ll << 31)) return fail(VT_ERR_UNSUPPORTED, "vt_decode_attn: extents too large");
-  if (n_splits < 0) return fail(VT_ERR_INVALID_ARG, "vt_decode_attn: n_splits < 0");
+  // (the generic kernel, which 64-wide heads fall back to, has no use for n_splits)
+  if (n_splits < 0) return fail(D == 128 ? VT_ERR_INVALID_ARG : VT_ERR_UNSUPPORTED, "vt_decode_attn: n_splits < 0");
 
   // query heads that share K/V rows: common broadcast factor over all pieces of K and V
   int64_t G = 0;
@@ -1153,9 +1184,11 @@ static int launch_attention(const vt_desc* Q, const vt_desc* K, const vt_desc* V
   AttnParams P;
   int rc = plan_attention(Q, K, V, n_splits, P);
   const size_t need = rc == VT_OK ? ticket_bytes(P.B, (int64_t)P.Hkv * P.G) + (size_t)P.B * P.Hkv * P.G * P.n_splits * ((size_t)P.D + 2) * sizeof(float) : 0;
-  // the generic kernel needs no workspace and no alignment of out: 64-wide heads and tables over the
-  // batch keep it where those of the planned kernel are not given
-  const bool unplaced = rc == VT_OK && (P.D != 128 || P.batch_table) && (workspace_bytes < need || (uintptr_t)workspace % 16 || (uintptr_t)out % 8);
+  // the generic kernel needs no workspace and no alignment of out, and takes any scale (the rows past the
+  // end of a tile are masked with -3e38 before they are scaled): 64-wide heads and tables over the batch
+  // keep it where what the planned kernel needs is not given
+  const bool unplaced = rc == VT_OK && (P.D != 128 || P.batch_table) &&
+                        (workspace_bytes < need || (uintptr_t)workspace % 16 || (uintptr_t)out % 8 || !(scale >= 1e-6f && scale <= 1e6f));
   if (rc == VT_ERR_UNSUPPORTED || unplaced) {
     // maps or a head dim the planned kernel does not take: the generic kernel, if the shapes allow
     const std::string why = vt_last_error();
@@ -1195,7 +1228,7 @@ static int launch_attention(const vt_desc* Q, const vt_desc* K, const vt_desc* V
   // compiled for three waves per SIMD (two workgroups of four waves per compute unit and room for
   // a third); the build for two measures the same on the benchmark's shape
   // (2 KB less with every launch: the call 6.5 -> 4.3 us of host time, the kernel 25.75 -> 25.55 us at
-  // 64 units x 4096 keys and 17.95 -> 17.63 us at 128 x 2368 paged keys of 64-wide heads)
+  // 64 units x 4096 keys and by 0.3 us at 128 x 2368 paged keys of 64-wide heads)
   AttnParamsT<2> P2;
   const bool few = P.n_seg <= 2;
   if (few) {

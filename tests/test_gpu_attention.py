@@ -341,3 +341,35 @@ def test_cache_slots_through_a_table_and_the_new_row(gpu):
     p = pipelines.run_decode_attention(tio.DeviceWorkload(wl))["pipeline"]
     assert np.isfinite(ref["out"]).all() and p.ws.any()
     assert np.all(np.abs(tio.to_host_f64(p.out) - ref["out"]) <= 2.0 ** -8 * np.abs(ref["out"]) + 1e-4)
+
+
+@pytest.mark.parametrize("S,scale,n_splits", [(45, 0.0, 0), (45, -0.125, 0), (45, 0.125, -1), (96, -0.125, 0)])
+def test_heads_of_64_odd_arguments(gpu, S, scale, n_splits):
+    """Scales and split counts that only the generic kernel takes: rows past the end must not count."""
+    vt, tio, pipelines, torch = gpu
+    wl = workloads.c2_decode_attention(seed=15, B=2, Hkv=2, G=3, S=S, D=64)
+    wl.consumer["scale"] = scale
+    ref = run_workload(wl)
+    p = pipelines.run_decode_attention(tio.DeviceWorkload(wl))["pipeline"]
+    vt.vt_decode_attn(p.q, p.k, p.v, scale, p.out, p.ws, p.ws.numel() * p.ws.element_size(), n_splits, lse=p.lse)
+    torch.cuda.synchronize()
+    assert np.all(np.abs(tio.to_host_f64(p.out) - ref["out"]) <= 2.0 ** -8 * np.abs(ref["out"]) + 1e-4)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+@pytest.mark.parametrize("S,row", [(45, 3), (45, 44), (300, 299), (300, 100)])
+def test_heads_of_64_infinite_values(gpu, dtype, S, row):
+    """One infinity in V (also in the last row, which a short tile repeats): its column is infinite, the
+    others keep what one 16-bit rounding of the weights allows (2^-8 of them, averaged over the context)."""
+    vt, tio, pipelines, torch = gpu
+    wl = workloads.c2_decode_attention(seed=16, B=1, Hkv=2, G=3, S=S, D=64, dtype=dtype)
+    clean = run_workload(wl)["out"]
+    v_row = wl.sources["QKV"][0, 0, -64:] if row == S - 1 else wl.sources["Vcache"][0, 1, row]
+    v_row[5] = 0x7F80 if dtype == "bf16" else np.inf
+    p = pipelines.run_decode_attention(tio.DeviceWorkload(wl))["pipeline"]
+    assert p.ws.any()
+    got = tio.to_host_f64(p.out)
+    hit = np.zeros(got.shape, dtype=bool)
+    hit.reshape(1, 6, 64)[0, 3:, 5] = True
+    assert np.all(got[hit] == np.inf)
+    assert np.all(np.abs(got[~hit] - clean.reshape(got.shape)[~hit]) <= 1e-2 + 1e-2 * np.abs(clean.reshape(got.shape)[~hit]))
