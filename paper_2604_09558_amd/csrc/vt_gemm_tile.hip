@@ -13,7 +13,7 @@
 // the fragment reads free of bank conflicts (4.3 million conflict cycles per launch without it, 6000
 // with it) is applied to what a lane asks for.  Waits count the requests by hand: a wave issues the
 // same number in every step and nothing else that goes through the vector memory counter.
-// Measured (f16/bf16, K = 4096): 333 x 4096 83 -> 26 us, 400 x 6144 91 -> 35 us, 1024 x 4096 90 -> 48 us.
+// Measured (f16/bf16, K = 4096): 333 x 4096 83 -> 25 us, 400 x 6144 91 -> 34 us, 1024 x 4096 90 -> 48 us.
 // A loop with the requests alone takes the same time, one without them half of it; rings twice as
 // deep, with the waves divided into readers of A and of B, measured no faster.
 #include <hip/hip_runtime.h>
