@@ -251,10 +251,12 @@ int vt_decode_attn_plan(const vt_desc* Q, const vt_desc* K, const vt_desc* V, in
  * splits the library picks for n_splits = 0, and with it the size of the partial results, depends
  * on it).  Host only. */
 size_t vt_decode_attn_workspace(int B, int Hq, int D, int S, int n_splits);
-/* Clears a freshly allocated workspace (its first bytes hold one arrival counter per (batch,
+/* Clears a freshly allocated workspace (its first 16 KiB hold one arrival counter per (batch,
  * kv head), which must be zero when vt_decode_attn starts and which vt_decode_attn leaves at
  * zero).  Call once after allocating, on the stream of the first vt_decode_attn, or clear
- * the buffer yourself.  Launches that share a workspace must not overlap in time. */
+ * the buffer yourself.  Launches that share a workspace must not overlap in time; they may be
+ * of different problems, one after the other, as long as the workspace is large enough for each.
+ * More than 4096 (batch, kv head) pairs run with one split, whatever n_splits. */
 int vt_decode_attn_workspace_init(void* workspace, size_t workspace_bytes, void* stream);
 
 /* For callers that cannot allocate device memory (code under HIP graph capture, tight serving
@@ -263,8 +265,8 @@ int vt_decode_attn_workspace_init(void* workspace, size_t workspace_bytes, void*
  * memory, vt_decode_attn_static_capacity() bytes (4 MiB) per GPU, held until the process ends.
  * The call allocates nothing and frees nothing; it queues a small fill kernel that clears the
  * arrival counters, then the same kernel as vt_decode_attn, and gives the same bits.  Problems
- * whose workspace (vt_decode_attn_workspace) exceeds the capacity return VT_ERR_INVALID_ARG with a
- * message naming both sizes; all other arguments and errors are those of vt_decode_attn.  All
+ * whose counters (4 bytes per batch and query head, in whole 256 bytes) and partial results exceed the
+ * capacity return VT_ERR_INVALID_ARG with a message naming both sizes; all other arguments and errors are those of vt_decode_attn.  All
  * calls on one GPU share that GPU's array: calls that overlap in time on one GPU (two streams,
  * two threads) race and give wrong results. */
 size_t vt_decode_attn_static_capacity(void);

@@ -112,7 +112,7 @@ struct AttnArgs {
   int32_t B, Hkv, G, S, D, n_splits, rows_per_split;
   int32_t batch_table;   // some operand finds a sequence's rows through a table over the batch
   float scale_log2;      // softmax scale * log2(e)
-  uint32_t* tickets;     // [B, Hkv], zero between launches
+  uint32_t* tickets;     // [B, Hkv] (with one split: not used), zero between launches
   float* ws_ml;          // [B, Hkv, n_splits, G, 2]
   float* ws_o;           // [B, Hkv, n_splits, G, D]
   void* out;             // [B, Hq, D]
@@ -588,11 +588,11 @@ k_decode_attn(const AttnParamsT<NS> P) {
   // every wave's stores to complete before one thread takes the ticket (a device-scope atomic);
   // the merging workgroup reads the partial results with device-scope atomic loads, which do
   // not hit stale cache lines.  atomicInc wraps to 0 at n_splits - 1, which leaves the counter
-  // ready for the next launch.  No wave ever waits for another workgroup.
+  // ready for the next launch.  No wave ever waits for another workgroup.  (One split: no counter.)
   __builtin_amdgcn_s_waitcnt(0);         // this wave's stores have completed (vmcnt = 0)
   __syncthreads();
   VT_PROF(3);
-  if (threadIdx.x == 0) ticket_sh = atomicInc(&a_tickets[bg], (uint32_t)(a_ns - 1));
+  if (threadIdx.x == 0) ticket_sh = a_ns > 1 ? atomicInc(&a_tickets[bg], (uint32_t)(a_ns - 1)) : 0u;
   __syncthreads();
   VT_PROF(4);
   if (ticket_sh != (uint32_t)(a_ns - 1)) {
@@ -1008,7 +1008,15 @@ constexpr int kWaves = 4;
 
 }  // namespace
 
-static size_t ticket_bytes(int64_t B, int64_t Hq) { return (size_t)((B * Hq * 4 + 255) / 256 * 256); }
+// The arrival counters' part of a workspace.  Its size is the same for every problem: where it ended with
+// the problem's own counters, a call with more (batch, kv head) pairs found the partial results of an earlier
+// one in their place.  Problems with more pairs than this have work for the whole chip without splits
+// (choose_splits splits below 512 pairs) and run with one, which needs no counters.
+constexpr int64_t kCounters = 4096;
+constexpr size_t kCounterBytes = kCounters * 4;
+// In the library's own array (cleared before every launch), and in a workspace that does not hold the whole
+// area (cleared after the launch), the partial results follow the problem's counters.
+static size_t counters_used(int64_t B, int64_t Hq) { return (size_t)((B * Hq * 4 + 255) / 256 * 256); }
 
 // Workspace of vt_decode_attn_static: a fixed array in the code object's own device memory, so
 // that the call needs no allocation.  Every GPU the library runs on holds its own copy at its
@@ -1043,7 +1051,7 @@ size_t vt_decode_attn_workspace(int B, int Hq, int D, int S, int n_splits) {
   // an upper bound that does not need the grouping: the fewest kv heads (16 query heads each)
   // give the most splits
   int ns = most_splits(B * std::max(1, Hq / 16), S, n_splits);
-  return ticket_bytes(B, Hq) + (size_t)B * Hq * ns * ((size_t)D + 2) * sizeof(float);
+  return kCounterBytes + (size_t)B * Hq * ns * ((size_t)D + 2) * sizeof(float);
 }
 
 int vt_decode_attn_workspace_init(void* workspace, size_t workspace_bytes, void* stream) {
@@ -1137,7 +1145,7 @@ static int plan_attention(const vt_desc* Q, const vt_desc* K, const vt_desc* V, 
     if ((uintptr_t)P.q_ptr % 16 || P.q_sb % 16 || P.q_sh % 16) return fail(VT_ERR_UNSUPPORTED, "Q: rows are not 16-byte aligned");
   }
   const int Hkv = (int)(Hq / G);
-  int ns = choose_splits((int)B * Hkv, (int)S, n_splits, D);
+  int ns = B * Hkv > kCounters ? 1 : choose_splits((int)B * Hkv, (int)S, n_splits, D);
   if (n_splits == 0 && D == 64) ns = std::min(ns, (int)(kWaves * kTile * D / 4 / G));   // what the merge below has room for
   int rows = (int)((S + ns - 1) / ns);
   rows = (rows + kTile - 1) / kTile * kTile;
@@ -1174,16 +1182,19 @@ int vt_decode_attn_plan(const vt_desc* Q, const vt_desc* K, const vt_desc* V, in
   return VT_OK;
 }
 
-// Everything after the plan: workspace carving, launch.  `clear_tickets` queues a small fill
+// Everything after the plan: workspace carving, launch.  `clear_counters` queues a small fill
 // kernel over the arrival counters first (for a workspace whose previous contents are not known
-// to be zero).
+// to be zero, and whose counters may end where this problem's do).
 static int launch_attention(const vt_desc* Q, const vt_desc* K, const vt_desc* V, float scale, void* out, float* lse,
-                            void* workspace, size_t workspace_bytes, int n_splits, bool clear_tickets,
+                            void* workspace, size_t workspace_bytes, int n_splits, bool clear_counters,
                             const char* who, void* stream) {
   if (!out || !workspace) return fail(VT_ERR_INVALID_ARG, std::string(who) + ": NULL argument");
   AttnParams P;
   int rc = plan_attention(Q, K, V, n_splits, P);
-  const size_t need = rc == VT_OK ? ticket_bytes(P.B, (int64_t)P.Hkv * P.G) + (size_t)P.B * P.Hkv * P.G * P.n_splits * ((size_t)P.D + 2) * sizeof(float) : 0;
+  const size_t partial = rc == VT_OK ? (size_t)P.B * P.Hkv * P.G * P.n_splits * ((size_t)P.D + 2) * sizeof(float) : 0;
+  const bool tight = clear_counters || workspace_bytes < kCounterBytes + partial;
+  const size_t counters = rc == VT_OK && tight ? counters_used(P.B, (int64_t)P.Hkv * P.G) : kCounterBytes;
+  const size_t need = counters + partial;
   // the generic kernel needs no workspace and no alignment of out, and takes any scale (the rows past the
   // end of a tile are masked with -3e38 before they are scaled): 64-wide heads and tables over the batch
   // keep it where what the planned kernel needs is not given
@@ -1213,13 +1224,13 @@ static int launch_attention(const vt_desc* Q, const vt_desc* K, const vt_desc* V
   if ((uintptr_t)workspace % 16 || (uintptr_t)out % 8) return fail(VT_ERR_INVALID_ARG, std::string(who) + ": misaligned workspace or out (16 and 8 bytes)");
   P.scale_log2 = scale * 1.4426950408889634f;
   P.tickets = static_cast<uint32_t*>(workspace);
-  P.ws_ml = reinterpret_cast<float*>(static_cast<char*>(workspace) + ticket_bytes(B, Hq));
+  P.ws_ml = reinterpret_cast<float*>(static_cast<char*>(workspace) + counters);
   P.ws_o = P.ws_ml + (size_t)B * Hq * ns_eff * 2;
   P.out = out;
   P.lse = lse;
   hipStream_t st = (hipStream_t)stream;
-  if (clear_tickets) {
-    const size_t words = ticket_bytes(B, Hq) / 4;
+  if (clear_counters) {
+    const size_t words = counters / 4;
     hipLaunchKernelGGL(k_zero_words, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, st, P.tickets, words);
     rc = check_launch(who);
     if (rc != VT_OK) return rc;
@@ -1257,7 +1268,13 @@ static int launch_attention(const vt_desc* Q, const vt_desc* K, const vt_desc* V
   }
 #undef VT_ATTN
 #undef VT_ATTN_NS
-  return check_launch(who);
+  rc = check_launch(who);
+  if (rc == VT_OK && tight && !clear_counters) {
+    const size_t words = std::min(kCounterBytes, workspace_bytes) / 4;
+    hipLaunchKernelGGL(k_zero_words, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, st, P.tickets, words);
+    rc = check_launch(who);
+  }
+  return rc;
 }
 
 int vt_decode_attn(const vt_desc* Q, const vt_desc* K, const vt_desc* V, float scale, void* out, float* lse,

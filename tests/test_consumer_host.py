@@ -1,0 +1,25 @@
+"""What the consumers decide or refuse on the host, before anything is launched (no GPU is used:
+the addresses are never dereferenced)."""
+import numpy as np
+import pytest
+
+import paper_2604_09558_amd as vt
+import workloads
+
+FAKE = 0x100000
+
+
+def decode_descs(B, Hkv, G, S, D, dtype="bf16"):
+    """Q, K, V of the decode chain at any size, without its data."""
+    shapes = {"QKV": (B, 1, (G + 2) * Hkv * D), "Kcache": (B, Hkv, S, D), "Vcache": (B, Hkv, S, D)}
+    spec = {k: (s, dtype, FAKE) for k, s in shapes.items()}
+    return [vt.build_chain(workloads.c2_chain(B, Hkv, G, S, D), spec, n) for n in ("Q", "K", "V")]
+
+
+def test_attention_plan_splits_only_where_every_pair_has_a_counter():
+    """4096 (batch, kv head) pairs keep the splits asked for; more run with one, which needs no counter."""
+    for B, want in ((512, 3), (513, 1)):
+        assert vt.vt_decode_attn_plan(*decode_descs(B, 8, 2, 400, 128), n_splits=3)["splits"] == want
+    # the counters' share of the workspace is the same for every problem
+    share = {vt.vt_decode_attn_workspace(B, 8, 128, 400, 1) - B * 8 * 130 * 4 for B in (1, 16, 4096)}
+    assert len(share) == 1

@@ -373,3 +373,27 @@ def test_heads_of_64_infinite_values(gpu, dtype, S, row):
     hit.reshape(1, 6, 64)[0, 3:, 5] = True
     assert np.all(got[hit] == np.inf)
     assert np.all(np.abs(got[~hit] - clean.reshape(got.shape)[~hit]) <= 1e-2 + 1e-2 * np.abs(clean.reshape(got.shape)[~hit]))
+
+
+@pytest.mark.parametrize("D,paged", [(64, False), (128, False), (64, True), (128, True)])
+@pytest.mark.parametrize("tight", [False, True])
+def test_one_workspace_for_batches_of_different_sizes(gpu, D, paged, tight):
+    """A serving loop's batch grows and shrinks on one workspace: what a call leaves behind as partial
+    results must not lie where a call with more (batch, kv head) pairs keeps its arrival counters.  tight:
+    calls that are given less than the whole counter area (their own counters and partial results only)."""
+    vt, tio, pipelines, torch = gpu
+    small, large = (workloads.paged_decode_attention(seed=17, B=B, Hkv=8, G=4, pages_per_seq=1, page=256, D=D) if paged else
+                    workloads.c2_decode_attention(seed=17, B=B, Hkv=8, G=4, S=400, D=D) for B in (1, 16))
+    ps = [pipelines.DecodeAttention(tio.DeviceWorkload(wl)) for wl in (small, large)]
+    refs = [run_workload(wl)["out"] for wl in (small, large)]
+    most = max(p.ws_bytes for p in ps)
+    ws = torch.empty(most, dtype=torch.uint8, device="cuda:0")
+    vt.vt_decode_attn_workspace_init(ws, most)
+    for i, less in ((0, tight), (1, False), (0, tight), (1, tight), (0, False), (1, False)):
+        p = ps[i]
+        p.out.fill_(float("nan"))
+        vt.vt_decode_attn(p.q, p.k, p.v, p.scale, p.out, ws, p.ws_bytes - 14000 if less else most)
+        torch.cuda.synchronize()
+        got = tio.to_host_f64(p.out)
+        assert np.isfinite(got).all(), i
+        check(got, refs[i])
