@@ -296,8 +296,9 @@ int vt_scatter(const vt_desc* src, const vt_desc* dst, void* stream);
  * rows run on the tiled kernel of vt_gemm with the map applied in its store stage (A and B then
  * obey vt_gemm's layout rules; the workspace is not used).
  * workspace: device pointer (16-byte aligned), at least vt_gemm_store_workspace(M, N, K) bytes,
- * cleared once with vt_gemm_store_workspace_init (arrival counters, left at zero by every call,
- * and the partial sums of the K slices); calls that share a workspace must not overlap in time.
+ * cleared once with vt_gemm_store_workspace_init (arrival counters in its first 4 KiB, left at zero by
+ * every call, and the partial sums of the K slices); calls that share a workspace must not overlap in
+ * time, and may be of different problems, one after the other, if it is large enough for each.
  * Results are bitwise reproducible from call to call.  Asynchronous on `stream`. */
 size_t vt_gemm_store_workspace(int64_t M, int64_t N, int64_t K);
 int vt_gemm_store_workspace_init(void* workspace, size_t workspace_bytes, void* stream);

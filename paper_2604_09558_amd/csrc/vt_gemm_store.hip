@@ -79,7 +79,7 @@ struct StoreParams {
   int32_t n_out;
   int32_t M, N, K;
   int32_t n_splits, k_per_split;   // k_per_split is a multiple of kTileK
-  uint32_t* tickets;       // [row blocks][column blocks], zero between launches
+  uint32_t* tickets;       // [row blocks][column blocks] (with one slice: not used), zero between launches
   float* partial;          // [row blocks][column blocks][n_splits][kBM][kBN]
 };
 
@@ -229,7 +229,7 @@ __global__ void __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_e
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
   VT_PROF(3);
-  if (threadIdx.x == 0) ticket_sh = atomicInc(&a_tickets[blk], (uint32_t)(a_ns - 1));
+  if (threadIdx.x == 0) ticket_sh = a_ns > 1 ? atomicInc(&a_tickets[blk], (uint32_t)(a_ns - 1)) : 0u;
   __syncthreads();
   VT_PROF(4);
   if (ticket_sh != (uint32_t)(a_ns - 1)) {
@@ -280,6 +280,11 @@ __global__ void k_zero_store_ws(uint32_t* p, size_t n) {
   if (i < n) p[i] = 0u;
 }
 
+// The arrival counters' part of a workspace: the same size for every problem, so that no call finds another's
+// partial sums where its counters are.  (More blocks than this keep every compute unit busy without slices.)
+constexpr int64_t kCounters = 1024;
+constexpr size_t kCounterBytes = kCounters * 4;
+
 int compute_units() {
   static const int n_cu = [] {
     int dev = 0, n = 256;
@@ -295,12 +300,14 @@ int compute_units() {
 // blocks: 4 slices 14.75 us, 5: 14.5, 6: 16.7, 7: 16.6, 8: 15.9), at least one tile per wave, at
 // most 64.  The slices are whole tiles and need not be equal.
 int choose_k_splits(int64_t blocks, int64_t K) {
+  if (blocks > kCounters) return 1;
   const int n_cu = compute_units();
   const int64_t max_splits = std::max<int64_t>(1, K / (kTileK * kWaves));
   return (int)std::min<int64_t>(std::min(std::max<int64_t>(1, n_cu / blocks), max_splits), 64);
 }
 
-size_t ticket_area(int64_t blocks) { return (size_t)((blocks * 4 + 255) / 256 * 256); }
+// A workspace that does not hold the whole counter area: the partial sums follow the problem's own counters.
+size_t counters_used(int64_t blocks) { return (size_t)((blocks * 4 + 255) / 256 * 256); }
 
 }  // namespace
 
@@ -309,7 +316,7 @@ extern "C" {
 size_t vt_gemm_store_workspace(int64_t M, int64_t N, int64_t K) {
   if (M < 1 || N < 1 || K < 1) return 0;
   const int64_t blocks = ((M + kBM - 1) / kBM) * ((N + kBN - 1) / kBN);
-  return ticket_area(blocks) + (size_t)blocks * choose_k_splits(blocks, K) * kBM * kBN * sizeof(float);
+  return kCounterBytes + (size_t)blocks * choose_k_splits(blocks, K) * kBM * kBN * sizeof(float);
 }
 
 int vt_gemm_store_workspace_init(void* workspace, size_t workspace_bytes, void* stream) {
@@ -404,8 +411,10 @@ int vt_gemm_store(const vt_desc* A, const vt_desc* B, const vt_desc* C, void* wo
   int kps = (int)((K + ns - 1) / ns);
   kps = (kps + kTileK - 1) / kTileK * kTileK;
   const int ns_eff = (int)((K + kps - 1) / kps);
-  const size_t need = ticket_area(rbs * cbs) + (size_t)rbs * cbs * ns_eff * kBM * kBN * sizeof(float);
-  if (workspace_bytes < need) return fail(VT_ERR_INVALID_ARG, "vt_gemm_store: workspace too small");
+  const size_t partial = (size_t)rbs * cbs * ns_eff * kBM * kBN * sizeof(float);
+  const bool tight = workspace_bytes < kCounterBytes + partial;
+  const size_t counters = tight ? counters_used(rbs * cbs) : kCounterBytes;
+  if (workspace_bytes < counters + partial) return fail(VT_ERR_INVALID_ARG, "vt_gemm_store: workspace too small");
   if ((uintptr_t)workspace % 16) return fail(VT_ERR_INVALID_ARG, "vt_gemm_store: misaligned workspace");
   P.M = (int32_t)M;
   P.N = (int32_t)N;
@@ -413,7 +422,7 @@ int vt_gemm_store(const vt_desc* A, const vt_desc* B, const vt_desc* C, void* wo
   P.n_splits = ns_eff;
   P.k_per_split = kps;
   P.tickets = static_cast<uint32_t*>(workspace);
-  P.partial = reinterpret_cast<float*>(static_cast<char*>(workspace) + ticket_area(rbs * cbs));
+  P.partial = reinterpret_cast<float*>(static_cast<char*>(workspace) + counters);
   // Several blocks of 16 rows: this kernel reads B once for each of them, and takes the time its busiest
   // compute unit needs to draw its share (40 GB/s, 6.5 us around it).  The tiled kernel takes over
   // where it is expected to be faster (us here / there: 4096 x 6144 with 32 rows 24.4 / 27.5, 48 rows
@@ -427,7 +436,13 @@ int vt_gemm_store(const vt_desc* A, const vt_desc* B, const vt_desc* C, void* wo
   hipStream_t st = (hipStream_t)stream;
   if (A->dtype == VT_BF16) hipLaunchKernelGGL((k_gemm_store<bf16_t>), grid, dim3(kWaves * 64), 0, st, P);
   else hipLaunchKernelGGL((k_gemm_store<f16_t>), grid, dim3(kWaves * 64), 0, st, P);
-  return check_launch("vt_gemm_store");
+  rc = check_launch("vt_gemm_store");
+  if (rc == VT_OK && tight) {
+    const size_t words = std::min(kCounterBytes, workspace_bytes) / 4;      // partial sums out of the counter area
+    hipLaunchKernelGGL(k_zero_store_ws, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, st, P.tickets, words);
+    rc = check_launch("vt_gemm_store");
+  }
+  return rc;
 }
 
 }  // extern "C"

@@ -200,3 +200,23 @@ def test_a_few_row_blocks_of_a_wide_projection(gpu, B, T):
     p.run()
     torch.cuda.synchronize()
     compare_stored(tio, dw, wl, ref)
+
+
+@pytest.mark.parametrize("tight", [False, True])
+def test_one_workspace_for_projections_of_different_widths(gpu, tight):
+    """The arrival counters of the wider projection must not lie where the narrower one left partial sums.
+    tight: the narrower one is given its own counters and partial sums only, not the whole counter area."""
+    vt, tio, pipelines, torch = gpu
+    wls = [workloads.qkv_proj_store(seed=8, B=2, hidden=1024, Hq=4, Hkv=2, D=128, cap=8, pos=3),
+           workloads.qkv_proj_store(seed=8, B=2, hidden=256, Hq=60, Hkv=20, D=128, cap=8, pos=3)]
+    refs = [run_workload(wl) for wl in wls]
+    need = [vt.vt_gemm_store_workspace(2, wl.sources["W"].shape[1], wl.sources["W"].shape[0]) for wl in wls]
+    ws = torch.empty(max(need), dtype=torch.uint8, device="cuda:0")
+    vt.vt_gemm_store_workspace_init(ws, max(need))
+    for i in (0, 1, 0, 1):
+        dw = tio.DeviceWorkload(wls[i])
+        p = pipelines.GemmStore(dw)
+        p.ws, p.ws_bytes = ws, need[0] - 3072 if tight and i == 0 else max(need)
+        p.run()
+        torch.cuda.synchronize()
+        compare_stored(tio, dw, wls[i], refs[i])
