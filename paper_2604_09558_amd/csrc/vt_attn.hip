@@ -26,7 +26,7 @@
 //                   already holds in exactly that layout.
 // Head dims 128 and 64 (a template argument): a tile of 64-wide heads is half as many bytes, eight
 // lanes read a K row and a lane's piece of a V row is 8 bytes.  Serving 16 sequences of 2368 paged
-// keys of 64-wide heads (77.7 MB): 18.3 us = 4.2 TB/s, against 10.8 ms when only 128 was planned
+// keys of 64-wide heads (77.7 MB): 18.5 us = 4.2 TB/s, against 10.8 ms when only 128 was planned
 // and every element went through the generic evaluator below.
 // The workgroup that finishes last for a (b, g) merges the splits' partial results (a ticket
 // counter per (b, g) in the workspace; no second launch, no spinning).
@@ -128,8 +128,10 @@ template <>
 struct Mfma<bf16_t> {
   typedef bf16x8 vec;
   static constexpr float kThreshold = 16.0f;   // p <= 2^16: far inside the bf16 exponent range
-  static constexpr uint16_t kInf = 0x7F80;
-  static constexpr float kTiny = 0x1p-126f;    // the smallest weight that keeps an infinity one
+  static constexpr float kScale = 1.0f, kStep = 1.0f;         // P_PARTS: three parts of 8 bits are all of p
+  // the two numbers of a register, exactly
+  static __device__ __forceinline__ float lo(uint32_t w) { return __builtin_bit_cast(float, w << 16); }
+  static __device__ __forceinline__ float hi(uint32_t w) { return __builtin_bit_cast(float, w & 0xFFFF0000u); }
   static __device__ __forceinline__ f32x4 run(vec a, vec b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
   }
@@ -142,8 +144,11 @@ template <>
 struct Mfma<f16_t> {
   typedef f16x8 vec;
   static constexpr float kThreshold = 0.0f;    // keep p <= 1 (f16 tops out at 65504)
-  static constexpr uint16_t kInf = 0x7C00;
-  static constexpr float kTiny = 0x1p-24f;
+  // P_PARTS: three parts of 11 bits, each scaled into the upper end of f16's range (the first is at most 2^14
+  // and leaves over at most 2^3, the last one ends at 2^-60 of p = 1)
+  static constexpr float kScale = 0x1p14f, kStep = 0x1p11f;
+  static __device__ __forceinline__ float lo(uint32_t w) { return (float)__builtin_bit_cast(f16_t, (uint16_t)w); }
+  static __device__ __forceinline__ float hi(uint32_t w) { return (float)__builtin_bit_cast(f16_t, (uint16_t)(w >> 16)); }
   static __device__ __forceinline__ f32x4 run(vec a, vec b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
   }
@@ -305,8 +310,21 @@ __device__ __forceinline__ void walk_advance(const AttnParamsT<NS>& P, TileWalk&
 }
 
 // D = head dim (64 or 128).  MANY: more than eight splits, the merge below divides them among its threads.
-// SPLIT: see kSplitP.
-template <typename T, int D, bool MANY, bool SPLIT, int NS, int WAVES, int OCC>
+// PMODE: how the probabilities enter the product with V.
+//   P_16     rounded to 16 bits (128-wide heads).
+//   P_PARTS  64-wide heads, and maps that used to run on the generic kernel, keep the probabilities' fp32 value,
+//            as that kernel does.  Up to five query heads a group leave two thirds of the product's 16 columns
+//            idle: the columns G.. and 2G.. hold the same heads again, and a probability is cut into three 16-bit
+//            parts, one for each of its columns, which are added up when the waves are merged.  us with 16-bit
+//            halves in two products (fewer bits) / with these parts / with P_F32: 128 units x 2368 paged keys, 64-wide
+//            heads, 4 a group 18.8 / 19.1 / 21.4, 2048 units x 500 keys 51.4 / 51.1 / 53.8, 128 units x 128 keys of
+//            128-wide heads behind a batch table 8.4 / 8.5 / 9.1.  (Parts in three products and accumulators
+//            spilled; an infinity in V times a part that is zero would also have to be told from a NaN there.)
+//   P_F32    the same with more heads a group: fp32 products, V converted exactly (256 units x 4096 paged keys, 8
+//            heads a group: 52.2 us, 5.2 TB/s; 45.7 with halves).
+enum { P_16, P_PARTS, P_F32 };
+constexpr int kPartHeads = 5;
+template <typename T, int D, bool MANY, int PMODE, int NS, int WAVES, int OCC>
 __global__ void __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(OCC, OCC)))
 k_decode_attn(const AttnParamsT<NS> P) {
   typedef Mfma<T> M;
@@ -315,10 +333,6 @@ k_decode_attn(const AttnParamsT<NS> P) {
   constexpr int LPR = kD / 8;                // lanes (and 16-byte chunks) per K row
   constexpr int KL = kTile * LPR / 64;       // K loads per tile
   constexpr int NE = kD / 16;                // columns of V per lane: 16 or 8 bytes of a row
-  // 64-wide heads, and maps that used to run on the generic kernel: the probabilities enter the product
-  // as a sum of two 16-bit numbers (their fp32 value to 2^-16 or better).  The matrix pipes idle here
-  // either way: the second product is free and the result carries one rounding, its own.
-  constexpr bool kSplitP = SPLIT;
   __shared__ uint4 lds[WAVES][kTile * LPR];  // per wave: 32 rows of LPR chunks of 16 bytes, swizzled
   __shared__ float red_ml[WAVES * 16 * 2];   // [WAVES][16][2]
   __shared__ uint32_t ticket_sh;
@@ -344,14 +358,17 @@ k_decode_attn(const AttnParamsT<NS> P) {
   const int t_end = min(P.S, t_begin + P.rows_per_split);
   const float c = P.scale_log2;
 
+  // the part of the probabilities in this lane's column, and the columns in use
+  const int p_part = PMODE != P_PARTS ? 0 : (l16 >= P.G ? 1 : 0) + (l16 >= 2 * P.G ? 1 : 0);
+  const int n_cols = PMODE == P_PARTS ? 3 * P.G : P.G;
   // Q^T operand: lane (head l16, k-group lg) holds 8 consecutive d for each of the kD / 32 k-steps
   opvec qreg[kD / 32];
   {
-    const char* qp = P.q_ptr + b * P.q_sb + (int64_t)(g * P.G + l16) * P.q_sh;
+    const char* qp = P.q_ptr + b * P.q_sb + (int64_t)(g * P.G + (PMODE == P_PARTS ? l16 - p_part * P.G : l16)) * P.q_sh;
 #pragma unroll
     for (int kk = 0; kk < kD / 32; ++kk) {
       uint4 raw = make_uint4(0, 0, 0, 0);
-      if (l16 < P.G) raw = *reinterpret_cast<const uint4*>(qp + (kk * 32 + lg * 8) * 2);
+      if (l16 < n_cols) raw = *reinterpret_cast<const uint4*>(qp + (kk * 32 + lg * 8) * 2);
       qreg[kk] = __builtin_bit_cast(opvec, raw);
     }
   }
@@ -479,52 +496,47 @@ k_decode_attn(const AttnParamsT<NS> P) {
 #pragma unroll
     for (int j = 0; j < 8; ++j) pv[j] = __builtin_amdgcn_exp2f(fmaf(sv[j], c, -m_ref));   // masked rows: exp2(-huge) = 0
     l_run += ((pv[0] + pv[1]) + (pv[2] + pv[3])) + ((pv[4] + pv[5]) + (pv[6] + pv[7]));
-    uint4 praw = make_uint4(M::pack2(pv[0], pv[1]), M::pack2(pv[2], pv[3]), M::pack2(pv[4], pv[5]),
-                            M::pack2(pv[6], pv[7]));
-    opvec pop = __builtin_bit_cast(opvec, praw);
-    opvec plo = pop;                     // what rounding the probabilities to 16 bits left over
-    if constexpr (kSplitP) {
-      float d[8];
+    if (PMODE != P_16 && partial) {      // the rows that a short tile repeats have no weight: an infinity there is not read
 #pragma unroll
-      for (int j = 0; j < 8; ++j) d[j] = pv[j] - (float)pop[j];
-      plo = __builtin_bit_cast(opvec, make_uint4(M::pack2(d[0], d[1]), M::pack2(d[2], d[3]), M::pack2(d[4], d[5]), M::pack2(d[6], d[7])));
-      // Infinities in V stay infinities, as with fp32 probabilities: the rows that a short tile repeats are
-      // cleared (their weight is zero), and in a tile that holds an infinity no half is zero or negative.
-      // (0.25 us of 18.9 at 128 units x 2368 paged keys of 64-wide heads; leaving the second product out of
-      // such tiles instead put a branch before every product: 1 us)
-      if (partial) {
+      for (int j = 0; j < 8; ++j)
+        if (r0 + (j >> 2) * 16 + lg * 4 + (j & 3) >= r_end)
 #pragma unroll
-        for (int j = 0; j < 8; ++j)
-          if (r0 + (j >> 2) * 16 + lg * 4 + (j & 3) >= r_end)
-#pragma unroll
-            for (int i = 0; i < NE / 2; ++i) vst[j].w[i] = 0;
-      }
-      typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
-      u16x2 big = {0, 0};
+          for (int i = 0; i < NE / 2; ++i) vst[j].w[i] = 0;
+    }
+    if constexpr (PMODE == P_F32) {
+      // ---- O^T += V^T . P^T : four context rows (slot j of the four lane groups) per product
 #pragma unroll
       for (int j = 0; j < 8; ++j)
 #pragma unroll
-        for (int i = 0; i < NE / 2; ++i) big = __builtin_elementwise_max(big, __builtin_bit_cast(u16x2, vst[j].w[i] & 0x7FFF7FFFu));
-      if (__builtin_amdgcn_ballot_w64(big[0] >= M::kInf || big[1] >= M::kInf) != 0) {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          d[j] = pv[j] > 0.f ? M::kTiny : 0.f;
-          pv[j] = pv[j] > 0.f ? fmaxf(pv[j], M::kTiny) : pv[j];
+        for (int e = 0; e < NE; ++e) {
+          const float v = (e & 1) ? M::hi(vst[j].w[e >> 1]) : M::lo(vst[j].w[e >> 1]);
+          acc[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(v, pv[j], acc[e], 0, 0, 0);
         }
-        pop = __builtin_bit_cast(opvec, make_uint4(M::pack2(pv[0], pv[1]), M::pack2(pv[2], pv[3]), M::pack2(pv[4], pv[5]), M::pack2(pv[6], pv[7])));
-        plo = __builtin_bit_cast(opvec, make_uint4(M::pack2(d[0], d[1]), M::pack2(d[2], d[3]), M::pack2(d[4], d[5]), M::pack2(d[6], d[7])));
+    } else {
+      if constexpr (PMODE == P_PARTS) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) pv[j] *= M::kScale;
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < 8; j += 2) {
+            const uint32_t w = M::pack2(pv[j], pv[j + 1]);
+            const float r0 = (pv[j] - M::lo(w)) * M::kStep, r1 = (pv[j + 1] - M::hi(w)) * M::kStep;    // left over, exactly
+            pv[j] = p_part > i ? r0 : pv[j];
+            pv[j + 1] = p_part > i ? r1 : pv[j + 1];
+          }
       }
-    }
-    // ---- O^T += V^T . P^T : transpose the lane's 8 x NE block, one MFMA per column e
+      const opvec pop = __builtin_bit_cast(opvec, make_uint4(M::pack2(pv[0], pv[1]), M::pack2(pv[2], pv[3]), M::pack2(pv[4], pv[5]),
+                                                             M::pack2(pv[6], pv[7])));
+      // ---- O^T += V^T . P^T : transpose the lane's 8 x NE block, one MFMA per column e
 #pragma unroll
-    for (int e = 0; e < NE; ++e) {
-      const uint32_t sel = (e & 1) ? 0x07060302u : 0x05040100u;
-      uint32_t w[4];
+      for (int e = 0; e < NE; ++e) {
+        const uint32_t sel = (e & 1) ? 0x07060302u : 0x05040100u;
+        uint32_t w[4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) w[u] = __builtin_amdgcn_perm(vst[2 * u + 1].w[e >> 1], vst[2 * u].w[e >> 1], sel);
-      uint4 traw = make_uint4(w[0], w[1], w[2], w[3]);
-      if constexpr (kSplitP) acc[e] = M::run(__builtin_bit_cast(opvec, traw), plo, acc[e]);
-      acc[e] = M::run(__builtin_bit_cast(opvec, traw), pop, acc[e]);
+        for (int u = 0; u < 4; ++u) w[u] = __builtin_amdgcn_perm(vst[2 * u + 1].w[e >> 1], vst[2 * u].w[e >> 1], sel);
+        acc[e] = M::run(__builtin_bit_cast(opvec, make_uint4(w[0], w[1], w[2], w[3])), pop, acc[e]);
+      }
     }
     if (more) issue_v(cur);              // next tile's V: lands while the next K tile is being scored
   }
@@ -546,14 +558,14 @@ k_decode_attn(const AttnParamsT<NS> P) {
   l_run += __shfl_xor(l_run, 32, 64);
   __syncthreads();                       // every wave is done with its K tile
   VT_PROF(2);
-  float* red_o = reinterpret_cast<float*>(&lds[0][0]);    // [WAVES][G][D] floats: at most the K tiles' memory
-  const int G = a_G;
-  if (l16 < G) {
+  float* red_o = reinterpret_cast<float*>(&lds[0][0]);    // [WAVES][columns][D] floats: at most the K tiles' memory
+  const int G = a_G, nc = PMODE == P_PARTS ? 3 * G : G;
+  if (l16 < nc) {
 #pragma unroll
     for (int e = 0; e < NE; ++e)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) red_o[(wave * G + l16) * kD + (lg * 4 + i) * NE + e] = acc[e][i];
-    if (lg == 0) {
+      for (int i = 0; i < 4; ++i) red_o[(wave * nc + l16) * kD + (lg * 4 + i) * NE + e] = acc[e][i];
+    if (lg == 0) {               // (of the first part's columns: the others say the same)
       red_ml[(wave * 16 + l16) * 2 + 0] = m_ref;
       red_ml[(wave * 16 + l16) * 2 + 1] = l_run;
     }
@@ -573,7 +585,16 @@ k_decode_attn(const AttnParamsT<NS> P) {
 #pragma unroll
     for (int w = 0; w < WAVES; ++w) {
       const float sc = __builtin_amdgcn_exp2f(red_ml[(w * 16 + h) * 2] - mx);
-      const float4 r = *reinterpret_cast<const float4*>(&red_o[(w * G + h) * kD + (idx - h * kD)]);
+      float4 r = *reinterpret_cast<const float4*>(&red_o[(w * nc + h) * kD + (idx - h * kD)]);
+      if constexpr (PMODE == P_PARTS) {
+        const float4 r1 = *reinterpret_cast<const float4*>(&red_o[(w * nc + G + h) * kD + (idx - h * kD)]);
+        const float4 r2 = *reinterpret_cast<const float4*>(&red_o[(w * nc + 2 * G + h) * kD + (idx - h * kD)]);
+        auto sum = [](float a, float b, float c) {
+          const float t = (a + (b + c * (1.0f / M::kStep)) * (1.0f / M::kStep)) * (1.0f / M::kScale);
+          return __builtin_fabsf(a) <= 3.4028235e38f ? t : a;     // an infinity in V: lesser parts may be zero (NaN) or negative
+        };
+        r = make_float4(sum(r.x, r1.x, r2.x), sum(r.y, r1.y, r2.y), sum(r.z, r1.z, r2.z), sum(r.w, r1.w, r2.w));
+      }
       o.x += r.x * sc; o.y += r.y * sc; o.z += r.z * sc; o.w += r.w * sc;
       l += red_ml[(w * 16 + h) * 2 + 1] * sc;
     }
@@ -1246,26 +1267,28 @@ static int launch_attention(const vt_desc* Q, const vt_desc* K, const vt_desc* V
     static_cast<AttnArgs&>(P2) = P;
     for (int i = 0; i < 2; ++i) P2.seg[i] = P.seg[i];
   }
-#define VT_ATTN_NS(TT, DD, MM, SP, OCC)                                                                               \
+#define VT_ATTN_NS(TT, DD, MM, PM, OCC)                                                                               \
   do {                                                                                                                \
-    if (few) hipLaunchKernelGGL((k_decode_attn<TT, DD, MM, SP, 2, kWaves, OCC>), grid, dim3(kWaves * 64), 0, st, P2);     \
-    else hipLaunchKernelGGL((k_decode_attn<TT, DD, MM, SP, kMaxSegs, kWaves, OCC>), grid, dim3(kWaves * 64), 0, st, P);   \
+    if (few) hipLaunchKernelGGL((k_decode_attn<TT, DD, MM, PM, 2, kWaves, OCC>), grid, dim3(kWaves * 64), 0, st, P2);     \
+    else hipLaunchKernelGGL((k_decode_attn<TT, DD, MM, PM, kMaxSegs, kWaves, OCC>), grid, dim3(kWaves * 64), 0, st, P);   \
   } while (0)
-#define VT_ATTN(TT, DD, SP, OCC)                                                                                      \
+#define VT_ATTN(TT, DD, PM, OCC)                                                                                      \
   do {                                                                                                                \
-    if (ns_eff > 8) VT_ATTN_NS(TT, DD, true, SP, OCC);                                                                    \
-    else VT_ATTN_NS(TT, DD, false, SP, OCC);                                                                              \
+    if (ns_eff > 8) VT_ATTN_NS(TT, DD, true, PM, OCC);                                                                    \
+    else VT_ATTN_NS(TT, DD, false, PM, OCC);                                                                              \
   } while (0)
-  if (P.D == 64) {
-    if (Q->dtype == VT_BF16) VT_ATTN(bf16_t, 64, true, 4);
-    else VT_ATTN(f16_t, 64, true, 4);
-  } else if (P.batch_table) {
-    if (Q->dtype == VT_BF16) VT_ATTN(bf16_t, 128, true, 2);
-    else VT_ATTN(f16_t, 128, true, 2);
-  } else {
-    if (Q->dtype == VT_BF16) VT_ATTN(bf16_t, 128, false, 3);
-    else VT_ATTN(f16_t, 128, false, 3);
-  }
+#define VT_ATTN_T(TT)                                                                                                 \
+  do {                                                                                                                \
+    const bool parts = P.G <= kPartHeads;                                                                               \
+    if (P.D == 64 && parts) VT_ATTN(TT, 64, P_PARTS, 4);                                                                \
+    else if (P.D == 64) VT_ATTN(TT, 64, P_F32, 4);                                                                      \
+    else if (P.batch_table && parts) VT_ATTN(TT, 128, P_PARTS, 2);                                                      \
+    else if (P.batch_table) VT_ATTN(TT, 128, P_F32, 2);                                                                 \
+    else VT_ATTN(TT, 128, P_16, 3);                                                                                     \
+  } while (0)
+  if (Q->dtype == VT_BF16) VT_ATTN_T(bf16_t);
+  else VT_ATTN_T(f16_t);
+#undef VT_ATTN_T
 #undef VT_ATTN
 #undef VT_ATTN_NS
   rc = check_launch(who);
