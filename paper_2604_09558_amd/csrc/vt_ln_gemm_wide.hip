@@ -139,7 +139,6 @@ k_ln_gemm_wide(const WideParams P) {
     constexpr int RPP = 64 / LP2, NP = WBM / RPP;
     constexpr int U = 2;           // passes whose rows are in flight together
     const int c0 = lane % LP2, r0 = lane / LP2;
-    const float inv_k = 1.0f / (float)K;
     for (int p0 = wave; p0 < NP; p0 += n_waves * U) {
       uint4 raw[U][CH];
 #pragma unroll
@@ -166,7 +165,7 @@ k_ln_gemm_wide(const WideParams P) {
           for (int j = 0; j < 8; ++j) x[h][j] = to_float(v.v[j]);
           s += ((x[h][0] + x[h][1]) + (x[h][2] + x[h][3])) + ((x[h][4] + x[h][5]) + (x[h][6] + x[h][7]));
         }
-        const float mean = row_sum<LP2>(s) * inv_k;
+        const float mean = row_sum<LP2>(s) / (float)K;
         float q = 0.f;
 #pragma unroll
         for (int h = 0; h < CH; ++h) {
@@ -177,7 +176,8 @@ k_ln_gemm_wide(const WideParams P) {
             q += x[h][j] * x[h][j];
           }
         }
-        const float rstd = __builtin_amdgcn_rsqf(row_sum<LP2>(q) * inv_k + P.eps);
+        // as in the generic kernel: a subnormal variance (eps = 0) has a finite root, which v_rsq_f32 does not give
+        const float rstd = 1.0f / sqrtf(row_sum<LP2>(q) / (float)K + P.eps);
         const int p = p0 + u * n_waves;
         if (p < NP) {
 #pragma unroll

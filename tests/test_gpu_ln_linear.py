@@ -147,3 +147,20 @@ def test_weight_streamed_kernel(gpu, B, R, win, C, N, dtype):
         p.run()
         torch.cuda.synchronize()
         assert torch.equal(p.out, first)
+
+
+@pytest.mark.parametrize("C", [40, 256])
+def test_subnormal_variance_without_eps(gpu, C):
+    """Rows of +-1e-21 and eps = 0: the variance is a subnormal fp32 number, the normalised row +-1."""
+    vt, tio, pipelines, torch = gpu
+    wl = workloads.c4_window_ln_linear(seed=9, B=1, R=6, win=3, C=C, N=72, dtype="bf16")
+    sign = np.where(np.arange(C) % 2 == 0, 1.0, -1.0)
+    wl.sources["X"] = workloads.encode(np.broadcast_to(sign * 1e-21, wl.sources["X"].shape).astype(np.float32), "bf16")
+    wl.consumer["eps"] = 0.0
+    ref = run_workload(wl)["out"]
+    p = pipelines.Gemm(tio.DeviceWorkload(wl), fused=True)
+    p.run()
+    torch.cuda.synchronize()
+    got = tio.to_host_f64(p.out).reshape(ref.shape)
+    assert np.isfinite(got).all()
+    check(got, ref)
