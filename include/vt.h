@@ -229,7 +229,7 @@ int vt_gemm(const vt_desc* const* A, const vt_desc* const* B, void* const* C, in
  * runs on a generic kernel that applies the whole map per element: same result to rounding,
  * far slower, no context splits; vt_decode_attn_plan reports VT_ERR_UNSUPPORTED for such operands.
  * D = 64 and tables over the batch also run there when the workspace or the alignment of out is not
- * what the planned kernel needs (otherwise that is an error) or scale is outside [1e-6, 1e6], so vt_decode_attn_plan reports
+ * what the planned kernel needs (otherwise that is an error) or scale is outside [-1e6, 1e6], so vt_decode_attn_plan reports
  * VT_ERR_UNSUPPORTED for them too.
  * workspace: device pointer (16-byte aligned) of at least vt_decode_attn_workspace(...) bytes,
  * holding arrival counters and the per-split partial results, prepared once with

@@ -471,13 +471,17 @@ k_decode_attn(const AttnParamsT<NS> P) {
     float sv[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) sv[j] = s[j >> 2][j & 3];
+    // (rows past the end of a short tile are masked behind the scale, which may be zero or negative)
+    float tv[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) tv[j] = sv[j] * c;
     if (partial) {
 #pragma unroll
       for (int j = 0; j < 8; ++j)
-        if (r0 + (j >> 2) * 16 + lg * 4 + (j & 3) >= r_end) sv[j] = -3.0e38f;
+        if (r0 + (j >> 2) * 16 + lg * 4 + (j & 3) >= r_end) tv[j] = -3.0e38f;
     }
-    float tmax = fmaxf(fmaxf(fmaxf(sv[0], sv[1]), fmaxf(sv[2], sv[3])), fmaxf(fmaxf(sv[4], sv[5]), fmaxf(sv[6], sv[7])));
-    tmax = fmaxf(tmax * c, -1.0e30f);
+    float tmax = fmaxf(fmaxf(fmaxf(tv[0], tv[1]), fmaxf(tv[2], tv[3])), fmaxf(fmaxf(tv[4], tv[5]), fmaxf(tv[6], tv[7])));
+    tmax = fmaxf(tmax, -1.0e30f);
     if (__builtin_amdgcn_ballot_w64(tmax > m_ref + M::kThreshold) != 0) {
       // move the reference maximum of every head to its new maximum and rescale what was
       // accumulated against the old one (rare after the first tiles)
@@ -494,7 +498,12 @@ k_decode_attn(const AttnParamsT<NS> P) {
     }
     float pv[8];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) pv[j] = __builtin_amdgcn_exp2f(fmaf(sv[j], c, -m_ref));   // masked rows: exp2(-huge) = 0
+    for (int j = 0; j < 8; ++j) pv[j] = __builtin_amdgcn_exp2f(fmaf(sv[j], c, -m_ref));
+    if (partial) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j)
+        if (r0 + (j >> 2) * 16 + lg * 4 + (j & 3) >= r_end) pv[j] = 0.f;
+    }
     l_run += ((pv[0] + pv[1]) + (pv[2] + pv[3])) + ((pv[4] + pv[5]) + (pv[6] + pv[7]));
     if (PMODE != P_16 && partial) {      // the rows that a short tile repeats have no weight: an infinity there is not read
 #pragma unroll
@@ -1216,11 +1225,11 @@ static int launch_attention(const vt_desc* Q, const vt_desc* K, const vt_desc* V
   const bool tight = clear_counters || workspace_bytes < kCounterBytes + partial;
   const size_t counters = rc == VT_OK && tight ? counters_used(P.B, (int64_t)P.Hkv * P.G) : kCounterBytes;
   const size_t need = counters + partial;
-  // the generic kernel needs no workspace and no alignment of out, and takes any scale (the rows past the
-  // end of a tile are masked with -3e38 before they are scaled): 64-wide heads and tables over the batch
-  // keep it where what the planned kernel needs is not given
+  // the generic kernel needs no workspace and no alignment of out, and scales of such size do not take its
+  // scores out of range through a factor of log2(e): 64-wide heads and tables over the batch keep it where
+  // what the planned kernel needs is not given
   const bool unplaced = rc == VT_OK && (P.D != 128 || P.batch_table) &&
-                        (workspace_bytes < need || (uintptr_t)workspace % 16 || (uintptr_t)out % 8 || !(scale >= 1e-6f && scale <= 1e6f));
+                        (workspace_bytes < need || (uintptr_t)workspace % 16 || (uintptr_t)out % 8 || !(std::fabs(scale) <= 1e6f));
   if (rc == VT_ERR_UNSUPPORTED || unplaced) {
     // maps or a head dim the planned kernel does not take: the generic kernel, if the shapes allow
     const std::string why = vt_last_error();

@@ -438,3 +438,22 @@ def test_attention_sink_of_64_wide_heads(gpu, dtype, G, S, sink, inf_row):
     eps = 2.0 ** -9 if dtype == "bf16" else 2.0 ** -12
     # below 2^-14 f16 is spaced by 2^-24; 1e-4: fp32 scores, exponentials and sums
     assert np.all(np.abs(got - ref) <= (2 * eps + 1e-4) * np.abs(ref) + 2.0 ** -25)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("S,scale", [(45, 0.0), (45, -0.125), (96, -0.125), (333, 0.0)])
+def test_scales_that_are_not_positive(gpu, D, S, scale):
+    """Rows that a short tile repeats must not count, whatever the sign of the scale."""
+    vt, tio, pipelines, torch = gpu
+    wl = workloads.c2_decode_attention(seed=15, B=2, Hkv=2, G=3, S=S, D=D)
+    wl.consumer["scale"] = scale
+    ref = run_workload(wl)
+    p = pipelines.DecodeAttention(tio.DeviceWorkload(wl))
+    p.out.fill_(float("nan"))
+    p.lse.fill_(float("nan"))
+    p.run()
+    torch.cuda.synchronize()
+    got = tio.to_host_f64(p.out)
+    assert np.isfinite(got).all()
+    check(got, ref["out"])
+    assert np.max(np.abs(tio.to_host_f64(p.lse) - ref["lse"])) <= 2e-3
