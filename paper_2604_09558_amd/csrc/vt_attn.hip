@@ -58,6 +58,7 @@ namespace {
 constexpr int kTile = 32;        // context rows per wave step
 constexpr int kMaxAttnPieces = 4;
 constexpr int kMaxSegs = 8;
+constexpr float kNoScore = -3.4028235e38f;   // below (or equal to) every finite score
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -373,7 +374,7 @@ k_decode_attn(const AttnParamsT<NS> P) {
     }
   }
 
-  float m_ref = -1.0e30f;   // reference maximum (log2 domain) of head l16, identical in the 4 lane groups
+  float m_ref = kNoScore;   // reference maximum (log2 domain) of head l16, identical in the 4 lane groups
   float l_run = 0.0f;       // this lane's share of the denominator, relative to m_ref
   f32x4 acc[NE];
 #pragma unroll
@@ -478,10 +479,10 @@ k_decode_attn(const AttnParamsT<NS> P) {
     if (partial) {
 #pragma unroll
       for (int j = 0; j < 8; ++j)
-        if (r0 + (j >> 2) * 16 + lg * 4 + (j & 3) >= r_end) tv[j] = -3.0e38f;
+        if (r0 + (j >> 2) * 16 + lg * 4 + (j & 3) >= r_end) tv[j] = kNoScore;
     }
     float tmax = fmaxf(fmaxf(fmaxf(tv[0], tv[1]), fmaxf(tv[2], tv[3])), fmaxf(fmaxf(tv[4], tv[5]), fmaxf(tv[6], tv[7])));
-    tmax = fmaxf(tmax, -1.0e30f);
+    tmax = fmaxf(tmax, kNoScore);
     if (__builtin_amdgcn_ballot_w64(tmax > m_ref + M::kThreshold) != 0) {
       // move the reference maximum of every head to its new maximum and rescale what was
       // accumulated against the old one (rare after the first tiles)
@@ -498,7 +499,8 @@ k_decode_attn(const AttnParamsT<NS> P) {
     }
     float pv[8];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) pv[j] = __builtin_amdgcn_exp2f(fmaf(sv[j], c, -m_ref));
+    for (int j = 0; j < 8; ++j) pv[j] = __builtin_amdgcn_exp2f(PMODE == P_16 ? fmaf(sv[j], c, -m_ref) : tv[j] - m_ref);
+    // (the maximum is one of the rounded products: in fp32 the difference to it is exact for scores of any size)
     if (partial) {
 #pragma unroll
       for (int j = 0; j < 8; ++j)
@@ -586,7 +588,7 @@ k_decode_attn(const AttnParamsT<NS> P) {
   // (written through to where every compute die sees them), whole cache lines per wave
   for (int idx = threadIdx.x * 4; idx < G * kD; idx += WAVES * 64 * 4) {
     const int h = idx / kD;
-    float mx = -1.0e30f;
+    float mx = kNoScore;
 #pragma unroll
     for (int w = 0; w < WAVES; ++w) mx = fmaxf(mx, red_ml[(w * 16 + h) * 2]);
     float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -674,10 +676,10 @@ k_decode_attn(const AttnParamsT<NS> P) {
     *reinterpret_cast<Vec<T, 4>*>(&out[hq * kD + d]) = r;
     if (a_lse && d == 0) a_lse[hq] = (mx + log2f(l)) * 0.6931471805599453f;
   };
-  float mx = -1.0e30f;
+  float mx = kNoScore;
   for (int idx = idx0; idx < G * kD; idx += WAVES * 64 * 4) {     // (one round if lw > 0)
     const int h = idx / kD, d = idx - h * kD;
-    mx = -1.0e30f;
+    mx = kNoScore;
     for (int sp = 0; sp < ns; ++sp) mx = fmaxf(mx, ml_sh[(sp * G + h) * 2]);
     float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
     float l = 0.f;

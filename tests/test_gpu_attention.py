@@ -457,3 +457,29 @@ def test_scales_that_are_not_positive(gpu, D, S, scale):
     assert np.isfinite(got).all()
     check(got, ref["out"])
     assert np.max(np.abs(tio.to_host_f64(p.lse) - ref["lse"])) <= 2e-3
+
+
+@pytest.mark.parametrize("D,paged", [(64, False), (64, True), (128, True)])
+@pytest.mark.parametrize("k", [-1e32, -1e36])
+def test_scores_of_large_magnitude(gpu, D, paged, k):
+    """All keys alike and all scores far below -1e30: equal weights."""
+    vt, tio, pipelines, torch = gpu
+    if paged:
+        wl = workloads.paged_decode_attention(seed=19, B=2, Hkv=2, G=3, pages_per_seq=1, page=64, D=D)
+        names = ("Qs", "Kpool")
+    else:
+        wl = workloads.c2_decode_attention(seed=19, B=2, Hkv=2, G=3, S=45, D=D)
+        names = ("QKV", "Kcache")
+    one, kk = (workloads.encode(np.array([x], dtype=np.float32), "bf16")[0] for x in (1.0, k))
+    q = wl.sources[names[0]]
+    q[..., :6 * D] = one
+    if not paged:
+        q[..., 6 * D:8 * D] = kk
+    wl.sources[names[1]][:] = kk
+    ref = run_workload(wl)["out"]
+    p = pipelines.DecodeAttention(tio.DeviceWorkload(wl))
+    p.out.fill_(float("nan"))
+    p.run()
+    torch.cuda.synchronize()
+    assert p.ws.any()
+    check(tio.to_host_f64(p.out), ref, atol=1e-4, rtol=2.0 ** -8)
