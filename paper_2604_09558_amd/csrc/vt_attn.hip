@@ -1001,7 +1001,8 @@ int plan_operand(const vt_desc& d, const char* name, int64_t G, AttnOperand* out
       }
     }
     a.page_rows = page_rows;
-    if (st * esz >= (1ll << 32) || st < 0) return fail(VT_ERR_UNSUPPORTED, std::string(name) + ": context stride too large");
+    // (a lane's row inside a tile is a 32-bit offset)
+    if (st >= (1ll << 32) / kTile / esz || st < 0) return fail(VT_ERR_UNSUPPORTED, std::string(name) + ": context stride too large");
     a.st = (uint32_t)(st * esz);
     a.t_lo = (int32_t)p.lo[2];
     a.t_hi = (int32_t)p.hi[2];

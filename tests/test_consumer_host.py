@@ -1,6 +1,5 @@
 """What the consumers decide or refuse on the host, before anything is launched (no GPU is used:
 the addresses are never dereferenced)."""
-import numpy as np
 import pytest
 
 import paper_2604_09558_amd as vt
@@ -23,3 +22,19 @@ def test_attention_plan_splits_only_where_every_pair_has_a_counter():
     # the counters' share of the workspace is the same for every problem
     share = {vt.vt_decode_attn_workspace(B, 8, 128, 400, 1) - B * 8 * 130 * 4 for B in (1, 16, 4096)}
     assert len(share) == 1
+
+
+@pytest.mark.parametrize("stride,taken", [((1 << 26) - 8, True), (1 << 26, False), (1 << 28, False)])
+def test_attention_plan_refuses_rows_beyond_a_32_bit_tile(stride, taken):
+    """32 rows of K or V have to lie within 4 GiB (a row's offset in its tile is a 32-bit number): rows
+    further apart run on the generic kernel, which the plan reports as unsupported."""
+    q = vt.build_chain([], {"Q": ((1, 1, 1, 128), "bf16", FAKE)}, "Q")
+    far = vt.build_chain([], {"K": ((1, 1, 40, 128), "bf16", FAKE, (40 * stride, 40 * stride, stride, 1))}, "K")
+    near = vt.build_chain([], {"K": ((1, 1, 40, 128), "bf16", FAKE)}, "K")
+    for k, v in ((far, near), (near, far)):
+        if taken:
+            assert vt.vt_decode_attn_plan(q, k, v)["splits"] == 1
+        else:
+            with pytest.raises(vt.VtError) as ei:
+                vt.vt_decode_attn_plan(q, k, v)
+            assert ei.value.code == vt.ERR_UNSUPPORTED
