@@ -1231,11 +1231,15 @@ static int launch_attention(const vt_desc* Q, const vt_desc* K, const vt_desc* V
   // the generic kernel needs no workspace and no alignment of out, and scales of such size do not take its
   // scores out of range through a factor of log2(e): 64-wide heads and tables over the batch keep it where
   // what the planned kernel needs is not given
-  const bool unplaced = rc == VT_OK && (P.D != 128 || P.batch_table) &&
-                        (workspace_bytes < need || (uintptr_t)workspace % 16 || (uintptr_t)out % 8 || !(std::fabs(scale) <= 1e6f));
+  const bool short_ws = workspace_bytes < need, misaligned = (uintptr_t)workspace % 16 || (uintptr_t)out % 8;
+  const bool unplaced = rc == VT_OK && (P.D != 128 || P.batch_table) && (short_ws || misaligned || !(std::fabs(scale) <= 1e6f));
+  const auto refusal = [&] {
+    return std::string(who) + (short_ws ? ": workspace too small (" + std::to_string(need) + " bytes needed, " + std::to_string(workspace_bytes) + " available)"
+                               : misaligned ? ": misaligned workspace or out (16 and 8 bytes)" : ": scale outside [-1e6, 1e6]");
+  };
   if (rc == VT_ERR_UNSUPPORTED || unplaced) {
     // maps or a head dim the planned kernel does not take: the generic kernel, if the shapes allow
-    const std::string why = vt_last_error();
+    const std::string why = unplaced ? refusal() + ", and too large for the generic kernel" : vt_last_error();
     const int64_t B = K->shape[0], Hq = K->shape[1], S = K->shape[2], D = K->shape[3];
     DevDesc DQ, DK, DV;
     int64_t o1, i1, o2, i2, o3, i3;
@@ -1251,10 +1255,7 @@ static int launch_attention(const vt_desc* Q, const vt_desc* K, const vt_desc* V
   if (rc != VT_OK) return rc;
   const int64_t B = P.B, Hq = (int64_t)P.Hkv * P.G;
   const int ns_eff = P.n_splits, Hkv = P.Hkv;
-  if (workspace_bytes < need)
-    return fail(VT_ERR_INVALID_ARG, std::string(who) + ": workspace too small (" + std::to_string(need) + " bytes needed, " +
-                                        std::to_string(workspace_bytes) + " available)");
-  if ((uintptr_t)workspace % 16 || (uintptr_t)out % 8) return fail(VT_ERR_INVALID_ARG, std::string(who) + ": misaligned workspace or out (16 and 8 bytes)");
+  if (short_ws || misaligned) return fail(VT_ERR_INVALID_ARG, refusal());
   P.scale_log2 = scale * 1.4426950408889634f;
   P.tickets = static_cast<uint32_t*>(workspace);
   P.ws_ml = reinterpret_cast<float*>(static_cast<char*>(workspace) + counters);

@@ -38,3 +38,15 @@ def test_attention_plan_refuses_rows_beyond_a_32_bit_tile(stride, taken):
             with pytest.raises(vt.VtError) as ei:
                 vt.vt_decode_attn_plan(q, k, v)
             assert ei.value.code == vt.ERR_UNSUPPORTED
+
+
+@pytest.mark.parametrize("ws_bytes,out,scale,word", [(16, FAKE, 0.125, "16 available"), (1 << 40, FAKE + 4, 0.125, "misaligned"), (1 << 40, FAKE, 1e9, "scale")])
+def test_attention_says_why_neither_kernel_takes_a_call(ws_bytes, out, scale, word):
+    """2^31 virtual elements are more than the generic kernel indexes: a call that it would otherwise take over
+    is refused with the reason why the planned kernel left it, not with an earlier call's message."""
+    q, k, v = decode_descs(1, 8, 16, 1 << 18, 64)
+    with pytest.raises(vt.VtError):
+        vt.vt_decode_attn(k, k, v, 0.125, FAKE, FAKE, 1 << 40)            # the earlier call: shapes do not fit
+    with pytest.raises(vt.VtError) as ei:
+        vt.vt_decode_attn(q, k, v, scale, out, FAKE, ws_bytes)
+    assert ei.value.code == vt.ERR_UNSUPPORTED and word in str(ei.value)
