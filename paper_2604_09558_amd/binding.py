@@ -316,23 +316,35 @@ def _ptr(t):
     return C.c_void_p(int(t))
 
 
-_torch = None
+_current_stream = None        # () -> handle of torch's current stream
+
+
+def _find_current_stream():
+    """How the current stream's handle is found, or None without torch or without a GPU.  torch.cuda.current_stream()
+    builds an object around the handle, which took 2.7 us of an 8 us call; torch's own functions for the bare handle
+    are used where this version of it has them."""
+    try:
+        import torch
+    except ImportError:
+        return None
+    if not torch.cuda.is_available():
+        return None
+    torch.cuda.init()
+    raw, device = (getattr(torch._C, n, None) for n in ("_cuda_getCurrentRawStream", "_cuda_getDevice"))
+    if raw is None or device is None:
+        return lambda: torch.cuda.current_stream().cuda_stream
+    return lambda: raw(device())
 
 
 def _stream(stream):
-    """The stream of a call: `stream`, or torch's current one.  The handle is asked for directly:
-    torch.cuda.current_stream() builds an object around it, which took 2.7 us of an 8 us call."""
-    global _torch
+    """The stream of a call: `stream`, or torch's current one (without torch or a GPU: the default stream)."""
+    global _current_stream
     if stream is None:
-        try:
-            if _torch is None:
-                import torch
-                _torch = torch
-            if _torch.cuda.is_initialized():
-                return C.c_void_p(_torch._C._cuda_getCurrentRawStream(_torch._C._cuda_getDevice()))
-            return C.c_void_p(_torch.cuda.current_stream().cuda_stream)
-        except Exception:
-            return None
+        if _current_stream is None:
+            _current_stream = _find_current_stream()
+            if _current_stream is None:
+                return None
+        return C.c_void_p(_current_stream())
     if hasattr(stream, "cuda_stream"):
         return C.c_void_p(stream.cuda_stream)
     return C.c_void_p(int(stream))

@@ -50,3 +50,29 @@ def test_attention_says_why_neither_kernel_takes_a_call(ws_bytes, out, scale, wo
     with pytest.raises(vt.VtError) as ei:
         vt.vt_decode_attn(q, k, v, scale, out, FAKE, ws_bytes)
     assert ei.value.code == vt.ERR_UNSUPPORTED and word in str(ei.value)
+
+
+def test_the_current_stream_is_never_lost(monkeypatch):
+    """A torch without the functions for the bare handle: the public call is asked, and what it raises is
+    raised, not turned into the default stream."""
+    import torch
+    from paper_2604_09558_amd import binding
+
+    class Stream:
+        cuda_stream = 0x5150
+
+    monkeypatch.setattr(binding, "_current_stream", None, raising=False)
+    monkeypatch.setattr(torch.cuda, "is_available", lambda: True)
+    monkeypatch.setattr(torch.cuda, "init", lambda: None)
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    for name in ("_cuda_getCurrentRawStream", "_cuda_getDevice"):
+        monkeypatch.delattr(torch._C, name, raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: Stream())
+    assert binding._stream(None).value == 0x5150
+    assert binding._stream(0x20).value == 0x20 and binding._stream(Stream()).value == 0x5150
+
+    def broken():
+        raise RuntimeError("no such device")
+    monkeypatch.setattr(torch.cuda, "current_stream", broken)
+    with pytest.raises(RuntimeError):
+        binding._stream(None)
