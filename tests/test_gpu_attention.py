@@ -26,6 +26,18 @@ def check(got, ref, atol=1e-2, rtol=1e-2):
     return err.max()
 
 
+def run_without_a_workspace(gpu, p, n_splits=0):
+    """The same call with 16 bytes of workspace: the generic kernel, which writes all of out and lse and
+    nothing of the workspace."""
+    vt, tio, pipelines, torch = gpu
+    p.out.fill_(float("nan"))
+    p.lse.fill_(float("nan"))
+    p.ws.fill_(0xA5)
+    vt.vt_decode_attn(p.q, p.k, p.v, p.scale, p.out, p.ws, 16, n_splits, lse=p.lse)
+    torch.cuda.synchronize()
+    assert bool((p.ws == 0xA5).all())
+
+
 CASES = [
     # B, Hkv, G, S, dtype, n_splits
     (2, 2, 4, 300, "bf16", 0),      # ragged tail inside a tile, several tiles per wave
@@ -103,7 +115,7 @@ def test_decode_attention_full_size(gpu):
 
 
 def test_other_head_dims_run_on_the_generic_kernel(gpu):
-    """Head dims other than 128 (and maps the planned kernel does not take) run on the generic
+    """Head dims other than 64 and 128 (and maps the planned kernel does not take) run on the generic
     kernel, which finds every element through the whole map."""
     vt, tio, pipelines, torch = gpu
     for D, S, G in ((64, 300, 2), (96, 70, 4), (256, 40, 1)):
@@ -264,12 +276,11 @@ def test_heads_of_64(gpu, B, Hkv, G, S, dtype, ns):
     p = res["pipeline"]
     assert p.ws.any()                                    # partial results: the planned kernel ran
     eps = 2.0 ** -8 if dtype == "bf16" else 2.0 ** -11
-    for _ in range(2):
+    for generic in (False, True):
+        if generic:
+            run_without_a_workspace(gpu, p, ns)
         assert np.all(np.abs(tio.to_host_f64(p.out) - ref["out"]) <= eps * np.abs(ref["out"]) + 1e-4)
         assert np.max(np.abs(tio.to_host_f64(p.lse) - ref["lse"])) <= 1e-4
-        # a workspace that holds no partial results: the generic kernel, which needs none
-        vt.vt_decode_attn(p.q, p.k, p.v, p.scale, p.out, p.ws, 16, ns, lse=p.lse)
-        torch.cuda.synchronize()
 
 
 @pytest.mark.parametrize("B,Hkv,G,P,page", [(2, 2, 4, 3, 32), (3, 1, 7, 2, 96)])
@@ -312,11 +323,11 @@ def test_one_page_per_sequence(gpu, B, Hkv, G, D, page):
     ref = run_workload(wl)
     p = pipelines.run_decode_attention(tio.DeviceWorkload(wl))["pipeline"]
     assert p.ws.any()
-    for _ in range(2):
+    for generic in (False, True):
+        if generic:
+            run_without_a_workspace(gpu, p)
         assert np.all(np.abs(tio.to_host_f64(p.out) - ref["out"]) <= 2.0 ** -8 * np.abs(ref["out"]) + 1e-4)
         assert np.max(np.abs(tio.to_host_f64(p.lse) - ref["lse"])) <= 1e-4
-        vt.vt_decode_attn(p.q, p.k, p.v, p.scale, p.out, p.ws, 16, lse=p.lse)
-        torch.cuda.synchronize()
 
 
 def test_cache_slots_through_a_table_and_the_new_row(gpu):
@@ -345,14 +356,19 @@ def test_cache_slots_through_a_table_and_the_new_row(gpu):
 
 @pytest.mark.parametrize("S,scale,n_splits", [(45, 0.0, 0), (45, -0.125, 0), (45, 0.125, -1), (96, -0.125, 0)])
 def test_heads_of_64_odd_arguments(gpu, S, scale, n_splits):
-    """Scales and split counts that only the generic kernel takes: rows past the end must not count."""
+    """Scales that are not positive, and a split count that only the generic kernel takes: rows past the end
+    must not count."""
     vt, tio, pipelines, torch = gpu
     wl = workloads.c2_decode_attention(seed=15, B=2, Hkv=2, G=3, S=S, D=64)
     wl.consumer["scale"] = scale
     ref = run_workload(wl)
-    p = pipelines.run_decode_attention(tio.DeviceWorkload(wl))["pipeline"]
-    vt.vt_decode_attn(p.q, p.k, p.v, scale, p.out, p.ws, p.ws.numel() * p.ws.element_size(), n_splits, lse=p.lse)
+    p = pipelines.DecodeAttention(tio.DeviceWorkload(wl))
+    p.out.fill_(float("nan"))
+    p.lse.fill_(float("nan"))
+    vt.vt_decode_attn(p.q, p.k, p.v, scale, p.out, p.ws, p.ws_bytes, n_splits, lse=p.lse)
     torch.cuda.synchronize()
+    assert bool(p.ws.any()) == (n_splits >= 0)           # partial results: the planned kernel
+    assert np.max(np.abs(tio.to_host_f64(p.lse) - ref["lse"])) <= 1e-4
     assert np.all(np.abs(tio.to_host_f64(p.out) - ref["out"]) <= 2.0 ** -8 * np.abs(ref["out"]) + 1e-4)
 
 

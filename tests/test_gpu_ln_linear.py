@@ -108,10 +108,12 @@ def test_c4_one_full_round_plus_a_partial_one_and_f32_output(gpu):
     check(out32.cpu().numpy().astype(np.float64).reshape(ref.shape), ref, atol=2e-3, rtol=2e-3)
 
 
-@pytest.mark.parametrize("B,R,win,C,N,dtype", [(1, 6, 3, 96, 200, "f16"), (1, 4, 2, 256, 520, "bf16"), (2, 6, 3, 40, 24, "f16")])
+@pytest.mark.parametrize("B,R,win,C,N,dtype", [(1, 6, 3, 96, 200, "f16"), (1, 4, 2, 256, 520, "bf16"), (2, 6, 3, 40, 24, "f16"),
+                                                (1, 6, 3, 36, 24, "f16"), (1, 4, 2, 1032, 40, "bf16"), (2, 6, 3, 64, 44, "f16")])
 def test_shapes_outside_the_fused_kernel_run_on_the_generic_one(gpu, B, R, win, C, N, dtype):
-    """Feature sizes other than 64 / 128 and more than 384 outputs: the LayerNorm prologue runs in
-    the generic kernel (whole map per element), same values to the same tolerance."""
+    """Feature sizes other than 64 / 128 and more than 384 outputs: the weight-streaming kernel, and the generic
+    one (whole map per element) for more than 1024 features or sizes that are not multiples of 8; same values
+    to the same tolerance."""
     vt, tio, pipelines, torch = gpu
     wl = workloads.c4_window_ln_linear(seed=5, B=B, R=R, win=win, C=C, N=N, dtype=dtype)
     ref = run_workload(wl)["out"]
