@@ -1024,7 +1024,7 @@ int most_splits(int units, int S, int n_splits) {
 
 // Two workgroups per compute unit (the 64-wide heads' tiles are half as many bytes, but four are no
 // faster: 16 sequences x 8 kv heads x 2368 keys 18.3 us with 4 splits and 1.3 more with 8), or one, where
-// the units divide the chip almost evenly and there are few of them: every split costs its partial
+// the units divide the chip's 256 compute units almost evenly and there are few of them: every split costs its partial
 // results and a share of the merge.  More than 16 splits only while each keeps 352 rows.
 //   units x keys, us with 512 / units, 256 / units and this rule's splits (128-wide heads, 4 a group):
 //   8 x 8192  23.3 (64) 16.5 (32) 15.3 (24)     8 x 4096  14.2 (32) 14.2 (32) 11.8 (16)     1 x 8192  15.8 (64)  13.2 (24)

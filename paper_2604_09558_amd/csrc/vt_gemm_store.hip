@@ -43,7 +43,7 @@ constexpr int kBM = 16;           // rows per workgroup (one MFMA block)
 constexpr int kTileK = 32;        // k-rows per wave step
 constexpr int kWaves = 4;
 constexpr int kMaxOutPieces = 4;
-constexpr int kTiledFrom = 128;   // more rows than this go to the 256 x 256 tiled kernel
+constexpr int kTiledFrom = 128;   // more rows than this always go to the tiled kernels
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
@@ -425,8 +425,8 @@ int vt_gemm_store(const vt_desc* A, const vt_desc* B, const vt_desc* C, void* wo
   P.partial = reinterpret_cast<float*>(static_cast<char*>(workspace) + counters);
   // Several blocks of 16 rows: this kernel reads B once for each of them, and takes the time its busiest
   // compute unit needs to draw its share (40 GB/s, 6.5 us around it).  The tiled kernel takes over
-  // where it is expected to be faster (us here / there: 4096 x 6144 with 32 rows 24.4 / 27.5, 48 rows
-  // 35.3 / 29.0, 90 rows 64.5 / 27.0; 2048 x 3072 with 48 rows 12.7 / 14.3, 90 rows 20.3 / 14.5).
+  // where it is expected to be faster (us here / there, operands in HBM: 4096 x 6144 with 32 rows 23.0 / 26.7,
+  // 48 rows 34.9 / 28.1, 90 rows 64.4 / 26.1; 2048 x 6144 with 48 rows 21.1 / 14.5, 90 rows 35.8 / 14.1).
   if (rbs > 1) {
     const int64_t rounds = (rbs * cbs * ns_eff + compute_units() - 1) / compute_units();
     rc = gemm_store_launch(*A, *B, *C, 6500 + rounds * kps * (kBN * 2) / 40, (hipStream_t)stream);

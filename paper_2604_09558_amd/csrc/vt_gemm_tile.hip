@@ -1,21 +1,23 @@
 // Tiled GEMM for products that the 256 x 256 tiles of vt_gemm.hip would spread over too few compute
 // units: the same product, operand maps, order of accumulation (identical bits) and tile walk, with
 // smaller tiles and a deeper pipeline.  A short prompt or a decode batch's experts are bound by
-// pulling the operands into the compute units, not by the matrix cores: a unit draws some 55 GB/s
-// from L2 and 40 GB/s from HBM, so what counts is how many units share the work and how few bytes
-// each has to read (BM + BN per K step and tile).
+// pulling the operands into the compute units, not by the matrix cores: a unit draws some 55 GB/s with
+// the operands in HBM and 75 GB/s with them in the caches, so what counts is how many units share the
+// work and how few bytes each has to read (BM + BN per K step and tile).
 //
 // One workgroup of 4 waves computes a BM x BN tile of C in 32 x 32 matrix-core blocks
 // (v_mfma_f32_32x32x16).  K steps of 64 run through a ring of STAGES tiles in LDS; operands go from
 // global memory straight into it (global_load_lds_dwordx4: no registers, no store instructions),
 // STAGES steps ahead, one barrier per step; a step's fragments are read into registers during the
 // step before.  The lanes of a request land in the order of their numbers, so the swizzle that keeps
-// the fragment reads free of bank conflicts (4.3 million conflict cycles per launch without it, 6000
-// with it) is applied to what a lane asks for.  Waits count the requests by hand: a wave issues the
+// the fragment reads free of bank conflicts (4.3 million conflict cycles per launch without it, 4600
+// with it, 333 x 4096 x 4096) is applied to what a lane asks for.  Waits count the requests by hand: a wave issues the
 // same number in every step and nothing else that goes through the vector memory counter.
-// Measured (f16/bf16, K = 4096): 333 x 4096 83 -> 25 us, 400 x 6144 91 -> 34 us, 1024 x 4096 90 -> 48 us.
-// A loop with the requests alone takes the same time, one without them half of it; rings twice as
-// deep, with the waves divided into readers of A and of B, measured no faster.
+// Measured (f16/bf16, K = 4096, 256 x 256 tiles -> these, operands in HBM / in the caches): 333 x 4096
+// 89 -> 32 / 83 -> 25 us, 400 x 6144 100 -> 40 / 91 -> 35 us, 1024 x 4096 90 -> 46 / 79 -> 41 us
+// (counters: profiles/small_tiles_streamed_ln_split_rowsum.txt).  A loop with the requests alone takes
+// the same time, one without them half of it; rings twice as deep, with the waves divided into
+// readers of A and of B, measured no faster.
 #include <hip/hip_runtime.h>
 
 #include <cstring>
@@ -308,14 +310,21 @@ int launch_tile(GemmParams P8, const typename std::conditional<MAPPED, OutMap, N
   return fail(VT_ERR_UNSUPPORTED, "vt_gemm: no such tile");
 }
 
-// The tile with the shortest time, by what one K step of 64 takes a compute unit (ns, measured at K = 4096
-// with every unit at work; a unit draws about 55 GB/s of operands whatever the depth of the ring, so the
-// smaller tiles are bound by their bytes) times the rounds of tiles.  64-row tiles run two to a unit.
+// The tile with the shortest time, by what one K step of 64 takes a compute unit (ns, for operands that come
+// from HBM, as weights do that are used once per layer; the smaller tiles are bound by their bytes) times the
+// rounds of tiles.  64-row tiles run two to a unit.  Every tile forced, inputs rotating over 600 MB; behind it
+// the same on inputs that stay in the caches, where the 64-row tiles gain most and the order is the same to
+// within 10 % except for 8 x 250 rows:
 //   rows x columns of C (K = 4096): us on 256x256 / 256x128 / 128x128 / 96x128 / 64x128 / 64x64
-//   16 x 4096       88 / 60 / 37 / 33 / 32 / 23        333 x 4096    88 / 65 / 41 / 37 / 33 / 33
-//   400 x 6144     100 / 70 / 46 / 40 / 50 / 54       1024 x 4096    91 / 70 / 49 / 66 / 58 / 72
-//   2048 x 4096     93 / 80 / 90 / 103 / 106 / 126    4000 x 4096   121 / 147 / 166 / 188 / 184 / 225
-//   8 x about 50 x 14336 (grouped)                                  251 / 298 / 217 / 213 / 210 / 239
+//   16 x 4096       88 / 59 / 36 / 32 / 31 / 22         82 / 58 / 35 / 30 / 25 / 18
+//   333 x 4096      89 / 65 / 40 / 36 / 32 / 33         83 / 60 / 36 / 31 / 25 / 26
+//   400 x 6144     100 / 68 / 44 / 40 / 49 / 53         91 / 64 / 40 / 35 / 39 / 49
+//   1024 x 4096     90 / 69 / 46 / 65 / 57 / 69         79 / 61 / 42 / 62 / 46 / 57
+//   1536 x 4096     91 / 70 / 83 / 76 / 79 / 94         80 / 63 / 74 / 68 / 73 / 81   (the rule takes 96x128)
+//   2048 x 4096     93 / 76 / 86 / 102 / 105 / 127      81 / 70 / 84 / 100 / 86 / 108
+//   4000 x 4096    118 / 149 / 166 / 190 / 184 / 228   116 / 141 / 164 / 196 / 167 / 205
+//   8 x 250 x 3584, K = 2048 (grouped)                  72 / 86 / 83 / 79 / 75 / 87     63 / 85 / 80 / 70 / 58 / 69
+//   8 x about 50 x 14336 (grouped, and the combine)    254 / 300 / 219 / 212 / 210 / 239   253 / 299 / 219 / 212 / 209 / 243
 // 0 x 0: the 256 x 256 kernel.  Returns the time of one K step in ns.
 int64_t choose_tile(const GemmParams& P, int* bm, int* bn) {
   static const int n_cu = [] {
@@ -324,7 +333,8 @@ int64_t choose_tile(const GemmParams& P, int* bm, int* bn) {
     return n > 0 ? n : 256;
   }();
   static const struct {
-    int bm, bn, ns, ns_shared;     // a unit's time per step with one tile, and per tile with two at a time
+    int bm, bn, ns, ns_shared;     // a unit's time per step with one tile, and per tile with two at a time (they order
+                                   // the tiles; as times they are up to a quarter above what a step of this kernel takes)
   } kTiles[] = {{256, 256, 1370, 0}, {256, 128, 1250, 0}, {128, 128, 750, 0}, {96, 128, 600, 0}, {64, 128, 500, 430}, {64, 64, 360, 270}};
   int64_t best = 0;
   for (const auto& t : kTiles) {
@@ -341,10 +351,9 @@ int64_t choose_tile(const GemmParams& P, int* bm, int* bn) {
   return best;
 }
 
-// bytes that an axis can span, or -1 for an index table on it
+// bytes that an axis can span (the columns of B carry no index table: make_axis refuses it)
 template <int ND>
 int64_t axis_span(const AxisMap<ND>& a) {
-  if (a.table) return -1;
   int64_t span = 0;
   for (int i = 0; i < ND; ++i) span += (int64_t)(a.radix[i].d - 1) * a.stride[i] * 2;
   return span;
@@ -364,7 +373,7 @@ int gemm_tile_launch(const GemmParams& P, const OutMap* O, int dtype, hipStream_
     const GemmGroup& g = P.g[i];
     if (!g.k64 || g.b_kmajor != P.g[0].b_kmajor) return fail(VT_ERR_UNSUPPORTED, no);
     // a lane's share of B's address is 32 bits
-    const int64_t span = axis_span(g.b_col) + (g.b_kmajor ? 128 : 8 * (g.b_row.stride[2] < 0 ? 1ll << 32 : g.b_row.stride[2]) * 2 + 16);
+    const int64_t span = axis_span(g.b_col) + (g.b_kmajor ? 128 : 8 * g.b_row.stride[2] * 2 + 16);
     if (span >= (1ll << 32)) return fail(VT_ERR_UNSUPPORTED, no);
   }
   int bm = 0, bn = 0;

@@ -7,7 +7,8 @@
 // A workgroup takes 64 or 128 rows: they are fetched through the map (16 bytes per lane, LP2 lanes per row,
 // one lane evaluates a row's offset for the wave), normalised in registers (fp32, two passes), rounded
 // to the operand type and parked in LDS, rows 16 bytes further apart than they are long, so that the
-// 16 rows of a fragment read start in different banks.  One barrier later every wave works alone: it
+// 16 rows of a fragment read start in different banks (0.9 of the kernel's 2.1 million LDS
+// cycles are conflicts all the same, 2 us of a unit's time).  One barrier later every wave works alone: it
 // owns a tile of 64 columns and walks K in steps of 32 with W straight from L2 - a lane loads 8
 // consecutive k of its 4 columns (128-byte row segments per 16 lanes), transposes the 8x4 block in
 // registers (v_perm_b32) and multiplies it with all rows, C^T += W^T . LN(A)^T on
@@ -16,10 +17,11 @@
 // next two K steps in flight while one is multiplied.  A lane ends up with 4 consecutive columns of a
 // row; a wave turns 16 rows at a time round in LDS and leaves with whole 128-byte row segments.
 // (64 rows x 128 columns per wave spilled; four or six register sets measured no faster than three.)
-// 25088 x 256 -> 768, bf16 (51.8 MB, 9.9 GFLOP): 20 us (26 us with inputs cold in every cache); 2295 us on the generic kernel, which evaluates
-// the map for every element of A and W.  What is left is latency: rows, statistics and W follow each
-// other inside a workgroup, and only two or three waves per SIMD overlap (matrix pipes busy 4.5 us,
-// vector instructions 6 us of the 26).
+// 25088 x 256 -> 768, bf16 (51.8 MB, 9.9 GFLOP): 21 us (27 us with inputs cold in every cache); 2295 us on the
+// generic kernel, which evaluates the map for every element of A and W.  What is left is latency: rows,
+// statistics and W follow each other inside a workgroup, and only two or three waves per SIMD overlap
+// (of the 27 us the matrix pipes of a working unit are busy 5, the vector instructions 7; counters:
+// profiles/small_tiles_streamed_ln_split_rowsum.txt).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -274,7 +276,7 @@ k_ln_gemm_wide(const WideParams P) {
 }
 
 // 128 rows per workgroup halve the reads of W and the rounds, once there are workgroups for most of
-// the chip (measured, us, 64 / 128 rows: 25088 x 256 -> 768: 28.0 / 26.2, 25088 x 512 -> 2048: 100 / 80,
+// the chip's 256 units (measured, us, 64 / 128 rows: 25088 x 256 -> 768: 28.0 / 26.2, 25088 x 512 -> 2048: 100 / 80,
 // 100352 x 128 -> 512: 45 / 43, but 18432 x 192 -> 200: 11.2 / 12.0 and 1568 x 512 -> 1536: 14.2 / 21.1).
 // Waves: four, two workgroups sharing a compute unit, or eight where there is at most one workgroup
 // per unit (100352 x 96 -> 288: 32.4 / 34.6 with four / eight, 25088 x 256 -> 768: 34.5 / 26.2).
