@@ -129,7 +129,7 @@ template <>
 struct Mfma<bf16_t> {
   typedef bf16x8 vec;
   static constexpr float kThreshold = 16.0f;   // p <= 2^16: far inside the bf16 exponent range
-  static constexpr float kScale = 1.0f, kStep = 1.0f;         // P_PARTS: three parts of 8 bits are all of p
+  static constexpr float kScale = 1.0f, kStep = 1.0f, kLeast = 0.0f;         // P_PARTS: three parts of 8 bits are all of p
   // the two numbers of a register, exactly
   static __device__ __forceinline__ float lo(uint32_t w) { return __builtin_bit_cast(float, w << 16); }
   static __device__ __forceinline__ float hi(uint32_t w) { return __builtin_bit_cast(float, w & 0xFFFF0000u); }
@@ -146,8 +146,9 @@ struct Mfma<f16_t> {
   typedef f16x8 vec;
   static constexpr float kThreshold = 0.0f;    // keep p <= 1 (f16 tops out at 65504)
   // P_PARTS: three parts of 11 bits, each scaled into the upper end of f16's range (the first is at most 2^14
-  // and leaves over at most 2^3, the last one ends at 2^-60 of p = 1)
-  static constexpr float kScale = 0x1p14f, kStep = 0x1p11f;
+  // and leaves over at most 2^3, the last one ends at 2^-60 of p = 1).  The first part of a probability that is not
+  // zero is at least 2^-24, so that an infinity in V meets no zero; the second then takes the difference back.
+  static constexpr float kScale = 0x1p14f, kStep = 0x1p11f, kLeast = 0x1p-24f;
   static __device__ __forceinline__ float lo(uint32_t w) { return (float)__builtin_bit_cast(f16_t, (uint16_t)w); }
   static __device__ __forceinline__ float hi(uint32_t w) { return (float)__builtin_bit_cast(f16_t, (uint16_t)(w >> 16)); }
   static __device__ __forceinline__ f32x4 run(vec a, vec b, f32x4 c) {
@@ -531,10 +532,14 @@ k_decode_attn(const AttnParamsT<NS> P) {
         for (int i = 0; i < 2; ++i)
 #pragma unroll
           for (int j = 0; j < 8; j += 2) {
-            const uint32_t w = M::pack2(pv[j], pv[j + 1]);
-            const float r0 = (pv[j] - M::lo(w)) * M::kStep, r1 = (pv[j + 1] - M::hi(w)) * M::kStep;    // left over, exactly
-            pv[j] = p_part > i ? r0 : pv[j];
-            pv[j + 1] = p_part > i ? r1 : pv[j + 1];
+            const bool first = i == 0 && M::kLeast > 0.f;
+            // (the middle one of p, the least part and p * 2^120: zero stays zero)
+            const float p0 = first ? __builtin_amdgcn_fmed3f(pv[j], M::kLeast, pv[j] * 0x1p120f) : pv[j];
+            const float p1 = first ? __builtin_amdgcn_fmed3f(pv[j + 1], M::kLeast, pv[j + 1] * 0x1p120f) : pv[j + 1];
+            const uint32_t w = M::pack2(p0, p1);
+            const float left0 = (pv[j] - M::lo(w)) * M::kStep, left1 = (pv[j + 1] - M::hi(w)) * M::kStep;    // exact
+            pv[j] = p_part > i ? left0 : p0;
+            pv[j + 1] = p_part > i ? left1 : p1;
           }
       }
       const opvec pop = __builtin_bit_cast(opvec, make_uint4(M::pack2(pv[0], pv[1]), M::pack2(pv[2], pv[3]), M::pack2(pv[4], pv[5]),
