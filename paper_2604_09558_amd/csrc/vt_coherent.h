@@ -12,8 +12,11 @@ namespace vt {
 
 typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
 
+// (The wait states: a store of more than 8 bytes reads its data late, and an instruction that overwrites
+// those registers within the next two reaches the last lanes first.  The compiler keeps that distance behind
+// its own stores; it does not know that there is one in here.)
 __device__ __forceinline__ void store_device_b128(void* p, u32x4_t v) {
-  asm volatile("global_store_dwordx4 %0, %1, off sc1" ::"v"(p), "v"(v) : "memory");
+  asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(p), "v"(v) : "memory");
 }
 
 // Four independent 16-byte loads in flight, then one wait.

@@ -76,3 +76,21 @@ def test_the_current_stream_is_never_lost(monkeypatch):
     monkeypatch.setattr(torch.cuda, "current_stream", broken)
     with pytest.raises(RuntimeError):
         binding._stream(None)
+
+
+def test_wide_stores_written_as_assembly_keep_their_wait_states():
+    """The compiler does not see a store inside an asm statement: with more than 8 bytes a lane, the registers of
+    its data must not be overwritten by the next two instructions, so the statement itself has to end in them."""
+    import glob
+    import os
+    import re
+    csrc = os.path.join(os.path.dirname(vt.__file__), "csrc")
+    seen = 0
+    for path in glob.glob(os.path.join(csrc, "*.h*")):
+        for text in re.findall(r"asm volatile\((.*?)\);", open(path).read(), re.S):
+            code = "".join(re.findall(r'"((?:[^"\\]|\\.)*)"', text.split(":")[0])).split("\\n\\t")
+            wide = [i for i, c in enumerate(code) if re.match(r"(global|flat|buffer)_store_dwordx[34]", c)]
+            for i in wide:
+                seen += 1
+                assert i + 1 < len(code) and re.match(r"s_nop [1-9]|s_waitcnt vmcnt\(0\)", code[i + 1]), (path, code)
+    assert seen >= 1
