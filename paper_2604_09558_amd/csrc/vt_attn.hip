@@ -26,7 +26,7 @@
 //                   already holds in exactly that layout.
 // Head dims 128 and 64 (a template argument): a tile of 64-wide heads is half as many bytes, eight
 // lanes read a K row and a lane's piece of a V row is 8 bytes.  Serving 16 sequences of 2368 paged
-// keys of 64-wide heads (77.7 MB): 18.5 us = 4.2 TB/s, against 10.8 ms when only 128 was planned
+// keys of 64-wide heads (77.7 MB): 18.2 us = 4.3 TB/s, against 10.8 ms when only 128 was planned
 // and every element went through the generic evaluator below.
 // The workgroup that finishes last for a (b, g) merges the splits' partial results (a ticket
 // counter per (b, g) in the workspace; no second launch, no spinning).
@@ -129,7 +129,7 @@ template <>
 struct Mfma<bf16_t> {
   typedef bf16x8 vec;
   static constexpr float kThreshold = 16.0f;   // p <= 2^16: far inside the bf16 exponent range
-  static constexpr float kScale = 1.0f, kStep = 1.0f, kLeast = 0.0f;         // P_PARTS: three parts of 8 bits are all of p
+  static constexpr float kScale = 1.0f, kStep = 1.0f, kLeast = 0.0f;         // three parts of 8 bits are all of p
   // the two numbers of a register, exactly
   static __device__ __forceinline__ float lo(uint32_t w) { return __builtin_bit_cast(float, w << 16); }
   static __device__ __forceinline__ float hi(uint32_t w) { return __builtin_bit_cast(float, w & 0xFFFF0000u); }
@@ -145,7 +145,7 @@ template <>
 struct Mfma<f16_t> {
   typedef f16x8 vec;
   static constexpr float kThreshold = 0.0f;    // keep p <= 1 (f16 tops out at 65504)
-  // P_PARTS: three parts of 11 bits, each scaled into the upper end of f16's range (the first is at most 2^14
+  // three parts of 11 bits, each scaled into the upper end of f16's range (the first is at most 2^14
   // and leaves over at most 2^3, the last one ends at 2^-60 of p = 1).  The first part of a probability that is not
   // zero is at least 2^-24, so that an infinity in V meets no zero; the second then takes the difference back.
   static constexpr float kScale = 0x1p14f, kStep = 0x1p11f, kLeast = 0x1p-24f;
@@ -311,22 +311,46 @@ __device__ __forceinline__ void walk_advance(const AttnParamsT<NS>& P, TileWalk&
   if (w.seg < P.n_seg) walk_fetch(P, w, b, g);
 }
 
+// Eight probabilities in three 16-bit parts: w[0] holds the upper bits, w[1] and w[2] what each left over.
+template <typename M>
+__device__ __forceinline__ void part_words(const float (&p)[8], uint4 (&w)[3]) {
+  float x[8];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) x[j] = p[j] * M::kScale;
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    uint32_t v[4];
+#pragma unroll
+    for (int j = 0; j < 8; j += 2) {
+      float a = x[j], b = x[j + 1];
+      if (i == 0 && M::kLeast > 0.f) {      // the middle one of p, the least part and p * 2^120: zero stays zero
+        a = __builtin_amdgcn_fmed3f(a, M::kLeast, a * 0x1p120f);
+        b = __builtin_amdgcn_fmed3f(b, M::kLeast, b * 0x1p120f);
+      }
+      v[j >> 1] = M::pack2(a, b);
+      x[j] = (x[j] - M::lo(v[j >> 1])) * M::kStep;           // exact
+      x[j + 1] = (x[j + 1] - M::hi(v[j >> 1])) * M::kStep;
+    }
+    w[i] = make_uint4(v[0], v[1], v[2], v[3]);
+  }
+}
+
 // D = head dim (64 or 128).  MANY: more than eight splits, the merge below divides them among its threads.
-// PMODE: how the probabilities enter the product with V.
-//   P_16     rounded to 16 bits (128-wide heads).
-//   P_PARTS  64-wide heads, and maps that used to run on the generic kernel, keep the probabilities' fp32 value,
-//            as that kernel does.  Up to five query heads a group leave two thirds of the product's 16 columns
-//            idle: the columns G.. and 2G.. hold the same heads again, and a probability is cut into three 16-bit
-//            parts, one for each of its columns, which are added up when the waves are merged.  us with 16-bit
-//            halves in two products (fewer bits) / with these parts / with P_F32: 128 units x 2368 paged keys, 64-wide
-//            heads, 4 a group 18.8 / 19.1 / 21.4, 2048 units x 500 keys 51.4 / 51.1 / 53.8, 128 units x 128 keys of
-//            128-wide heads behind a batch table 8.4 / 8.5 / 9.1.  (Parts in three products and accumulators
-//            spilled; an infinity in V times a part that is zero would also have to be told from a NaN there.)
-//   P_F32    the same with more heads a group: fp32 products, V converted exactly (256 units x 4096 paged keys, 8
-//            heads a group: 52.2 us, 5.2 TB/s; 45.7 with halves).
-enum { P_16, P_PARTS, P_F32 };
-constexpr int kPartHeads = 5;
-template <typename T, int D, bool MANY, int PMODE, int NS, int WAVES, int OCC>
+// ROUNDS: how the probabilities enter the product with V.
+//   0        rounded to 16 bits (128-wide heads).
+//   1 2 3    64-wide heads, and maps that used to run on the generic kernel, keep the probabilities' fp32 value,
+//            as that kernel does: a probability is cut into three 16-bit parts (part_words).  Up to five query heads a
+//            group leave two thirds of the product's 16 columns idle: the columns G.. and 2G.. hold the same heads
+//            again, each with another part, and one product does.  Up to eight heads take two: parts 0 and 2 in the
+//            columns 0.. and G.. of the first, part 1 in the second; more take three.  Every product has its own
+//            accumulator, and the parts' sums are added up when the waves are merged.
+//   us with 16-bit halves in two products (fewer bits) / with these parts / with fp32 products (v_mfma_f32_16x16x4):
+//   128 units x 2368 paged keys, 64-wide, 4 heads a group  18.8 / 19.1 / 21.4, f16 19.5 / 19.9 / 22.4
+//   256 units x 4096 paged keys, 64-wide, 8 heads a group  45.7 / 46.0 / 53.3, 16 heads 48.4 / 48.3 / 56.0
+//   2048 units x 500 keys, 64-wide, 4 heads a group        52.5 / 52.7 / 53.8
+//   128 units x 128 keys, 128-wide behind a batch table    8.4 / 8.2 / 9.1
+enum { kRounded = 0 };
+template <typename T, int D, bool MANY, int ROUNDS, int NS, int WAVES, int OCC>
 __global__ void __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(OCC, OCC)))
 k_decode_attn(const AttnParamsT<NS> P) {
   typedef Mfma<T> M;
@@ -360,13 +384,13 @@ k_decode_attn(const AttnParamsT<NS> P) {
   const int t_end = min(P.S, t_begin + P.rows_per_split);
   const float c = P.scale_log2;
 
-  // the part of the probabilities in this lane's column, and the columns in use
-  const int p_part = PMODE != P_PARTS ? 0 : (l16 >= P.G ? 1 : 0) + (l16 >= 2 * P.G ? 1 : 0);
-  const int n_cols = PMODE == P_PARTS ? 3 * P.G : P.G;
+  // which of the sets of G columns this lane's is in, and the columns in use
+  const int p_set = ROUNDS == 1 ? (l16 >= P.G ? 1 : 0) + (l16 >= 2 * P.G ? 1 : 0) : ROUNDS == 2 && l16 >= P.G ? 1 : 0;
+  const int n_cols = (ROUNDS == 1 ? 3 : ROUNDS == 2 ? 2 : 1) * P.G;
   // Q^T operand: lane (head l16, k-group lg) holds 8 consecutive d for each of the kD / 32 k-steps
   opvec qreg[kD / 32];
   {
-    const char* qp = P.q_ptr + b * P.q_sb + (int64_t)(g * P.G + (PMODE == P_PARTS ? l16 - p_part * P.G : l16)) * P.q_sh;
+    const char* qp = P.q_ptr + b * P.q_sb + (int64_t)(g * P.G + l16 - p_set * P.G) * P.q_sh;
 #pragma unroll
     for (int kk = 0; kk < kD / 32; ++kk) {
       uint4 raw = make_uint4(0, 0, 0, 0);
@@ -377,9 +401,12 @@ k_decode_attn(const AttnParamsT<NS> P) {
 
   float m_ref = kNoScore;   // reference maximum (log2 domain) of head l16, identical in the 4 lane groups
   float l_run = 0.0f;       // this lane's share of the denominator, relative to m_ref
-  f32x4 acc[NE];
+  constexpr int NA = ROUNDS > 1 ? ROUNDS : 1;
+  f32x4 acc[NA][NE];
 #pragma unroll
-  for (int e = 0; e < NE; ++e) acc[e] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int i = 0; i < NA; ++i)
+#pragma unroll
+    for (int e = 0; e < NE; ++e) acc[i][e] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   // Loads of one tile.  K: 16 bytes per lane, LPR lanes per row, instruction j covers RPL rows
   // from RPL * j; V: 2 * NE bytes per lane, 16 lanes per row, instruction j is contraction slot j of the lane group, row (j>>2)*16 + lg*4 + (j&3).
@@ -494,13 +521,15 @@ k_decode_attn(const AttnParamsT<NS> P) {
       m_ref = mn;
       l_run *= alpha;
 #pragma unroll
-      for (int e = 0; e < NE; ++e) {
-        acc[e][0] *= alpha; acc[e][1] *= alpha; acc[e][2] *= alpha; acc[e][3] *= alpha;
-      }
+      for (int i = 0; i < NA; ++i)
+#pragma unroll
+        for (int e = 0; e < NE; ++e) {
+          acc[i][e][0] *= alpha; acc[i][e][1] *= alpha; acc[i][e][2] *= alpha; acc[i][e][3] *= alpha;
+        }
     }
     float pv[8];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) pv[j] = __builtin_amdgcn_exp2f(PMODE == P_16 ? fmaf(sv[j], c, -m_ref) : tv[j] - m_ref);
+    for (int j = 0; j < 8; ++j) pv[j] = __builtin_amdgcn_exp2f(ROUNDS == kRounded ? fmaf(sv[j], c, -m_ref) : tv[j] - m_ref);
     // (the maximum is one of the rounded products: in fp32 the difference to it is exact for scores of any size)
     if (partial) {
 #pragma unroll
@@ -508,51 +537,39 @@ k_decode_attn(const AttnParamsT<NS> P) {
         if (r0 + (j >> 2) * 16 + lg * 4 + (j & 3) >= r_end) pv[j] = 0.f;
     }
     l_run += ((pv[0] + pv[1]) + (pv[2] + pv[3])) + ((pv[4] + pv[5]) + (pv[6] + pv[7]));
-    if (PMODE != P_16 && partial) {      // the rows that a short tile repeats have no weight: an infinity there is not read
+    if (ROUNDS != kRounded && partial) {      // the rows that a short tile repeats have no weight: an infinity there is not read
 #pragma unroll
       for (int j = 0; j < 8; ++j)
         if (r0 + (j >> 2) * 16 + lg * 4 + (j & 3) >= r_end)
 #pragma unroll
           for (int i = 0; i < NE / 2; ++i) vst[j].w[i] = 0;
     }
-    if constexpr (PMODE == P_F32) {
-      // ---- O^T += V^T . P^T : four context rows (slot j of the four lane groups) per product
-#pragma unroll
-      for (int j = 0; j < 8; ++j)
-#pragma unroll
-        for (int e = 0; e < NE; ++e) {
-          const float v = (e & 1) ? M::hi(vst[j].w[e >> 1]) : M::lo(vst[j].w[e >> 1]);
-          acc[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(v, pv[j], acc[e], 0, 0, 0);
-        }
-    } else {
-      if constexpr (PMODE == P_PARTS) {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) pv[j] *= M::kScale;
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-          for (int j = 0; j < 8; j += 2) {
-            const bool first = i == 0 && M::kLeast > 0.f;
-            // (the middle one of p, the least part and p * 2^120: zero stays zero)
-            const float p0 = first ? __builtin_amdgcn_fmed3f(pv[j], M::kLeast, pv[j] * 0x1p120f) : pv[j];
-            const float p1 = first ? __builtin_amdgcn_fmed3f(pv[j + 1], M::kLeast, pv[j + 1] * 0x1p120f) : pv[j + 1];
-            const uint32_t w = M::pack2(p0, p1);
-            const float left0 = (pv[j] - M::lo(w)) * M::kStep, left1 = (pv[j + 1] - M::hi(w)) * M::kStep;    // exact
-            pv[j] = p_part > i ? left0 : p0;
-            pv[j + 1] = p_part > i ? left1 : p1;
-          }
+    opvec pop[NA];
+    {
+      uint4 w[3];
+      if constexpr (ROUNDS == kRounded) {
+        w[0] = make_uint4(M::pack2(pv[0], pv[1]), M::pack2(pv[2], pv[3]), M::pack2(pv[4], pv[5]), M::pack2(pv[6], pv[7]));
+      } else {
+        part_words<M>(pv, w);
+        auto pick = [&](const uint4& x, const uint4& y, bool second) {
+          return make_uint4(second ? y.x : x.x, second ? y.y : x.y, second ? y.z : x.z, second ? y.w : x.w);
+        };
+        if (ROUNDS == 1) w[0] = pick(pick(w[0], w[1], p_set == 1), w[2], p_set == 2);
+        if (ROUNDS == 2) w[0] = pick(w[0], w[2], p_set == 1);        // (the second set's other columns are not read)
       }
-      const opvec pop = __builtin_bit_cast(opvec, make_uint4(M::pack2(pv[0], pv[1]), M::pack2(pv[2], pv[3]), M::pack2(pv[4], pv[5]),
-                                                             M::pack2(pv[6], pv[7])));
-      // ---- O^T += V^T . P^T : transpose the lane's 8 x NE block, one MFMA per column e
 #pragma unroll
-      for (int e = 0; e < NE; ++e) {
-        const uint32_t sel = (e & 1) ? 0x07060302u : 0x05040100u;
-        uint32_t w[4];
+      for (int i = 0; i < NA; ++i) pop[i] = __builtin_bit_cast(opvec, w[i]);
+    }
+    // ---- O^T += V^T . P^T : transpose the lane's 8 x NE block, one MFMA per column e (and round)
 #pragma unroll
-        for (int u = 0; u < 4; ++u) w[u] = __builtin_amdgcn_perm(vst[2 * u + 1].w[e >> 1], vst[2 * u].w[e >> 1], sel);
-        acc[e] = M::run(__builtin_bit_cast(opvec, make_uint4(w[0], w[1], w[2], w[3])), pop, acc[e]);
-      }
+    for (int e = 0; e < NE; ++e) {
+      const uint32_t sel = (e & 1) ? 0x07060302u : 0x05040100u;
+      uint32_t w[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) w[u] = __builtin_amdgcn_perm(vst[2 * u + 1].w[e >> 1], vst[2 * u].w[e >> 1], sel);
+      const opvec vt = __builtin_bit_cast(opvec, make_uint4(w[0], w[1], w[2], w[3]));
+#pragma unroll
+      for (int i = 0; i < NA; ++i) acc[i][e] = M::run(vt, pop[i], acc[i][e]);
     }
     if (more) issue_v(cur);              // next tile's V: lands while the next K tile is being scored
   }
@@ -574,14 +591,29 @@ k_decode_attn(const AttnParamsT<NS> P) {
   l_run += __shfl_xor(l_run, 32, 64);
   __syncthreads();                       // every wave is done with its K tile
   VT_PROF(2);
-  float* red_o = reinterpret_cast<float*>(&lds[0][0]);    // [WAVES][columns][D] floats: at most the K tiles' memory
-  const int G = a_G, nc = PMODE == P_PARTS ? 3 * G : G;
+  // [WAVES][columns][D] floats: at most the K tiles' memory.  Chunk c (four floats) of column l lies at c ^ l, so
+  // that the 16 columns that are written at once fall into different banks.
+  float4* red_o = reinterpret_cast<float4*>(&lds[0][0]);
+  auto red_at = [](int column, int chunk, int l) { return column * (kD / 4) + (chunk ^ l); };
+  const int G = a_G, nc = (ROUNDS == 1 ? 3 : ROUNDS == 2 ? 2 : 1) * G;
+  // a set's share of the result: its parts, scaled back.  Where the first part's sum is not finite (an infinity in
+  // V) it stands alone: the lesser parts may be zero, which gives a NaN, or negative.
+  auto finite = [](float x) { return __builtin_fabsf(x) <= 3.4028235e38f; };
+  auto share = [&](int e, int i) {
+    constexpr float kBack = 1.0f / M::kScale, kBack1 = kBack / M::kStep, kBack2 = kBack1 / M::kStep;
+    const float a = acc[0][e][i];
+    if constexpr (ROUNDS == 1) return a * (p_set == 0 ? kBack : p_set == 1 ? kBack1 : kBack2);
+    if constexpr (ROUNDS == 2) return p_set == 1 ? a * kBack2 : finite(a) ? a * kBack + acc[NA - 1][e][i] * kBack1 : a;
+    if constexpr (ROUNDS == 3) return finite(a) ? a * kBack + (acc[1 % NA][e][i] * kBack1 + acc[NA - 1][e][i] * kBack2) : a;
+    return a;
+  };
   if (l16 < nc) {
 #pragma unroll
-    for (int e = 0; e < NE; ++e)
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) red_o[(wave * nc + l16) * kD + (lg * 4 + i) * NE + e] = acc[e][i];
-    if (lg == 0) {               // (of the first part's columns: the others say the same)
+      for (int e = 0; e < NE; e += 4)
+        red_o[red_at(wave * nc + l16, (lg * 4 + i) * (NE / 4) + e / 4, l16)] = make_float4(share(e, i), share(e + 1, i), share(e + 2, i), share(e + 3, i));
+    if (lg == 0) {               // (of the first set's columns: the others say the same)
       red_ml[(wave * 16 + l16) * 2 + 0] = m_ref;
       red_ml[(wave * 16 + l16) * 2 + 1] = l_run;
     }
@@ -601,14 +633,12 @@ k_decode_attn(const AttnParamsT<NS> P) {
 #pragma unroll
     for (int w = 0; w < WAVES; ++w) {
       const float sc = __builtin_amdgcn_exp2f(red_ml[(w * 16 + h) * 2] - mx);
-      float4 r = *reinterpret_cast<const float4*>(&red_o[(w * nc + h) * kD + (idx - h * kD)]);
-      if constexpr (PMODE == P_PARTS) {
-        const float4 r1 = *reinterpret_cast<const float4*>(&red_o[(w * nc + G + h) * kD + (idx - h * kD)]);
-        const float4 r2 = *reinterpret_cast<const float4*>(&red_o[(w * nc + 2 * G + h) * kD + (idx - h * kD)]);
-        auto sum = [](float a, float b, float c) {
-          const float t = (a + (b + c * (1.0f / M::kStep)) * (1.0f / M::kStep)) * (1.0f / M::kScale);
-          return __builtin_fabsf(a) <= 3.4028235e38f ? t : a;     // an infinity in V: lesser parts may be zero (NaN) or negative
-        };
+      const int ch = (idx - h * kD) / 4;
+      float4 r = red_o[red_at(w * nc + h, ch, h)];
+      if constexpr (ROUNDS == 1 || ROUNDS == 2) {
+        const float4 r1 = red_o[red_at(w * nc + G + h, ch, G + h)];
+        const float4 r2 = ROUNDS == 2 ? make_float4(0.f, 0.f, 0.f, 0.f) : red_o[red_at(w * nc + 2 * G + h, ch, 2 * G + h)];
+        auto sum = [&](float x, float y, float z) { return finite(x) ? x + (y + z) : x; };
         r = make_float4(sum(r.x, r1.x, r2.x), sum(r.y, r1.y, r2.y), sum(r.z, r1.z, r2.z), sum(r.w, r1.w, r2.w));
       }
       o.x += r.x * sc; o.y += r.y * sc; o.z += r.z * sc; o.w += r.w * sc;
@@ -1285,24 +1315,26 @@ static int launch_attention(const vt_desc* Q, const vt_desc* K, const vt_desc* V
     static_cast<AttnArgs&>(P2) = P;
     for (int i = 0; i < 2; ++i) P2.seg[i] = P.seg[i];
   }
-#define VT_ATTN_NS(TT, DD, MM, PM, OCC)                                                                               \
+#define VT_ATTN_NS(TT, DD, MM, RR, OCC)                                                                               \
   do {                                                                                                                \
-    if (few) hipLaunchKernelGGL((k_decode_attn<TT, DD, MM, PM, 2, kWaves, OCC>), grid, dim3(kWaves * 64), 0, st, P2);     \
-    else hipLaunchKernelGGL((k_decode_attn<TT, DD, MM, PM, kMaxSegs, kWaves, OCC>), grid, dim3(kWaves * 64), 0, st, P);   \
+    if (few) hipLaunchKernelGGL((k_decode_attn<TT, DD, MM, RR, 2, kWaves, OCC>), grid, dim3(kWaves * 64), 0, st, P2);     \
+    else hipLaunchKernelGGL((k_decode_attn<TT, DD, MM, RR, kMaxSegs, kWaves, OCC>), grid, dim3(kWaves * 64), 0, st, P);   \
   } while (0)
-#define VT_ATTN(TT, DD, PM, OCC)                                                                                      \
+#define VT_ATTN(TT, DD, RR, OCC)                                                                                      \
   do {                                                                                                                \
-    if (ns_eff > 8) VT_ATTN_NS(TT, DD, true, PM, OCC);                                                                    \
-    else VT_ATTN_NS(TT, DD, false, PM, OCC);                                                                              \
+    if (ns_eff > 8) VT_ATTN_NS(TT, DD, true, RR, OCC);                                                                    \
+    else VT_ATTN_NS(TT, DD, false, RR, OCC);                                                                              \
   } while (0)
 #define VT_ATTN_T(TT)                                                                                                 \
   do {                                                                                                                \
-    const bool parts = P.G <= kPartHeads;                                                                               \
-    if (P.D == 64 && parts) VT_ATTN(TT, 64, P_PARTS, 4);                                                                \
-    else if (P.D == 64) VT_ATTN(TT, 64, P_F32, 4);                                                                      \
-    else if (P.batch_table && parts) VT_ATTN(TT, 128, P_PARTS, 2);                                                      \
-    else if (P.batch_table) VT_ATTN(TT, 128, P_F32, 2);                                                                 \
-    else VT_ATTN(TT, 128, P_16, 3);                                                                                     \
+    const int rounds = P.G <= 5 ? 1 : P.G <= 8 ? 2 : 3;         /* sets of G columns in 16 */                         \
+    if (P.D == 128 && !P.batch_table) VT_ATTN(TT, 128, kRounded, 3);                                                  \
+    else if (P.D == 128 && rounds == 1) VT_ATTN(TT, 128, 1, 2);                                                       \
+    else if (P.D == 128 && rounds == 2) VT_ATTN(TT, 128, 2, 2);                                                       \
+    else if (P.D == 128) VT_ATTN(TT, 128, 3, 2);                                                                      \
+    else if (rounds == 1) VT_ATTN(TT, 64, 1, 4);                                                                      \
+    else if (rounds == 2) VT_ATTN(TT, 64, 2, 3);                                                                      \
+    else VT_ATTN(TT, 64, 3, 3);                                                                                       \
   } while (0)
   if (Q->dtype == VT_BF16) VT_ATTN_T(bf16_t);
   else VT_ATTN_T(f16_t);

@@ -436,7 +436,7 @@ def sink_workload(dtype, D, G, S, sink, inf_row=None):
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
-@pytest.mark.parametrize("G", [2, 5, 6])               # either side of the heads whose parts fit one product
+@pytest.mark.parametrize("G", [2, 5, 6, 8, 9, 16])     # heads whose parts take one, two and three products
 @pytest.mark.parametrize("S,sink,inf_row", [(32, 8.0, None), (32, 16.0, None), (45, 17.0, None), (300, 17.0, None), (45, 12.0, 3), (45, 12.0, 43), (45, 30.0, 3)])
 def test_attention_sink_of_64_wide_heads(gpu, dtype, G, S, sink, inf_row):
     """The weights of the keys beside a dominant one (whose V row is zero) keep their fp32 value: the sum of
