@@ -425,8 +425,9 @@ int vt_gemm_store(const vt_desc* A, const vt_desc* B, const vt_desc* C, void* wo
   P.partial = reinterpret_cast<float*>(static_cast<char*>(workspace) + counters);
   // Several blocks of 16 rows: this kernel reads B once for each of them, and takes the time its busiest
   // compute unit needs to draw its share (40 GB/s, 6.5 us around it).  The tiled kernel takes over
-  // where it is expected to be faster (us here / there, operands in HBM: 4096 x 6144 with 32 rows 23.0 / 26.7,
-  // 48 rows 34.9 / 28.1, 90 rows 64.4 / 26.1; 2048 x 6144 with 48 rows 21.1 / 14.5, 90 rows 35.8 / 14.1).
+  // where it is expected to be faster (us here / there, operands in HBM: 4096 x 6144 with 32 rows 22.7 / 25.4,
+  // 48 rows 33.7 / 26.8, 90 rows 62.4 / 25.1; 2048 x 6144 with 17 rows 14.7 / 14.5, 48 rows 20.5 / 16.1, 90 rows
+  // 34.6 / 15.3; 768 x 768 with 17 rows 9.5 / 8.5).
   if (rbs > 1) {
     const int64_t rounds = (rbs * cbs * ns_eff + compute_units() - 1) / compute_units();
     rc = gemm_store_launch(*A, *B, *C, 6500 + rounds * kps * (kBN * 2) / 40, (hipStream_t)stream);

@@ -1,9 +1,9 @@
 // Tiled GEMM for products that the 256 x 256 tiles of vt_gemm.hip would spread over too few compute
 // units: the same product, operand maps, order of accumulation (identical bits) and tile walk, with
 // smaller tiles and a deeper pipeline.  A short prompt or a decode batch's experts are bound by
-// pulling the operands into the compute units, not by the matrix cores: a unit draws some 55 GB/s with
-// the operands in HBM and 75 GB/s with them in the caches, so what counts is how many units share the
-// work and how few bytes each has to read (BM + BN per K step and tile).
+// pulling the operands into the compute units, not by the matrix cores: the requests alone, with the
+// operands in the caches, go at some 100 GB/s a unit and 22 TB/s in all (in HBM, at two thirds of that), so what
+// counts is how many units share the work and how few bytes each has to read (BM + BN per K step and tile).
 //
 // One workgroup of 4 waves computes a BM x BN tile of C in 32 x 32 matrix-core blocks
 // (v_mfma_f32_32x32x16).  K steps of 64 run through a ring of STAGES tiles in LDS; operands go from
@@ -13,11 +13,10 @@
 // the fragment reads free of bank conflicts (4.3 million conflict cycles per launch without it, 4600
 // with it, 333 x 4096 x 4096) is applied to what a lane asks for.  Waits count the requests by hand: a wave issues the
 // same number in every step and nothing else that goes through the vector memory counter.
-// Measured (f16/bf16, K = 4096, 256 x 256 tiles -> these, operands in HBM / in the caches): 333 x 4096
-// 89 -> 32 / 83 -> 25 us, 400 x 6144 100 -> 40 / 91 -> 35 us, 1024 x 4096 90 -> 46 / 79 -> 41 us
-// (counters: profiles/small_tiles_streamed_ln_split_rowsum.txt).  A loop with the requests alone takes
-// the same time, one without them half of it; rings twice as deep, with the waves divided into
-// readers of A and of B, measured no faster.
+// Measured (f16/bf16, K = 4096, operands in HBM / in the caches, us): 333 x 4096 30.5 / 21.8 (256 x 256 tiles 88 / 83),
+// 400 x 6144 34.5 / 30.0 (90 / 84), 1024 x 4096 43.3 / 36.5 (89 / 80); the requests of the first without anything
+// else 27.4 / 18.1.  A step of 64 x 128 takes 265 ns there, of which the requests need 231.  Rings twice as
+// deep, and waves divided over K instead of over the tile (half the LDS reads), measured no faster.
 #include <hip/hip_runtime.h>
 
 #include <cstring>
@@ -36,20 +35,12 @@ constexpr int kMaxSteps = 256;        // K <= 16384
 
 typedef __attribute__((address_space(3))) void* lptr_t;
 
-// N requests of 16 bytes per lane: lane l's bytes of request i, from base[i] + off[i], land at LDS byte
-// dst + 1024 i + 16 l.  (M0 holds the destination; it is saved and put back.)
-template <int N>
-__device__ __forceinline__ void request(const uint32_t* off, const char* const* base, uint32_t dst) {
+// 16 bytes per lane: lane l's, from base + off, land at LDS byte dst + 16 l.  (M0 holds the destination; it is
+// saved and put back.)
+__device__ __forceinline__ void request(uint32_t off, const char* base, uint32_t dst) {
   uint32_t m0_saved;
-  if constexpr (N >= 2) {
-    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %5\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %3\n\t"
-                 "s_add_u32 m0, m0, 0x400\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %4\n\ts_nop 0\n\ts_mov_b32 m0, %0"
-                 : "=&s"(m0_saved) : "v"(off[0]), "v"(off[1]), "s"(base[0]), "s"(base[1]), "s"(dst) : "memory", "scc");
-    if constexpr (N > 2) request<N - 2>(off + 2, base + 2, dst + 2048);
-  } else {
-    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2\n\ts_nop 0\n\ts_mov_b32 m0, %0"
-                 : "=&s"(m0_saved) : "v"(off[0]), "s"(base[0]), "s"(dst) : "memory");
-  }
+  asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2\n\ts_nop 0\n\ts_mov_b32 m0, %0"
+               : "=&s"(m0_saved) : "v"(off), "s"(base), "s"(dst) : "memory");
 }
 
 // The swizzle: chunk c (16 bytes) of a 128-byte row r lies at position c ^ row_key(r): the 16 rows of a
@@ -116,19 +107,20 @@ k_gemm_tile(const GemmParamsT<NG> P, const typename std::conditional<MAPPED, Out
   }
   __syncthreads();
   const uint32_t lds0 = (uint32_t)(uintptr_t)(lptr_t)&lds[0];
-  auto issue = [&](const uint4& o, int slot) {
-    const uint32_t ao = __builtin_amdgcn_readfirstlane(o.x), b_lo = __builtin_amdgcn_readfirstlane(o.y),
-                   b_hi = __builtin_amdgcn_readfirstlane(o.z);
-    const char* const as = a_base + ao;
-    const char* const bs = b_base + (int64_t)(((uint64_t)b_hi << 32) | b_lo);
+  // request q (the AI of A, then the BI of B) of the step that starts at `as` and `bs`, into stage `slot`
+  auto request_one = [&](int q, const char* as, const char* bs, int slot) {
     const uint32_t dst = lds0 + slot * kStage;
-    const char *sa[AI], *sb[BI];
-#pragma unroll
-    for (int i = 0; i < AI; ++i) sa[i] = as;
-#pragma unroll
-    for (int i = 0; i < BI; ++i) sb[i] = B_KMAJOR ? bs : bs + (wave * BI + i) * RB * b_kstride;
-    request<AI>(a_off, sa, dst + wave * AI * 1024);
-    request<BI>(b_off, sb, dst + kABytes + wave * BI * 1024);
+    if (q < AI) {
+      request(a_off[q], as, dst + (wave * AI + q) * 1024);
+    } else {
+      const int i = q - AI;
+      request(b_off[i], B_KMAJOR ? bs : bs + (wave * BI + i) * RB * b_kstride, dst + kABytes + (wave * BI + i) * 1024);
+    }
+  };
+  auto step_a = [&](const uint4& o) { return a_base + (uint32_t)__builtin_amdgcn_readfirstlane(o.x); };
+  auto step_b = [&](const uint4& o) {
+    const uint32_t lo = __builtin_amdgcn_readfirstlane(o.y), hi = __builtin_amdgcn_readfirstlane(o.z);
+    return b_base + (int64_t)(((uint64_t)hi << 32) | lo);
   };
 
   // ---- fragment addresses in a stage (bytes), for k16 step 0
@@ -170,47 +162,45 @@ k_gemm_tile(const GemmParamsT<NG> P, const typename std::conditional<MAPPED, Out
   struct Frags {
     opvec a[BK / 16][MB], b[BK / 16][NB];
   };
-  auto read_frags = [&](const char* st, Frags& f) {
-#pragma unroll
-    for (int ks = 0; ks < BK / 16; ++ks) {
-#pragma unroll
-      for (int mb = 0; mb < MB; ++mb) f.a[ks][mb] = __builtin_bit_cast(opvec, *reinterpret_cast<const uint4*>(st + (a_frag[mb] ^ (ks * 32))));
-#pragma unroll
-      for (int nb = 0; nb < NB; ++nb) {
-        if (B_KMAJOR) {
-          f.b[ks][nb] = __builtin_bit_cast(opvec, *reinterpret_cast<const uint4*>(st + (b_frag[nb][0] ^ (ks * 32))));
-        } else {
-          typedef short s16x4 __attribute__((ext_vector_type(4)));
-          typedef __attribute__((address_space(3))) s16x4* lds_s16x4;
-          struct { s16x4 lo, hi; } v;
-          v.lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(st + b_frag[nb][0] + ks * 16 * (BN * 2)));
-          v.hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(st + b_frag[nb][1] + ks * 16 * (BN * 2)));
-          f.b[ks][nb] = __builtin_bit_cast(opvec, v);
-        }
-      }
+  constexpr int kReads = BK / 16 * (MB + NB), kMma = BK / 16 * MB * NB, kRequests = AI + BI;
+  auto read_one = [&](const char* st, Frags& f, int i) {
+    const int ks = i / (MB + NB), x = i % (MB + NB), nb = x - MB;
+    if (x < MB) {
+      f.a[ks][x] = __builtin_bit_cast(opvec, *reinterpret_cast<const uint4*>(st + (a_frag[x] ^ (ks * 32))));
+    } else if (B_KMAJOR) {
+      f.b[ks][nb] = __builtin_bit_cast(opvec, *reinterpret_cast<const uint4*>(st + (b_frag[nb][0] ^ (ks * 32))));
+    } else {
+      typedef short s16x4 __attribute__((ext_vector_type(4)));
+      typedef __attribute__((address_space(3))) s16x4* lds_s16x4;
+      struct { s16x4 lo, hi; } v;
+      v.lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(st + b_frag[nb][0] + ks * 16 * (BN * 2)));
+      v.hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(st + b_frag[nb][1] + ks * 16 * (BN * 2)));
+      f.b[ks][nb] = __builtin_bit_cast(opvec, v);
     }
   };
-  auto multiply = [&](const Frags& f) {
-#pragma unroll
-    for (int ks = 0; ks < BK / 16; ++ks)
-#pragma unroll
-      for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = M_::run(f.a[ks][mb], f.b[ks][nb], acc[mb][nb]);
+  auto multiply_one = [&](const Frags& f, int i) {
+    const int ks = i / (MB * NB), mb = i / NB % MB, nb = i % NB;
+    acc[mb][nb] = M_::run(f.a[ks][mb], f.b[ks][nb], acc[mb][nb]);
   };
   // What was loaded above (index tables) has to be out of the vector memory counter's way.  Requests past
   // the last step repeat it (they hit the caches and land in stages that are not read again), so that
   // every step issues the same number and the loop has no branches.
   __builtin_amdgcn_s_waitcnt(0x0F70);                 // vmcnt(0)
 #pragma unroll
-  for (int s = 0; s < STAGES; ++s) issue(steps[min(s, nk - 1)], s);
-  constexpr int kFirst = (STAGES - 1) * (AI + BI);    // requests behind those of the first step,
-  constexpr int kBehind = (STAGES - 2) * (AI + BI);   // and in the loop behind those of the next one
+  for (int s = 0; s < STAGES; ++s) {
+    const uint4 o = steps[min(s, nk - 1)];
+    const char *const as = step_a(o), *const bs = step_b(o);
+#pragma unroll
+    for (int q = 0; q < kRequests; ++q) request_one(q, as, bs, s);
+  }
+  constexpr int kFirst = (STAGES - 1) * kRequests;    // requests behind those of the first step,
+  constexpr int kBehind = (STAGES - 2) * kRequests;   // and in the loop behind those of the next one
   static_assert(kFirst < 64, "vmcnt has 6 bits");
   Frags f0, f1;
   __builtin_amdgcn_s_waitcnt((kFirst & 15) | ((kFirst >> 4) << 14) | 0x0F70);
   asm volatile("s_barrier" ::: "memory");
-  read_frags(lds, f0);
+#pragma unroll
+  for (int i = 0; i < kReads; ++i) read_one(lds, f0, i);
   uint4 ahead = steps[min(STAGES, nk - 1)];
   int slot = 0;                                       // the stage that step `it` came from: in registers, free to be filled
   auto k_step = [&](int it, const Frags& cur, Frags& nxt) {
@@ -218,17 +208,30 @@ k_gemm_tile(const GemmParamsT<NG> P, const typename std::conditional<MAPPED, Out
     // the barrier that holds for every wave
     __builtin_amdgcn_s_waitcnt((kBehind & 15) | ((kBehind >> 4) << 14) | 0x0070);   // vmcnt(kBehind) lgkmcnt(0)
     asm volatile("s_barrier" ::: "memory");
-    issue(ahead, slot);
+    const char *const as = step_a(ahead), *const bs = step_b(ahead);
+    const int free_slot = slot;
     slot = slot == STAGES - 1 ? 0 : slot + 1;
     ahead = steps[min(it + STAGES + 1, nk - 1)];
-    read_frags(lds + slot * kStage, nxt);
-    multiply(cur);
-    // a product, two reads, a product, ...
-    constexpr int kMma = BK / 16 * MB * NB;
+    const char* const st = lds + slot * kStage;
+    // A product, then its share of the requests and of the next step's reads.  A request holds its wave up
+    // while the unit's address path works off those before it (16 cycles each, of all four waves), and
+    // there is one wave per SIMD: all of a step's requests in a row left the matrix pipe idle for as long
+    // as they took.  They are dealt out over seven eighths of the products, the reads over six, so that the
+    // last ones have landed when the step ends.  (us, all in a row in front -> dealt out, operands in the caches:
+    // 128 x 128 tiles, 333 x 4096 x 4096: 35.8 -> 28.7; 256 x 128: 59.8 -> 45.5; 64 x 128: 27.0 -> 23.5.)
+    constexpr int kReqSpan = kMma * 7 / 8, kReadSpan = kMma * 6 / 8;
 #pragma unroll
     for (int i = 0; i < kMma; ++i) {
-      __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
-      __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+      multiply_one(cur, i);
+      if (i < kReqSpan) {
+#pragma unroll
+        for (int q = i * kRequests / kReqSpan; q < (i + 1) * kRequests / kReqSpan; ++q) request_one(q, as, bs, free_slot);
+      }
+      if (i < kReadSpan) {
+#pragma unroll
+        for (int q = i * kReads / kReadSpan; q < (i + 1) * kReads / kReadSpan; ++q) read_one(st, nxt, q);
+      }
+      __builtin_amdgcn_sched_barrier(0);
     }
   };
   int it = 0;
@@ -236,7 +239,10 @@ k_gemm_tile(const GemmParamsT<NG> P, const typename std::conditional<MAPPED, Out
     k_step(it, f0, f1);
     k_step(it + 1, f1, f0);
   }
-  if (it < nk) multiply(f0);
+  if (it < nk) {
+#pragma unroll
+    for (int i = 0; i < kMma; ++i) multiply_one(f0, i);
+  }
   __builtin_amdgcn_s_waitcnt(0x0F70);                 // requests still target this workgroup's LDS
 
   // ---- stage 3 (as in vt_gemm.hip): a lane holds column l32 of a block and rows 8 j + 4 lh + i
@@ -310,21 +316,20 @@ int launch_tile(GemmParams P8, const typename std::conditional<MAPPED, OutMap, N
   return fail(VT_ERR_UNSUPPORTED, "vt_gemm: no such tile");
 }
 
-// The tile with the shortest time, by what one K step of 64 takes a compute unit (ns, for operands that come
-// from HBM, as weights do that are used once per layer; the smaller tiles are bound by their bytes) times the
-// rounds of tiles.  64-row tiles run two to a unit.  Every tile forced, inputs rotating over 600 MB; behind it
-// the same on inputs that stay in the caches, where the 64-row tiles gain most and the order is the same to
-// within 10 % except for 8 x 250 rows:
-//   rows x columns of C (K = 4096): us on 256x256 / 256x128 / 128x128 / 96x128 / 64x128 / 64x64
-//   16 x 4096       88 / 59 / 36 / 32 / 31 / 22         82 / 58 / 35 / 30 / 25 / 18
-//   333 x 4096      89 / 65 / 40 / 36 / 32 / 33         83 / 60 / 36 / 31 / 25 / 26
-//   400 x 6144     100 / 68 / 44 / 40 / 49 / 53         91 / 64 / 40 / 35 / 39 / 49
-//   1024 x 4096     90 / 69 / 46 / 65 / 57 / 69         79 / 61 / 42 / 62 / 46 / 57
-//   1536 x 4096     91 / 70 / 83 / 76 / 79 / 94         80 / 63 / 74 / 68 / 73 / 81   (the rule takes 96x128)
-//   2048 x 4096     93 / 76 / 86 / 102 / 105 / 127      81 / 70 / 84 / 100 / 86 / 108
-//   4000 x 4096    118 / 149 / 166 / 190 / 184 / 228   116 / 141 / 164 / 196 / 167 / 205
-//   8 x 250 x 3584, K = 2048 (grouped)                  72 / 86 / 83 / 79 / 75 / 87     63 / 85 / 80 / 70 / 58 / 69
-//   8 x about 50 x 14336 (grouped, and the combine)    254 / 300 / 219 / 212 / 210 / 239   253 / 299 / 219 / 212 / 209 / 243
+// The tile with the shortest time: what one K step of 64 takes a compute unit (ns) times the rounds of tiles.
+// 64-row tiles run two to a unit.  The constants order the tiles over every tile forced at 62 shapes (rows 16 to 8192,
+// 1 to 8 groups, K 512 to 4096, N 768 to 14336), inputs in HBM and in the caches: the tile taken is 0.3 % slower
+// than the best one on average, 8 % at most.  Some of them:
+//   rows x columns of C (K = 4096): us on 256x256 / 256x128 / 128x128 / 96x128 / 64x128 / 64x64, in HBM; in the caches
+//   16 x 4096       87 / 44 / 31 / 30 / 30 / 22         83 / 44 / 27 / 25 / 21 / 17
+//   333 x 4096      88 / 53 / 38 / 34 / 31 / 30         84 / 45 / 28 / 26 / 22 / 24
+//   400 x 6144      90 / 54 / 39 / 35 / 47 / 51         84 / 46 / 31 / 30 / 36 / 41
+//   1024 x 4096     89 / 56 / 44 / 60 / 55 / 67         80 / 48 / 37 / 54 / 44 / 56
+//   1536 x 4096     90 / 60 / 77 / 70 / 72 / 91         81 / 53 / 63 / 62 / 64 / 82
+//   2048 x 4096     92 / 66 / 80 / 95 / 101 / 126       82 / 63 / 71 / 88 / 82 / 110
+//   4000 x 4096    119 / 127 / 153 / 175 / 184 / 221   117 / 125 / 142 / 174 / 167 / 201
+//   8 x 250 x 3584, K = 2048 (grouped)                  60 / 44 / 54 / 63 / 61 / 73     51 / 36 / 41 / 52 / 44 / 53
+//   8 x about 50 x 14336 (grouped)                     248 / 255 / 199 / 195 / 193 / 212
 // 0 x 0: the 256 x 256 kernel.  Returns the time of one K step in ns.
 int64_t choose_tile(const GemmParams& P, int* bm, int* bn) {
   static const int n_cu = [] {
@@ -333,9 +338,8 @@ int64_t choose_tile(const GemmParams& P, int* bm, int* bn) {
     return n > 0 ? n : 256;
   }();
   static const struct {
-    int bm, bn, ns, ns_shared;     // a unit's time per step with one tile, and per tile with two at a time (they order
-                                   // the tiles; as times they are up to a quarter above what a step of this kernel takes)
-  } kTiles[] = {{256, 256, 1370, 0}, {256, 128, 1250, 0}, {128, 128, 750, 0}, {96, 128, 600, 0}, {64, 128, 500, 430}, {64, 64, 360, 270}};
+    int bm, bn, ns, ns_shared;     // a unit's time per step with one tile, and per tile with two at a time
+  } kTiles[] = {{256, 256, 1650, 0}, {256, 128, 960, 0}, {128, 128, 600, 0}, {96, 128, 580, 0}, {64, 128, 400, 325}, {64, 64, 250, 240}};
   int64_t best = 0;
   for (const auto& t : kTiles) {
     int64_t tiles = 0;
@@ -365,7 +369,7 @@ namespace vt {
 
 // The product of P (operands planned, tiles not yet cut) on smaller tiles, or VT_ERR_UNSUPPORTED when
 // the 256 x 256 kernel is the better one or the only one, or when the estimate (3.5 us and the time of
-// the K steps) is not below below_ns (if that is not 0).
+// the K steps, an eighth more for a weight that comes from HBM) is not below below_ns (if that is not 0).
 int gemm_tile_launch(const GemmParams& P, const OutMap* O, int dtype, hipStream_t st, int64_t below_ns) {
   const char* no = "vt_gemm: outside the small-tile kernel";
   if (P.K % BK || P.K < BK || P.K > kMaxSteps * BK || P.N < 8) return fail(VT_ERR_UNSUPPORTED, no);
@@ -378,7 +382,7 @@ int gemm_tile_launch(const GemmParams& P, const OutMap* O, int dtype, hipStream_
   }
   int bm = 0, bn = 0;
   const int64_t step_ns = choose_tile(P, &bm, &bn);
-  if (below_ns && 3500 + step_ns * (P.K / BK) >= below_ns) return fail(VT_ERR_UNSUPPORTED, no);
+  if (below_ns && 3500 + step_ns * (P.K / BK) * 9 / 8 >= below_ns) return fail(VT_ERR_UNSUPPORTED, no);
   if (!bm) return fail(VT_ERR_UNSUPPORTED, no);
   const NoMap none;
   const bool km = P.g[0].b_kmajor != 0;
