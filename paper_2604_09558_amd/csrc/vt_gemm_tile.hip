@@ -19,6 +19,7 @@
 // deep, and waves divided over K instead of over the tile (half the LDS reads), measured no faster.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstring>
 #include <type_traits>
 
@@ -95,10 +96,14 @@ k_gemm_tile(const GemmParamsT<NG> P, const typename std::conditional<MAPPED, Out
       b_off[i] = (uint32_t)(axis_off(G.b_col, (uint32_t)min(tn * BN + r, N - 1)) * 2) + (uint32_t)((p8 ^ row_key(r)) * 16);
     }
   } else {
+    // a lane's k-row in request i: (wave * BI + i) * RB + kr, of which the first part is whole periods of the key
+    static_assert(BI * RB % 4 == 0, "the key's period");
     const int kr = lane / LB;
-    const uint32_t n = (uint32_t)min(tn * BN + ((lane % LB) ^ k_key<BN>(kr)) * 8, N - 8);
 #pragma unroll
-    for (int i = 0; i < BI; ++i) b_off[i] = (uint32_t)(axis_off(G.b_col, n) * 2) + (uint32_t)(kr * b_kstride);
+    for (int i = 0; i < BI; ++i) {
+      const uint32_t n = (uint32_t)min(tn * BN + ((lane % LB) ^ k_key<BN>(i * RB + kr)) * 8, N - 8);
+      b_off[i] = (uint32_t)(axis_off(G.b_col, n) * 2) + (uint32_t)(kr * b_kstride);
+    }
   }
   if ((int)threadIdx.x < nk) {
     const uint32_t k = threadIdx.x * BK;
@@ -307,29 +312,31 @@ int launch_tile(GemmParams P8, const typename std::conditional<MAPPED, OutMap, N
     hipLaunchKernelGGL((k_gemm_tile<T, C_F32, MAPPED, B_KMAJOR, NG, BM_, BN_, WM_, S_>), grid, dim3(256), 0, st, P, O); \
     return check_launch(MAPPED ? "vt_gemm_store" : "vt_gemm");                                                      \
   }
-  VT_TILE(256, 128, 2, 3)
+  VT_TILE(128, 256, 2, 3)
   VT_TILE(128, 128, 2, 4)
   VT_TILE(96, 128, 1, 5)
+  VT_TILE(64, 512, 1, 2)
+  VT_TILE(64, 256, 1, 3)
   VT_TILE(64, 128, 2, 3)
   VT_TILE(64, 64, 2, 4)
 #undef VT_TILE
   return fail(VT_ERR_UNSUPPORTED, "vt_gemm: no such tile");
 }
 
-// The tile with the shortest time: what one K step of 64 takes a compute unit (ns) times the rounds of tiles.
-// 64-row tiles run two to a unit.  The constants order the tiles over every tile forced at 62 shapes (rows 16 to 8192,
-// 1 to 8 groups, K 512 to 4096, N 768 to 14336), inputs in HBM and in the caches: the tile taken is 0.3 % slower
-// than the best one on average, 8 % at most.  Some of them:
-//   rows x columns of C (K = 4096): us on 256x256 / 256x128 / 128x128 / 96x128 / 64x128 / 64x64, in HBM; in the caches
-//   16 x 4096       87 / 44 / 31 / 30 / 30 / 22         83 / 44 / 27 / 25 / 21 / 17
-//   333 x 4096      88 / 53 / 38 / 34 / 31 / 30         84 / 45 / 28 / 26 / 22 / 24
-//   400 x 6144      90 / 54 / 39 / 35 / 47 / 51         84 / 46 / 31 / 30 / 36 / 41
-//   1024 x 4096     89 / 56 / 44 / 60 / 55 / 67         80 / 48 / 37 / 54 / 44 / 56
-//   1536 x 4096     90 / 60 / 77 / 70 / 72 / 91         81 / 53 / 63 / 62 / 64 / 82
-//   2048 x 4096     92 / 66 / 80 / 95 / 101 / 126       82 / 63 / 71 / 88 / 82 / 110
-//   4000 x 4096    119 / 127 / 153 / 175 / 184 / 221   117 / 125 / 142 / 174 / 167 / 201
-//   8 x 250 x 3584, K = 2048 (grouped)                  60 / 44 / 54 / 63 / 61 / 73     51 / 36 / 41 / 52 / 44 / 53
-//   8 x about 50 x 14336 (grouped)                     248 / 255 / 199 / 195 / 193 / 212
+// The tile with the shortest time: what one K step of 64 takes a compute unit (ns) times the rounds of tiles, but
+// for narrow tiles at least the step's share of B at 4 TB/s: a narrow tile reads 128 or 256 bytes of every k-row, a
+// wide one 512 or 1024, and HBM delivers more for the latter (the requests alone, 64 rows of A and 0.94 GB of B:
+// 64 x 64 tiles 191 us, 64 x 128 176, 64 x 256 156, 64 x 512 150).  Two of the 64-row tiles up to 128 columns run to a
+// unit.  The constants order the tiles over every tile forced at 62 shapes (rows 16 to 16384, 1 to 8 groups, K 512 to
+// 4096, N 768 to 14336), inputs in HBM and in the caches: the tile taken is 0.1 % slower than the best one on average,
+// 3 % at most.  Some of them:
+//   rows x columns of C (K = 4096): us on 256x256 / 128x256 / 128x128 / 96x128 / 64x512 / 64x256 / 64x128 / 64x64
+//   333 x 4096, in the caches           83 /  46 /  29 /  26 /  65 /  31 /  22 /  24
+//   400 x 6144, in the caches           84 /  47 /  31 /  30 /  68 /  33 /  36 /  41
+//   1024 x 4096, in the caches          79 /  48 /  36 /  54 /  68 /  40 /  44 /  55
+//   8 x 50 x 14336 (groups)            240 / 175 / 198 / 194 / 159 / 169 / 193 / 212
+//   8 x 50 x 8192                      133 /  98 / 106 / 105 / 124 /  93 / 104 / 123
+//   8 x 200 x 14336                    250 / 283 / 304 / 353 / 439 / 351 / 356 / 419
 // 0 x 0: the 256 x 256 kernel.  Returns the time of one K step in ns.
 int64_t choose_tile(const GemmParams& P, int* bm, int* bn) {
   static const int n_cu = [] {
@@ -338,14 +345,17 @@ int64_t choose_tile(const GemmParams& P, int* bm, int* bn) {
     return n > 0 ? n : 256;
   }();
   static const struct {
-    int bm, bn, ns, ns_shared;     // a unit's time per step with one tile, and per tile with two at a time
-  } kTiles[] = {{256, 256, 1650, 0}, {256, 128, 960, 0}, {128, 128, 600, 0}, {96, 128, 580, 0}, {64, 128, 400, 325}, {64, 64, 250, 240}};
+    int bm, bn, ns;
+  } kTiles[] = {{256, 256, 1650}, {128, 256, 960}, {128, 128, 590}, {96, 128, 540}, {64, 512, 1160}, {64, 256, 640}, {64, 128, 300}, {64, 64, 250}};
+  int64_t weights = 0;             // groups that are pieces of one A share their B
+  for (int i = 0; i < P.n_groups; ++i) weights += i == 0 || P.g[i].b != P.g[i - 1].b;
+  const int64_t b_ns = weights * P.N * BK * 2 / 4050;
   int64_t best = 0;
   for (const auto& t : kTiles) {
     int64_t tiles = 0;
     for (int i = 0; i < P.n_groups; ++i) tiles += ((int64_t)P.g[i].M + t.bm - 1) / t.bm * ((P.N + t.bn - 1) / t.bn);
     const int64_t rounds = (tiles + n_cu - 1) / n_cu;
-    const int64_t cost = rounds > 1 && t.ns_shared ? rounds * t.ns_shared : rounds * t.ns;
+    const int64_t cost = t.bn > 128 ? rounds * t.ns : std::max(rounds * t.ns, b_ns);
     if (best == 0 || cost < best) {
       best = cost;
       *bm = t.bm, *bn = t.bn;

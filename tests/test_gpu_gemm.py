@@ -249,6 +249,42 @@ def test_tile_shapes(gpu, M, K, N, dtype):
     assert torch.equal(f32[:M].to(p.out.dtype), p.out) and bool((f32[M] == 7.0).all())
 
 
+# the tiles 256 and 512 columns wide: one K step, an odd number, fewer than the ring holds and more; ragged rows and columns
+@pytest.mark.parametrize("M,K,N", [(50, 192, 40008), (3, 64, 40008), (33, 64, 70008), (64, 320, 70008)])
+def test_wide_tiles(gpu, M, K, N):
+    """W as [K,N] and as [N,K] through a Permute, and stored through a map over two tensors: fp32 outputs against the
+    oracle (sums of K terms of about 0.05: 1e-4), equal bits for both weights, the 16-bit results the fp32 one rounded
+    once, nothing written behind the last row."""
+    vt, tio, pipelines, torch = gpu
+    from paper_2604_09558_amd import binding
+    rng = np.random.default_rng(37)
+    x = workloads.encode(rng.normal(size=(M, K)).astype(np.float32), "bf16")
+    w = workloads.encode((rng.normal(size=(K, N)) * 0.05).astype(np.float32), "bf16")
+    n0 = N // 2 // 8 * 8
+    blank = {"P": np.zeros((M, n0), w.dtype), "Q": np.zeros((M, N - n0), w.dtype)}
+    chain = [("Bt", "permute", ("Wt",), {"perm": (1, 0)}), ("C", "concat", ("P", "Q"), {"dim": 1})]
+    dw = tio.DeviceWorkload(workloads.Workload("wide", "bf16", {"X": x, "W": w, "Wt": np.ascontiguousarray(w.T), **blank}, chain, {}))
+    a, b, bt = dw.build("X"), dw.build("W"), dw.build("Bt")
+    f32 = torch.full((M + 1, N), 7.0, device="cuda:0")
+    out, out_t = (torch.empty((M, N), dtype=torch.bfloat16, device="cuda:0") for _ in range(2))
+    vt.vt_gemm([a], [b], [f32], "f32")
+    vt.vt_gemm([a], [b], [out], "bf16")
+    vt.vt_gemm([a], [bt], [out_t], "bf16")
+    nbytes = binding.vt_gemm_store_workspace(M, N, K)
+    ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda:0")
+    binding.vt_gemm_store_workspace_init(ws, nbytes)
+    binding.vt_gemm_store(a, b, dw.build("C"), ws, nbytes)
+    torch.cuda.synchronize()
+    ref = consumers.gemm(consumers.decode(x, "bf16"), consumers.decode(w, "bf16"))
+    assert np.abs(f32[:M].cpu().numpy() - ref).max() <= 1e-4
+    assert torch.equal(f32[:M].to(torch.bfloat16), out) and torch.equal(out, out_t) and bool((f32[M] == 7.0).all())
+    stored = torch.cat([dw.tensors["P"].view(torch.bfloat16), dw.tensors["Q"].view(torch.bfloat16)], dim=1)
+    if M > 16:       # (up to 16 rows the projection store sums K in slices)
+        assert torch.equal(stored, out)
+    else:
+        assert (stored.float() - f32[:M]).abs().max() <= 2.0 ** -8 * f32[:M].abs().max() + 1e-4
+
+
 @pytest.fixture(scope="module")
 def c5_full(gpu):
     """Config 5 at the benchmark's size, launched once as the benchmark launches it (8 experts in
