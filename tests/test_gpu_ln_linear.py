@@ -151,6 +151,40 @@ def test_weight_streamed_kernel(gpu, B, R, win, C, N, dtype):
         assert torch.equal(p.out, first)
 
 
+# K = 64, 96, 128 from 512 blocks of 64 rows on: one to three slices of 512 columns, waves with no, one
+# and two tiles of 64, ragged columns and a ragged last block
+@pytest.mark.parametrize("B,R,win,C,N,dtype", [(1, 182, 7, 96, 24, "bf16"), (1, 182, 7, 96, 328, "f16"), (1, 182, 7, 128, 520, "bf16"),
+                                                (1, 182, 7, 64, 1032, "f16"), (2, 182, 7, 96, 64, "bf16")])
+def test_weight_slice_kernel(gpu, B, R, win, C, N, dtype):
+    """Against the oracle (bound as in test_weight_streamed_kernel); the 16-bit result is the fp32 one rounded once;
+    nothing written behind the last row; constant rows give zero, rows of subnormal variance with eps = 0 the
+    oracle's values."""
+    vt, tio, pipelines, torch = gpu
+    wl = workloads.c4_window_ln_linear(seed=7, B=B, R=R, win=win, C=C, N=N, dtype=dtype)
+    ref = run_workload(wl)["out"]
+    p = pipelines.Gemm(tio.DeviceWorkload(wl), fused=True)
+    p.run()
+    f32 = torch.full((B * R * R + 1, N), 7.0, device="cuda:0")
+    vt.vt_gemm(p.A, p.B, [f32], "f32", vt.GEMM_LAYERNORM, p.eps)
+    torch.cuda.synchronize()
+    check(tio.to_host_f64(p.out).reshape(ref.shape), ref)
+    assert np.max(np.abs(tio.to_host_f64(f32[:-1]).reshape(ref.shape) - ref)) <= 4e-3 and bool((f32[-1] == 7.0).all())
+    assert torch.equal(f32[:-1].to(p.out.dtype).reshape(p.out.shape), p.out)
+    wl.sources["X"][:] = workloads.encode(np.full(1, 3.25, np.float32), dtype)[0]
+    p = pipelines.Gemm(tio.DeviceWorkload(wl), fused=True)
+    p.run()
+    torch.cuda.synchronize()
+    assert np.all(tio.to_host_f64(p.out) == 0.0)
+    if dtype == "bf16":
+        sign = np.where(np.arange(C) % 2 == 0, 1.0, -1.0)
+        wl.sources["X"] = workloads.encode(np.broadcast_to(sign * 1e-21, wl.sources["X"].shape).astype(np.float32), "bf16")
+        wl.consumer["eps"] = 0.0
+        p = pipelines.Gemm(tio.DeviceWorkload(wl), fused=True)
+        p.run()
+        torch.cuda.synchronize()
+        check(tio.to_host_f64(p.out).reshape(ref.shape), run_workload(wl)["out"])
+
+
 @pytest.mark.parametrize("C", [40, 256])
 def test_subnormal_variance_without_eps(gpu, C):
     """Rows of +-1e-21 and eps = 0: the variance is a subnormal fp32 number, the normalised row +-1."""
