@@ -572,6 +572,7 @@ int plan_b(const vt_desc& d, GemmGroup* g, int64_t* K, int64_t* N) {
 namespace vt {
 int ln_gemm_launch(const vt_desc& A, const vt_desc& B, void* C, int c_dtype, float eps, hipStream_t st);
 int ln_gemm_slice_launch(const vt_desc& A, const vt_desc& B, void* C, int c_dtype, float eps, hipStream_t st);
+int ln_gemm_ring_launch(const vt_desc& A, const vt_desc& B, void* C, int c_dtype, float eps, hipStream_t st);
 int ln_gemm_wide_launch(const vt_desc& A, const vt_desc& B, void* C, int c_dtype, float eps, hipStream_t st);
 int gemm_tile_launch(const gemm::GemmParams& P, const gemm::OutMap* O, int dtype, hipStream_t st, int64_t below_ns = 0);
 }
@@ -652,9 +653,10 @@ extern "C" int vt_gemm(const vt_desc* const* A, const vt_desc* const* B, void* c
       if (!A[i] || !B[i] || !C[i]) return fail(VT_ERR_INVALID_ARG, "vt_gemm: NULL descriptor or output");
       if (A[i]->dtype != dt || B[i]->dtype != dt) return fail(VT_ERR_INVALID_ARG, "vt_gemm: mixed operand dtypes");
       int rc = ln_gemm_launch(*A[i], *B[i], C[i], c_dtype, eps, st);
-      // K or N that the kernel with W in registers is not built for: the one that holds a slice of W, the one
-      // that streams W; maps that none takes: the generic kernel with the same prologue
+      // K or N that the kernel with W in registers is not built for: the one that holds a slice of W, those
+      // that stream W (through LDS, through registers); maps that none takes: the generic kernel with the same prologue
       if (rc == VT_ERR_UNSUPPORTED) rc = ln_gemm_slice_launch(*A[i], *B[i], C[i], c_dtype, eps, st);
+      if (rc == VT_ERR_UNSUPPORTED) rc = ln_gemm_ring_launch(*A[i], *B[i], C[i], c_dtype, eps, st);
       if (rc == VT_ERR_UNSUPPORTED) rc = ln_gemm_wide_launch(*A[i], *B[i], C[i], c_dtype, eps, st);
       if (rc == VT_ERR_UNSUPPORTED) rc = launch_generic(*A[i], *B[i], C[i], c_dtype, true, eps, st);
       if (rc != VT_OK) return rc;

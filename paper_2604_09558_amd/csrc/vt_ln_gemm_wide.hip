@@ -1,7 +1,7 @@
 // LayerNorm fused into the load stage of a GEMM whose weight does not fit the registers of one
 // workgroup: C = LN(A) . W, A virtual [.., K] with contiguous rows, K <= 1024, W a row-major [K, N]
-// matrix, any N (K and N multiples of 8).  (vt_ln_gemm.hip keeps W in registers for K = 64 / 128 and
-// N <= 384.)  Bound by HBM at small K (a token's K values are read once and its N outputs written
+// matrix, any N (K and N multiples of 8).  (vt_ln_gemm.hip and vt_ln_gemm_slice.hip keep W in registers for up to
+// 128 features; vt_ln_gemm_ring.hip takes most calls of 128 to 512 features in multiples of 64 from 1024 rows on.)  Bound by HBM at small K (a token's K values are read once and its N outputs written
 // once), by the matrix pipes and the reads of W from L2 as K and N grow.
 //
 // A workgroup takes 64 or 128 rows: they are fetched through the map (16 bytes per lane, LP2 lanes per row,
@@ -17,8 +17,8 @@
 // next two K steps in flight while one is multiplied.  A lane ends up with 4 consecutive columns of a
 // row; a wave turns 16 rows at a time round in LDS and leaves with whole 128-byte row segments.
 // (64 rows x 128 columns per wave spilled; four or six register sets measured no faster than three.)
-// 25088 x 256 -> 768, bf16 (51.8 MB, 9.9 GFLOP): 21 us (27 us with inputs cold in every cache); 2295 us on the
-// generic kernel, which evaluates the map for every element of A and W.  What is left is latency: rows,
+// 25088 x 256 -> 768, bf16 (51.8 MB, 9.9 GFLOP): 21 us (27 us with inputs cold in every cache; 18 through the rings); 2295 us on
+// the generic kernel, which evaluates the map for every element of A and W.  What is left is latency: rows,
 // statistics and W follow each other inside a workgroup, and only two or three waves per SIMD overlap
 // (of the 27 us the matrix pipes of a working unit are busy 5, the vector instructions 7; counters:
 // profiles/small_tiles_streamed_ln_split_rowsum.txt).

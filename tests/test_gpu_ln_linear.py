@@ -185,6 +185,44 @@ def test_weight_slice_kernel(gpu, B, R, win, C, N, dtype):
         check(tio.to_host_f64(p.out).reshape(ref.shape), run_workload(wl)["out"])
 
 
+# From 1024 rows (or 16384 of at most 256 columns) and 128 features (multiples of 64) on: every height of a block with its ragged last one, one to
+# eight groups of columns, waves with no, one and two tiles, ragged columns, rows of odd and even multiples of 128 bytes
+@pytest.mark.parametrize("B,R,win,C,N,dtype", [(1, 33, 1, 128, 392, "bf16"), (1, 130, 5, 192, 8, "f16"), (1, 35, 5, 320, 712, "bf16"),
+                                                (1, 40, 5, 384, 1032, "f16"), (1, 91, 7, 256, 520, "bf16"), (1, 158, 2, 128, 520, "f16"), (1, 147, 7, 512, 72, "f16"),
+                                                (1, 149, 1, 256, 264, "f16"), (1, 162, 9, 384, 136, "bf16"), (1, 183, 3, 192, 584, "bf16"),
+                                                (1, 33, 3, 512, 1096, "bf16")])
+def test_weight_ring_kernel(gpu, B, R, win, C, N, dtype):
+    """Against the oracle (bound as in test_weight_streamed_kernel); the 16-bit result is the fp32 one rounded once;
+    nothing written behind the last row; constant rows give zero, rows of subnormal variance with eps = 0 the
+    oracle's values."""
+    vt, tio, pipelines, torch = gpu
+    wl = workloads.c4_window_ln_linear(seed=8, B=B, R=R, win=win, C=C, N=N, dtype=dtype)
+    ref = run_workload(wl)["out"]
+    p = pipelines.Gemm(tio.DeviceWorkload(wl), fused=True)
+    out = torch.full((B * R * R + 1, N), 7.0, dtype=p.out.dtype, device="cuda:0")
+    f32 = torch.full((B * R * R + 1, N), 7.0, device="cuda:0")
+    vt.vt_gemm(p.A, p.B, [out], dtype, vt.GEMM_LAYERNORM, p.eps)
+    vt.vt_gemm(p.A, p.B, [f32], "f32", vt.GEMM_LAYERNORM, p.eps)
+    torch.cuda.synchronize()
+    check(tio.to_host_f64(out[:-1]).reshape(ref.shape), ref)
+    assert np.max(np.abs(tio.to_host_f64(f32[:-1]).reshape(ref.shape) - ref)) <= 4e-3
+    assert bool((f32[-1] == 7.0).all()) and bool((out[-1] == 7.0).all())
+    assert torch.equal(f32[:-1].to(out.dtype), out[:-1])
+    wl.sources["X"][:] = workloads.encode(np.full(1, 3.25, np.float32), dtype)[0]
+    p = pipelines.Gemm(tio.DeviceWorkload(wl), fused=True)
+    p.run()
+    torch.cuda.synchronize()
+    assert np.all(tio.to_host_f64(p.out) == 0.0)
+    if dtype == "bf16":
+        sign = np.where(np.arange(C) % 2 == 0, 1.0, -1.0)
+        wl.sources["X"] = workloads.encode(np.broadcast_to(sign * 1e-21, wl.sources["X"].shape).astype(np.float32), "bf16")
+        wl.consumer["eps"] = 0.0
+        p = pipelines.Gemm(tio.DeviceWorkload(wl), fused=True)
+        p.run()
+        torch.cuda.synchronize()
+        check(tio.to_host_f64(p.out).reshape(ref.shape), run_workload(wl)["out"])
+
+
 @pytest.mark.parametrize("C", [40, 256])
 def test_subnormal_variance_without_eps(gpu, C):
     """Rows of +-1e-21 and eps = 0: the variance is a subnormal fp32 number, the normalised row +-1."""
