@@ -65,3 +65,40 @@ def test_moe_combine_full_size_every_output(gpu):
         ref = consumers.weighted_sum(consumers.decode(env["x"][r:r + 2048], "bf16"),
                                      consumers.decode(env["y"][r:r + 2048], "bf16"), w[r:r + 2048])
         check(tio.to_host_f64(p.out[r:r + 2048]), ref, 2.0 ** -8)
+
+
+# One row in several workgroups (the last of them short), several rows in one, vectors per thread from one to eight and
+# their remainders; `pieces`: x is two sources behind each other, which only the evaluator takes
+@pytest.mark.parametrize("pieces", [False, True])
+@pytest.mark.parametrize("R,C,dtype", [(1, 8, "bf16"), (1, 14336, "f16"), (3, 2056, "bf16"), (700, 8, "f16"), (517, 1000, "bf16"), (2100, 2080, "bf16"),
+                                        (5200, 1032, "f16"), (40000, 16, "bf16"), (9, 40960, "bf16")])
+def test_row_kernel_shapes(gpu, R, C, dtype, pieces):
+    """Against the sum in float64: two products and a sum in fp32 (or fma: 3 roundings of 2^-24) and one to the type."""
+    vt, tio, pipelines, torch = gpu
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(R + C)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float16
+    pool = torch.randn((R + 5, C), generator=g, device="cuda:0").to(dt)
+    more = torch.randn((R + 2, C), generator=g, device="cuda:0").to(dt)
+    w = torch.rand((R, 2), generator=g, device="cuda:0")
+    idx = np.random.default_rng(R).integers(0, R + 5, R).astype(np.int32)
+    tab = torch.from_numpy(idx).to("cuda:0")
+    src = {"P": (tuple(pool.shape), dtype, pool.data_ptr()), "M": (tuple(more.shape), dtype, more.data_ptr())}
+    gather = vt.build_chain([("y", "index_select", ("P",), {"dim": 0, "index": "i"})], src, "y", {"i": idx}, {"i": tab.data_ptr()})
+    y = pool[tab.long()]
+    if pieces:
+        cut = R // 2
+        chain = [("c", "concat", ("M", "P"), {"dim": 0}), ("x", "slice", ("c",), {"dim": 0, "start": R + 2 - cut, "stop": 2 * R + 2 - cut})]
+        xd = vt.build_chain(chain, src, "x", {}, {})
+        x = torch.cat((more, pool))[R + 2 - cut:2 * R + 2 - cut]
+    else:
+        xd = vt.build_chain([("x", "slice", ("M",), {"dim": 0, "start": 2, "stop": R + 2})], src, "x", {}, {})
+        x = more[2:]
+    out = torch.full((R + 1, C), 7.0, dtype=dt, device="cuda:0")
+    vt.vt_weighted_sum(xd, gather, w, out)
+    torch.cuda.synchronize()
+    px, py = w[:, :1].double() * x.double(), w[:, 1:].double() * y.double()
+    ref = px + py
+    bound = ref.abs() * (2.0 ** -8 if dtype == "bf16" else 2.0 ** -11) + 2.0 ** -22 * (px.abs() + py.abs()) + 2.0 ** -25
+    assert bool(((out[:R].double() - ref).abs() <= bound).all())
+    assert bool((out[R] == 7.0).all())
