@@ -323,21 +323,21 @@ int launch_tile(GemmParams P8, const typename std::conditional<MAPPED, OutMap, N
   return fail(VT_ERR_UNSUPPORTED, "vt_gemm: no such tile");
 }
 
-// The tile with the shortest time: what one K step of 64 takes a compute unit (ns) times the rounds of tiles, but
-// for narrow tiles at least the step's share of B at 4 TB/s: a narrow tile reads 128 or 256 bytes of every k-row, a
-// wide one 512 or 1024, and HBM delivers more for the latter (the requests alone, 64 rows of A and 0.94 GB of B:
-// 64 x 64 tiles 191 us, 64 x 128 176, 64 x 256 156, 64 x 512 150).  Two of the 64-row tiles up to 128 columns run to a
-// unit.  The constants order the tiles over every tile forced at 62 shapes (rows 16 to 16384, 1 to 8 groups, K 512 to
-// 4096, N 768 to 14336), inputs in HBM and in the caches: the tile taken is 0.1 % slower than the best one on average,
-// 3 % at most.  Some of them:
-//   rows x columns of C (K = 4096): us on 256x256 / 128x256 / 128x128 / 96x128 / 64x512 / 64x256 / 64x128 / 64x64
-//   333 x 4096, in the caches           83 /  46 /  29 /  26 /  65 /  31 /  22 /  24
-//   400 x 6144, in the caches           84 /  47 /  31 /  30 /  68 /  33 /  36 /  41
-//   1024 x 4096, in the caches          79 /  48 /  36 /  54 /  68 /  40 /  44 /  55
-//   8 x 50 x 14336 (groups)            240 / 175 / 198 / 194 / 159 / 169 / 193 / 212
-//   8 x 50 x 8192                      133 /  98 / 106 / 105 / 124 /  93 / 104 / 123
-//   8 x 200 x 14336                    250 / 283 / 304 / 353 / 439 / 351 / 356 / 419
-// 0 x 0: the 256 x 256 kernel.  Returns the time of one K step in ns.
+// The tile with the shortest estimated time: a launch, a start for every round of tiles over the compute units, and per K
+// step of 64 a share for every round and one for every tile of an average unit (a last round that is nearly empty costs less
+// than a full one, and the board's power limit slows full ones), and the weights at 4 TB/s.  The five constants
+// of each tile are fitted over every tile forced at 163 shapes (rows 17 to 16384, 1 to 8 groups, K 512 to 4096, N 768 to
+// 14336): the tile taken is 0.2 % slower than the best one there on average, 10 % at most.  (One time per step and round
+// for each tile, the rule before: 1.9 %, 25 % at most, with its losses at K = 1024, at few rows and at two to five rounds.)
+// Some of them:
+//   rows x columns of C: us on 256x256 / 128x256 / 128x128 / 96x128 / 64x512 / 64x256 / 64x128 / 64x64
+//   333 x 4096, K = 4096, in the caches  83 /  46 /  29 /  26 /  65 /  31 /  22 /  24
+//   400 x 6144, K = 4096, in the caches  84 /  47 /  31 /  30 /  68 /  33 /  36 /  41
+//   8 x 50 x 14336, K = 4096 (groups)   240 / 175 / 198 / 194 / 159 / 169 / 193 / 212
+//   8 x 200 x 8192, K = 2048             76 /  88 / 105 / 126 / 120 / 111 / 113 / 134
+//   4 x 254 x 8192, K = 4096            107 / 129 / 129 / 118 / 190 / 137 / 132 / 156   (the rule before: 64 x 128)
+//   8 x 18 x 1408, K = 1024              32 /  19 /  13 /  12 /  24 /  13 /  10 / 8.5   (64 x 128)
+// 0 x 0: the 256 x 256 kernel.  Returns the estimate in ns.
 int64_t choose_tile(const GemmParams& P, int* bm, int* bn) {
   static const int n_cu = [] {
     int dev = 0, n = 256;
@@ -345,17 +345,19 @@ int64_t choose_tile(const GemmParams& P, int* bm, int* bn) {
     return n > 0 ? n : 256;
   }();
   static const struct {
-    int bm, bn, ns;
-  } kTiles[] = {{256, 256, 1650}, {128, 256, 960}, {128, 128, 590}, {96, 128, 540}, {64, 512, 1160}, {64, 256, 640}, {64, 128, 300}, {64, 64, 250}};
+    int bm, bn, launch, round, step_round, step_tile, weights;
+  } kTiles[] = {{256, 256, 493, 3154, 1381, 171, 238}, {128, 256, 286, 7322, 299, 645, 324}, {128, 128, 1005, 5144, 214, 208, 852},
+                {96, 128, 185, 3883, 332, 185, 320},   {64, 512, 7, 5596, 711, 628, 279},    {64, 256, 256, 5514, 282, 420, 259},
+                {64, 128, 2424, 363, 343, 8, 344},     {64, 64, 3102, 293, 204, 42, 289}};
   int64_t weights = 0;             // groups that are pieces of one A share their B
   for (int i = 0; i < P.n_groups; ++i) weights += i == 0 || P.g[i].b != P.g[i - 1].b;
-  const int64_t b_ns = weights * P.N * BK * 2 / 4050;
+  const int64_t weights_ns = weights * P.N * P.K * 2 / 4000, steps = P.K / BK;
   int64_t best = 0;
   for (const auto& t : kTiles) {
     int64_t tiles = 0;
     for (int i = 0; i < P.n_groups; ++i) tiles += ((int64_t)P.g[i].M + t.bm - 1) / t.bm * ((P.N + t.bn - 1) / t.bn);
     const int64_t rounds = (tiles + n_cu - 1) / n_cu;
-    const int64_t cost = t.bn > 128 ? rounds * t.ns : std::max(rounds * t.ns, b_ns);
+    const int64_t cost = t.launch + rounds * t.round + steps * (rounds * t.step_round + tiles * t.step_tile / n_cu) + weights_ns * t.weights / 1000;
     if (best == 0 || cost < best) {
       best = cost;
       *bm = t.bm, *bn = t.bn;
@@ -378,8 +380,8 @@ int64_t axis_span(const AxisMap<ND>& a) {
 namespace vt {
 
 // The product of P (operands planned, tiles not yet cut) on smaller tiles, or VT_ERR_UNSUPPORTED when
-// the 256 x 256 kernel is the better one or the only one, or when the estimate (3.5 us and the time of
-// the K steps, an eighth more for a weight that comes from HBM) is not below below_ns (if that is not 0).
+// the 256 x 256 kernel is the better one or the only one, or when the estimate, and 0.9 us for
+// the mapped store, is not below below_ns (if that is not 0; 27 x 1024 -> 512: 9.5 us here, 9.1 on the projection store).
 int gemm_tile_launch(const GemmParams& P, const OutMap* O, int dtype, hipStream_t st, int64_t below_ns) {
   const char* no = "vt_gemm: outside the small-tile kernel";
   if (P.K % BK || P.K < BK || P.K > kMaxSteps * BK || P.N < 8) return fail(VT_ERR_UNSUPPORTED, no);
@@ -391,8 +393,8 @@ int gemm_tile_launch(const GemmParams& P, const OutMap* O, int dtype, hipStream_
     if (span >= (1ll << 32)) return fail(VT_ERR_UNSUPPORTED, no);
   }
   int bm = 0, bn = 0;
-  const int64_t step_ns = choose_tile(P, &bm, &bn);
-  if (below_ns && 3500 + step_ns * (P.K / BK) * 9 / 8 >= below_ns) return fail(VT_ERR_UNSUPPORTED, no);
+  const int64_t estimate_ns = choose_tile(P, &bm, &bn);
+  if (below_ns && estimate_ns + 900 >= below_ns) return fail(VT_ERR_UNSUPPORTED, no);
   if (!bm) return fail(VT_ERR_UNSUPPORTED, no);
   const NoMap none;
   const bool km = P.g[0].b_kmajor != 0;
