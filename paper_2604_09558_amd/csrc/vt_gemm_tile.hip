@@ -49,7 +49,7 @@ __device__ __forceinline__ void request(uint32_t off, const char* base, uint32_t
 // four k-rows x 64 bytes that 32 lanes of a transposing read touch.
 __device__ __forceinline__ int row_key(int r) { return r >> 1 & 7; }
 template <int BN>
-__device__ __forceinline__ int k_key(int k) { return BN == 64 ? (k >> 1 & 1) << 2 : (k & 3) << 2; }
+__device__ __forceinline__ int k_key(int k) { return BN == 32 ? 0 : BN == 64 ? (k >> 1 & 1) << 2 : (k & 3) << 2; }
 
 template <typename T, bool C_F32, bool MAPPED, bool B_KMAJOR, int NG, int BM, int BN, int WM, int STAGES>
 __global__ void __launch_bounds__(256)
@@ -298,6 +298,195 @@ k_gemm_tile(const GemmParamsT<NG> P, const typename std::conditional<MAPPED, Out
     }
 }
 
+// For few tiles.  A short prompt's 64-row tiles leave most of the chip idle (32 x 2048 -> 2048: 32 tiles), and a step of
+// theirs takes 0.2 us on a chain of barrier, fragment reads and four dependent products, at half of what a unit draws.  Here the
+// tiles are 32 x 32 or 32 x 64 and divided over K instead of over the tile: each of the 4 waves computes the whole
+// tile over every fourth K step, out of a ring of its own in LDS that nobody else reads (two stages: two workgroups of 32 x 32
+// share a unit; three for 32 x 64), so there are no barriers until the partial sums meet in LDS at the end (added in
+// the order of the waves; the other kernels add the K steps in one chain).  Bound by the unit's draw of its operands.
+// Measured (us, 64 x 64 tiles -> 32 x 32 / 32 x 64): 34 x 2048 -> 1000 10.4 -> 6.3 / 8.3, 62 x 1024 -> 2048 7.3 -> 5.3 / 6.8, 100 x
+// 4096 -> 1000 17.0 -> 11.8 / 15.3, 212 x 4096 -> 2048 (mapped) 19.4 -> 19.1 / 16.1; past one round of 256 tiles of 32 x 64 the
+// larger tiles win (168 x 1024 -> 4096 7.6 -> 11.8 / 11.8).  64 x 64 tiles divided like this: no faster than over the tile.
+template <typename T, bool C_F32, bool MAPPED, bool B_KMAJOR, int NG, int BM, int BN, int STAGES>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BM + BN == 64 ? 2 : 1, 2)))
+k_gemm_ksplit(const GemmParamsT<NG> P, const typename std::conditional<MAPPED, OutMap, NoMap>::type O) {
+  typedef Mma<T> M_;
+  typedef typename M_::vec opvec;
+  constexpr int W = 4, MB = BM / 32, NB = BN / 32;
+  constexpr int kABytes = BM * BK * 2, kStage = (BM + BN) * BK * 2;
+  constexpr int AI = BM / 8, BI = BN / 8, kRequests = AI + BI;      // of 1 KB each, per step
+  static_assert(BM * BN * 4 <= STAGES * kStage, "a wave's partial sums fit its ring");
+  static_assert((STAGES - 1) * kRequests < 64, "vmcnt has 6 bits");
+  __shared__ __attribute__((aligned(1024))) char lds[W * STAGES * kStage];
+  __shared__ uint4 steps[kMaxSteps];
+  __shared__ int64_t rowoff[MAPPED ? 4 * BM : 1];
+
+  int gi, tm, tn;
+  if (!pick_tile(P, blockIdx.x, &gi, &tm, &tn)) return;
+  const GemmGroup& G = P.g[gi];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l32 = lane & 31, lh = lane >> 5;
+  const int Mg = G.M, N = P.N, nk = P.K / BK;
+
+  // ---- stage 1 through the map, as in the kernel above; every wave asks for whole steps
+  const char* const a_base = G.a;
+  const char* const b_base = G.b;
+  const int r8 = lane >> 3, p8 = lane & 7;
+  uint32_t a_off[AI], b_off[B_KMAJOR ? BI : 1];
+#pragma unroll
+  for (int i = 0; i < AI; ++i) {
+    const int r = i * 8 + r8;
+    const uint32_t m = (uint32_t)min(tm * BM + r, Mg - 1);
+    const int64_t ro = G.a_row.tdig >= 0 ? axis_off_table(G.a_row, m) : axis_off(G.a_row, m);
+    a_off[i] = (uint32_t)(ro * 2) + (uint32_t)((p8 ^ row_key(r)) * 16);
+  }
+  constexpr int LB = BN / 8, RB = 64 / LB;           // lanes per k-row of B, k-rows per request: whole periods of the key
+  const int64_t b_kstride = G.b_row.stride[2] * 2;
+  if constexpr (B_KMAJOR) {
+#pragma unroll
+    for (int i = 0; i < BI; ++i) {
+      const int r = i * 8 + r8;
+      b_off[i] = (uint32_t)(axis_off(G.b_col, (uint32_t)min(tn * BN + r, N - 1)) * 2) + (uint32_t)((p8 ^ row_key(r)) * 16);
+    }
+  } else {
+    const int kr = lane / LB;
+    const uint32_t n = (uint32_t)min(tn * BN + ((lane % LB) ^ k_key<BN>(kr)) * 8, N - 8);
+    b_off[0] = (uint32_t)(axis_off(G.b_col, n) * 2) + (uint32_t)(kr * b_kstride);
+  }
+  if ((int)threadIdx.x < nk) {
+    const uint32_t k = threadIdx.x * BK;
+    const uint64_t bo = (uint64_t)(axis_off(G.b_row, k) * 2);
+    steps[threadIdx.x] = make_uint4((uint32_t)(axis_off(G.a_col, k) * 2), (uint32_t)bo, (uint32_t)(bo >> 32), 0);
+  }
+  if constexpr (MAPPED)
+    for (int pc = 0; pc < O.n; ++pc)
+      for (int r = threadIdx.x; r < BM; r += 256) rowoff[pc * BM + r] = axis_off(O.p[pc].row, (uint32_t)min(tm * BM + r, Mg - 1));
+  __syncthreads();
+
+  char* const ring = lds + wave * (STAGES * kStage);
+  const uint32_t ring_dst = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lptr_t)ring);
+  const int n_my = (nk - wave + W - 1) / W;          // steps wave, wave + W, ...
+  auto request_step = [&](int i, int slot) {         // this wave's step i (past its last one: that again, not read)
+    const uint4 o = steps[wave + min(i, n_my - 1) * W];
+    const char* const as = a_base + (uint32_t)__builtin_amdgcn_readfirstlane(o.x);
+    const uint32_t lo = __builtin_amdgcn_readfirstlane(o.y), hi = __builtin_amdgcn_readfirstlane(o.z);
+    const char* const bs = b_base + (int64_t)(((uint64_t)hi << 32) | lo);
+    const uint32_t dst = ring_dst + slot * kStage;
+#pragma unroll
+    for (int q = 0; q < AI; ++q) request(a_off[q], as, dst + q * 1024);
+#pragma unroll
+    for (int q = 0; q < BI; ++q) request(b_off[B_KMAJOR ? q : 0], B_KMAJOR ? bs : bs + q * RB * b_kstride, dst + kABytes + q * 1024);
+  };
+
+  // ---- fragment addresses in a stage (bytes), for k16 step 0, as in the kernel above
+  uint32_t a_frag[MB], b_frag[NB][2];
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb) a_frag[mb] = (mb * 32 + l32) * 128 + ((lh ^ row_key(mb * 32 + l32)) * 16);
+  const int lq = lane >> 4, ll = lane & 15;
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) {
+    if (B_KMAJOR) {
+      b_frag[nb][0] = kABytes + (nb * 32 + l32) * 128 + ((lh ^ row_key(nb * 32 + l32)) * 16);
+      b_frag[nb][1] = 0;
+    } else {
+      const int chunk = nb * 4 + 2 * (lq & 1) + ((ll & 3) >> 1);
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int k = 8 * (lq >> 1) + (ll >> 2) + 4 * h;
+        b_frag[nb][h] = kABytes + k * (BN * 2) + ((chunk ^ k_key<BN>(k)) * 16) + (ll & 1) * 8;
+      }
+    }
+  }
+
+  f32x16 acc[MB][NB];
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+  if (n_my > 0) {
+    __builtin_amdgcn_s_waitcnt(0x0F70);               // vmcnt(0): index tables out of the counter's way
+#pragma unroll
+    for (int s = 0; s < STAGES; ++s) request_step(s, s);
+    int slot = 0;
+    for (int i = 0; i < n_my; ++i) {
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"((STAGES - 1) * kRequests) : "memory");
+      const char* const st = ring + slot * kStage;
+      opvec a[BK / 16][MB], b[BK / 16][NB];
+#pragma unroll
+      for (int ks = 0; ks < BK / 16; ++ks) {
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) a[ks][mb] = __builtin_bit_cast(opvec, *reinterpret_cast<const uint4*>(st + (a_frag[mb] ^ (ks * 32))));
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+          if (B_KMAJOR) {
+            b[ks][nb] = __builtin_bit_cast(opvec, *reinterpret_cast<const uint4*>(st + (b_frag[nb][0] ^ (ks * 32))));
+          } else {
+            typedef short s16x4 __attribute__((ext_vector_type(4)));
+            typedef __attribute__((address_space(3))) s16x4* lds_s16x4;
+            struct { s16x4 lo, hi; } v;
+            v.lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(st + b_frag[nb][0] + ks * 16 * (BN * 2)));
+            v.hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(st + b_frag[nb][1] + ks * 16 * (BN * 2)));
+            b[ks][nb] = __builtin_bit_cast(opvec, v);
+          }
+        }
+      }
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");            // the stage is in registers
+      request_step(i + STAGES, slot);
+      slot = slot == STAGES - 1 ? 0 : slot + 1;
+#pragma unroll
+      for (int ks = 0; ks < BK / 16; ++ks)
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+          for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = M_::run(a[ks][mb], b[ks][nb], acc[mb][nb]);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                // requests still target this wave's ring
+  }
+
+  // ---- the partial sums, each in its wave's ring: [BM][BN]; a lane holds column l32 of a block and rows 8 j + 4 lh + i
+  float* const mine = reinterpret_cast<float*>(ring);
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) mine[(mb * 32 + 8 * j + 4 * lh + i) * BN + nb * 32 + l32] = acc[mb][nb][4 * j + i];
+  __syncthreads();
+  // ---- stage 3: a thread has one column
+  const int c = threadIdx.x % BN, col = tn * BN + c;
+  if (col >= N) return;
+  typedef typename std::conditional<C_F32, float, T>::type CT;
+  CT* base;
+  const int64_t* ro = rowoff;
+  if constexpr (MAPPED) {
+    int pc = 0;
+#pragma unroll
+    for (int i = 1; i < 4; ++i)
+      if (i < O.n && col >= O.p[i].col_lo) pc = i;
+    base = reinterpret_cast<CT*>(O.p[pc].base) + axis_off(O.p[pc].col, (uint32_t)(col - O.p[pc].col_lo));
+    ro = rowoff + pc * BM;
+  } else {
+    base = reinterpret_cast<CT*>(G.c) + (size_t)(tm * BM) * N + col;
+  }
+  const float* const part = reinterpret_cast<const float*>(lds) + c;
+  constexpr int kPart = STAGES * kStage / 4;          // floats between two waves' partial sums
+#pragma unroll
+  for (int i = 0; i < BM * BN / 256; ++i) {
+    const int r = threadIdx.x / BN + i * (256 / BN);
+    float v = part[r * BN];
+#pragma unroll
+    for (int w = 1; w < W; ++w) v += part[w * kPart + r * BN];
+    if (tm * BM + r < Mg) {
+      if constexpr (MAPPED) base[ro[r]] = from_float<CT>(v);
+      else base[(size_t)r * N] = from_float<CT>(v);
+    }
+  }
+}
+
 template <typename T, bool C_F32, bool MAPPED, bool B_KMAJOR, int NG = 1>
 int launch_tile(GemmParams P8, const typename std::conditional<MAPPED, OutMap, NoMap>::type& O, int bm, int bn, hipStream_t st) {
   if constexpr (NG == 1 && !MAPPED)
@@ -320,6 +509,14 @@ int launch_tile(GemmParams P8, const typename std::conditional<MAPPED, OutMap, N
   VT_TILE(64, 128, 2, 3)
   VT_TILE(64, 64, 2, 4)
 #undef VT_TILE
+#define VT_KSPLIT(BM_, BN_, S_)                                                                                     \
+  if (bm == BM_ && bn == BN_) {                                                                                     \
+    hipLaunchKernelGGL((k_gemm_ksplit<T, C_F32, MAPPED, B_KMAJOR, NG, BM_, BN_, S_>), grid, dim3(256), 0, st, P, O); \
+    return check_launch(MAPPED ? "vt_gemm_store" : "vt_gemm");                                                      \
+  }
+  VT_KSPLIT(32, 32, 2)   // (three or four stages, one workgroup to a unit: 3 to 30 % slower)
+  VT_KSPLIT(32, 64, 3)
+#undef VT_KSPLIT
   return fail(VT_ERR_UNSUPPORTED, "vt_gemm: no such tile");
 }
 
@@ -327,7 +524,8 @@ int launch_tile(GemmParams P8, const typename std::conditional<MAPPED, OutMap, N
 // step of 64 a share for every round and one for every tile of an average unit (a last round that is nearly empty costs less
 // than a full one, and the board's power limit slows full ones), and the weights at 4 TB/s.  The five constants
 // of each tile are fitted over every tile forced at 163 shapes (rows 17 to 16384, 1 to 8 groups, K 512 to 4096, N 768 to
-// 14336): the tile taken is 0.2 % slower than the best one there on average, 10 % at most.  (One time per step and round
+// 14336): the tile taken is 0.2 % slower than the best one there on average, 10 % at most (before the 32-row tiles, whose constants are
+// fitted at 77 of the shapes).  (One time per step and round
 // for each tile, the rule before: 1.9 %, 25 % at most, with its losses at K = 1024, at few rows and at two to five rounds.)
 // Some of them:
 //   rows x columns of C: us on 256x256 / 128x256 / 128x128 / 96x128 / 64x512 / 64x256 / 64x128 / 64x64
@@ -348,7 +546,8 @@ int64_t choose_tile(const GemmParams& P, int* bm, int* bn) {
     int bm, bn, launch, round, step_round, step_tile, weights;
   } kTiles[] = {{256, 256, 493, 3154, 1381, 171, 238}, {128, 256, 286, 7322, 299, 645, 324}, {128, 128, 1005, 5144, 214, 208, 852},
                 {96, 128, 185, 3883, 332, 185, 320},   {64, 512, 7, 5596, 711, 628, 279},    {64, 256, 256, 5514, 282, 420, 259},
-                {64, 128, 2424, 363, 343, 8, 344},     {64, 64, 3102, 293, 204, 42, 289}};
+                {64, 128, 2424, 363, 343, 8, 344},     {64, 64, 3102, 293, 204, 42, 289},
+                {32, 64, 700, 3091, 161, 5, 460},       {32, 32, 3342, 1190, 9, 132, 200}};
   int64_t weights = 0;             // groups that are pieces of one A share their B
   for (int i = 0; i < P.n_groups; ++i) weights += i == 0 || P.g[i].b != P.g[i - 1].b;
   const int64_t weights_ns = weights * P.N * P.K * 2 / 4000, steps = P.K / BK;
@@ -380,8 +579,8 @@ int64_t axis_span(const AxisMap<ND>& a) {
 namespace vt {
 
 // The product of P (operands planned, tiles not yet cut) on smaller tiles, or VT_ERR_UNSUPPORTED when
-// the 256 x 256 kernel is the better one or the only one, or when the estimate, and 0.9 us for
-// the mapped store, is not below below_ns (if that is not 0; 27 x 1024 -> 512: 9.5 us here, 9.1 on the projection store).
+// the 256 x 256 kernel is the better one or the only one, or when the estimate, 0.9 us for the
+// mapped store and 0.07 us per step (few tiles with weights from HBM) are not below below_ns (if that is not 0).
 int gemm_tile_launch(const GemmParams& P, const OutMap* O, int dtype, hipStream_t st, int64_t below_ns) {
   const char* no = "vt_gemm: outside the small-tile kernel";
   if (P.K % BK || P.K < BK || P.K > kMaxSteps * BK || P.N < 8) return fail(VT_ERR_UNSUPPORTED, no);
@@ -389,12 +588,12 @@ int gemm_tile_launch(const GemmParams& P, const OutMap* O, int dtype, hipStream_
     const GemmGroup& g = P.g[i];
     if (!g.k64 || g.b_kmajor != P.g[0].b_kmajor) return fail(VT_ERR_UNSUPPORTED, no);
     // a lane's share of B's address is 32 bits
-    const int64_t span = axis_span(g.b_col) + (g.b_kmajor ? 128 : 8 * g.b_row.stride[2] * 2 + 16);
+    const int64_t span = axis_span(g.b_col) + (g.b_kmajor ? 128 : 16 * g.b_row.stride[2] * 2 + 16);
     if (span >= (1ll << 32)) return fail(VT_ERR_UNSUPPORTED, no);
   }
   int bm = 0, bn = 0;
   const int64_t estimate_ns = choose_tile(P, &bm, &bn);
-  if (below_ns && estimate_ns + 900 >= below_ns) return fail(VT_ERR_UNSUPPORTED, no);
+  if (below_ns && estimate_ns + 900 + P.K / BK * 70 >= below_ns) return fail(VT_ERR_UNSUPPORTED, no);
   if (!bm) return fail(VT_ERR_UNSUPPORTED, no);
   const NoMap none;
   const bool km = P.g[0].b_kmajor != 0;
