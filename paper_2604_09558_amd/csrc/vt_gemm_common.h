@@ -73,6 +73,17 @@ __device__ __forceinline__ int64_t axis_off_table(const AxisMap<ND>& a, uint32_t
 
 __device__ __forceinline__ uint32_t word(const uint4& v, int i) { return i == 0 ? v.x : i == 1 ? v.y : i == 2 ? v.z : v.w; }
 
+// x / k: the product with the reciprocal and what it left over (a division is ten instructions).
+__device__ __forceinline__ float over_k(float x, float k, float inv_k) {
+  const float d = x * inv_k;
+  return fmaf(fmaf(-d, k, x), inv_k, d);
+}
+// The same for a sum of squares: one past fp32's range stays infinite (nothing is left over; inf - inf is not a number),
+// so that its reciprocal root is zero, as with a division.
+__device__ __forceinline__ float squares_over_k(float q, float k, float inv_k) {
+  return q < __builtin_inff() ? over_k(q, k, inv_k) : q;
+}
+
 template <typename T>
 struct Mma;
 template <>

@@ -161,12 +161,7 @@ k_ln_gemm_ring(const RingParams P) {
 #pragma unroll
       for (int s = 0; s < STAGES; ++s) request_stage(s);
     }
-    // x / K: the product with the reciprocal and what it left over
     const float k = (float)K, inv_k = 1.0f / k;
-    auto by_k = [&](float x) {
-      const float d = x * inv_k;
-      return fmaf(fmaf(-d, k, x), inv_k, d);
-    };
     constexpr int Q = NP < 4 ? NP : 4;               // passes that share a root and a division
 #pragma unroll
     for (int p0 = 0; p0 < NP; p0 += Q) {
@@ -182,7 +177,7 @@ k_ln_gemm_ring(const RingParams P) {
           for (int j = 0; j < 8; ++j) x[i][h][j] = to_float(v.v[j]);
           s += ((x[i][h][0] + x[i][h][1]) + (x[i][h][2] + x[i][h][3])) + ((x[i][h][4] + x[i][h][5]) + (x[i][h][6] + x[i][h][7]));
         }
-        const float mean = by_k(row_sum<LP2>(s));
+        const float mean = over_k(row_sum<LP2>(s), k, inv_k);
         float d2 = 0.f;
 #pragma unroll
         for (int h = 0; h < CH; ++h) {
@@ -202,7 +197,7 @@ k_ln_gemm_ring(const RingParams P) {
 #pragma unroll
       for (int i = 1; i < Q; ++i)
         if (p0 + i < NP) qs = (lane & 3) == i ? q[i] : qs;
-      const float rstd = 1.0f / sqrtf(by_k(qs) + P.eps);
+      const float rstd = 1.0f / sqrtf(squares_over_k(qs, k, inv_k) + P.eps);
 #pragma unroll
       for (int i = 0; i < Q; ++i) {
         if (p0 + i >= NP) continue;

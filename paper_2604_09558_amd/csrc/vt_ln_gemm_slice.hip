@@ -168,10 +168,6 @@ k_ln_gemm_slice(const SliceParams P) {
 
   // ---- LayerNorm in place of the rows that landed in tile `slot`: a lane reads back the 16 bytes of its own request
   constexpr float k = (float)K, inv_k = 1.0f / k;
-  auto by_k = [&](float x) {                          // x / K: the product with the reciprocal and what it left over
-    const float d = x * inv_k;
-    return fmaf(fmaf(-d, k, x), inv_k, d);
-  };
   auto norm_tile = [&](int slot) {
     uint4* mine = &tiles[slot * kTileUnits + wave * RW * LPR + lane];
     float x[PASSES][8], q[PASSES];
@@ -182,7 +178,7 @@ k_ln_gemm_slice(const SliceParams P) {
 #pragma unroll
       for (int e = 0; e < 8; ++e) x[i][e] = to_float(v.v[e]);
       const float s = ((x[i][0] + x[i][1]) + (x[i][2] + x[i][3])) + ((x[i][4] + x[i][5]) + (x[i][6] + x[i][7]));
-      const float mean = by_k(row_sum<LPR>(in ? s : 0.f));
+      const float mean = over_k(row_sum<LPR>(in ? s : 0.f), k, inv_k);
       float d2 = 0.f;
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
@@ -197,7 +193,7 @@ k_ln_gemm_slice(const SliceParams P) {
     float qs = q[0];
 #pragma unroll
     for (int i = 1; i < PASSES; ++i) qs = (lane & (PASSES - 1)) == i ? q[i] : qs;
-    const float rstd = 1.0f / sqrtf(by_k(qs) + P.eps);
+    const float rstd = 1.0f / sqrtf(squares_over_k(qs, k, inv_k) + P.eps);
 #pragma unroll
     for (int i = 0; i < PASSES; ++i) {
       const bool in = kChunks == LPR || (a_c ^ key(a_r0 + RPP * i)) < kChunks;

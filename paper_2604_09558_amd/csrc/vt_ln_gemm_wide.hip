@@ -141,12 +141,7 @@ k_ln_gemm_wide(const WideParams P) {
     constexpr int RPP = 64 / LP2, NP = WBM / RPP;
     constexpr int U = 2;           // passes whose rows are in flight together
     const int c0 = lane % LP2, r0 = lane / LP2;
-    // x / K: the product with the reciprocal and what it left over (a division is ten instructions in this chain)
     const float k = (float)K, inv_k = 1.0f / k;
-    auto by_k = [&](float x) {
-      const float d = x * inv_k;
-      return fmaf(fmaf(-d, k, x), inv_k, d);
-    };
     for (int p0 = wave; p0 < NP; p0 += n_waves * U) {
       uint4 raw[U][CH];
 #pragma unroll
@@ -173,7 +168,7 @@ k_ln_gemm_wide(const WideParams P) {
           for (int j = 0; j < 8; ++j) x[h][j] = to_float(v.v[j]);
           s += ((x[h][0] + x[h][1]) + (x[h][2] + x[h][3])) + ((x[h][4] + x[h][5]) + (x[h][6] + x[h][7]));
         }
-        const float mean = by_k(row_sum<LP2>(s));
+        const float mean = over_k(row_sum<LP2>(s), k, inv_k);
         float q = 0.f;
 #pragma unroll
         for (int h = 0; h < CH; ++h) {
@@ -185,7 +180,7 @@ k_ln_gemm_wide(const WideParams P) {
           }
         }
         // as in the generic kernel: a subnormal variance (eps = 0) has a finite root, which v_rsq_f32 does not give
-        const float rstd = 1.0f / sqrtf(by_k(row_sum<LP2>(q)) + P.eps);
+        const float rstd = 1.0f / sqrtf(squares_over_k(row_sum<LP2>(q), k, inv_k) + P.eps);
         const int p = p0 + u * n_waves;
         if (p < NP) {
 #pragma unroll

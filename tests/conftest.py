@@ -17,3 +17,17 @@ def vt():
     """The Python binding over the C-ABI library (built beforehand, in-tree)."""
     import paper_2604_09558_amd as pkg
     return pkg
+
+
+@pytest.fixture(scope="session")
+def kernels():
+    """kernels(call): names of the HIP kernels that call() launches, template arguments included."""
+    import torch
+    from torch.profiler import ProfilerActivity, profile
+
+    def names(call):
+        with profile(activities=[ProfilerActivity.CUDA]) as prof:
+            call()
+            torch.cuda.synchronize()
+        return [e.name for e in prof.events() if str(e.device_type).endswith("CUDA")]
+    return names

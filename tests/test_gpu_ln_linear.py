@@ -238,3 +238,24 @@ def test_subnormal_variance_without_eps(gpu, C):
     got = tio.to_host_f64(p.out).reshape(ref.shape)
     assert np.isfinite(got).all()
     check(got, ref)
+
+
+# the kernel that holds W, the one that holds a slice of it, those that stream it through LDS and through registers, the generic one
+@pytest.mark.parametrize("R,C,N,kernel", [(20, 128, 384, "k_ln_gemm<"), (182, 96, 72, "k_ln_gemm_slice<"), (40, 256, 264, "k_ln_gemm_ring<"),
+                                          (35, 512, 264, "k_ln_gemm_ring<"), (20, 256, 72, "k_ln_gemm_wide<"), (20, 36, 24, "k_gemm_generic<")])
+def test_squares_past_the_range_of_fp32(gpu, kernels, R, C, N, kernel):
+    """Rows of +-1e19 in bf16: finite, but their squares sum to infinity, whose reciprocal root is zero, and with it the row;
+    the rows beside them are not touched (bound as in test_weight_streamed_kernel)."""
+    vt, tio, pipelines, torch = gpu
+    wl = workloads.c4_window_ln_linear(seed=10, B=1, R=R, win=1, C=C, N=N, dtype="bf16")
+    ref = run_workload(wl)["out"].reshape(R * R, N)
+    big = np.zeros(R * R, bool)
+    big[[0, 3, 34, 77, R * R - 1]] = True
+    sign = np.where(np.arange(C) % 2 == 0, 1.0, -1.0).astype(np.float32)
+    wl.sources["X"].reshape(R * R, C)[big] = workloads.encode(sign * np.float32(1e19), "bf16")
+    p = pipelines.Gemm(tio.DeviceWorkload(wl), fused=True)
+    names = kernels(p.run)
+    assert any(kernel in n for n in names), names
+    got = tio.to_host_f64(p.out).reshape(R * R, N)
+    check(got[~big], ref[~big])
+    assert np.all(got[big] == 0.0), got[big]
