@@ -6,6 +6,7 @@
 
 #include <cstring>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "vt_device.h"
@@ -16,7 +17,9 @@ namespace gemm {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef __attribute__((address_space(3))) void* lptr_t;
 
 template <int ND>
 struct AxisMap {
@@ -84,6 +87,31 @@ __device__ __forceinline__ float squares_over_k(float q, float k, float inv_k) {
   return q < __builtin_inff() ? over_k(q, k, inv_k) : q;
 }
 
+// 16 bytes per lane straight from global memory into LDS: lane l's, from base + off, land at LDS byte dst + 16 l.  (M0 holds
+// the destination; it is saved and put back.)  Written as assembly so that the request stays unknown to the compiler, which
+// would otherwise order every later LDS access of the kernel behind it; the waits for these requests are written by hand.
+__device__ __forceinline__ void request(uint32_t off, const char* base, uint32_t dst) {
+  uint32_t m0_saved;
+  asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2\n\ts_nop 0\n\ts_mov_b32 m0, %0"
+               : "=&s"(m0_saved) : "v"(off), "s"(base), "s"(dst) : "memory");
+}
+
+// two results that lie side by side
+template <typename T>
+__device__ __forceinline__ uint32_t pack2(float a, float b) {
+  if constexpr (std::is_same<T, bf16_t>::value) {
+    typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+    typedef float f2 __attribute__((ext_vector_type(2)));
+    const f2 v = {a, b};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, b2));
+  } else {
+    Vec<T, 2> v;
+    v.v[0] = from_float<T>(a), v.v[1] = from_float<T>(b);
+    return __builtin_bit_cast(uint32_t, v);
+  }
+}
+
+// the matrix cores: 32 x 32 blocks, 16 of K; 16 x 16 blocks, 32 of K
 template <typename T>
 struct Mma;
 template <>
@@ -99,6 +127,19 @@ struct Mma<f16_t> {
   static __device__ __forceinline__ f32x16 run(vec a, vec b, f32x16 c) {
     return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
   }
+};
+
+template <typename T>
+struct Mma16;
+template <>
+struct Mma16<bf16_t> {
+  typedef bf16x8 vec;
+  static __device__ __forceinline__ f32x4 run(vec a, vec b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
+};
+template <>
+struct Mma16<f16_t> {
+  typedef f16x8 vec;
+  static __device__ __forceinline__ f32x4 run(vec a, vec b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0); }
 };
 
 // ---------------------------------------------------------------- host: descriptor -> axis maps

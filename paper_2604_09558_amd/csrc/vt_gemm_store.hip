@@ -45,22 +45,6 @@ constexpr int kWaves = 4;
 constexpr int kMaxOutPieces = 4;
 constexpr int kTiledFrom = 128;   // more rows than this always go to the tiled kernels
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-template <typename T>
-struct Mma16;
-template <>
-struct Mma16<bf16_t> {
-  typedef bf16x8 vec;
-  static __device__ __forceinline__ f32x4 run(vec a, vec b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
-};
-template <>
-struct Mma16<f16_t> {
-  typedef f16x8 vec;
-  static __device__ __forceinline__ f32x4 run(vec a, vec b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0); }
-};
 
 // Columns [col_lo, col_hi) of the virtual output live in one physical tensor:
 // element (m, n) at base + 2 * (row(m) + col(n - col_lo)).

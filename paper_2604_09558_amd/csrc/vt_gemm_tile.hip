@@ -34,15 +34,6 @@ namespace {
 constexpr int BK = 64;
 constexpr int kMaxSteps = 256;        // K <= 16384
 
-typedef __attribute__((address_space(3))) void* lptr_t;
-
-// 16 bytes per lane: lane l's, from base + off, land at LDS byte dst + 16 l.  (M0 holds the destination; it is
-// saved and put back.)
-__device__ __forceinline__ void request(uint32_t off, const char* base, uint32_t dst) {
-  uint32_t m0_saved;
-  asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2\n\ts_nop 0\n\ts_mov_b32 m0, %0"
-               : "=&s"(m0_saved) : "v"(off), "s"(base), "s"(dst) : "memory");
-}
 
 // The swizzle: chunk c (16 bytes) of a 128-byte row r lies at position c ^ row_key(r): the 16 rows of a
 // fragment read fall into different banks.  Chunk c of B's k-row k lies at c ^ k_key(k): so do the

@@ -33,24 +33,6 @@ VT_PROF_DECLARE(ln_gemm)
 
 namespace {
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-template <typename T>
-struct Mma16;
-template <>
-struct Mma16<bf16_t> {
-  typedef bf16x8 vec;
-  static __device__ __forceinline__ f32x4 run(vec a, vec b, f32x4 c) {
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
-  }
-};
-template <>
-struct Mma16<f16_t> {
-  typedef f16x8 vec;
-  static __device__ __forceinline__ f32x4 run(vec a, vec b, f32x4 c) {
-    return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
-  }
-};
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
@@ -139,20 +121,13 @@ k_ln_gemm(const LnGemmParams P) {
     const int64_t ro = P.a_row.tdig >= 0 ? axis_off_table(P.a_row, (uint32_t)m) : axis_off(P.a_row, (uint32_t)m);
     ro32 = (uint32_t)(ro * 2);
   };
-  typedef __attribute__((address_space(3))) void* lptr_t;
-  auto load_rows = [&](int j, int slot) {               // block j of the evaluated batch -> tile `slot`
+    auto load_rows = [&](int j, int slot) {               // block j of the evaluated batch -> tile `slot`
 #pragma unroll
     for (int i = 0; i < PASSES; ++i) {
       const uint32_t o = (uint32_t)__shfl((int)ro32, j * 8 + i * RW + lane / LPR, 64);
       const int r = a_r0 + RPP * i;                     // row of the block this lane serves
-      // lane l of the wave lands at (wave base) + 16 l.  Written as assembly so that the request
-      // stays unknown to the compiler, which would otherwise order every later LDS access of the
-      // kernel behind it; the waits for these requests are the explicit ones below.
       const uint32_t dst = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lptr_t)&tiles[slot * kTileUnits + (wave * RW + RPP * i) * LPR]);
-      // (M0 holds the LDS destination; it is saved and put back, so nothing is clobbered)
-      uint32_t m0_saved;
-      asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2\n\ts_nop 0\n\ts_mov_b32 m0, %0"
-                   : "=&s"(m0_saved) : "v"(o + ((a_c ^ (r & 7)) * 16)), "s"(P.a), "s"(dst) : "memory");
+      request(o + ((a_c ^ (r & 7)) * 16), P.a, dst);
     }
   };
   // the first two blocks' rows are requested before anything else: their latency hides behind the W prologue

@@ -30,9 +30,7 @@ using namespace vt::gemm;
 
 namespace {
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) void* lptr_t;
 
 constexpr int kWaves = 8;
 constexpr int kLds = 160 * 1024;
@@ -51,14 +49,6 @@ struct RingParams {
   int32_t tiles_per_group;        // column tiles of one workgroup, dealt to its waves in turn
 };
 
-// 16 bytes per lane: lane l's, from base + off, land at LDS byte dst + 16 l.  (M0 holds the destination; it is
-// saved and put back.)
-__device__ __forceinline__ void request(uint32_t off, const char* base, uint32_t dst) {
-  uint32_t m0_saved;
-  asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2\n\ts_nop 0\n\ts_mov_b32 m0, %0"
-               : "=&s"(m0_saved) : "v"(off), "s"(base), "s"(dst) : "memory");
-}
-
 // at most N vector memory operations outstanding, no LDS operation
 template <int N>
 __device__ __forceinline__ void wait_ops() {
@@ -71,21 +61,6 @@ __device__ __forceinline__ float row_sum(float v) {
   v = group_sum<16>(v);
   if (LP2 >= 32) v += __shfl_xor(v, 16, 64);
   return v;
-}
-
-// two results that lie side by side
-template <typename T>
-__device__ __forceinline__ uint32_t pack2(float a, float b) {
-  if constexpr (std::is_same<T, bf16_t>::value) {
-    typedef __bf16 b2 __attribute__((ext_vector_type(2)));
-    typedef float f2 __attribute__((ext_vector_type(2)));
-    const f2 v = {a, b};
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, b2));
-  } else {
-    Vec<T, 2> v;
-    v.v[0] = from_float<T>(a), v.v[1] = from_float<T>(b);
-    return __builtin_bit_cast(uint32_t, v);
-  }
 }
 
 // MB blocks of 32 rows per workgroup; LP2 lanes hold a row, two chunks of 8 elements each: K <= 16 * LP2; rings of STAGES

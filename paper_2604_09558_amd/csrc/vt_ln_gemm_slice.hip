@@ -28,22 +28,7 @@ using namespace vt::gemm;
 
 namespace {
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) void* lptr_t;
-
-template <typename T>
-struct Mma16;
-template <>
-struct Mma16<bf16_t> {
-  typedef bf16x8 vec;
-  static __device__ __forceinline__ f32x4 run(vec a, vec b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
-};
-template <>
-struct Mma16<f16_t> {
-  typedef f16x8 vec;
-  static __device__ __forceinline__ f32x4 run(vec a, vec b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0); }
-};
 
 constexpr int SBM = 64;           // rows per block
 constexpr int kThreads = 512;
@@ -65,20 +50,6 @@ struct SliceParams {
 template <int LPR>
 __device__ __forceinline__ float row_sum(float v) {
   return group_sum<LPR>(v);
-}
-
-// two results that lie side by side
-template <typename T>
-__device__ __forceinline__ void from_float2(float a, float b, T* o) {
-  if constexpr (std::is_same<T, bf16_t>::value) {
-    typedef __bf16 b2 __attribute__((ext_vector_type(2)));
-    typedef float f2 __attribute__((ext_vector_type(2)));
-    const f2 v = {a, b};
-    const uint32_t w = __builtin_bit_cast(uint32_t, __builtin_convertvector(v, b2));
-    o[0].bits = (uint16_t)w, o[1].bits = (uint16_t)(w >> 16);
-  } else {
-    o[0] = from_float<T>(a), o[1] = from_float<T>(b);
-  }
 }
 
 template <int N>
@@ -132,10 +103,8 @@ k_ln_gemm_slice(const SliceParams P) {
       const uint32_t o = (uint32_t)__shfl((int)ro32, jb * 8 + i * RW + lane / LPR, 64);
       const int c = a_c ^ key(a_r0 + RPP * i);
       const uint32_t dst = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lptr_t)&tiles[slot * kTileUnits + (wave * RW + RPP * i) * LPR]);
-      uint32_t m0_saved;
       if (kChunks == LPR || c < kChunks)              // (some lane of a wave always has a chunk: the requests of a step can be counted)
-        asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2\n\ts_nop 0\n\ts_mov_b32 m0, %0"
-                     : "=&s"(m0_saved) : "v"(o + c * 16), "s"(P.a), "s"(dst) : "memory");
+        request(o + c * 16, P.a, dst);
     }
   };
   eval_rows(0);
@@ -198,10 +167,10 @@ k_ln_gemm_slice(const SliceParams P) {
     for (int i = 0; i < PASSES; ++i) {
       const bool in = kChunks == LPR || (a_c ^ key(a_r0 + RPP * i)) < kChunks;
       const float r = PASSES == 1 ? rstd : i == 0 ? dpp_move<0x00>(rstd) : i == 1 ? dpp_move<0x55>(rstd) : i == 2 ? dpp_move<0xAA>(rstd) : dpp_move<0xFF>(rstd);
-      Vec<T, 8> o;
+      uint32_t o[4];
 #pragma unroll
-      for (int e = 0; e < 8; e += 2) from_float2(x[i][e] * r, x[i][e + 1] * r, &o.v[e]);
-      if (in) mine[i * RPP * LPR] = __builtin_bit_cast(uint4, o);
+      for (int e = 0; e < 4; ++e) o[e] = pack2<T>(x[i][2 * e] * r, x[i][2 * e + 1] * r);
+      if (in) mine[i * RPP * LPR] = make_uint4(o[0], o[1], o[2], o[3]);
     }
   };
 

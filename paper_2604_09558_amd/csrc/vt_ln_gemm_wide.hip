@@ -35,20 +35,6 @@ using namespace vt::gemm;
 
 namespace {
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-template <typename T>
-struct Mma16;
-template <>
-struct Mma16<bf16_t> {
-  typedef bf16x8 vec;
-  static __device__ __forceinline__ f32x4 run(vec a, vec b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
-};
-template <>
-struct Mma16<f16_t> {
-  typedef f16x8 vec;
-  static __device__ __forceinline__ f32x4 run(vec a, vec b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0); }
-};
 
 constexpr int WBN = 64;           // columns per wave
 constexpr int kMaxWaves = 8;
