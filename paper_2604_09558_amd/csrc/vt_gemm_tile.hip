@@ -6,17 +6,24 @@
 // counts is how many units share the work and how few bytes each has to read (BM + BN per K step and tile).
 //
 // One workgroup of 4 waves computes a BM x BN tile of C in 32 x 32 matrix-core blocks
-// (v_mfma_f32_32x32x16).  K steps of 64 run through a ring of STAGES tiles in LDS; operands go from
+// (v_mfma_f32_32x32x16; tiles of 32 rows: 16 x 16 blocks).  K steps of 64 run through a ring of STAGES stages in LDS, each of
+// one step or, for 32 rows, two; operands go from
 // global memory straight into it (global_load_lds_dwordx4: no registers, no store instructions),
-// STAGES steps ahead, one barrier per step; a step's fragments are read into registers during the
-// step before.  The lanes of a request land in the order of their numbers, so the swizzle that keeps
+// STAGES stages ahead, one barrier per stage; a stage's fragments are read into registers during the
+// one before.  The lanes of a request land in the order of their numbers, so the swizzle that keeps
 // the fragment reads free of bank conflicts (4.3 million conflict cycles per launch without it, 4600
 // with it, 333 x 4096 x 4096) is applied to what a lane asks for.  Waits count the requests by hand: a wave issues the
-// same number in every step and nothing else that goes through the vector memory counter.
+// same number in every stage and nothing else that goes through the vector memory counter.
 // Measured (f16/bf16, K = 4096, operands in HBM / in the caches, us): 333 x 4096 30.5 / 21.8 (256 x 256 tiles 88 / 83),
 // 400 x 6144 34.5 / 30.0 (90 / 84), 1024 x 4096 43.3 / 36.5 (89 / 80); the requests of the first without anything
 // else 27.4 / 18.1.  A step of 64 x 128 takes 265 ns there, of which the requests need 231.  Rings twice as
 // deep, and waves divided over K instead of over the tile (half the LDS reads), measured no faster.
+// Few tiles (a short prompt) leave most of the chip idle, and a step of 64 x 64 then takes 0.2 us on a chain of barrier,
+// fragment reads and four dependent products of 60 cycles.  Tiles of 32 rows bring four times the units to work, blocks of 16 halve
+// the chain, two steps per stage the barriers.  Measured (us, 64 x 64 / 32 x 64 / 32 x 32; in the caches): 34 x 2048 -> 1000 10.5 / 8.6 / 7.2,
+// 62 x 1024 -> 2048 7.4 / 6.3 / 5.4, 100 x 4096 -> 1000 16.9 / 13.9 / 11.8, 212 x 4096 -> 2048 (mapped) 19.6 / 16.1 / 18.3, 168 x 1024 ->
+// 4096 7.8 / 7.9 / 9.1.  (In 32 x 32 blocks, one or two waves multiplying: 8.2 for the first; K divided among the waves and their four
+// sums added: 6.3, in bits that depend on how many tiles the launch has.  One step per stage 7.8, four 7.7, longer rings 7.4 to 8.3.)
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -34,23 +41,42 @@ namespace {
 constexpr int BK = 64;
 constexpr int kMaxSteps = 256;        // K <= 16384
 
-
 // The swizzle: chunk c (16 bytes) of a 128-byte row r lies at position c ^ row_key(r): the 16 rows of a
 // fragment read fall into different banks.  Chunk c of B's k-row k lies at c ^ k_key(k): so do the
-// four k-rows x 64 bytes that 32 lanes of a transposing read touch.
+// four k-rows x 64 bytes that 32 lanes of a transposing read touch (blocks of 16: twice four, eight apart, x 32 bytes).
 __device__ __forceinline__ int row_key(int r) { return r >> 1 & 7; }
-template <int BN>
-__device__ __forceinline__ int k_key(int k) { return BN == 32 ? 0 : BN == 64 ? (k >> 1 & 1) << 2 : (k & 3) << 2; }
+template <int BN, int BLK>
+__device__ __forceinline__ int k_key(int k) {
+  if (BLK == 16) return (BN == 32 ? 0 : (k >> 1 & 1) << 2) | (k >> 3 & 1) << 1;
+  return BN == 64 ? (k >> 1 & 1) << 2 : (k & 3) << 2;
+}
 
-template <typename T, bool C_F32, bool MAPPED, bool B_KMAJOR, int NG, int BM, int BN, int WM, int STAGES>
+// Matrix-core blocks of 32 x 32 (16 of K at a time) or, in tiles too small for four waves of those, 16 x 16 (32 of K).  Both add
+// the products of a chain in the same order: the same bits (test_every_tile_gives_the_same_bits).
+template <typename T, int BLK>
+struct BlockMma {
+  typedef typename Mma<T>::vec vec;
+  typedef f32x16 acc;
+  static constexpr int K = 16, kRows = 4;            // a lane holds rows 8 j + 4 lh + i of its column, j < kRows
+  static __device__ __forceinline__ acc run(vec a, vec b, acc c) { return Mma<T>::run(a, b, c); }
+};
+template <typename T>
+struct BlockMma<T, 16> {
+  typedef typename Mma16<T>::vec vec;
+  typedef f32x4 acc;
+  static constexpr int K = 32, kRows = 1;            // rows 4 lq + i
+  static __device__ __forceinline__ acc run(vec a, vec b, acc c) { return Mma16<T>::run(a, b, c); }
+};
+
+template <typename T, bool C_F32, bool MAPPED, bool B_KMAJOR, int NG, int BM, int BN, int WM, int STAGES, int R, int BLK>
 __global__ void __launch_bounds__(256)
 k_gemm_tile(const GemmParamsT<NG> P, const typename std::conditional<MAPPED, OutMap, NoMap>::type O) {
-  typedef Mma<T> M_;
+  typedef BlockMma<T, BLK> M_;
   typedef typename M_::vec opvec;
-  constexpr int kABytes = BM * BK * 2, kStage = (BM + BN) * BK * 2;
-  constexpr int AI = BM / 32, BI = BN / 32;          // requests per wave and step (1 KB each)
+  constexpr int kABytes = BM * BK * 2, kStep = (BM + BN) * BK * 2, kStage = R * kStep;
+  constexpr int AI = BM / 32, BI = BN / 32;          // requests per wave and K step (1 KB each)
   constexpr int WN = 4 / WM;                         // the waves' grid
-  constexpr int MB = BM / (32 * WM), NB = BN / (32 * WN);   // 32 x 32 blocks per wave
+  constexpr int MB = BM / (BLK * WM), NB = BN / (BLK * WN);   // blocks per wave
   static_assert(!MAPPED || 4 * BM * 8 <= STAGES * kStage, "the row offsets of the output fit the ring");
   __shared__ __attribute__((aligned(1024))) char lds[STAGES * kStage];
   // byte offsets of every K step along A's columns and B's rows (a step of 64 stays inside the
@@ -62,7 +88,7 @@ k_gemm_tile(const GemmParamsT<NG> P, const typename std::conditional<MAPPED, Out
   const GemmGroup& G = P.g[gi];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave / WN, wn = wave % WN;
-  const int l32 = lane & 31, lh = lane >> 5;
+  const int lb = lane % BLK, lh = lane / BLK;        // a lane's row (A) or column (B) of a block, and its 8 of the block's K
   const int Mg = G.M, N = P.N, nk = P.K / BK;
 
   // ---- stage 1 through the map.  A: 8 lanes per row of 64 k, 8 rows per request; B: BN / 8 lanes per
@@ -88,11 +114,11 @@ k_gemm_tile(const GemmParamsT<NG> P, const typename std::conditional<MAPPED, Out
     }
   } else {
     // a lane's k-row in request i: (wave * BI + i) * RB + kr, of which the first part is whole periods of the key
-    static_assert(BI * RB % 4 == 0, "the key's period");
+    static_assert(BI * RB % (BLK == 16 ? 16 : 4) == 0, "the key's period");
     const int kr = lane / LB;
 #pragma unroll
     for (int i = 0; i < BI; ++i) {
-      const uint32_t n = (uint32_t)min(tn * BN + ((lane % LB) ^ k_key<BN>(i * RB + kr)) * 8, N - 8);
+      const uint32_t n = (uint32_t)min(tn * BN + ((lane % LB) ^ k_key<BN, BLK>(i * RB + kr)) * 8, N - 8);
       b_off[i] = (uint32_t)(axis_off(G.b_col, n) * 2) + (uint32_t)(kr * b_kstride);
     }
   }
@@ -103,75 +129,93 @@ k_gemm_tile(const GemmParamsT<NG> P, const typename std::conditional<MAPPED, Out
   }
   __syncthreads();
   const uint32_t lds0 = (uint32_t)(uintptr_t)(lptr_t)&lds[0];
-  // request q (the AI of A, then the BI of B) of the step that starts at `as` and `bs`, into stage `slot`
-  auto request_one = [&](int q, const char* as, const char* bs, int slot) {
-    const uint32_t dst = lds0 + slot * kStage;
-    if (q < AI) {
-      request(a_off[q], as, dst + (wave * AI + q) * 1024);
-    } else {
-      const int i = q - AI;
-      request(b_off[i], B_KMAJOR ? bs : bs + (wave * BI + i) * RB * b_kstride, dst + kABytes + (wave * BI + i) * 1024);
-    }
+  // a stage holds R K steps: where their operands start
+  struct Starts {
+    const char *a[R], *b[R];
   };
-  auto step_a = [&](const uint4& o) { return a_base + (uint32_t)__builtin_amdgcn_readfirstlane(o.x); };
-  auto step_b = [&](const uint4& o) {
-    const uint32_t lo = __builtin_amdgcn_readfirstlane(o.y), hi = __builtin_amdgcn_readfirstlane(o.z);
-    return b_base + (int64_t)(((uint64_t)hi << 32) | lo);
+  struct Offsets {
+    uint4 o[R];
+  };
+  auto offsets_of = [&](int stage) {
+    Offsets f;
+#pragma unroll
+    for (int r = 0; r < R; ++r) f.o[r] = steps[min(stage * R + r, nk - 1)];
+    return f;
+  };
+  auto starts_of = [&](const Offsets& f) {
+    Starts s;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const uint32_t lo = __builtin_amdgcn_readfirstlane(f.o[r].y), hi = __builtin_amdgcn_readfirstlane(f.o[r].z);
+      s.a[r] = a_base + (uint32_t)__builtin_amdgcn_readfirstlane(f.o[r].x);
+      s.b[r] = b_base + (int64_t)(((uint64_t)hi << 32) | lo);
+    }
+    return s;
+  };
+  // request q (of each step the AI of A, then the BI of B) of the stage that starts at `s`, into ring position `slot`
+  auto request_one = [&](int q, const Starts& s, int slot) {
+    const int r = q / (AI + BI), i = q % (AI + BI), j = i - AI;
+    const uint32_t dst = lds0 + slot * kStage + r * kStep;
+    if (i < AI) request(a_off[i], s.a[r], dst + (wave * AI + i) * 1024);
+    else request(b_off[j], B_KMAJOR ? s.b[r] : s.b[r] + (wave * BI + j) * RB * b_kstride, dst + kABytes + (wave * BI + j) * 1024);
   };
 
-  // ---- fragment addresses in a stage (bytes), for k16 step 0
+  // ---- fragment addresses in a stage (bytes), for its first MFMA
   uint32_t a_frag[MB], b_frag[NB][2];
 #pragma unroll
   for (int mb = 0; mb < MB; ++mb) {
-    const int r = (wm * MB + mb) * 32 + l32;
-    a_frag[mb] = r * 128 + ((lh ^ row_key(r)) * 16);    // chunk 2 ks + lh: XOR with 32 ks
+    const int r = (wm * MB + mb) * BLK + lb;
+    a_frag[mb] = r * 128 + ((lh ^ row_key(r)) * 16);    // chunk K / 8 ks + lh: XOR with 2 K ks
   }
   const int lq = lane >> 4, ll = lane & 15;
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) {
     if (B_KMAJOR) {
-      const int r = (wn * NB + nb) * 32 + l32;
+      const int r = (wn * NB + nb) * BLK + lb;
       b_frag[nb][0] = kABytes + r * 128 + ((lh ^ row_key(r)) * 16);
       b_frag[nb][1] = 0;
     } else {
-      // lane ll of a 16-lane group points at k-row (ll >> 2) (and 4 further), columns 4 (ll & 3) .. + 3;
+      // lane ll of a 16-lane group points at k-row (ll >> 2) (and 4 further) of the group's 8, columns 4 (ll & 3) .. + 3;
       // it receives the 4 consecutive k of column ll
-      const int chunk = (wn * NB + nb) * 4 + 2 * (lq & 1) + ((ll & 3) >> 1);
+      const int k8 = BLK == 16 ? lq : lq >> 1;
+      const int chunk = (wn * NB + nb) * (BLK / 8) + (BLK == 16 ? 0 : 2 * (lq & 1)) + ((ll & 3) >> 1);
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
-        const int k = 8 * (lq >> 1) + (ll >> 2) + 4 * h;
-        b_frag[nb][h] = kABytes + k * (BN * 2) + ((chunk ^ k_key<BN>(k)) * 16) + (ll & 1) * 8;
+        const int k = 8 * k8 + (ll >> 2) + 4 * h;
+        b_frag[nb][h] = kABytes + k * (BN * 2) + ((chunk ^ k_key<BN, BLK>(k)) * 16) + (ll & 1) * 8;
       }
     }
   }
 
-  f32x16 acc[MB][NB];
+  typename M_::acc acc[MB][NB];
 #pragma unroll
   for (int i = 0; i < MB; ++i)
 #pragma unroll
     for (int j = 0; j < NB; ++j)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+      for (int e = 0; e < 4 * M_::kRows; ++e) acc[i][j][e] = 0.f;
 
-  // all fragments of one K step: read from LDS during the step before, so that neither the barrier
-  // nor the latency of the reads stands between two steps' products
+  // all fragments of one stage: read from LDS during the stage before, so that neither the barrier
+  // nor the latency of the reads stands between two stages' products
+  constexpr int KS = BK / M_::K;
   struct Frags {
-    opvec a[BK / 16][MB], b[BK / 16][NB];
+    opvec a[R * KS][MB], b[R * KS][NB];
   };
-  constexpr int kReads = BK / 16 * (MB + NB), kMma = BK / 16 * MB * NB, kRequests = AI + BI;
-  auto read_one = [&](const char* st, Frags& f, int i) {
-    const int ks = i / (MB + NB), x = i % (MB + NB), nb = x - MB;
+  constexpr int kReads = R * KS * (MB + NB), kMma = R * KS * MB * NB, kRequests = R * (AI + BI);
+  auto read_one = [&](const char* stage, Frags& f, int i) {
+    const int km = i / (MB + NB), ks = km % KS, x = i % (MB + NB), nb = x - MB;
+    const char* const st = stage + km / KS * kStep;
     if (x < MB) {
-      f.a[ks][x] = __builtin_bit_cast(opvec, *reinterpret_cast<const uint4*>(st + (a_frag[x] ^ (ks * 32))));
+      f.a[km][x] = __builtin_bit_cast(opvec, *reinterpret_cast<const uint4*>(st + (a_frag[x] ^ (ks * 2 * M_::K))));
     } else if (B_KMAJOR) {
-      f.b[ks][nb] = __builtin_bit_cast(opvec, *reinterpret_cast<const uint4*>(st + (b_frag[nb][0] ^ (ks * 32))));
+      f.b[km][nb] = __builtin_bit_cast(opvec, *reinterpret_cast<const uint4*>(st + (b_frag[nb][0] ^ (ks * 2 * M_::K))));
     } else {
       typedef short s16x4 __attribute__((ext_vector_type(4)));
       typedef __attribute__((address_space(3))) s16x4* lds_s16x4;
       struct { s16x4 lo, hi; } v;
-      v.lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(st + b_frag[nb][0] + ks * 16 * (BN * 2)));
-      v.hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(st + b_frag[nb][1] + ks * 16 * (BN * 2)));
-      f.b[ks][nb] = __builtin_bit_cast(opvec, v);
+      v.lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(st + b_frag[nb][0] + ks * M_::K * (BN * 2)));
+      v.hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(st + b_frag[nb][1] + ks * M_::K * (BN * 2)));
+      f.b[km][nb] = __builtin_bit_cast(opvec, v);
     }
   };
   auto multiply_one = [&](const Frags& f, int i) {
@@ -184,10 +228,9 @@ k_gemm_tile(const GemmParamsT<NG> P, const typename std::conditional<MAPPED, Out
   __builtin_amdgcn_s_waitcnt(0x0F70);                 // vmcnt(0)
 #pragma unroll
   for (int s = 0; s < STAGES; ++s) {
-    const uint4 o = steps[min(s, nk - 1)];
-    const char *const as = step_a(o), *const bs = step_b(o);
+    const Starts first = starts_of(offsets_of(s));
 #pragma unroll
-    for (int q = 0; q < kRequests; ++q) request_one(q, as, bs, s);
+    for (int q = 0; q < kRequests; ++q) request_one(q, first, s);
   }
   constexpr int kFirst = (STAGES - 1) * kRequests;    // requests behind those of the first step,
   constexpr int kBehind = (STAGES - 2) * kRequests;   // and in the loop behind those of the next one
@@ -197,17 +240,17 @@ k_gemm_tile(const GemmParamsT<NG> P, const typename std::conditional<MAPPED, Out
   asm volatile("s_barrier" ::: "memory");
 #pragma unroll
   for (int i = 0; i < kReads; ++i) read_one(lds, f0, i);
-  uint4 ahead = steps[min(STAGES, nk - 1)];
+  Offsets ahead = offsets_of(STAGES);
   int slot = 0;                                       // the stage that step `it` came from: in registers, free to be filled
   auto k_step = [&](int it, const Frags& cur, Frags& nxt) {
     // this wave has its fragments of step `it`, and its requests of step it + 1 have landed; behind
     // the barrier that holds for every wave
     __builtin_amdgcn_s_waitcnt((kBehind & 15) | ((kBehind >> 4) << 14) | 0x0070);   // vmcnt(kBehind) lgkmcnt(0)
     asm volatile("s_barrier" ::: "memory");
-    const char *const as = step_a(ahead), *const bs = step_b(ahead);
+    const Starts next = starts_of(ahead);
     const int free_slot = slot;
     slot = slot == STAGES - 1 ? 0 : slot + 1;
-    ahead = steps[min(it + STAGES + 1, nk - 1)];
+    ahead = offsets_of(it + STAGES + 1);
     const char* const st = lds + slot * kStage;
     // A product, then its share of the requests and of the next step's reads.  A request holds its wave up
     // while the unit's address path works off those before it (16 cycles each, of all four waves), and
@@ -221,7 +264,7 @@ k_gemm_tile(const GemmParamsT<NG> P, const typename std::conditional<MAPPED, Out
       multiply_one(cur, i);
       if (i < kReqSpan) {
 #pragma unroll
-        for (int q = i * kRequests / kReqSpan; q < (i + 1) * kRequests / kReqSpan; ++q) request_one(q, as, bs, free_slot);
+        for (int q = i * kRequests / kReqSpan; q < (i + 1) * kRequests / kReqSpan; ++q) request_one(q, next, free_slot);
       }
       if (i < kReadSpan) {
 #pragma unroll
@@ -230,18 +273,27 @@ k_gemm_tile(const GemmParamsT<NG> P, const typename std::conditional<MAPPED, Out
       __builtin_amdgcn_sched_barrier(0);
     }
   };
+  // full stages, then the last one, which may hold fewer steps than R = 2: the first of them
+  const int n_full = nk / R;
   int it = 0;
-  for (; it + 1 < nk; it += 2) {
+  for (; it + 1 < n_full; it += 2) {
     k_step(it, f0, f1);
     k_step(it + 1, f1, f0);
   }
-  if (it < nk) {
+  if (nk % R) {
+    if (it < n_full) {
+      k_step(it, f0, f1);
+      f0 = f1;
+    }
+#pragma unroll
+    for (int i = 0; i < kMma / R; ++i) multiply_one(f0, i);
+  } else if (it < n_full) {
 #pragma unroll
     for (int i = 0; i < kMma; ++i) multiply_one(f0, i);
   }
   __builtin_amdgcn_s_waitcnt(0x0F70);                 // requests still target this workgroup's LDS
 
-  // ---- stage 3 (as in vt_gemm.hip): a lane holds column l32 of a block and rows 8 j + 4 lh + i
+  // ---- stage 3 (as in vt_gemm.hip): a lane holds column lb of a block and rows 8 j + 4 lh + i
   if constexpr (MAPPED) {
     __syncthreads();
     int64_t* rowoff = reinterpret_cast<int64_t*>(lds);               // [pieces][BM]
@@ -250,7 +302,7 @@ k_gemm_tile(const GemmParamsT<NG> P, const typename std::conditional<MAPPED, Out
     __syncthreads();
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
-      const int col = tn * BN + (wn * NB + nb) * 32 + l32;
+      const int col = tn * BN + (wn * NB + nb) * BLK + lb;
       if (col >= N) continue;
       int pc = 0;
 #pragma unroll
@@ -260,9 +312,9 @@ k_gemm_tile(const GemmParamsT<NG> P, const typename std::conditional<MAPPED, Out
       const int64_t* ro = rowoff + pc * BM;
 #pragma unroll
       for (int mb = 0; mb < MB; ++mb) {
-        const int r0 = (wm * MB + mb) * 32 + lh * 4;
+        const int r0 = (wm * MB + mb) * BLK + lh * 4;
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+        for (int j = 0; j < M_::kRows; ++j)
 #pragma unroll
           for (int i = 0; i < 4; ++i)
             if (tm * BM + r0 + 8 * j + i < Mg) base[ro[r0 + 8 * j + i]] = from_float<T>(acc[mb][nb][4 * j + i]);
@@ -276,206 +328,17 @@ k_gemm_tile(const GemmParamsT<NG> P, const typename std::conditional<MAPPED, Out
   for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
-      const int col = tn * BN + (wn * NB + nb) * 32 + l32;
-      const int row0 = tm * BM + (wm * MB + mb) * 32 + lh * 4;
+      const int col = tn * BN + (wn * NB + nb) * BLK + lb;
+      const int row0 = tm * BM + (wm * MB + mb) * BLK + lh * 4;
       CT* cp = cbase + (size_t)row0 * N + col;
       if (col < N) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+        for (int j = 0; j < M_::kRows; ++j)
 #pragma unroll
           for (int i = 0; i < 4; ++i)
             if (row0 + 8 * j + i < Mg) cp[(size_t)(8 * j + i) * N] = from_float<CT>(acc[mb][nb][4 * j + i]);
       }
     }
-}
-
-// For few tiles.  A short prompt's 64-row tiles leave most of the chip idle (32 x 2048 -> 2048: 32 tiles), and a step of
-// theirs takes 0.2 us on a chain of barrier, fragment reads and four dependent products, at half of what a unit draws.  Here the
-// tiles are 32 x 32 or 32 x 64 and divided over K instead of over the tile: each of the 4 waves computes the whole
-// tile over every fourth K step, out of a ring of its own in LDS that nobody else reads (two stages: two workgroups of 32 x 32
-// share a unit; three for 32 x 64), so there are no barriers until the partial sums meet in LDS at the end (added in
-// the order of the waves; the other kernels add the K steps in one chain).  Bound by the unit's draw of its operands.
-// Measured (us, 64 x 64 tiles -> 32 x 32 / 32 x 64): 34 x 2048 -> 1000 10.4 -> 6.3 / 8.3, 62 x 1024 -> 2048 7.3 -> 5.3 / 6.8, 100 x
-// 4096 -> 1000 17.0 -> 11.8 / 15.3, 212 x 4096 -> 2048 (mapped) 19.4 -> 19.1 / 16.1; past one round of 256 tiles of 32 x 64 the
-// larger tiles win (168 x 1024 -> 4096 7.6 -> 11.8 / 11.8).  64 x 64 tiles divided like this: no faster than over the tile.
-template <typename T, bool C_F32, bool MAPPED, bool B_KMAJOR, int NG, int BM, int BN, int STAGES>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BM + BN == 64 ? 2 : 1, 2)))
-k_gemm_ksplit(const GemmParamsT<NG> P, const typename std::conditional<MAPPED, OutMap, NoMap>::type O) {
-  typedef Mma<T> M_;
-  typedef typename M_::vec opvec;
-  constexpr int W = 4, MB = BM / 32, NB = BN / 32;
-  constexpr int kABytes = BM * BK * 2, kStage = (BM + BN) * BK * 2;
-  constexpr int AI = BM / 8, BI = BN / 8, kRequests = AI + BI;      // of 1 KB each, per step
-  static_assert(BM * BN * 4 <= STAGES * kStage, "a wave's partial sums fit its ring");
-  static_assert((STAGES - 1) * kRequests < 64, "vmcnt has 6 bits");
-  __shared__ __attribute__((aligned(1024))) char lds[W * STAGES * kStage];
-  __shared__ uint4 steps[kMaxSteps];
-  __shared__ int64_t rowoff[MAPPED ? 4 * BM : 1];
-
-  int gi, tm, tn;
-  if (!pick_tile(P, blockIdx.x, &gi, &tm, &tn)) return;
-  const GemmGroup& G = P.g[gi];
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int l32 = lane & 31, lh = lane >> 5;
-  const int Mg = G.M, N = P.N, nk = P.K / BK;
-
-  // ---- stage 1 through the map, as in the kernel above; every wave asks for whole steps
-  const char* const a_base = G.a;
-  const char* const b_base = G.b;
-  const int r8 = lane >> 3, p8 = lane & 7;
-  uint32_t a_off[AI], b_off[B_KMAJOR ? BI : 1];
-#pragma unroll
-  for (int i = 0; i < AI; ++i) {
-    const int r = i * 8 + r8;
-    const uint32_t m = (uint32_t)min(tm * BM + r, Mg - 1);
-    const int64_t ro = G.a_row.tdig >= 0 ? axis_off_table(G.a_row, m) : axis_off(G.a_row, m);
-    a_off[i] = (uint32_t)(ro * 2) + (uint32_t)((p8 ^ row_key(r)) * 16);
-  }
-  constexpr int LB = BN / 8, RB = 64 / LB;           // lanes per k-row of B, k-rows per request: whole periods of the key
-  const int64_t b_kstride = G.b_row.stride[2] * 2;
-  if constexpr (B_KMAJOR) {
-#pragma unroll
-    for (int i = 0; i < BI; ++i) {
-      const int r = i * 8 + r8;
-      b_off[i] = (uint32_t)(axis_off(G.b_col, (uint32_t)min(tn * BN + r, N - 1)) * 2) + (uint32_t)((p8 ^ row_key(r)) * 16);
-    }
-  } else {
-    const int kr = lane / LB;
-    const uint32_t n = (uint32_t)min(tn * BN + ((lane % LB) ^ k_key<BN>(kr)) * 8, N - 8);
-    b_off[0] = (uint32_t)(axis_off(G.b_col, n) * 2) + (uint32_t)(kr * b_kstride);
-  }
-  if ((int)threadIdx.x < nk) {
-    const uint32_t k = threadIdx.x * BK;
-    const uint64_t bo = (uint64_t)(axis_off(G.b_row, k) * 2);
-    steps[threadIdx.x] = make_uint4((uint32_t)(axis_off(G.a_col, k) * 2), (uint32_t)bo, (uint32_t)(bo >> 32), 0);
-  }
-  if constexpr (MAPPED)
-    for (int pc = 0; pc < O.n; ++pc)
-      for (int r = threadIdx.x; r < BM; r += 256) rowoff[pc * BM + r] = axis_off(O.p[pc].row, (uint32_t)min(tm * BM + r, Mg - 1));
-  __syncthreads();
-
-  char* const ring = lds + wave * (STAGES * kStage);
-  const uint32_t ring_dst = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lptr_t)ring);
-  const int n_my = (nk - wave + W - 1) / W;          // steps wave, wave + W, ...
-  auto request_step = [&](int i, int slot) {         // this wave's step i (past its last one: that again, not read)
-    const uint4 o = steps[wave + min(i, n_my - 1) * W];
-    const char* const as = a_base + (uint32_t)__builtin_amdgcn_readfirstlane(o.x);
-    const uint32_t lo = __builtin_amdgcn_readfirstlane(o.y), hi = __builtin_amdgcn_readfirstlane(o.z);
-    const char* const bs = b_base + (int64_t)(((uint64_t)hi << 32) | lo);
-    const uint32_t dst = ring_dst + slot * kStage;
-#pragma unroll
-    for (int q = 0; q < AI; ++q) request(a_off[q], as, dst + q * 1024);
-#pragma unroll
-    for (int q = 0; q < BI; ++q) request(b_off[B_KMAJOR ? q : 0], B_KMAJOR ? bs : bs + q * RB * b_kstride, dst + kABytes + q * 1024);
-  };
-
-  // ---- fragment addresses in a stage (bytes), for k16 step 0, as in the kernel above
-  uint32_t a_frag[MB], b_frag[NB][2];
-#pragma unroll
-  for (int mb = 0; mb < MB; ++mb) a_frag[mb] = (mb * 32 + l32) * 128 + ((lh ^ row_key(mb * 32 + l32)) * 16);
-  const int lq = lane >> 4, ll = lane & 15;
-#pragma unroll
-  for (int nb = 0; nb < NB; ++nb) {
-    if (B_KMAJOR) {
-      b_frag[nb][0] = kABytes + (nb * 32 + l32) * 128 + ((lh ^ row_key(nb * 32 + l32)) * 16);
-      b_frag[nb][1] = 0;
-    } else {
-      const int chunk = nb * 4 + 2 * (lq & 1) + ((ll & 3) >> 1);
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int k = 8 * (lq >> 1) + (ll >> 2) + 4 * h;
-        b_frag[nb][h] = kABytes + k * (BN * 2) + ((chunk ^ k_key<BN>(k)) * 16) + (ll & 1) * 8;
-      }
-    }
-  }
-
-  f32x16 acc[MB][NB];
-#pragma unroll
-  for (int i = 0; i < MB; ++i)
-#pragma unroll
-    for (int j = 0; j < NB; ++j)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-  if (n_my > 0) {
-    __builtin_amdgcn_s_waitcnt(0x0F70);               // vmcnt(0): index tables out of the counter's way
-#pragma unroll
-    for (int s = 0; s < STAGES; ++s) request_step(s, s);
-    int slot = 0;
-    for (int i = 0; i < n_my; ++i) {
-      asm volatile("s_waitcnt vmcnt(%0)" ::"n"((STAGES - 1) * kRequests) : "memory");
-      const char* const st = ring + slot * kStage;
-      opvec a[BK / 16][MB], b[BK / 16][NB];
-#pragma unroll
-      for (int ks = 0; ks < BK / 16; ++ks) {
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb) a[ks][mb] = __builtin_bit_cast(opvec, *reinterpret_cast<const uint4*>(st + (a_frag[mb] ^ (ks * 32))));
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb) {
-          if (B_KMAJOR) {
-            b[ks][nb] = __builtin_bit_cast(opvec, *reinterpret_cast<const uint4*>(st + (b_frag[nb][0] ^ (ks * 32))));
-          } else {
-            typedef short s16x4 __attribute__((ext_vector_type(4)));
-            typedef __attribute__((address_space(3))) s16x4* lds_s16x4;
-            struct { s16x4 lo, hi; } v;
-            v.lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(st + b_frag[nb][0] + ks * 16 * (BN * 2)));
-            v.hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(st + b_frag[nb][1] + ks * 16 * (BN * 2)));
-            b[ks][nb] = __builtin_bit_cast(opvec, v);
-          }
-        }
-      }
-      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");            // the stage is in registers
-      request_step(i + STAGES, slot);
-      slot = slot == STAGES - 1 ? 0 : slot + 1;
-#pragma unroll
-      for (int ks = 0; ks < BK / 16; ++ks)
-#pragma unroll
-        for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-          for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = M_::run(a[ks][mb], b[ks][nb], acc[mb][nb]);
-    }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                // requests still target this wave's ring
-  }
-
-  // ---- the partial sums, each in its wave's ring: [BM][BN]; a lane holds column l32 of a block and rows 8 j + 4 lh + i
-  float* const mine = reinterpret_cast<float*>(ring);
-#pragma unroll
-  for (int mb = 0; mb < MB; ++mb)
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int i = 0; i < 4; ++i) mine[(mb * 32 + 8 * j + 4 * lh + i) * BN + nb * 32 + l32] = acc[mb][nb][4 * j + i];
-  __syncthreads();
-  // ---- stage 3: a thread has one column
-  const int c = threadIdx.x % BN, col = tn * BN + c;
-  if (col >= N) return;
-  typedef typename std::conditional<C_F32, float, T>::type CT;
-  CT* base;
-  const int64_t* ro = rowoff;
-  if constexpr (MAPPED) {
-    int pc = 0;
-#pragma unroll
-    for (int i = 1; i < 4; ++i)
-      if (i < O.n && col >= O.p[i].col_lo) pc = i;
-    base = reinterpret_cast<CT*>(O.p[pc].base) + axis_off(O.p[pc].col, (uint32_t)(col - O.p[pc].col_lo));
-    ro = rowoff + pc * BM;
-  } else {
-    base = reinterpret_cast<CT*>(G.c) + (size_t)(tm * BM) * N + col;
-  }
-  const float* const part = reinterpret_cast<const float*>(lds) + c;
-  constexpr int kPart = STAGES * kStage / 4;          // floats between two waves' partial sums
-#pragma unroll
-  for (int i = 0; i < BM * BN / 256; ++i) {
-    const int r = threadIdx.x / BN + i * (256 / BN);
-    float v = part[r * BN];
-#pragma unroll
-    for (int w = 1; w < W; ++w) v += part[w * kPart + r * BN];
-    if (tm * BM + r < Mg) {
-      if constexpr (MAPPED) base[ro[r]] = from_float<CT>(v);
-      else base[(size_t)r * N] = from_float<CT>(v);
-    }
-  }
 }
 
 template <typename T, bool C_F32, bool MAPPED, bool B_KMAJOR, int NG = 1>
@@ -487,27 +350,21 @@ int launch_tile(GemmParams P8, const typename std::conditional<MAPPED, OutMap, N
   static_cast<GemmSizes&>(P) = P8;
   for (int i = 0; i < NG; ++i) P.g[i] = P8.g[i];
   const dim3 grid(P.chunk * 8);
-#define VT_TILE(BM_, BN_, WM_, S_)                                                                                  \
+#define VT_TILE(BM_, BN_, WM_, S_, R_, BLK_)                                                                        \
   if (bm == BM_ && bn == BN_) {                                                                                     \
-    hipLaunchKernelGGL((k_gemm_tile<T, C_F32, MAPPED, B_KMAJOR, NG, BM_, BN_, WM_, S_>), grid, dim3(256), 0, st, P, O); \
+    hipLaunchKernelGGL((k_gemm_tile<T, C_F32, MAPPED, B_KMAJOR, NG, BM_, BN_, WM_, S_, R_, BLK_>), grid, dim3(256), 0, st, P, O); \
     return check_launch(MAPPED ? "vt_gemm_store" : "vt_gemm");                                                      \
   }
-  VT_TILE(128, 256, 2, 3)
-  VT_TILE(128, 128, 2, 4)
-  VT_TILE(96, 128, 1, 5)
-  VT_TILE(64, 512, 1, 2)
-  VT_TILE(64, 256, 1, 3)
-  VT_TILE(64, 128, 2, 3)
-  VT_TILE(64, 64, 2, 4)
+  VT_TILE(128, 256, 2, 3, 1, 32)
+  VT_TILE(128, 128, 2, 4, 1, 32)
+  VT_TILE(96, 128, 1, 5, 1, 32)
+  VT_TILE(64, 512, 1, 2, 1, 32)
+  VT_TILE(64, 256, 1, 3, 1, 32)
+  VT_TILE(64, 128, 2, 3, 1, 32)
+  VT_TILE(64, 64, 2, 4, 1, 32)
+  VT_TILE(32, 64, 2, 3, 2, 16)
+  VT_TILE(32, 32, 2, 3, 2, 16)
 #undef VT_TILE
-#define VT_KSPLIT(BM_, BN_, S_)                                                                                     \
-  if (bm == BM_ && bn == BN_) {                                                                                     \
-    hipLaunchKernelGGL((k_gemm_ksplit<T, C_F32, MAPPED, B_KMAJOR, NG, BM_, BN_, S_>), grid, dim3(256), 0, st, P, O); \
-    return check_launch(MAPPED ? "vt_gemm_store" : "vt_gemm");                                                      \
-  }
-  VT_KSPLIT(32, 32, 2)   // (three or four stages, one workgroup to a unit: 3 to 30 % slower)
-  VT_KSPLIT(32, 64, 3)
-#undef VT_KSPLIT
   return fail(VT_ERR_UNSUPPORTED, "vt_gemm: no such tile");
 }
 
@@ -516,7 +373,7 @@ int launch_tile(GemmParams P8, const typename std::conditional<MAPPED, OutMap, N
 // than a full one, and the board's power limit slows full ones), and the weights at 4 TB/s.  The five constants
 // of each tile are fitted over every tile forced at 163 shapes (rows 17 to 16384, 1 to 8 groups, K 512 to 4096, N 768 to
 // 14336): the tile taken is 0.2 % slower than the best one there on average, 10 % at most (before the 32-row tiles, whose constants are
-// fitted at 77 of the shapes).  (One time per step and round
+// fitted at 1505 others).  (One time per step and round
 // for each tile, the rule before: 1.9 %, 25 % at most, with its losses at K = 1024, at few rows and at two to five rounds.)
 // Some of them:
 //   rows x columns of C: us on 256x256 / 128x256 / 128x128 / 96x128 / 64x512 / 64x256 / 64x128 / 64x64
@@ -538,7 +395,7 @@ int64_t choose_tile(const GemmParams& P, int* bm, int* bn) {
   } kTiles[] = {{256, 256, 493, 3154, 1381, 171, 238}, {128, 256, 286, 7322, 299, 645, 324}, {128, 128, 1005, 5144, 214, 208, 852},
                 {96, 128, 185, 3883, 332, 185, 320},   {64, 512, 7, 5596, 711, 628, 279},    {64, 256, 256, 5514, 282, 420, 259},
                 {64, 128, 2424, 363, 343, 8, 344},     {64, 64, 3102, 293, 204, 42, 289},
-                {32, 64, 700, 3091, 161, 5, 460},       {32, 32, 3342, 1190, 9, 132, 200}};
+                {32, 64, 2955, 953, 168, 0, 355},       {32, 32, 2299, 266, 125, 0, 321}};
   int64_t weights = 0;             // groups that are pieces of one A share their B
   for (int i = 0; i < P.n_groups; ++i) weights += i == 0 || P.g[i].b != P.g[i - 1].b;
   const int64_t weights_ns = weights * P.N * P.K * 2 / 4000, steps = P.K / BK;

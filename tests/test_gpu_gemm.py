@@ -1,5 +1,7 @@
 """GPU parity of the GEMM consumer (bf16/f16 operands, fp32 accumulation) against the CPU
 oracle: |gpu - oracle| <= 1e-2 + 1e-2 |oracle| (the benchmark's stated bar)."""
+import re
+
 import numpy as np
 import pytest
 
@@ -220,8 +222,8 @@ def test_operand_stacked_by_a_concat_along_the_rows(gpu):
     assert torch.equal(p.out, m.out)
 
 
-# every tile shape of the small-tile kernel (64x64, 64x128, 96x128, 128x128, 256x128, then back to
-# 256x256), K of one step, of fewer steps than its ring holds, of an odd number; ragged rows and columns
+# from one row and eight columns to several rounds of tiles, K of one step, of fewer steps than a ring holds, of an odd
+# number; ragged rows and columns
 @pytest.mark.parametrize("M,K,N,dtype", [(1, 64, 8, "bf16"), (65, 192, 520, "f16"), (333, 320, 4088, "bf16"), (391, 448, 5992, "f16"),
                                          (1000, 128, 4040, "bf16"), (2000, 704, 4000, "f16"), (2100, 64, 6088, "bf16")])
 def test_tile_shapes(gpu, M, K, N, dtype):
@@ -249,7 +251,7 @@ def test_tile_shapes(gpu, M, K, N, dtype):
     assert torch.equal(f32[:M].to(p.out.dtype), p.out) and bool((f32[M] == 7.0).all())
 
 
-# the tiles 256 and 512 columns wide: one K step, an odd number, fewer than the ring holds and more; ragged rows and columns
+# few rows of very wide products: one K step, an odd number, fewer than the ring holds and more; ragged rows and columns
 @pytest.mark.parametrize("M,K,N", [(50, 192, 40008), (3, 64, 40008), (33, 64, 70008), (64, 320, 70008)])
 def test_wide_tiles(gpu, M, K, N):
     """W as [K,N] and as [N,K] through a Permute, and stored through a map over two tensors: fp32 outputs against the
@@ -285,7 +287,7 @@ def test_wide_tiles(gpu, M, K, N):
         assert (stored.float() - f32[:M]).abs().max() <= 2.0 ** -8 * f32[:M].abs().max() + 1e-4
 
 
-# the 32-row tiles, divided over K: no step for some waves (K = 64, 192), one, an odd number for some, many; ragged rows and columns
+# few tiles (32-row ones, two K steps to a stage of their ring): one K step, odd and even numbers, many; ragged rows and columns
 @pytest.mark.parametrize("M,K,N", [(33, 64, 200), (5, 192, 72), (65, 320, 1000), (100, 576, 2056), (31, 1024, 264), (190, 1024, 2056), (225, 2048, 1544),
                                    (150, 448, 3080)])
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
@@ -323,6 +325,72 @@ def test_tiles_divided_over_k(gpu, M, K, N, dtype):
     stored = torch.cat([dw.tensors["P"].view(td), dw.tensors["Q"].view(td)], dim=1)
     eps = 2.0 ** -8 if dtype == "bf16" else 2.0 ** -11
     assert bool(((stored.float() - f32[:M]).abs() <= eps * f32[:M].abs() + 1e-4).all())
+
+
+def tiles_run(names):
+    """Tiles of the GEMM kernels among the names: (rows, columns), (256, 256) for the large kernel.  (Names with _Float16 in
+    them come mangled.)"""
+    found = []
+    for n in names:
+        m = re.search(r"k_gemm_tile<[^,]*, \w+, \w+, \w+, \d+, (\d+), (\d+),", n) or re.search(r"k_gemm_tileIDF16_Lb.ELb.ELb.ELi\d+ELi(\d+)ELi(\d+)E", n)
+        if m:
+            found.append((int(m.group(1)), int(m.group(2))))
+        elif "k_gemm<" in n or "k_gemmI" in n:
+            found.append((256, 256))
+    return found
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f16"])
+def test_every_tile_gives_the_same_bits(gpu, kernels, dtype):
+    """A row's fp32 sums do not depend on how many rows are with it, on the weight's layout, on how A is cut into pieces or on the other
+    groups of the launch, nor on whether A is read through a map that only the large tiles take: all tiles add the
+    K steps in one chain in the same order.  Values over eleven binades, so that another order shows."""
+    vt, tio, pipelines, torch = gpu
+    rng = np.random.default_rng(47)
+
+    def values(shape):
+        return workloads.encode((rng.normal(size=shape) * 2.0 ** rng.integers(-6, 6, shape)).astype(np.float32), dtype)
+
+    def product(descs_a, descs_b, rows, N):
+        outs = [torch.empty((m, N), device="cuda:0") for m in rows]
+        names = kernels(lambda: vt.vt_gemm(descs_a, descs_b, outs, "f32"))
+        return outs, tiles_run(names)
+
+    seen = set()
+    for K, N in ((2048, 1000), (448, 4096), (64, 8200)):               # rows among more rows
+        x, w = values((2600, K)), values((K, N))
+        chain = [("Bt", "permute", ("Wt",), {"perm": (1, 0)})] + [("A%d" % m, "slice", ("X",), {"dim": 0, "start": 0, "stop": m})
+                                                                   for m in (20, 70, 160, 330, 700, 1400, 2600)]
+        dw = tio.DeviceWorkload(workloads.Workload("rows", dtype, {"X": x, "W": w, "Wt": np.ascontiguousarray(w.T)}, chain, {}))
+        first = None
+        for m in (20, 70, 160, 330, 700, 1400, 2600):
+            for b in ("W", "Bt"):
+                (out,), tiles = product([dw.build("A%d" % m)], [dw.build(b)], [m], N)
+                seen.update(tiles)
+                first = out if first is None else first
+                assert torch.equal(out[:20], first), (K, N, m, b, tiles)
+    assert len(seen) >= 6, seen
+
+    src = {"P": values((33, 512)), "Q": values((33, 512)), "R": values((34, 512)), "W": values((512, 768))}
+    src["D"] = np.concatenate([src["P"], src["Q"], src["R"]])
+    dw = tio.DeviceWorkload(workloads.Workload("stack", dtype, src, [("A", "concat", ("P", "Q", "R"), {"dim": 0})], {}))
+    assert torch.equal(product([dw.build("A")], [dw.build("W")], [100], 768)[0][0], product([dw.build("D")], [dw.build("W")], [100], 768)[0][0])
+
+    src = {"X%d" % e: values((25, 1024)) for e in range(8)}
+    src.update({"W%d" % e: values((1024, 1408)) for e in range(8)})
+    dw = tio.DeviceWorkload(workloads.Workload("experts", dtype, src, [], {}))
+    together = product([dw.build("X%d" % e) for e in range(8)], [dw.build("W%d" % e) for e in range(8)], [25] * 8, 1408)[0]
+    for e in range(8):
+        assert torch.equal(product([dw.build("X%d" % e)], [dw.build("W%d" % e)], [25], 1408)[0][0], together[e])
+
+    src = {"O": values((1, 16, 40, 32)), "W": values((512, 768))}      # heads of 32: a K step reaches over two of them
+    src["D"] = np.ascontiguousarray(src["O"].transpose(0, 2, 1, 3)).reshape(40, 512)
+    dw = tio.DeviceWorkload(workloads.Workload("heads", dtype, src, [("o", "permute", ("O",), {"perm": (0, 2, 1, 3)}),
+                                                                      ("A", "reshape", ("o",), {"shape": (40, 512)})], {}))
+    (a,), tile_a = product([dw.build("A")], [dw.build("W")], [40], 768)
+    (d,), tile_d = product([dw.build("D")], [dw.build("W")], [40], 768)
+    assert tile_a == [(256, 256)] and tile_d == [(32, 32)]
+    assert torch.equal(a, d)
 
 
 @pytest.fixture(scope="module")
