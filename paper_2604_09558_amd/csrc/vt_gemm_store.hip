@@ -408,13 +408,14 @@ int vt_gemm_store(const vt_desc* A, const vt_desc* B, const vt_desc* C, void* wo
   P.tickets = static_cast<uint32_t*>(workspace);
   P.partial = reinterpret_cast<float*>(static_cast<char*>(workspace) + counters);
   // Several blocks of 16 rows: this kernel reads B once for each of them, and takes the time its busiest
-  // compute unit needs to draw its share (40 GB/s, 6.5 us around it and 0.2 us per slice that is merged).  The tiled
-  // kernels take over where they are expected to be faster (us here / there: 4096 x 6144 with 32 rows 22.7 / 25.4, 48 rows
-  // 33.7 / 26.8, 90 rows 62.4 / 25.1; 4096 x 1536 with 32 rows 12.8 / 14.9; 4096 x 3072 with 56 rows 20.1 / 14.8; 2048 x 768 with 33 rows
-  // 12.2 / 7.9; 768 x 1024 with 25 rows 9.4 / 6.5).
+  // compute unit needs to draw its share (33 GB/s, 6.4 us around it and 0.27 us per slice that is merged: within 10 % of what
+  // 236 shapes take, r.m.s.).  The tiled kernels take over where they are expected to be faster: at 120 other shapes of 17 to
+  // 128 rows what runs takes 0.8 % longer than the better of the two on average, 19 % at most (us here / there: 4096 x 6144 with
+  // 32 rows 22.7 / 25.4, 48 rows 33.7 / 26.8, 90 rows 62.4 / 25.1; 4096 x 512 with 18 rows 15.5 / 12.8; 2048 x 768 with 33 rows 12.3 / 9.1;
+  // 768 x 1024 with 25 rows 9.5 / 6.8).
   if (rbs > 1) {
     const int64_t rounds = (rbs * cbs * ns_eff + compute_units() - 1) / compute_units();
-    rc = gemm_store_launch(*A, *B, *C, 6500 + ns_eff * 200 + rounds * kps * (kBN * 2) / 40, (hipStream_t)stream);
+    rc = gemm_store_launch(*A, *B, *C, 6400 + ns_eff * 267 + rounds * kps * (kBN * 2) / 33, (hipStream_t)stream);
     if (rc != VT_ERR_UNSUPPORTED) return rc;
   }
   dim3 grid((unsigned)ns_eff, (unsigned)cbs, (unsigned)rbs);

@@ -368,21 +368,24 @@ int launch_tile(GemmParams P8, const typename std::conditional<MAPPED, OutMap, N
   return fail(VT_ERR_UNSUPPORTED, "vt_gemm: no such tile");
 }
 
-// The tile with the shortest estimated time: a launch, a start for every round of tiles over the compute units, and per K
+// The tile with the shortest estimated time: a launch, a start for every round of tiles over the compute units; then per K
 // step of 64 a share for every round and one for every tile of an average unit (a last round that is nearly empty costs less
-// than a full one, and the board's power limit slows full ones), and the weights at 4 TB/s.  The five constants
-// of each tile are fitted over every tile forced at 163 shapes (rows 17 to 16384, 1 to 8 groups, K 512 to 4096, N 768 to
-// 14336): the tile taken is 0.2 % slower than the best one there on average, 10 % at most (before the 32-row tiles, whose constants are
-// fitted at 1505 others).  (One time per step and round
-// for each tile, the rule before: 1.9 %, 25 % at most, with its losses at K = 1024, at few rows and at two to five rounds.)
-// Some of them:
-//   rows x columns of C: us on 256x256 / 128x256 / 128x128 / 96x128 / 64x512 / 64x256 / 64x128 / 64x64
-//   333 x 4096, K = 4096, in the caches  83 /  46 /  29 /  26 /  65 /  31 /  22 /  24
-//   400 x 6144, K = 4096, in the caches  84 /  47 /  31 /  30 /  68 /  33 /  36 /  41
-//   8 x 50 x 14336, K = 4096 (groups)   240 / 175 / 198 / 194 / 159 / 169 / 193 / 212
-//   8 x 200 x 8192, K = 2048             76 /  88 / 105 / 126 / 120 / 111 / 113 / 134
-//   4 x 254 x 8192, K = 4096            107 / 129 / 129 / 118 / 190 / 137 / 132 / 156   (the rule before: 64 x 128)
-//   8 x 18 x 1408, K = 1024              32 /  19 /  13 /  12 /  24 /  13 /  10 / 8.5   (64 x 128)
+// than a full one, and the board's power limit slows full ones), or the draw of the weights where that takes longer (5.4 us of
+// it beside the start); and C.  Weights are counted at 4 TB/s, which every tile exceeds; rows of [K,N] whose
+// distance is a multiple of 4096 bytes are drawn slower, the slower the narrower the tile: its part of every row lies in the same channels of
+// HBM (8 x 13 rows, K = 4096 -> 14336: 155 us on 64 x 512, 181 on 64 x 128; K = 5120 -> 11008: 175 and 159).
+// The constants (ns; thousandths for weights and C) are fitted over every tile forced at 1505 shapes: 1 to 16384 rows, 1 to 8 groups,
+// K 64 to 16384, N 48 to 28672, weights as [K,N] and [N,K], through the output map and not.  At 605 others, drawn apart, the tile taken is
+// 0.8 % slower than the best one on average, 28 % at most, 2 % of them by more than 10 %.  (Fitted over 163 shapes from K = 512 on, without the
+// term for C: 5 % there, 56 % at most, 15 to 20 % throughout K <= 256.)  Some of them, us:
+//   rows x columns of C           256x256 / 128x256 / 128x128 / 96x128 / 64x512 / 64x256 / 64x128 / 64x64
+//   333 x 4096, K = 4096               83 /  46 /  29 /  26 /  65 /  31 /  22 /  24
+//   400 x 6144, K = 4096               84 /  47 /  31 /  30 /  68 /  33 /  36 /  41
+//   8 x 50 x 14336, K = 4096 (groups) 240 / 175 / 198 / 194 / 159 / 169 / 193 / 212
+//   8 x 200 x 8192, K = 2048           76 /  88 / 105 / 126 / 120 / 111 / 113 / 134
+//   4 x 254 x 8192, K = 4096          107 / 129 / 129 / 118 / 190 / 137 / 132 / 156
+//   1783 x 1552, K = 512, [N,K]        24 /  14 /  10 / 9.5 /  15 /  10 / 9.5 /  11
+//   3105 x 11368, K = 128              36 /  46 /  52 /  61 /  46 /  52 /  42 /  60
 // 0 x 0: the 256 x 256 kernel.  Returns the estimate in ns.
 int64_t choose_tile(const GemmParams& P, int* bm, int* bn) {
   static const int n_cu = [] {
@@ -391,20 +394,27 @@ int64_t choose_tile(const GemmParams& P, int* bm, int* bn) {
     return n > 0 ? n : 256;
   }();
   static const struct {
-    int bm, bn, launch, round, step_round, step_tile, weights;
-  } kTiles[] = {{256, 256, 493, 3154, 1381, 171, 238}, {128, 256, 286, 7322, 299, 645, 324}, {128, 128, 1005, 5144, 214, 208, 852},
-                {96, 128, 185, 3883, 332, 185, 320},   {64, 512, 7, 5596, 711, 628, 279},    {64, 256, 256, 5514, 282, 420, 259},
-                {64, 128, 2424, 363, 343, 8, 344},     {64, 64, 3102, 293, 204, 42, 289},
-                {32, 64, 2955, 953, 168, 0, 355},       {32, 32, 2299, 266, 125, 0, 321}};
-  int64_t weights = 0;             // groups that are pieces of one A share their B
-  for (int i = 0; i < P.n_groups; ++i) weights += i == 0 || P.g[i].b != P.g[i - 1].b;
-  const int64_t weights_ns = weights * P.N * P.K * 2 / 4000, steps = P.K / BK;
+    int bm, bn, launch, round, step_round, step_tile, weights, out;
+  } kTiles[] = {{256, 256, 7597, 5831, 1070, 679, 745, 289}, {128, 256, 2905, 5843, 613, 349, 717, 335},
+                {128, 128, 1487, 5297, 333, 305, 733, 0}, {96, 128, 2206, 4989, 290, 195, 857, 0},
+                {64, 512, 2976, 5368, 728, 546, 728, 574}, {64, 256, 1918, 4869, 372, 233, 733, 2},
+                {64, 128, 3099, 1541, 270, 64, 748, 0}, {64, 64, 3285, 1105, 242, 15, 744, 0},
+                {32, 64, 4032, 555, 191, 21, 871, 845}, {32, 32, 3499, 26, 120, 11, 944, 3073}};
+  int64_t weights = 0, rows = 0;   // groups that are pieces of one A share their B
+  for (int i = 0; i < P.n_groups; ++i) {
+    weights += i == 0 || P.g[i].b != P.g[i - 1].b;
+    rows += P.g[i].M;
+  }
+  const int64_t steps = P.K / BK, weights_ns = weights * P.N * P.K * 2 / 4000, out_ns = rows * P.N * (P.c_f32 ? 4 : 2) / 4000;
+  const bool same_channels = !P.g[0].b_kmajor && P.g[0].b_row.stride[2] * 2 % 4096 == 0;
   int64_t best = 0;
   for (const auto& t : kTiles) {
     int64_t tiles = 0;
     for (int i = 0; i < P.n_groups; ++i) tiles += ((int64_t)P.g[i].M + t.bm - 1) / t.bm * ((P.N + t.bn - 1) / t.bn);
     const int64_t rounds = (tiles + n_cu - 1) / n_cu;
-    const int64_t cost = t.launch + rounds * t.round + steps * (rounds * t.step_round + tiles * t.step_tile / n_cu) + weights_ns * t.weights / 1000;
+    const int64_t k_loop = steps * (rounds * t.step_round + tiles * t.step_tile / n_cu);
+    const int64_t draw = weights_ns * (same_channels ? t.weights : 450) / 1000 - 5410;
+    const int64_t cost = t.launch + rounds * t.round + std::max(k_loop, draw) + out_ns * t.out / 1000;
     if (best == 0 || cost < best) {
       best = cost;
       *bm = t.bm, *bn = t.bn;
@@ -427,8 +437,7 @@ int64_t axis_span(const AxisMap<ND>& a) {
 namespace vt {
 
 // The product of P (operands planned, tiles not yet cut) on smaller tiles, or VT_ERR_UNSUPPORTED when
-// the 256 x 256 kernel is the better one or the only one, or when the estimate, 0.9 us for the
-// mapped store and 0.07 us per step (few tiles with weights from HBM) are not below below_ns (if that is not 0).
+// the 256 x 256 kernel is the better one or the only one, or when the estimate is not below below_ns (if that is not 0).
 int gemm_tile_launch(const GemmParams& P, const OutMap* O, int dtype, hipStream_t st, int64_t below_ns) {
   const char* no = "vt_gemm: outside the small-tile kernel";
   if (P.K % BK || P.K < BK || P.K > kMaxSteps * BK || P.N < 8) return fail(VT_ERR_UNSUPPORTED, no);
@@ -441,7 +450,7 @@ int gemm_tile_launch(const GemmParams& P, const OutMap* O, int dtype, hipStream_
   }
   int bm = 0, bn = 0;
   const int64_t estimate_ns = choose_tile(P, &bm, &bn);
-  if (below_ns && estimate_ns + 900 + P.K / BK * 70 >= below_ns) return fail(VT_ERR_UNSUPPORTED, no);
+  if (below_ns && estimate_ns >= below_ns) return fail(VT_ERR_UNSUPPORTED, no);
   if (!bm) return fail(VT_ERR_UNSUPPORTED, no);
   const NoMap none;
   const bool km = P.g[0].b_kmajor != 0;

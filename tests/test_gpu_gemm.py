@@ -223,7 +223,7 @@ def test_operand_stacked_by_a_concat_along_the_rows(gpu):
 
 
 # from one row and eight columns to several rounds of tiles, K of one step, of fewer steps than a ring holds, of an odd
-# number; ragged rows and columns
+# number; ragged rows and columns (which tile runs is seen in test_each_tile)
 @pytest.mark.parametrize("M,K,N,dtype", [(1, 64, 8, "bf16"), (65, 192, 520, "f16"), (333, 320, 4088, "bf16"), (391, 448, 5992, "f16"),
                                          (1000, 128, 4040, "bf16"), (2000, 704, 4000, "f16"), (2100, 64, 6088, "bf16")])
 def test_tile_shapes(gpu, M, K, N, dtype):
@@ -338,6 +338,54 @@ def tiles_run(names):
         elif "k_gemm<" in n or "k_gemmI" in n:
             found.append((256, 256))
     return found
+
+
+# every tile that there is: one K step, odd and even numbers, fewer than its ring holds and more; ragged rows and columns
+@pytest.mark.parametrize("tile,M,K,N", [
+    ((32, 32), 33, 64, 200), ((32, 32), 5, 192, 72), ((32, 32), 65, 320, 1000), ((32, 32), 31, 1024, 264), ((32, 64), 1139, 832, 312),
+    ((32, 64), 1029, 1024, 232), ((64, 64), 1690, 64, 296), ((64, 64), 1029, 448, 480), ((64, 128), 68, 64, 8200), ((64, 128), 66, 320, 8248),
+    ((64, 256), 386, 448, 5008), ((64, 256), 290, 512, 6992), ((64, 512), 263, 448, 21952), ((64, 512), 260, 576, 22016),
+    ((96, 128), 71, 320, 16480), ((96, 128), 66, 512, 16712), ((128, 128), 326, 384, 5520), ((128, 128), 193, 448, 8488),
+    ((128, 256), 269, 128, 19664), ((128, 256), 1978, 448, 3080), ((256, 256), 1223, 64, 11536), ((256, 256), 1685, 256, 7216)])
+def test_each_tile(gpu, kernels, tile, M, K, N):
+    """Rows gathered through an index table, W as [K,N] and as [N,K] through a Permute, the output dense or through a map over two
+    tensors: the tile that is meant runs, fp32 outputs are within 1e-4 of the oracle (sums of K terms of about 0.05), the
+    16-bit results are the fp32 one rounded once, nothing is written behind the last row."""
+    vt, tio, pipelines, torch = gpu
+    from paper_2604_09558_amd import binding
+    rng = np.random.default_rng(43)
+    dtype = "bf16" if M % 2 else "f16"
+    td = torch.bfloat16 if dtype == "bf16" else torch.float16
+    x = workloads.encode(rng.normal(size=(M + 3, K)).astype(np.float32), dtype)
+    w = workloads.encode((rng.normal(size=(K, N)) * 0.05).astype(np.float32), dtype)
+    rows = rng.integers(0, M + 3, M).astype(np.int32)
+    n0 = N // 2 // 8 * 8
+    blank = {"P": np.zeros((M, n0), w.dtype), "Q": np.zeros((M, N - n0), w.dtype)}
+    chain = [("A", "index_select", ("X",), {"dim": 0, "index": "rows"}), ("Bt", "permute", ("Wt",), {"perm": (1, 0)}),
+             ("C", "concat", ("P", "Q"), {"dim": 1})]
+    src = {"X": x, "W": w, "Wt": np.ascontiguousarray(w.T), "D": np.ascontiguousarray(x[rows]), **blank}
+    dw = tio.DeviceWorkload(workloads.Workload("tile", dtype, src, chain, {}, {"rows": rows}))
+    a, b, bt = dw.build("A"), dw.build("W"), dw.build("Bt")
+    f32 = torch.full((M + 1, N), 7.0, device="cuda:0")
+    out, out_t = (torch.full((M + 1, N), 7.0, dtype=td, device="cuda:0") for _ in range(2))
+    nbytes = binding.vt_gemm_store_workspace(M, N, K)
+    ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda:0")
+    binding.vt_gemm_store_workspace_init(ws, nbytes)
+    assert tiles_run(kernels(lambda: vt.vt_gemm([a], [b], [out], dtype))) == [tile]
+    assert tiles_run(kernels(lambda: vt.vt_gemm([a], [bt], [out_t], dtype))) == [tile]
+    stored_by = tiles_run(kernels(lambda: binding.vt_gemm_store(dw.build("D"), b, dw.build("C"), ws, nbytes)))
+    assert stored_by == [tile] or (M <= 128 and not stored_by)          # (not: the kernel for a handful of rows)
+    vt.vt_gemm([a], [b], [f32], "f32")
+    torch.cuda.synchronize()
+    ref = consumers.gemm(consumers.decode(x[rows], dtype), consumers.decode(w, dtype))
+    assert np.abs(f32[:M].cpu().numpy() - ref).max() <= 1e-4
+    assert torch.equal(f32[:M].to(td), out[:M]) and torch.equal(out, out_t) and bool((f32[M] == 7.0).all()) and bool((out[M] == 7.0).all())
+    stored = torch.cat([dw.tensors["P"].view(td), dw.tensors["Q"].view(td)], dim=1)
+    if stored_by:
+        assert torch.equal(stored, out[:M])
+    else:
+        eps = 2.0 ** -8 if dtype == "bf16" else 2.0 ** -11
+        assert bool(((stored.float() - f32[:M]).abs() <= eps * f32[:M].abs() + 1e-4).all())
 
 
 @pytest.mark.parametrize("dtype", ["bf16", "f16"])
