@@ -984,6 +984,10 @@ struct CombineShape {
   FastDiv vecs, chunks;                // vecs_per; workgroups per row
 };
 
+// w.x x + w.y y with two roundings, the same two in both kernels (left to the compiler, which product is rounded first
+// changes with the element's place among a thread's)
+__device__ __forceinline__ float weighted(float2 w, float x, float y) { return fmaf(w.x, x, w.y * y); }
+
 constexpr uint32_t kCombineRows = 256;
 static_assert(sizeof(RowDescs) + sizeof(CombineShape) + 16 <= 4096, "kernel arguments");
 
@@ -1042,7 +1046,7 @@ __global__ void __launch_bounds__(256) k_weighted_sum_rows(const Maps P, const C
       const Vec<T, 8> av = __builtin_bit_cast(Vec<T, 8>, a[u]), bv = __builtin_bit_cast(Vec<T, 8>, b[u]);
       Vec<T, 8> o;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) o.v[e] = from_float<T>(ww[u].x * to_float(av.v[e]) + ww[u].y * to_float(bv.v[e]));
+      for (int e = 0; e < 8; ++e) o.v[e] = from_float<T>(weighted(ww[u], to_float(av.v[e]), to_float(bv.v[e])));
       __builtin_nontemporal_store(__builtin_bit_cast(u32x4, o), o0 + i);
     }
   }
@@ -1058,7 +1062,7 @@ __global__ void __launch_bounds__(256) k_weighted_sum_generic(const DevDesc X, c
   vtd_eval(X, 0, i, &ox, &px);
   vtd_eval(Y, 0, i, &oy, &py);
   const uint32_t row = i / C;
-  out[i] = from_float<T>(w[2 * row] * to_float(static_cast<const T*>(px)[ox]) + w[2 * row + 1] * to_float(static_cast<const T*>(py)[oy]));
+  out[i] = from_float<T>(weighted(make_float2(w[2 * row], w[2 * row + 1]), to_float(static_cast<const T*>(px)[ox]), to_float(static_cast<const T*>(py)[oy])));
 }
 
 template <typename T>

@@ -102,3 +102,33 @@ def test_row_kernel_shapes(gpu, R, C, dtype, pieces):
     bound = ref.abs() * (2.0 ** -8 if dtype == "bf16" else 2.0 ** -11) + 2.0 ** -22 * (px.abs() + py.abs()) + 2.0 ** -25
     assert bool(((out[:R].double() - ref).abs() <= bound).all())
     assert bool((out[R] == 7.0).all())
+
+
+@pytest.mark.parametrize("R,C,dtype", [(700, 264, "bf16"), (700, 264, "f16"), (5, 8192, "bf16")])
+def test_every_path_gives_the_same_bits(gpu, kernels, R, C, dtype):
+    """The same rows alone and among others, as one tensor and as two behind each other, and with an output that is not
+    aligned for whole vectors: the row kernel (both of its maps, every place in a workgroup) and the generic one round alike."""
+    vt, tio, pipelines, torch = gpu
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(R)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float16
+    x = torch.randn((R, C), generator=g, device="cuda:0").to(dt)
+    y = (-x.float() + 0.01 * torch.randn((R, C), generator=g, device="cuda:0")).to(dt)          # sums that cancel: roundings show
+    w = 0.5 + 0.001 * torch.rand((R, 2), generator=g, device="cuda:0")
+    cut = R // 3
+    parts = {"X0": ((cut, C), dtype, x[:cut].data_ptr()), "X1": ((R - cut, C), dtype, x[cut:].data_ptr())}
+    whole = {"X": ((R, C), dtype, x.data_ptr())}
+    xd, yd = vt.build_chain([], whole, "X"), vt.build_chain([], {"Y": ((R, C), dtype, y.data_ptr())}, "Y")
+    xc = vt.build_chain([("c", "concat", ("X0", "X1"), {"dim": 0})], parts, "c")
+    out, out_c = (torch.zeros((R, C), dtype=dt, device="cuda:0") for _ in range(2))
+    store = torch.zeros(R * C + 1, dtype=dt, device="cuda:0")
+    names = [kernels(lambda d=d, o=o: vt.vt_weighted_sum(d, yd, w, o)) for d, o in ((xd, out), (xc, out_c), (xd, store[1:]))]
+    for n, kernel in zip(names, ("k_weighted_sum_rows", "k_weighted_sum_rows", "k_weighted_sum_generic")):
+        assert any(kernel in k for k in n), n
+    assert torch.equal(out, out_c) and torch.equal(out, store[1:].view(R, C))
+    for r in (0, R // 2, R - 1):
+        one = torch.zeros((1, C), dtype=dt, device="cuda:0")
+        vt.vt_weighted_sum(vt.build_chain([], {"X": ((1, C), dtype, x[r].data_ptr())}, "X"), vt.build_chain([], {"Y": ((1, C), dtype, y[r].data_ptr())}, "Y"),
+                           w[r:r + 1].contiguous(), one)
+        torch.cuda.synchronize()
+        assert torch.equal(one[0], out[r]), r
