@@ -47,6 +47,7 @@ struct RingParams {
   int32_t M, N, K;
   float eps;
   int32_t tiles_per_group;        // column tiles of one workgroup, dealt to its waves in turn
+  int32_t stream;                 // 16-bit results leave as streaming stores
 };
 
 // at most N vector memory operations outstanding, no LDS operation
@@ -269,7 +270,8 @@ k_ln_gemm_ring(const RingParams P) {
           const u32x4 v = __builtin_bit_cast(u32x4, *reinterpret_cast<const uint4*>(turn + rr * 128 + ((ch ^ (rr >> 1 & 7)) * 16)));
           const int col = tile * TBN + ch * 8;
           const uint32_t off = col < N ? (uint32_t)((mb * 32 + rr) * N + col) * 2u : 0x80000000u;
-          __builtin_amdgcn_raw_buffer_store_b128(v, rsrc, (int)off, 0, 2);   // streaming: whole lines, not read again here
+          if (P.stream) __builtin_amdgcn_raw_buffer_store_b128(v, rsrc, (int)off, 0, 2);   // whole lines, not read again here
+          else __builtin_amdgcn_raw_buffer_store_b128(v, rsrc, (int)off, 0, 0);
         }
       }
     }
@@ -407,6 +409,7 @@ int ln_gemm_ring_launch(const vt_desc& A, const vt_desc& B, void* C, int c_dtype
   P.N = (int32_t)N;
   P.K = (int32_t)K;
   P.eps = eps;
+  P.stream = streaming_rows(M, N);
   int mb = 0, groups = 1;
   if (!choose_ring(M, N, K, &mb, &groups)) return fail(VT_ERR_UNSUPPORTED, no);
   const bool c32 = c_dtype == VT_F32;

@@ -44,6 +44,7 @@ struct SliceParams {
   float eps;
   int32_t n_slices, slice_cols;   // slice_cols: a multiple of 64
   int32_t groups, n_blocks;       // workgroups per slice; blocks of SBM rows: group g takes blocks g, g + groups, ..
+  int32_t stream;                 // 16-bit results leave as streaming stores
 };
 
 // Sum over LPR = 8, 16 or 32 consecutive lanes, every lane gets the total.
@@ -233,7 +234,8 @@ k_ln_gemm_slice(const SliceParams P) {
           const u32x4 v = __builtin_bit_cast(u32x4, mine[rr * 8 + (ch ^ (rr >> 1))]);
           const int col = col_ct + ch * 8;
           const uint32_t off = col < N ? (uint32_t)((r0 + rr) * N + col) * 2u : 0x80000000u;
-          __builtin_amdgcn_raw_buffer_store_b128(v, rsrc, (int)off, 0, 2);   // streaming: whole lines, not read again here
+          if (P.stream) __builtin_amdgcn_raw_buffer_store_b128(v, rsrc, (int)off, 0, 2);   // whole lines, not read again here
+          else __builtin_amdgcn_raw_buffer_store_b128(v, rsrc, (int)off, 0, 0);
         }
       }
     }
@@ -339,6 +341,7 @@ int ln_gemm_slice_launch(const vt_desc& A, const vt_desc& B, void* C, int c_dtyp
   P.M = (int32_t)M;
   P.N = (int32_t)N;
   P.eps = eps;
+  P.stream = streaming_rows(M, N);
   P.n_blocks = (int32_t)((M + SBM - 1) / SBM);
   const int64_t tiles = (N + 63) / 64;
   P.n_slices = (int32_t)((N + kSliceCols - 1) / kSliceCols);

@@ -223,6 +223,32 @@ def test_weight_ring_kernel(gpu, B, R, win, C, N, dtype):
         check(tio.to_host_f64(p.out).reshape(ref.shape), run_workload(wl)["out"])
 
 
+# W in registers, a slice of it, through LDS (both: streaming and, from 32 MiB of ragged rows on, plain stores), through registers
+@pytest.mark.parametrize("M,C,N,dtype,kernel", [(1000, 128, 384, "bf16", "k_ln_gemm"), (33000, 96, 328, "f16", "k_ln_gemm_slice"), (33500, 64, 520, "bf16", "k_ln_gemm_slice"),
+                                                (1681, 256, 1560, "bf16", "k_ln_gemm_ring"), (8281, 320, 1040, "f16", "k_ln_gemm_ring"), (17000, 128, 1032, "bf16", "k_ln_gemm_ring"),
+                                                (400, 256, 72, "bf16", "k_ln_gemm_wide")])
+def test_rows_through_a_table_and_a_weight_with_rows_apart(gpu, kernels, M, C, N, dtype, kernel):
+    """Rows gathered through an index table and a W that is a range of a wider matrix's columns: the same kernel as on dense
+    copies of both, and the same bits; those against the oracle (bound as in test_weight_streamed_kernel)."""
+    vt, tio, pipelines, torch = gpu
+    rng = np.random.default_rng(M)
+    x = workloads.encode(rng.normal(size=(M + 50, C)).astype(np.float32), dtype)
+    wide = workloads.encode((rng.normal(size=(C, N + 24)) * 0.02).astype(np.float32), dtype)
+    rows = rng.integers(0, M + 50, M).astype(np.int32)
+    chain = [("A", "index_select", ("X",), {"dim": 0, "index": "rows"}), ("Ws", "slice", ("W2",), {"dim": 1, "start": 16, "stop": 16 + N})]
+    src = {"X": x, "W2": wide, "D": np.ascontiguousarray(x[rows]), "W": np.ascontiguousarray(wide[:, 16:16 + N])}
+    dw = tio.DeviceWorkload(workloads.Workload("table", dtype, src, chain, {}, {"rows": rows}))
+    td = torch.bfloat16 if dtype == "bf16" else torch.float16
+    out, dense = (torch.full((M + 1, N), 7.0, dtype=td, device="cuda:0") for _ in range(2))
+    for a, w, o in (("A", "Ws", out), ("D", "W", dense)):
+        names = kernels(lambda: vt.vt_gemm([dw.build(a)], [dw.build(w)], [o], dtype, vt.GEMM_LAYERNORM, 1e-5))
+        assert any(kernel + "<" in n or kernel + "I" in n for n in names), names
+    assert torch.equal(out, dense) and bool((out[M] == 7.0).all())
+    wl = workloads.Workload("ln", dtype, {"D": src["D"], "W": src["W"]}, [], {"kind": "ln_linear", "x": "D", "w": "W", "eps": 1e-5})
+    ref = run_workload(wl)["out"]
+    check(tio.to_host_f64(dense[:M]), ref.reshape(M, N))
+
+
 @pytest.mark.parametrize("C", [40, 256])
 def test_subnormal_variance_without_eps(gpu, C):
     """Rows of +-1e-21 and eps = 0: the variance is a subnormal fp32 number, the normalised row +-1."""
