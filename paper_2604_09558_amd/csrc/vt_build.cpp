@@ -608,6 +608,12 @@ static void finalize_piece(const vt_desc& d, Piece& p) {
       }
     normalize(s.digits);
   }
+  for (auto& g : p.v.groups)
+    for (Digit& dg : g)
+      if (dg.table >= 0) {
+        const int32_t* e = d.tables[dg.table].host.data() + dg.table_off;
+        dg.table_max = *std::max_element(e, e + dg.radix);
+      }
   // top stage: walk digits from the innermost dim while they form a dense suffix
   int n = (int)p.v.shape.size();
   int64_t run = 1, expect = 1;

@@ -34,6 +34,7 @@ struct Digit {
   int64_t stride = 0;
   int table = -1;          // index into Desc::tables, -1 = plain digit
   int64_t table_off = 0;   // first table entry this digit uses
+  int64_t table_max = 0;   // the largest of its `radix` entries (filled by finalize)
 };
 
 struct Stage {

@@ -518,17 +518,7 @@ int plan_a(const vt_desc& d, GemmGroup* g, int64_t* M, int64_t* K, size_t pi = 0
   const vt_source& src = d.sources[p.src];
   if (!src.ptr) return fail(VT_ERR_INVALID_ARG, "vt_gemm: A source without a device pointer");
   g->a = static_cast<const char*>(src.ptr) + p.v.base * 2;
-  {
-    int64_t span = 0;
-    for (int i = 0; i < 5; ++i) span += (int64_t)(g->a_row.radix[i].d - 1) * g->a_row.stride[i];
-    for (int i = 0; i < 3; ++i) span += (int64_t)(g->a_col.radix[i].d - 1) * g->a_col.stride[i];
-    if (g->a_row.table) {
-      // a table digit can reach any row of the source dim it indexes: bound by the source size
-      span = 1;
-      for (int i = 0; i < src.ndim; ++i) span *= src.shape[i];
-    }
-    if (span * 2 >= (1ll << 32)) return fail(VT_ERR_UNSUPPORTED, "vt_gemm: A spans 4 GiB or more");
-  }
+  if (reach(d, p) > kReach32) return fail(VT_ERR_UNSUPPORTED, "vt_gemm: A spans more than 4 GiB");
   const AxisMap<3>& c = g->a_col;
   bool ok = *K % 8 == 0 && (uintptr_t)g->a % 16 == 0 && strides_multiple_of(g->a_row, 8, 0);
   ok = ok && c.nd >= 1 && c.stride[2] == 1 && c.radix[2].d % 8 == 0 && strides_multiple_of(c, 8, 1);

@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstring>
 #include <string>
 #include <type_traits>
@@ -193,6 +194,22 @@ int make_axis(const vt_desc& d, const Piece& p, int d0, int d1, AxisMap<ND>* out
 // streaming / plain: 13942 x 128 -> 2448 38.7 / 20.3, 54670 x 64 -> 472 24.9 / 14.3; below, or with whole units: 58088 x 96 ->
 // 288 12.2 / 15.3, 73324 x 96 -> 72 10.5 / 12.4).
 inline bool streaming_rows(int64_t M, int64_t N) { return N % 32 == 0 || M * N * 2 < (32ll << 20); }
+
+// Elements of its source that a piece with one stage can reach, counted from the piece's base: the farthest one that its
+// digits name (a source's rows may lie apart; the entries of a table over a Concat count from the first of its
+// inputs), with a table the whole of a dense source at least.
+inline int64_t reach(const vt_desc& d, const Piece& p) {
+  int64_t last = 0, all = 0;
+  for (const auto& group : p.v.groups)
+    for (const Digit& g : group) {
+      last += (g.table >= 0 ? g.table_max : g.radix - 1) * g.stride;
+      if (g.table >= 0) all = 1;
+    }
+  const vt_source& s = d.sources[p.src];
+  for (int i = 0; i < s.ndim; ++i) all *= s.shape[i];
+  return std::max(last + 1, all);
+}
+constexpr int64_t kReach32 = 1ll << 31;   // of 16-bit elements: their byte offsets take 32 bits
 
 template <int ND>
 bool strides_multiple_of(const AxisMap<ND>& a, int64_t q, int skip_inner) {

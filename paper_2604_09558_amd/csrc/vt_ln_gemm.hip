@@ -449,15 +449,7 @@ int ln_gemm_launch(const vt_desc& A, const vt_desc& B, void* C, int c_dtype, flo
   if ((uintptr_t)P.a % 16 || !strides_multiple_of(P.a_row, 8, 0))
     return fail(VT_ERR_UNSUPPORTED, "vt_gemm(layernorm): rows of A must be 16-byte aligned");
   if ((uintptr_t)C % 16) return fail(VT_ERR_INVALID_ARG, "vt_gemm(layernorm): C must be 16-byte aligned");
-  {
-    int64_t span = 0;
-    for (int i = 0; i < 5; ++i) span += (int64_t)(P.a_row.radix[i].d - 1) * P.a_row.stride[i];
-    if (P.a_row.table) {
-      span = 1;
-      for (int i = 0; i < sa.ndim; ++i) span *= sa.shape[i];
-    }
-    if ((span + K) * 2 >= (1ll << 32)) return fail(VT_ERR_UNSUPPORTED, "vt_gemm(layernorm): A spans 4 GiB or more");
-  }
+  if (reach(A, pa) > kReach32) return fail(VT_ERR_UNSUPPORTED, "vt_gemm(layernorm): A spans more than 4 GiB");
   P.w_rows_of_8 = (uintptr_t)P.b % 16 == 0 && P.b_col.stride[2] == 1 && P.b_col.radix[2].d % 8 == 0 &&
                   strides_multiple_of(P.b_col, 8, 1) && strides_multiple_of(P.b_row, 8, 0);
   P.w_k_runs_of_8 = P.b_row.radix[2].d % 8 == 0;

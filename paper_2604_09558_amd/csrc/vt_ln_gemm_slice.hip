@@ -325,19 +325,7 @@ int ln_gemm_slice_launch(const vt_desc& A, const vt_desc& B, void* C, int c_dtyp
   const bool w_ok = b_row.nd == 1 && b_col.nd == 1 && b_col.stride[2] == 1 && P.ldb % 8 == 0 && P.ldb >= 0 && (uintptr_t)P.b % 16 == 0 &&
                     P.ldb * 48 + N * 2 < (1ll << 32);
   if (!rows_ok || !w_ok || (uintptr_t)P.c % 16) return fail(VT_ERR_UNSUPPORTED, no);
-  {
-    // a row's byte offset is 32 bits and not negative (a table digit can reach any row of the source dim that it indexes)
-    int64_t span = 0;
-    for (int i = 0; i < 5; ++i) {
-      if (P.a_row.stride[i] < 0) return fail(VT_ERR_UNSUPPORTED, no);
-      span += (int64_t)(P.a_row.radix[i].d - 1) * P.a_row.stride[i];
-    }
-    if (P.a_row.table) {
-      span = 1;
-      for (int i = 0; i < sa.ndim; ++i) span *= sa.shape[i];
-    }
-    if ((span + K) * 2 >= (1ll << 32)) return fail(VT_ERR_UNSUPPORTED, no);
-  }
+  if (reach(A, pa) > kReach32) return fail(VT_ERR_UNSUPPORTED, no);   // a row's byte offset is 32 bits
   P.M = (int32_t)M;
   P.N = (int32_t)N;
   P.eps = eps;

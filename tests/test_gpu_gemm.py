@@ -441,6 +441,44 @@ def test_every_tile_gives_the_same_bits(gpu, kernels, dtype):
     assert torch.equal(a, d)
 
 
+# plain: K steps of the tiled kernels; LayerNorm: W in registers, a slice of it
+@pytest.mark.parametrize("M,K,N,ln", [(300, 256, 264, False), (1000, 128, 384, True), (33000, 96, 72, True)])
+@pytest.mark.parametrize("far", ["rows", "inputs"])
+def test_table_that_reaches_past_4_gib(gpu, kernels, M, K, N, ln, far):
+    """Kernels whose row offsets are 32 bits leave a table to the others where its entries reach further: rows of a source
+    that lie apart (its elements alone would fit), entries that count from the first input of a Concat.  Against a dense copy of
+    the rows, within two roundings to bf16 of results of about 1."""
+    vt, tio, pipelines, torch = gpu
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(M)
+    pool = torch.randn((40, K), generator=g, device="cuda:0").bfloat16()
+    idx = np.random.default_rng(M).integers(0, 40, M).astype(np.int32)
+    if far == "rows":
+        apart = (1 << 31) // 32
+        space = torch.empty(39 * apart + K, dtype=torch.bfloat16, device="cuda:0")
+        rows = torch.as_strided(space, (40, K), (apart, 1))
+        rows.copy_(pool)
+        src, chain, entries = {"X": ((40, K), "bf16", rows.data_ptr(), (apart, 1))}, [], idx
+    else:
+        before = (1 << 31) // K                      # rows of the first input: no entry names them
+        space = torch.empty(before * K, dtype=torch.bfloat16, device="cuda:0")
+        src = {"P": ((before, K), "bf16", space.data_ptr()), "Q": ((40, K), "bf16", pool.data_ptr())}
+        chain, entries = [("X", "concat", ("P", "Q"), {"dim": 0})], idx + before
+    entries = entries.astype(np.int32)
+    tab = torch.from_numpy(entries).to("cuda:0")
+    a = vt.build_chain(chain + [("A", "index_select", ("X",), {"dim": 0, "index": "i"})], src, "A", {"i": entries}, {"i": tab.data_ptr()})
+    dense = pool[torch.from_numpy(idx).to("cuda:0").long()].contiguous()
+    w = (torch.randn((K, N), generator=g, device="cuda:0") / K ** 0.5).bfloat16()
+    b = vt.build_chain([], {"W": ((K, N), "bf16", w.data_ptr())}, "W")
+    out, ref = (torch.full((M, N), 7.0, dtype=torch.bfloat16, device="cuda:0") for _ in range(2))
+    prologue = vt.GEMM_LAYERNORM if ln else vt.GEMM_PLAIN
+    names = kernels(lambda: vt.vt_gemm([a], [b], [out], "bf16", prologue, 1e-5))
+    vt.vt_gemm([vt.build_chain([], {"D": ((M, K), "bf16", dense.data_ptr())}, "D")], [b], [ref], "bf16", prologue, 1e-5)
+    torch.cuda.synchronize()
+    assert not any(k in n for n in names for k in ("k_gemm_tile", "k_gemm<", "k_ln_gemm<", "k_ln_gemm_slice")), names
+    assert bool(((out.float() - ref.float()).abs() <= 2.0 ** -7 * ref.float().abs() + 2.0 ** -6).all())
+
+
 @pytest.fixture(scope="module")
 def c5_full(gpu):
     """Config 5 at the benchmark's size, launched once as the benchmark launches it (8 experts in
