@@ -2,6 +2,8 @@
 GEMM's load stage, and the unfused LayerNorm kernel + GEMM) against the CPU oracle.
 Tolerance |gpu - oracle| <= 1e-2 + 1e-2 |oracle| (the benchmark states none for fp16: the bf16
 bar is used; observed errors are ~1e-3, see the asserts on the maximum)."""
+import re
+
 import numpy as np
 import pytest
 
@@ -221,6 +223,33 @@ def test_weight_ring_kernel(gpu, B, R, win, C, N, dtype):
         p.run()
         torch.cuda.synchronize()
         check(tio.to_host_f64(p.out).reshape(ref.shape), run_workload(wl)["out"])
+
+
+# Two and three tiles for a wave (waits that count the stores of the tile before), in blocks of every height with either ring;
+# streaming and plain stores, ragged columns and a ragged last block
+@pytest.mark.parametrize("M,C,N,dtype,instance", [(16650, 384, 1120, "bf16", (3, 32, 4)), (16650, 512, 1096, "f16", (3, 32, 4)),
+                                                   (24650, 384, 1096, "bf16", (4, 32, 4)), (24650, 320, 1120, "f16", (4, 32, 4)),
+                                                   (24650, 192, 1096, "bf16", (4, 16, 6)), (33130, 192, 1120, "f16", (5, 16, 4)),
+                                                   (12330, 448, 1544, "bf16", (2, 32, 6))])
+def test_ring_of_several_tiles(gpu, kernels, M, C, N, dtype, instance):
+    """The instance that is meant runs (rows / 32, lanes of half a row, stages), its fp32 results agree with the oracle (bound as
+    in test_weight_streamed_kernel), its 16-bit ones are those rounded once; nothing behind the last row is written."""
+    vt, tio, pipelines, torch = gpu
+    rng = np.random.default_rng(M + C)
+    src = {"X": workloads.encode(rng.normal(size=(M, C)).astype(np.float32), dtype),
+           "W": workloads.encode((rng.normal(size=(C, N)) * 0.02).astype(np.float32), dtype)}
+    wl = workloads.Workload("ln", dtype, src, [], {"kind": "ln_linear", "x": "X", "w": "W", "eps": 1e-5})
+    dw = tio.DeviceWorkload(wl)
+    a, b = dw.build("X"), dw.build("W")
+    td = torch.bfloat16 if dtype == "bf16" else torch.float16
+    out = torch.full((M + 1, N), 7.0, dtype=td, device="cuda:0")
+    f32 = torch.full((M + 1, N), 7.0, device="cuda:0")
+    for o, kind in ((out, dtype), (f32, "f32")):
+        names = kernels(lambda: vt.vt_gemm([a], [b], [o], kind, vt.GEMM_LAYERNORM, 1e-5))
+        assert any(re.search(r"k_ln_gemm_ring(<.*, %d, %d, %d>|I.*ELi%dELi%dELi%dE)" % (instance * 2), n) for n in names), names
+    ref = run_workload(wl)["out"].reshape(M, N)
+    assert np.max(np.abs(f32[:M].cpu().numpy() - ref)) <= 4e-3
+    assert torch.equal(f32[:M].to(td), out[:M]) and bool((f32[M] == 7.0).all()) and bool((out[M] == 7.0).all())
 
 
 # W in registers, a slice of it, through LDS (both: streaming and, from 32 MiB of ragged rows on, plain stores), through registers
