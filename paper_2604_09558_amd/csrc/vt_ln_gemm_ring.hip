@@ -264,14 +264,21 @@ k_ln_gemm_ring(const RingParams P) {
           for (int j = 0; j < 4; ++j)
             *reinterpret_cast<uint2*>(turn + l32 * 128 + (((nb * 4 + j) ^ (l32 >> 1 & 7)) * 16) + lh * 8) =
                 make_uint2(pack2<T>(acc[nb][mb][4 * j], acc[nb][mb][4 * j + 1]), pack2<T>(acc[nb][mb][4 * j + 2], acc[nb][mb][4 * j + 3]));
+        u32x4 v[4];
+        uint32_t off[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           const int rr = q * 8 + (lane >> 3), ch = lane & 7;   // 8 lanes per row of 64 columns
-          const u32x4 v = __builtin_bit_cast(u32x4, *reinterpret_cast<const uint4*>(turn + rr * 128 + ((ch ^ (rr >> 1 & 7)) * 16)));
+          v[q] = __builtin_bit_cast(u32x4, *reinterpret_cast<const uint4*>(turn + rr * 128 + ((ch ^ (rr >> 1 & 7)) * 16)));
           const int col = tile * TBN + ch * 8;
-          const uint32_t off = col < N ? (uint32_t)((mb * 32 + rr) * N + col) * 2u : 0x80000000u;
-          if (P.stream) __builtin_amdgcn_raw_buffer_store_b128(v, rsrc, (int)off, 0, 2);   // whole lines, not read again here
-          else __builtin_amdgcn_raw_buffer_store_b128(v, rsrc, (int)off, 0, 0);
+          off[q] = col < N ? (uint32_t)((mb * 32 + rr) * N + col) * 2u : 0x80000000u;
+        }
+        if (P.stream) {                                // whole lines, not read again here (asked once for the four: 18.1 -> 17.9 us)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) __builtin_amdgcn_raw_buffer_store_b128(v[q], rsrc, (int)off[q], 0, 2);
+        } else {
+#pragma unroll
+          for (int q = 0; q < 4; ++q) __builtin_amdgcn_raw_buffer_store_b128(v[q], rsrc, (int)off[q], 0, 0);
         }
       }
     }

@@ -228,14 +228,21 @@ k_ln_gemm_slice(const SliceParams P) {
           for (int e = 0; e < 8; ++e) o.v[e] = from_float<T>(acc[e & 3][mb][2 * h + (e >> 2)]);
           mine[l16 * 8 + ((lg * 2 + h) ^ (l16 >> 1))] = __builtin_bit_cast(uint4, o);
         }
+        u32x4 v[2];
+        uint32_t off[2];
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
           const int rr = q * 8 + (lane >> 3), ch = lane & 7;   // 8 lanes per row of 64 columns
-          const u32x4 v = __builtin_bit_cast(u32x4, mine[rr * 8 + (ch ^ (rr >> 1))]);
+          v[q] = __builtin_bit_cast(u32x4, mine[rr * 8 + (ch ^ (rr >> 1))]);
           const int col = col_ct + ch * 8;
-          const uint32_t off = col < N ? (uint32_t)((r0 + rr) * N + col) * 2u : 0x80000000u;
-          if (P.stream) __builtin_amdgcn_raw_buffer_store_b128(v, rsrc, (int)off, 0, 2);   // whole lines, not read again here
-          else __builtin_amdgcn_raw_buffer_store_b128(v, rsrc, (int)off, 0, 0);
+          off[q] = col < N ? (uint32_t)((r0 + rr) * N + col) * 2u : 0x80000000u;
+        }
+        if (P.stream) {                                // whole lines, not read again here
+          __builtin_amdgcn_raw_buffer_store_b128(v[0], rsrc, (int)off[0], 0, 2);
+          __builtin_amdgcn_raw_buffer_store_b128(v[1], rsrc, (int)off[1], 0, 2);
+        } else {
+          __builtin_amdgcn_raw_buffer_store_b128(v[0], rsrc, (int)off[0], 0, 0);
+          __builtin_amdgcn_raw_buffer_store_b128(v[1], rsrc, (int)off[1], 0, 0);
         }
       }
     }
