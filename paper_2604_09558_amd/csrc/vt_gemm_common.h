@@ -190,10 +190,10 @@ int make_axis(const vt_desc& d, const Piece& p, int d0, int d1, AxisMap<ND>* out
 }
 
 // Rows of N 16-bit results in pieces of 64 columns: streaming stores, unless rows are not whole 64-byte units and C is larger
-// than the L2 caches (8 x 4 MB), which then write every unit at a piece's end twice, half filled (LayerNorm + linear, us,
-// streaming / plain: 13942 x 128 -> 2448 38.7 / 20.3, 54670 x 64 -> 472 24.9 / 14.3; below, or with whole units: 58088 x 96 ->
-// 288 12.2 / 15.3, 73324 x 96 -> 72 10.5 / 12.4).
-inline bool streaming_rows(int64_t M, int64_t N) { return N % 32 == 0 || M * N * 2 < (32ll << 20); }
+// than what the L2 caches (8 x 4 MB) keep of it: every unit at a piece's end is then written twice, half filled.  LayerNorm + linear,
+// plain : streaming over 79 such shapes, 0.97 up to 20 MB (0.93 to 1.10), 0.92 from there to 32 MB, 0.70 above (us: 10076 x 256 ->
+// 1304 17.9 / 20.7, 31074 x 128 -> 2480 41.1 / 83.6, 86546 x 128 -> 3496 131 / 300); over 51 of whole units 1.06 up to 60 MB.
+inline bool streaming_rows(int64_t M, int64_t N) { return N % 32 == 0 || M * N * 2 < (20ll << 20); }
 
 // Elements of its source that a piece with one stage can reach, counted from the piece's base: the farthest one that its
 // digits name (a source's rows may lie apart; the entries of a table over a Concat count from the first of its
