@@ -341,20 +341,22 @@ int launch_ring(RingParams P, int mb, int groups, hipStream_t st) {
 // Rows per workgroup and groups of columns (each normalises its rows again), or false where the kernel that streams W
 // through registers is the better one.  The model, fitted over 238 shapes (K 128 to 512, N 200 to 4 K, M 324 to 96100)
 // and every choice there: rounds of 256 workgroups of 2.5 us each, LayerNorm 0.36 us per 32 rows x 64 features, and per four
-// tiles of 64 columns (one wave of each SIMD) what W's arrival, the product and the stores take.  What it picks takes 0.9 %
-// longer than the best choice on average, and 0.86 of the time of the other kernel.  Some of them (bf16, us):
+// tiles of 64 columns (one wave of each SIMD) what W's arrival, the product and the stores take.  Some of them (bf16, us):
 //   M x K -> N           other kernel   64 rows   96   128   160
 //   25088 x 256 -> 768       21            22     28    18    20
 //   21904 x 512 -> 512       45            30     20     -     -
 //   33600 x 192 -> 768       34            31     27    32    22
 //   12544 x 192 -> 768       12.8          10.3   11.7  13.1  14.9
 //    7744 x 256 -> 768       10.5     8.9 in two groups
-//    1600 x 384 -> 1536      12.9     11.7 in eight groups
-// The other kernel stays for fewer than 1024 rows (324 x 512 -> 2048: 11.1 against 12.1, 588 x 384 -> 384: 9.7 against 9.9), for at most 256 columns where its
-// blocks of 64 rows make one round (4096 x 192 -> 200, f16: 6.0 against 6.6), and for more than 384 features where
-// its blocks of 128 rows, which do not fit here, need fewer rounds than blocks of 96 (24964 x 512 -> 512: 26 against 29).
+// The other kernel stays for fewer than 1024 rows (324 x 512 -> 2048: 11.1 against 12.1, 588 x 384 -> 384: 9.7 against 9.9); for more than 384
+// features where its blocks of 128 rows, which do not fit here, need fewer rounds than blocks of 96 (24964 x 512 -> 512: 26 against
+// 29); and where its blocks of 64 rows make one round with less than a tile for each of its eight waves, if there are up to
+// 256 columns (4096 x 192 -> 200, f16: 6.0 against 6.6), rows are not whole 64-byte units, whose pieces are stored
+// slower here, or the choice here would be taller blocks that several groups normalise again (5058 x 192 -> 768: 28 % longer here).
+// At 750 shapes drawn apart (M from 1000, two thirds of them below 18000, operands in turn) the choice takes 1.3 % longer
+// than the best one on average, 25 % at most, 27 of them more than 10 %.  (Without the last two: 2.9 %, 90 of them.)
 bool choose_ring(int64_t M, int64_t N, int64_t K, int* mb_out, int* groups_out) {
-  if (M < 1024 || (N <= 256 && M <= 256 * 64)) return false;
+  if (M < 1024) return false;
   auto rounds = [](int64_t wgs) { return (wgs + 255) / 256; };
   if (K > 384 && M >= 192 * 128 && M <= 512 * 128 && rounds((M + 95) / 96) > rounds((M + 127) / 128)) return false;
   const int64_t tiles = (N + TBN - 1) / TBN, k = K / 64;
@@ -370,6 +372,10 @@ bool choose_ring(int64_t M, int64_t N, int64_t K, int* mb_out, int* groups_out) 
         *mb_out = mb, *groups_out = g;
       }
     }
+  }
+  if (best != 0 && M <= 256 * 64) {
+    const int64_t groups = std::max<int64_t>(1, std::min(256 / ((M + 63) / 64), (tiles + 1) / 2));   // the other kernel's
+    if ((tiles + groups - 1) / groups < 8 && (N <= 256 || N % 32 || (*mb_out >= 3 && *groups_out > 1))) return false;
   }
   return best != 0;
 }

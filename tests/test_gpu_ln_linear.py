@@ -187,8 +187,8 @@ def test_weight_slice_kernel(gpu, B, R, win, C, N, dtype):
         check(tio.to_host_f64(p.out).reshape(ref.shape), run_workload(wl)["out"])
 
 
-# From 1024 rows (or 16384 of at most 256 columns) and 128 features (multiples of 64) on: every height of a block with its ragged last one, one to
-# eight groups of columns, waves with no, one and two tiles, ragged columns, rows of odd and even multiples of 128 bytes
+# From 1024 rows and 128 features (multiples of 64) on: ragged last blocks, waves with no, one and two tiles, ragged columns, rows of odd and even
+# multiples of 128 bytes (on either of the kernels that stream the weight; which one runs, and in how many groups, is seen below)
 @pytest.mark.parametrize("B,R,win,C,N,dtype", [(1, 33, 1, 128, 392, "bf16"), (1, 130, 5, 192, 8, "f16"), (1, 35, 5, 320, 712, "bf16"),
                                                 (1, 40, 5, 384, 1032, "f16"), (1, 91, 7, 256, 520, "bf16"), (1, 158, 2, 128, 520, "f16"), (1, 147, 7, 512, 72, "f16"),
                                                 (1, 149, 1, 256, 264, "f16"), (1, 162, 9, 384, 136, "bf16"), (1, 183, 3, 192, 584, "bf16"),
@@ -225,9 +225,11 @@ def test_weight_ring_kernel(gpu, B, R, win, C, N, dtype):
         check(tio.to_host_f64(p.out).reshape(ref.shape), run_workload(wl)["out"])
 
 
-# Two and three tiles for a wave (waits that count the stores of the tile before), in blocks of every height with either ring;
-# streaming and plain stores, ragged columns and a ragged last block
-@pytest.mark.parametrize("M,C,N,dtype,instance", [(16650, 384, 1120, "bf16", (3, 32, 4)), (16650, 512, 1096, "f16", (3, 32, 4)),
+# No tile for some waves, one, and up to four (waits that count the stores of the tile before), in blocks of every height with either
+# ring, in one group of columns and several; streaming and plain stores, ragged columns and a ragged last block
+@pytest.mark.parametrize("M,C,N,dtype,instance", [(1030, 512, 7688, "bf16", (2, 32, 6)), (3100, 192, 4104, "f16", (2, 16, 6)), (2130, 256, 3976, "bf16", (3, 16, 6)),
+                                                   (16900, 192, 8, "f16", (3, 16, 6)), (26250, 384, 136, "bf16", (4, 32, 4)), (8290, 256, 520, "f16", (2, 16, 6)),
+                                                   (16650, 384, 1120, "bf16", (3, 32, 4)), (16650, 512, 1096, "f16", (3, 32, 4)),
                                                    (24650, 384, 1096, "bf16", (4, 32, 4)), (24650, 320, 1120, "f16", (4, 32, 4)),
                                                    (24650, 192, 1096, "bf16", (4, 16, 6)), (33130, 192, 1120, "f16", (5, 16, 4)),
                                                    (12330, 448, 1544, "bf16", (2, 32, 6))])
@@ -254,7 +256,7 @@ def test_ring_of_several_tiles(gpu, kernels, M, C, N, dtype, instance):
 
 # W in registers, a slice of it, through LDS (both: streaming and, from 32 MiB of ragged rows on, plain stores), through registers
 @pytest.mark.parametrize("M,C,N,dtype,kernel", [(1000, 128, 384, "bf16", "k_ln_gemm"), (33000, 96, 328, "f16", "k_ln_gemm_slice"), (33500, 64, 520, "bf16", "k_ln_gemm_slice"),
-                                                (1681, 256, 1560, "bf16", "k_ln_gemm_ring"), (8281, 320, 1040, "f16", "k_ln_gemm_ring"), (17000, 128, 1032, "bf16", "k_ln_gemm_ring"),
+                                                (1681, 256, 4104, "bf16", "k_ln_gemm_ring"), (8281, 320, 1040, "f16", "k_ln_gemm_ring"), (17000, 128, 1032, "bf16", "k_ln_gemm_ring"),
                                                 (400, 256, 72, "bf16", "k_ln_gemm_wide")])
 def test_rows_through_a_table_and_a_weight_with_rows_apart(gpu, kernels, M, C, N, dtype, kernel):
     """Rows gathered through an index table and a W that is a range of a wider matrix's columns: the same kernel as on dense
@@ -296,8 +298,8 @@ def test_subnormal_variance_without_eps(gpu, C):
 
 
 # the kernel that holds W, the one that holds a slice of it, those that stream it through LDS and through registers, the generic one
-@pytest.mark.parametrize("R,C,N,kernel", [(20, 128, 384, "k_ln_gemm<"), (182, 96, 72, "k_ln_gemm_slice<"), (40, 256, 264, "k_ln_gemm_ring<"),
-                                          (35, 512, 264, "k_ln_gemm_ring<"), (20, 256, 72, "k_ln_gemm_wide<"), (20, 36, 24, "k_gemm_generic<")])
+@pytest.mark.parametrize("R,C,N,kernel", [(20, 128, 384, "k_ln_gemm<"), (182, 96, 72, "k_ln_gemm_slice<"), (130, 256, 264, "k_ln_gemm_ring<"),
+                                          (130, 512, 264, "k_ln_gemm_ring<"), (35, 512, 264, "k_ln_gemm_wide<"), (20, 256, 72, "k_ln_gemm_wide<"), (20, 36, 24, "k_gemm_generic<")])
 def test_squares_past_the_range_of_fp32(gpu, kernels, R, C, N, kernel):
     """Rows of +-1e19 in bf16: finite, but their squares sum to infinity, whose reciprocal root is zero, and with it the row;
     the rows beside them are not touched (bound as in test_weight_streamed_kernel)."""
