@@ -47,7 +47,6 @@ struct RingParams {
   int32_t M, N, K;
   float eps;
   int32_t tiles_per_group;        // column tiles of one workgroup, dealt to its waves in turn
-  int32_t stream;                 // 16-bit results leave as streaming stores
 };
 
 // at most N vector memory operations outstanding, no LDS operation
@@ -64,8 +63,9 @@ __device__ __forceinline__ float row_sum(float v) {
   return v;
 }
 
-// MB blocks of 32 rows per workgroup; LP2 lanes hold a row, two chunks of 8 elements each: K <= 16 * LP2; rings of STAGES
-template <typename T, bool C_F32, int MB, int LP2, int STAGES>
+// MB blocks of 32 rows per workgroup; LP2 lanes hold a row, two chunks of 8 elements each: K <= 16 * LP2; rings of STAGES.
+// STREAM: 16-bit results leave as streaming stores (asked for in the kernel, both kinds' code costs 0.15 us a launch).
+template <typename T, bool C_F32, bool STREAM, int MB, int LP2, int STAGES>
 __global__ void __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
 k_ln_gemm_ring(const RingParams P) {
   typedef Mma<T> M_;
@@ -264,21 +264,13 @@ k_ln_gemm_ring(const RingParams P) {
           for (int j = 0; j < 4; ++j)
             *reinterpret_cast<uint2*>(turn + l32 * 128 + (((nb * 4 + j) ^ (l32 >> 1 & 7)) * 16) + lh * 8) =
                 make_uint2(pack2<T>(acc[nb][mb][4 * j], acc[nb][mb][4 * j + 1]), pack2<T>(acc[nb][mb][4 * j + 2], acc[nb][mb][4 * j + 3]));
-        u32x4 v[4];
-        uint32_t off[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           const int rr = q * 8 + (lane >> 3), ch = lane & 7;   // 8 lanes per row of 64 columns
-          v[q] = __builtin_bit_cast(u32x4, *reinterpret_cast<const uint4*>(turn + rr * 128 + ((ch ^ (rr >> 1 & 7)) * 16)));
+          const u32x4 v = __builtin_bit_cast(u32x4, *reinterpret_cast<const uint4*>(turn + rr * 128 + ((ch ^ (rr >> 1 & 7)) * 16)));
           const int col = tile * TBN + ch * 8;
-          off[q] = col < N ? (uint32_t)((mb * 32 + rr) * N + col) * 2u : 0x80000000u;
-        }
-        if (P.stream) {                                // whole lines, not read again here (asked once for the four: 18.1 -> 17.9 us)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) __builtin_amdgcn_raw_buffer_store_b128(v[q], rsrc, (int)off[q], 0, 2);
-        } else {
-#pragma unroll
-          for (int q = 0; q < 4; ++q) __builtin_amdgcn_raw_buffer_store_b128(v[q], rsrc, (int)off[q], 0, 0);
+          const uint32_t off = col < N ? (uint32_t)((mb * 32 + rr) * N + col) * 2u : 0x80000000u;
+          __builtin_amdgcn_raw_buffer_store_b128(v, rsrc, (int)off, 0, STREAM ? 2 : 0);   // (streaming: whole lines, not read again here)
         }
       }
     }
@@ -322,14 +314,14 @@ k_ln_gemm_ring(const RingParams P) {
 // LDS of blocks of 32 mb rows and of the shortest rings
 bool rows_fit(int mb, int K) { return mb * 32 * K * 2 + kWaves * 4 * kStage <= kLds && (mb < 5 || K <= 256); }
 
-template <typename T, bool C_F32>
+template <typename T, bool C_F32, bool STREAM>
 int launch_ring(RingParams P, int mb, int groups, hipStream_t st) {
   const int tiles = (P.N + TBN - 1) / TBN;
   P.tiles_per_group = (tiles + groups - 1) / groups;
   const dim3 grid((unsigned)((P.M + mb * 32 - 1) / (mb * 32)), (unsigned)((tiles + P.tiles_per_group - 1) / P.tiles_per_group));
 #define VT_RING(MB, LP2, S)                                                                             \
   if (mb == MB && (P.K <= 256) == (LP2 == 16) && MB * 32 * P.K * 2 + kWaves * S * kStage <= kLds) {     \
-    hipLaunchKernelGGL((k_ln_gemm_ring<T, C_F32, MB, LP2, S>), grid, dim3(kWaves * 64), 0, st, P);      \
+    hipLaunchKernelGGL((k_ln_gemm_ring<T, C_F32, STREAM, MB, LP2, S>), grid, dim3(kWaves * 64), 0, st, P);      \
     return check_launch("vt_gemm(layernorm)");                                                          \
   }
   VT_RING(2, 16, 6) VT_RING(3, 16, 6) VT_RING(4, 16, 6) VT_RING(5, 16, 4)   // (160 rows: longer rings spill)
@@ -422,12 +414,12 @@ int ln_gemm_ring_launch(const vt_desc& A, const vt_desc& B, void* C, int c_dtype
   P.N = (int32_t)N;
   P.K = (int32_t)K;
   P.eps = eps;
-  P.stream = streaming_rows(M, N);
   int mb = 0, groups = 1;
   if (!choose_ring(M, N, K, &mb, &groups)) return fail(VT_ERR_UNSUPPORTED, no);
-  const bool c32 = c_dtype == VT_F32;
-  if (A.dtype == VT_BF16) return c32 ? launch_ring<bf16_t, true>(P, mb, groups, st) : launch_ring<bf16_t, false>(P, mb, groups, st);
-  return c32 ? launch_ring<f16_t, true>(P, mb, groups, st) : launch_ring<f16_t, false>(P, mb, groups, st);
+  const bool c32 = c_dtype == VT_F32, stream = streaming_rows(M, N);
+  if (A.dtype == VT_BF16)
+    return c32 ? launch_ring<bf16_t, true, false>(P, mb, groups, st) : stream ? launch_ring<bf16_t, false, true>(P, mb, groups, st) : launch_ring<bf16_t, false, false>(P, mb, groups, st);
+  return c32 ? launch_ring<f16_t, true, false>(P, mb, groups, st) : stream ? launch_ring<f16_t, false, true>(P, mb, groups, st) : launch_ring<f16_t, false, false>(P, mb, groups, st);
 }
 
 }  // namespace vt
