@@ -210,7 +210,7 @@ int vt_weighted_sum(const vt_desc* x, const vt_desc* y, const float* weights, vo
  * prologue = VT_GEMM_LAYERNORM applies per-row LayerNorm (gamma 1, beta 0, eps) over K to A,
  * rounded to the operand dtype, before the product, inside the load stage (the normalised
  * tensor is never stored).  The fused kernels take contiguous, 16-byte aligned rows of A, K <= 1024
- * and a row-major W, K and N multiples of 8 (K = 64 or 128 with N <= 384 keeps W in registers);
+ * and a row-major W, K and N multiples of 8 (W stays in registers or streams past rows in LDS, by the sizes);
  * other shapes and maps run on the generic kernel with the same prologue (far slower).
  * A, B, C are host arrays of n_groups pointers. */
 typedef enum { VT_GEMM_PLAIN = 0, VT_GEMM_LAYERNORM = 1 } vt_gemm_prologue;

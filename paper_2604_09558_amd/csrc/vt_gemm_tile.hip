@@ -14,8 +14,8 @@
 // the fragment reads free of bank conflicts (4.3 million conflict cycles per launch without it, 4600
 // with it, 333 x 4096 x 4096) is applied to what a lane asks for.  Waits count the requests by hand: a wave issues the
 // same number in every stage and nothing else that goes through the vector memory counter.
-// Measured (f16/bf16, K = 4096, operands in HBM / in the caches, us): 333 x 4096 30.5 / 21.8 (256 x 256 tiles 88 / 83),
-// 400 x 6144 34.5 / 30.0 (90 / 84), 1024 x 4096 43.3 / 36.5 (89 / 80); the requests of the first without anything
+// Measured (f16/bf16, K = 4096, operands in HBM / in the caches, us): 333 x 4096 32.5 / 22.2 (256 x 256 tiles 88 / 83),
+// 400 x 6144 37.3 / 31.6 (90 / 84), 1024 x 4096 43.3 / 36.5 (89 / 80); the requests of the first without anything
 // else 27.4 / 18.1.  A step of 64 x 128 takes 265 ns there, of which the requests need 231.  Rings twice as
 // deep, and waves divided over K instead of over the tile (half the LDS reads), measured no faster.
 // Few tiles (a short prompt) leave most of the chip idle, and a step of 64 x 64 then takes 0.2 us on a chain of barrier,

@@ -1,8 +1,9 @@
 // LayerNorm fused into the load stage of a GEMM whose weight does not fit the registers of one
 // workgroup: C = LN(A) . W, A virtual [.., K] with contiguous rows, K <= 1024, W a row-major [K, N]
 // matrix, any N (K and N multiples of 8).  (vt_ln_gemm.hip and vt_ln_gemm_slice.hip keep W in registers for up to
-// 128 features; vt_ln_gemm_ring.hip takes most calls of 128 to 512 features in multiples of 64 from 1024 rows on.)  Bound by HBM at small K (a token's K values are read once and its N outputs written
-// once), by the matrix pipes and the reads of W from L2 as K and N grow.
+// 128 features; vt_ln_gemm_ring.hip takes most calls of 128 to 512 features in multiples of 64 with many rows.)
+// Bound by HBM at small K (a token's K values are read once and its N outputs written once), by the matrix pipes and
+// the reads of W from L2 as K and N grow.
 //
 // A workgroup takes 64 or 128 rows: they are fetched through the map (16 bytes per lane, LP2 lanes per row,
 // one lane evaluates a row's offset for the wave), normalised in registers (fp32, two passes), rounded
@@ -17,9 +18,9 @@
 // next two K steps in flight while one is multiplied.  A lane ends up with 4 consecutive columns of a
 // row; a wave turns 16 rows at a time round in LDS and leaves with whole 128-byte row segments.
 // (64 rows x 128 columns per wave spilled; four or six register sets measured no faster than three.)
-// 25088 x 256 -> 768, bf16 (51.8 MB, 9.9 GFLOP): 21 us (27 us with inputs cold in every cache; 18 through the rings); 2295 us on
-// the generic kernel, which evaluates the map for every element of A and W.  What is left is latency: rows,
-// statistics and W follow each other inside a workgroup, and only two or three waves per SIMD overlap
+// 25088 x 264 -> 768, bf16 (51.8 MB, 10.2 GFLOP): 25.6 us; 25088 x 256 -> 768 27 us with inputs cold in every cache (24
+// through the rings, which take it), 2295 us on the generic kernel, which evaluates the map for every element of A and W.  What is
+// left is latency: rows, statistics and W follow each other inside a workgroup, and only two or three waves per SIMD overlap
 // (of the 27 us the matrix pipes of a working unit are busy 5, the vector instructions 7; counters:
 // profiles/small_tiles_streamed_ln_split_rowsum.txt).
 #include <hip/hip_runtime.h>
@@ -34,7 +35,6 @@ using namespace vt;
 using namespace vt::gemm;
 
 namespace {
-
 
 constexpr int WBN = 64;           // columns per wave
 constexpr int kMaxWaves = 8;
@@ -263,12 +263,12 @@ k_ln_gemm_wide(const WideParams P) {
 }
 
 // 128 rows per workgroup halve the reads of W and the rounds, once there are workgroups for most of
-// the chip's 256 units (measured, us, 64 / 128 rows: 25088 x 256 -> 768: 28.0 / 26.2, 25088 x 512 -> 2048: 100 / 80,
-// 100352 x 128 -> 512: 45 / 43, but 18432 x 192 -> 200: 11.2 / 12.0 and 1568 x 512 -> 1536: 14.2 / 21.1).
+// the chip's 256 units (measured, us, 64 / 128 rows: 25088 x 264 -> 768: 43.7 / 25.6, 25088 x 328 -> 1312: 83 / 41,
+// 100352 x 72 -> 288: 28.2 / 26.5, but 18432 x 200 -> 200: 10.8 / 11.6 and 1568 x 328 -> 1312: 12.1 / 18.7).
 // Waves: four, two workgroups sharing a compute unit, or eight where there is at most one workgroup
-// per unit (100352 x 96 -> 288: 32.4 / 34.6 with four / eight, 25088 x 256 -> 768: 34.5 / 26.2).
+// per unit (100352 x 72 -> 288: 26.4 / 30.8 with four / eight, 25088 x 264 -> 768: 36.4 / 25.6).
 // Column groups only to reach the units that the rows leave idle: each group normalises its rows
-// again (25088 x 256 -> 768 in one / two / four groups: 28.0 / 33.1 / 38).
+// again (25088 x 264 -> 768 in one / two / four groups: 25.6 / 35.8 / 61; 1568 x 328 -> 1312: 23.5 / 17.2 / 12.8).
 template <typename T, bool C_F32>
 int launch_wide(const WideParams& P, hipStream_t st) {
   const int tiles = (P.N + WBN - 1) / WBN;
