@@ -2,8 +2,8 @@
 // virtual-tensor descriptors (Sec. 3.1: the attention kernel reads the un-expanded cache and
 // the freshly projected K/V rows where the producer left them).  gfx950, wave64, MFMA.
 //
-// Work split: one workgroup per (batch b, kv head g, context split s); WAVES waves share the
-// split's rows in tiles of 32.  All G query heads of the group are served from one read of
+// Work split: one workgroup per (batch b, kv head g, context split s); WAVES waves (four or eight, choose_splits)
+// share the split's rows in tiles of 32.  All G query heads of the group are served from one read of
 // K and V (the broadcast digit of the descriptor, i.e. the Expand that is never executed).
 // The context is cut into segments at the piece boundaries of the two descriptors (the
 // Concat that is never executed).  Inside a segment a row address is one wave-uniform base
@@ -110,7 +110,7 @@ struct AttnArgs {
   int32_t n_seg;
   const char* q_ptr;
   int64_t q_sb, q_sh;    // bytes
-  int32_t B, Hkv, G, S, D, n_splits, rows_per_split;
+  int32_t B, Hkv, G, S, D, n_splits, rows_per_split, waves;
   int32_t ticket_step;   // words between two counters
   int32_t batch_table;   // some operand finds a sequence's rows through a table over the batch
   float scale_log2;      // softmax scale * log2(e)
@@ -1132,19 +1132,55 @@ int most_splits(int units, int S, int n_splits) {
   return std::min(want, max_splits);
 }
 
-// Two workgroups per compute unit (the 64-wide heads' tiles are half as many bytes, but four are no
-// faster: 16 sequences x 8 kv heads x 2368 keys 18.3 us with 4 splits and 1.3 more with 8), or one, where
-// the units divide the chip's 256 compute units almost evenly and there are few of them: every split costs its partial
-// results and a share of the merge.  More than 16 splits only while each keeps 352 rows.
-//   units x keys, us with 512 / units, 256 / units and this rule's splits (128-wide heads, 4 a group):
-//   8 x 8192  23.3 (64) 16.5 (32) 15.3 (24)     8 x 4096  14.2 (32) 14.2 (32) 11.8 (16)     1 x 8192  15.8 (64)  13.2 (24)
-//   16 x 4096 18.7 (32) 14.4 (16)               32 x 2048 14.7 (16) 12.0 (8)                32 x 8192 28.2 (16)  25.8 (8)
-//   64 x 4096 25.9 (8)  25.8 (4)                128 x 2048 25.8 (4) 25.8 (2)
-int choose_splits(int units, int S, int n_splits, int64_t D) {
-  if (n_splits > 0) return n_splits;
-  int ns = most_splits(units, S, 0);
-  if (D == 128 && units < 64 && 256 / units * units >= 230) ns = std::min(ns, 256 / units);
-  return std::min(ns, std::max(16, (S + 351) / 352));
+// Splits of the context and waves of a workgroup.  What decides, in the order of the lines below (a compute unit holds one
+// workgroup of eight waves, or two or three of four):
+//   up to 128 keys   one 32-row tile for each of four waves: one split, whose workgroup has the result (a merge is 2.2 us of 7.3)
+//   up to 256        one for each of eight
+//   129 units and more   one split of eight waves on a compute unit, with nothing to merge; up to 160 units of 64-wide heads
+//                    that leaves too much of the chip idle from 1025 keys on, and above 224 units of 128-wide ones, which draw what
+//                    the memory gives, four waves are better from 513 on
+//   96 to 128 units  one split of eight waves up to 65536 rows in all of 128-wide heads, else 512 / units, or 256 / units of them from 1537 keys on
+//   64-wide heads    two workgroups of four waves per compute unit, eight waves from 4096 keys of few units on
+//   128-wide heads   one workgroup per compute unit, and up to 16 splits or what leaves each 352 rows: every split costs its partial results and a
+//                    share of the merge.  From 33 units on 2049 to 4096 keys have two per compute unit (the two are within 2 % there).
+// Contexts of more than two segments have four waves only, and 512 / units or 256 / units splits; so have more than 256 units.
+//   units x keys, us with (waves x splits)
+//   8 x 200    7.4 (4 x 2)   6.9 (8 x 1)         1 x 8192   13.5 (4 x 24)  12.0 (8 x 24)     8 x 8192    13.6 (4 x 24)  12.5 (8 x 24)
+//   64 x 2048  16.3 (4 x 8)  15.7 (4 x 4)        64 x 8192  46.5 (4 x 8)   43.8 (4 x 4)      64 x 4096   26.1 (4 x 8)   25.2 (4 x 4)
+//   128 x 512  10.6 (4 x 4)  10.7 (8 x 1)        128 x 2048 25.5 (4 x 4)   25.1 (4 x 2)      128 x 4096  46.1 (4 x 4)   43.4 (4 x 2)
+//   160 x 512  12.6 (4 x 3)  11.1 (8 x 1)        192 x 2048 40.6 (4 x 3)   33.1 (8 x 1)      256 x 4096  85.8 (4 x 2)   77.7 (4 x 1)  82.5 (8 x 1)
+//   64-wide: 8 x 8192  12.1 (4 x 24)  11.8 (8 x 24)    128 x 2048  15.8 (4 x 4)  20.3 (8 x 1)    160 x 2048  19.1 (4 x 4)  19.7 (8 x 1)
+//            192 x 2048  22.7 (4 x 3)  20.5 (8 x 1)    256 x 4096  44.6 (4 x 2)  42.8 (8 x 1)
+struct Splits {
+  int n, waves;
+};
+Splits choose_splits(int units, int S, int n_splits, int64_t D, int n_seg) {
+  if (n_splits > 0) return {n_splits, 4};
+  const int most = most_splits(units, S, 0), per_unit = std::max(1, 256 / units);
+  const int few_rows = std::max(16, (S + 351) / 352);
+  if (n_seg > 2 || units > 256)
+    return {std::min(D == 128 && units < 64 && per_unit * units >= 230 ? std::min(most, per_unit) : most, few_rows), 4};
+  if (S <= 128) return {1, 4};
+  if (S <= 256) return {1, 8};
+  if (units > 128) {
+    if (D == 64 && units <= 160 && S > 1024) return {most, 4};
+    return {1, D == 128 && units > 224 && S > 512 ? 4 : 8};
+  }
+  if (units >= 96) {
+    if (D == 128 && (int64_t)units * S <= 65536) return {1, 8};
+    return {D == 128 && S > 1536 ? std::min(most, per_unit) : most, 4};
+  }
+  Splits c = D == 64 ? Splits{std::min(S >= 4096 && units <= 32 ? per_unit : 512 / units, 24), S >= 4096 && units <= 32 ? 8 : 4}
+             : units > 32 && S > 2048 && S <= 4096 ? Splits{std::min(most, few_rows), 4}
+                                                  : Splits{std::min(per_unit, few_rows), units <= 32 && S >= 2560 ? 8 : 4};
+  c.n = std::min(c.n, most);
+  // a quarter more splits where that saves every wave a tile (46 units x 735 keys: 9.7 us with 5 splits of 160 rows, 9.1 with 6)
+  const int tiles = ((S + c.n - 1) / c.n + 32 * c.waves - 1) / (32 * c.waves);
+  if (tiles > 1) {
+    const int more = (S + (tiles - 1) * 32 * c.waves - 1) / ((tiles - 1) * 32 * c.waves);
+    if (more <= most && more * 4 <= c.n * 5 && (c.waves == 4 || more <= per_unit)) c.n = more;
+  }
+  return c;
 }
 
 constexpr int kWaves = 4;
@@ -1288,7 +1324,8 @@ static int plan_attention(const vt_desc* Q, const vt_desc* K, const vt_desc* V, 
     if ((uintptr_t)P.q_ptr % 16 || P.q_sb % 16 || P.q_sh % 16) return fail(VT_ERR_UNSUPPORTED, "Q: rows are not 16-byte aligned");
   }
   const int Hkv = (int)(Hq / G);
-  int ns = B * Hkv > kCounters ? 1 : choose_splits((int)B * Hkv, (int)S, n_splits, D);
+  const Splits chosen = B * Hkv > kCounters ? Splits{1, kWaves} : choose_splits((int)B * Hkv, (int)S, n_splits, D, P.n_seg);
+  int ns = chosen.n;
   if (n_splits == 0 && D == 64) ns = std::min(ns, (int)(kWaves * kTile * D / 4 / G));   // what the merge below has room for
   int rows = (int)((S + ns - 1) / ns);
   rows = (rows + kTile - 1) / kTile * kTile;
@@ -1302,6 +1339,7 @@ static int plan_attention(const vt_desc* Q, const vt_desc* K, const vt_desc* V, 
   P.D = (int)D;
   P.batch_table = ko.batch_table || vo.batch_table;
   P.n_splits = ns_eff;
+  P.waves = chosen.waves;
   P.rows_per_split = rows;
   return VT_OK;
 }
@@ -1394,9 +1432,11 @@ static int launch_attention(const vt_desc* Q, const vt_desc* K, const vt_desc* V
     static_cast<AttnArgs&>(P2) = P;
     for (int i = 0; i < 2; ++i) P2.seg[i] = P.seg[i];
   }
+  // (eight waves: one workgroup on a compute unit, two waves per SIMD, whatever registers they need)
 #define VT_ATTN_NS(TT, DD, MM, RR, OCC)                                                                               \
   do {                                                                                                                \
-    if (few) hipLaunchKernelGGL((k_decode_attn<TT, DD, MM, RR, 2, kWaves, OCC>), grid, dim3(kWaves * 64), 0, st, P2);     \
+    if (few && P.waves == 8) hipLaunchKernelGGL((k_decode_attn<TT, DD, MM, RR, 2, 8, 2>), grid, dim3(8 * 64), 0, st, P2); \
+    else if (few) hipLaunchKernelGGL((k_decode_attn<TT, DD, MM, RR, 2, kWaves, OCC>), grid, dim3(kWaves * 64), 0, st, P2); \
     else hipLaunchKernelGGL((k_decode_attn<TT, DD, MM, RR, kMaxSegs, kWaves, OCC>), grid, dim3(kWaves * 64), 0, st, P);   \
   } while (0)
 #define VT_ATTN(TT, DD, RR, OCC)                                                                                      \

@@ -314,6 +314,26 @@ def test_merge_of_many_splits(gpu, Hkv, G, D, S, ns):
     assert torch.equal(p.out, first)
 
 
+# eight waves: one split whose last tiles are short, missing or continue in the appended row (129, 250, 256 keys), sixteen
+# heads, more than 128 units; several splits and more than eight of them, and the counters of few pairs lines apart
+@pytest.mark.parametrize("B,Hkv,G,D,S", [(1, 2, 4, 128, 129), (2, 1, 16, 128, 250), (1, 2, 7, 64, 256), (17, 8, 1, 64, 300), (33, 4, 2, 128, 270),
+                                         (1, 1, 8, 128, 2600), (4, 8, 2, 128, 2561), (1, 2, 4, 64, 4100)])
+@pytest.mark.parametrize("paged", [False, True])
+def test_eight_waves(gpu, B, Hkv, G, D, S, paged):
+    vt, tio, pipelines, torch = gpu
+    wl = workloads.paged_decode_attention(seed=21, B=B, Hkv=Hkv, G=G, pages_per_seq=(S + 31) // 32, page=32, D=D) if paged else \
+        workloads.c2_decode_attention(seed=21, B=B, Hkv=Hkv, G=G, S=S, D=D)
+    ref = run_workload(wl)
+    p = pipelines.run_decode_attention(tio.DeviceWorkload(wl))["pipeline"]
+    first = p.out.clone()
+    assert np.max(np.abs(tio.to_host_f64(p.out) - ref["out"])) <= 8e-3        # 2^-9 of outputs up to 2, and of every weight
+    assert np.max(np.abs(tio.to_host_f64(p.lse) - ref["lse"])) <= 1e-3
+    for _ in range(3):
+        p.run()
+    torch.cuda.synchronize()
+    assert torch.equal(p.out, first)
+
+
 @pytest.mark.parametrize("B,Hkv,G,D,page", [(3, 2, 4, 128, 64), (5, 1, 7, 64, 32), (2, 2, 1, 128, 128)])
 def test_one_page_per_sequence(gpu, B, Hkv, G, D, page):
     """The table digit sits in the batch dim: planned, with the probabilities' fp32 value in the product, as in
