@@ -6,14 +6,14 @@
 // only the store stage of the kernel changes).  gfx950, wave64, v_mfma_f32_16x16x32.
 //
 // The kernel is bound by reading B (the weight) once from HBM.  Work split: one workgroup per
-// (128-column block, slice of K, block of 16 rows); its 4 waves take tiles of 32 k-rows.  Per
+// (128-column block, slice of K, block of 16 rows); its 4 or 8 waves take tiles of 32 k-rows.  Per
 // tile a lane loads 8 rows of its own 8-column chunk of B (whole 256-byte row segments per 16
 // lanes), transposes the 8x8 block inside its registers (v_perm_b32) and feeds it as the MFMA's
 // first operand, C^T += B^T . A^T; the contraction index is permuted identically for A, whose
 // fragment is two 8-byte loads per lane.  B never touches LDS.  The waves of a workgroup are
 // summed through LDS, the K slices through a workspace: the workgroup that finishes last for a
 // (column block, row block) adds the partial sums in slice order (a ticket counter; no second
-// launch, no spinning, bitwise reproducible) and performs the mapped store.
+// launch, no spinning, bitwise reproducible) and performs the mapped store.  One slice is stored at once.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -34,6 +34,7 @@ VT_PROF_DECLARE(gemm_store)
 
 namespace vt {
 int gemm_store_launch(const vt_desc& A, const vt_desc& B, const vt_desc& Cd, int64_t below_ns, hipStream_t st);   // vt_gemm.hip
+int64_t gemm_tile_estimate_ns(int64_t M, int64_t N, int64_t K, int64_t ldb);                                       // vt_gemm_tile.hip
 }
 
 namespace {
@@ -41,7 +42,6 @@ namespace {
 constexpr int kBN = 128;          // columns per workgroup
 constexpr int kBM = 16;           // rows per workgroup (one MFMA block)
 constexpr int kTileK = 32;        // k-rows per wave step
-constexpr int kWaves = 4;
 constexpr int kMaxOutPieces = 4;
 constexpr int kTiledFrom = 128;   // more rows than this always go to the tiled kernels
 
@@ -63,8 +63,9 @@ struct StoreParams {
   int32_t n_out;
   int32_t M, N, K;
   int32_t n_splits, k_per_split;   // k_per_split is a multiple of kTileK
+  int32_t ticket_step;     // words between two counters
   uint32_t* tickets;       // [row blocks][column blocks] (with one slice: not used), zero between launches
-  float* partial;          // [row blocks][column blocks][n_splits][kBM][kBN]
+  float* partial;          // [row blocks][column blocks][n_splits][kBM][kBN] (one slice: not used)
 };
 
 struct Regs16 {
@@ -80,7 +81,8 @@ __device__ __forceinline__ Regs16 load16(const char* p) {
   return r;
 }
 
-template <typename T>
+// kWaves = 4 or 8 (see vt_gemm_store)
+template <typename T, int kWaves>
 __global__ void __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 2))) k_gemm_store(const StoreParams P) {
   typedef Mma16<T> M_;
   typedef typename M_::vec opvec;
@@ -184,8 +186,8 @@ __global__ void __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_e
   // front of each of the dependent steps below)
   uint32_t* a_tickets = P.tickets;
   float* a_partial = P.partial;
-  int a_ns = P.n_splits, a_nout = P.n_out;
-  asm volatile("" : "+s"(a_tickets), "+s"(a_partial), "+s"(a_ns), "+s"(a_nout));
+  int a_ns = P.n_splits, a_nout = P.n_out, a_tstep = P.ticket_step;
+  asm volatile("" : "+s"(a_tickets), "+s"(a_partial), "+s"(a_ns), "+s"(a_nout), "+s"(a_tstep));
 
   // ---- sum the waves through LDS.  acc[e][i] is C[m = l16][n = (lg*4 + i)*8 + e] of the block.
 #pragma unroll
@@ -194,6 +196,23 @@ __global__ void __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_e
     for (int i = 0; i < 4; ++i) red[wave][l16 * kBN + (lg * 4 + i) * 8 + e] = acc[e][i];
   __syncthreads();
   VT_PROF(2);
+  // stage 3 through the map: which physical tensor holds column n, and where
+  auto store = [&](int idx, float4 s) {
+    const float sv[4] = {s.x, s.y, s.z, s.w};
+    const int mm = rb * kBM + idx / kBN;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const int n = cb * kBN + idx % kBN + c;
+      if (n >= N) continue;
+      int pc = 0;
+#pragma unroll
+      for (int i = 1; i < kMaxOutPieces; ++i)
+        if (i < a_nout && n >= out_sh[i].col_lo) pc = i;
+      const OutPiece& o = out_sh[pc];
+      const int64_t off = axis_off(o.row, (uint32_t)mm) + axis_off(o.col, (uint32_t)(n - o.col_lo));
+      *reinterpret_cast<T*>(o.base + off * 2) = from_float<T>(sv[c]);
+    }
+  };
   const size_t blk = (size_t)rb * gridDim.y + cb;
   float* mine = a_partial + (blk * a_ns + split) * (kBM * kBN);
   const int n_valid = min(kBM, M - rb * kBM) * kBN;     // rows past M are neither summed nor stored
@@ -205,7 +224,12 @@ __global__ void __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_e
       const float4 t = *reinterpret_cast<const float4*>(&red[w][idx]);
       s.x += t.x; s.y += t.y; s.z += t.z; s.w += t.w;
     }
-    store_device_b128(&mine[idx], __builtin_bit_cast(u32x4_t, s));
+    if (a_ns == 1) store(idx, s);
+    else store_device_b128(&mine[idx], __builtin_bit_cast(u32x4_t, s));
+  }
+  if (a_ns == 1) {
+    VT_PROF_FLUSH(gemm_store, STORE_WG);
+    return;
   }
   // ---- the last workgroup of this block to arrive adds the K slices and stores.  The barrier
   // waits for every wave's stores to complete before one thread takes the ticket; atomicInc
@@ -213,44 +237,26 @@ __global__ void __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_e
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
   VT_PROF(3);
-  if (threadIdx.x == 0) ticket_sh = a_ns > 1 ? atomicInc(&a_tickets[blk], (uint32_t)(a_ns - 1)) : 0u;
+  if (threadIdx.x == 0) ticket_sh = atomicInc(&a_tickets[blk * a_tstep], (uint32_t)(a_ns - 1));
   __syncthreads();
   VT_PROF(4);
   if (ticket_sh != (uint32_t)(a_ns - 1)) {
     VT_PROF_FLUSH(gemm_store, STORE_WG);
     return;
   }
-  const float* all = a_partial + blk * a_ns * (kBM * kBN);
+  // every slice of four columns in one round trip: sixteen requests at a time, past the last slice out of the buffer
+  // descriptor's range (no access, zero); the slices are added in order, so that the sum is reproducible
+  const __amdgpu_buffer_rsrc_t all = __builtin_amdgcn_make_buffer_rsrc(a_partial + blk * a_ns * (kBM * kBN), 0, a_ns * (kBM * kBN * 4), 0x00020000);
   for (int idx = threadIdx.x * 4; idx < n_valid; idx += kWaves * 64 * 4) {
     float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int sp0 = 0; sp0 < a_ns; sp0 += 4) {      // slices in order: the sum is reproducible
-      u32x4_t v[4];
-      const float* q[4];
+    for (int sp0 = 0; sp0 < a_ns; sp0 += 16) {
+      float4 t[16];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) q[u] = &all[(size_t)min(sp0 + u, a_ns - 1) * (kBM * kBN) + idx];
-      load_device_4xb128(q[0], q[1], q[2], q[3], v);
+      for (int u = 0; u < 16; ++u) t[u] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(all, ((sp0 + u) * (kBM * kBN) + idx) * 4, 0, 16));   // sc1
 #pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (sp0 + u < a_ns) {
-          const float4 t = __builtin_bit_cast(float4, v[u]);
-          s.x += t.x; s.y += t.y; s.z += t.z; s.w += t.w;
-        }
+      for (int u = 0; u < 16; ++u) s.x += t[u].x, s.y += t[u].y, s.z += t[u].z, s.w += t[u].w;
     }
-    const float sv[4] = {s.x, s.y, s.z, s.w};
-    const int mm = rb * kBM + idx / kBN;
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const int n = cb * kBN + idx % kBN + c;
-      if (n >= N) continue;
-      // stage 3 through the map: which physical tensor holds column n, and where
-      int pc = 0;
-#pragma unroll
-      for (int i = 1; i < kMaxOutPieces; ++i)
-        if (i < a_nout && n >= out_sh[i].col_lo) pc = i;
-      const OutPiece& o = out_sh[pc];
-      const int64_t off = axis_off(o.row, (uint32_t)mm) + axis_off(o.col, (uint32_t)(n - o.col_lo));
-      *reinterpret_cast<T*>(o.base + off * 2) = from_float<T>(sv[c]);
-    }
+    store(idx, s);
   }
 #ifdef VT_PROFILE
   __builtin_amdgcn_s_waitcnt(0);
@@ -281,14 +287,14 @@ int compute_units() {
 // Slices of K per block: as many as keep every workgroup on a compute unit of its own (one unit
 // draws only about 40 GB/s from memory, so the matrix has to be spread over all of them, and a
 // second workgroup on a unit would finish last; measured on the 4096 x 6144 projection, 48 column
-// blocks: 4 slices 14.75 us, 5: 14.5, 6: 16.7, 7: 16.6, 8: 15.9), at least one tile per wave, at
-// most 64.  The slices are whole tiles and need not be equal.
-int choose_k_splits(int64_t blocks, int64_t K) {
+// blocks: 4 slices 14.75 us, 5: 14.5, 6: 16.7, 7: 16.6, 8: 15.9), at least 128 rows of B each, and at
+// most 16, which the merge reads in one round trip (8 x 4096 x 768: 16 slices 7.1 us, 24 7.5, 32 7.9).  The slices are whole tiles and need not be equal.
+// (The size of the workspace follows from most_k_splits.)
+int most_k_splits(int64_t blocks, int64_t K) {
   if (blocks > kCounters) return 1;
-  const int n_cu = compute_units();
-  const int64_t max_splits = std::max<int64_t>(1, K / (kTileK * kWaves));
-  return (int)std::min<int64_t>(std::min(std::max<int64_t>(1, n_cu / blocks), max_splits), 64);
+  return (int)std::min<int64_t>(std::min(std::max<int64_t>(1, compute_units() / blocks), std::max<int64_t>(1, K / 128)), 64);
 }
+int choose_k_splits(int64_t blocks, int64_t K) { return std::min(most_k_splits(blocks, K), 16); }
 
 // A workspace that does not hold the whole counter area: the partial sums follow the problem's own counters.
 size_t counters_used(int64_t blocks) { return (size_t)((blocks * 4 + 255) / 256 * 256); }
@@ -300,7 +306,7 @@ extern "C" {
 size_t vt_gemm_store_workspace(int64_t M, int64_t N, int64_t K) {
   if (M < 1 || N < 1 || K < 1) return 0;
   const int64_t blocks = ((M + kBM - 1) / kBM) * ((N + kBN - 1) / kBN);
-  return kCounterBytes + (size_t)blocks * choose_k_splits(blocks, K) * kBM * kBN * sizeof(float);
+  return kCounterBytes + (size_t)blocks * most_k_splits(blocks, K) * kBM * kBN * sizeof(float);
 }
 
 int vt_gemm_store_workspace_init(void* workspace, size_t workspace_bytes, void* stream) {
@@ -405,23 +411,45 @@ int vt_gemm_store(const vt_desc* A, const vt_desc* B, const vt_desc* C, void* wo
   P.K = (int32_t)K;
   P.n_splits = ns_eff;
   P.k_per_split = kps;
+  P.ticket_step = 1;       // (few blocks' counters in lines of their own: tickets in one line are taken one after the other)
+  while (!tight && P.ticket_step < 32 && rbs * cbs * P.ticket_step * 2 <= kCounters) P.ticket_step *= 2;
   P.tickets = static_cast<uint32_t*>(workspace);
   P.partial = reinterpret_cast<float*>(static_cast<char*>(workspace) + counters);
-  // Several blocks of 16 rows: this kernel reads B once for each of them, and takes the time its busiest
-  // compute unit needs to draw its share (33 GB/s, 6.4 us around it and 0.27 us per slice that is merged: within 10 % of what
-  // 236 shapes take, r.m.s.).  The tiled kernels take over where they are expected to be faster: at 120 other shapes of 17 to
-  // 128 rows what runs takes 0.8 % longer than the better of the two on average, 19 % at most (us here / there: 4096 x 6144 with
-  // 32 rows 22.7 / 25.4, 48 rows 33.7 / 26.8, 90 rows 62.4 / 25.1; 4096 x 512 with 18 rows 15.5 / 12.8; 2048 x 768 with 33 rows 12.3 / 9.1;
-  // 768 x 1024 with 25 rows 9.5 / 6.8).
-  if (rbs > 1) {
-    const int64_t rounds = (rbs * cbs * ns_eff + compute_units() - 1) / compute_units();
-    rc = gemm_store_launch(*A, *B, *C, 6400 + ns_eff * 267 + rounds * kps * (kBN * 2) / 33, (hipStream_t)stream);
+  // Eight waves from 9 rows on: the waves' sums and the slices of 16 rows keep 256 threads busy for two rounds, and a workgroup's
+  // requests are what its unit draws (16 x 4096 x 1536: 13.7 -> 9.7 us; 8 rows: 10.3 / 10.2); if each has a tile (20 x 64 x 16384:
+  // 4.5 us with four, 5.5 with eight).
+  const int waves = M > 8 && kps >= 8 * kTileK ? 8 : 4;
+  // The small tiles take over where they are expected to be faster.  Several blocks of 16 rows: this kernel reads B once for each of
+  // them, and takes the time its busiest compute unit needs to draw its share (33 GB/s, 6.4 us around it and 0.27 us per slice that is
+  // merged: within 10 % of what 236 shapes take, r.m.s.).  At 120 other shapes of 17 to 128 rows what runs takes 0.8 % longer than the better
+  // of the two on average, 19 % at most (us here / there: 4096 x 6144 with 32 rows 22.7 / 25.4, 48 rows 33.7 / 26.8, 90 rows 62.4 / 25.1;
+  // 2048 x 768 with 33 rows 12.3 / 9.1; 768 x 1024 with 25 rows 9.5 / 6.8).
+  // One block: launch and merge, the rows of a slice, B, 3 us for workgroups that have to wait for others' places, the rows merged; within 3 %
+  // (four waves) and 5 % (eight) of what 165 shapes take, r.m.s., K 512 to 8192, N 192 to 10240; the tiles' estimate is 10 to 15 % low for so
+  // few rows, and by more beyond that width (6 x 64 x 63488: 6.6 us here, 11.3 there).  What runs is 0.5 % above the better of the two on average, 12 % at most (us here / there: 16 x 2048 x 6144 10.6 / 9.8,
+  // 13 x 1024 x 6144 8.5 / 7.7, 8 x 768 x 384 6.1 / 5.4, 4 x 4096 x 2304 8.1 / 13.0, 8 x 4096 x 6144 13.9 / 14.5).
+  const int64_t wgs = rbs * cbs * ns_eff, rounds = (wgs + compute_units() - 1) / compute_units(), draw_mb = N * K * 2 / 1000;
+  const int64_t waiting_ns = (wgs - 1) / (compute_units() * (waves == 4 ? 2 : 1)) * 3000;
+  const int64_t here_ns = rbs > 1      ? 6400 + ns_eff * 267 + rounds * kps * (kBN * 2) / 33
+                          : waves == 4 ? 4960 + waiting_ns + rounds * kps * 4617 / 1000 + draw_mb * 80 / 1000 + M * 113
+                                       : 6240 + waiting_ns + rounds * kps * 5078 / 1000 + draw_mb * 46 / 1000 + M * 51;
+  const int64_t below_ns = rbs > 1 ? here_ns : here_ns * 100 / 115;
+  const int64_t there_ns = rbs > 1 || N <= 12288 ? gemm_tile_estimate_ns(M, N, K, P.ldb) : 0;
+  if (there_ns && there_ns < below_ns) {
+    rc = gemm_store_launch(*A, *B, *C, below_ns, (hipStream_t)stream);
     if (rc != VT_ERR_UNSUPPORTED) return rc;
   }
   dim3 grid((unsigned)ns_eff, (unsigned)cbs, (unsigned)rbs);
   hipStream_t st = (hipStream_t)stream;
-  if (A->dtype == VT_BF16) hipLaunchKernelGGL((k_gemm_store<bf16_t>), grid, dim3(kWaves * 64), 0, st, P);
-  else hipLaunchKernelGGL((k_gemm_store<f16_t>), grid, dim3(kWaves * 64), 0, st, P);
+#define VT_STORE(T, W) hipLaunchKernelGGL((k_gemm_store<T, W>), grid, dim3(W * 64), 0, st, P)
+  if (A->dtype == VT_BF16) {
+    if (waves == 8) VT_STORE(bf16_t, 8);
+    else VT_STORE(bf16_t, 4);
+  } else {
+    if (waves == 8) VT_STORE(f16_t, 8);
+    else VT_STORE(f16_t, 4);
+  }
+#undef VT_STORE
   rc = check_launch("vt_gemm_store");
   if (rc == VT_OK && tight) {
     const size_t words = std::min(kCounterBytes, workspace_bytes) / 4;      // partial sums out of the counter area

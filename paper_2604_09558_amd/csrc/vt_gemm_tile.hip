@@ -387,7 +387,13 @@ int launch_tile(GemmParams P8, const typename std::conditional<MAPPED, OutMap, N
 //   1783 x 1552, K = 512, [N,K]        24 /  14 /  10 / 9.5 /  15 /  10 / 9.5 /  11
 //   3105 x 11368, K = 128              36 /  46 /  52 /  61 /  46 /  52 /  42 /  60
 // 0 x 0: the 256 x 256 kernel.  Returns the estimate in ns.
-int64_t choose_tile(const GemmParams& P, int* bm, int* bn) {
+struct TileWork {
+  int64_t N, K, weights;
+  int n_groups;
+  bool c_f32, same_channels;     // rows of [K,N] a multiple of 4096 bytes apart
+};
+template <typename Rows>         // group -> rows
+int64_t choose_tile(const TileWork& P, Rows M, int* bm, int* bn) {
   static const int n_cu = [] {
     int dev = 0, n = 256;
     if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) n = 256;
@@ -400,20 +406,16 @@ int64_t choose_tile(const GemmParams& P, int* bm, int* bn) {
                 {64, 512, 2976, 5368, 728, 546, 728, 574}, {64, 256, 1918, 4869, 372, 233, 733, 2},
                 {64, 128, 3099, 1541, 270, 64, 748, 0}, {64, 64, 3285, 1105, 242, 15, 744, 0},
                 {32, 64, 4032, 555, 191, 21, 871, 845}, {32, 32, 3499, 26, 120, 11, 944, 3073}};
-  int64_t weights = 0, rows = 0;   // groups that are pieces of one A share their B
-  for (int i = 0; i < P.n_groups; ++i) {
-    weights += i == 0 || P.g[i].b != P.g[i - 1].b;
-    rows += P.g[i].M;
-  }
-  const int64_t steps = P.K / BK, weights_ns = weights * P.N * P.K * 2 / 4000, out_ns = rows * P.N * (P.c_f32 ? 4 : 2) / 4000;
-  const bool same_channels = !P.g[0].b_kmajor && P.g[0].b_row.stride[2] * 2 % 4096 == 0;
+  int64_t rows = 0;
+  for (int i = 0; i < P.n_groups; ++i) rows += M(i);
+  const int64_t steps = P.K / BK, weights_ns = P.weights * P.N * P.K * 2 / 4000, out_ns = rows * P.N * (P.c_f32 ? 4 : 2) / 4000;
   int64_t best = 0;
   for (const auto& t : kTiles) {
     int64_t tiles = 0;
-    for (int i = 0; i < P.n_groups; ++i) tiles += ((int64_t)P.g[i].M + t.bm - 1) / t.bm * ((P.N + t.bn - 1) / t.bn);
+    for (int i = 0; i < P.n_groups; ++i) tiles += ((int64_t)M(i) + t.bm - 1) / t.bm * ((P.N + t.bn - 1) / t.bn);
     const int64_t rounds = (tiles + n_cu - 1) / n_cu;
     const int64_t k_loop = steps * (rounds * t.step_round + tiles * t.step_tile / n_cu);
-    const int64_t draw = weights_ns * (same_channels ? t.weights : 450) / 1000 - 5410;
+    const int64_t draw = weights_ns * (P.same_channels ? t.weights : 450) / 1000 - 5410;
     const int64_t cost = t.launch + rounds * t.round + std::max(k_loop, draw) + out_ns * t.out / 1000;
     if (best == 0 || cost < best) {
       best = cost;
@@ -436,6 +438,13 @@ int64_t axis_span(const AxisMap<ND>& a) {
 
 namespace vt {
 
+// The estimate for one product of M rows with a [K,N] weight whose rows are `ldb` elements apart; 0: outside these tiles.
+int64_t gemm_tile_estimate_ns(int64_t M, int64_t N, int64_t K, int64_t ldb) {
+  if (K % BK || K < BK || K > kMaxSteps * BK || N < 8) return 0;
+  int bm, bn;
+  return choose_tile(TileWork{N, K, 1, 1, false, ldb * 2 % 4096 == 0}, [&](int) { return M; }, &bm, &bn);
+}
+
 // The product of P (operands planned, tiles not yet cut) on smaller tiles, or VT_ERR_UNSUPPORTED when
 // the 256 x 256 kernel is the better one or the only one, or when the estimate is not below below_ns (if that is not 0).
 int gemm_tile_launch(const GemmParams& P, const OutMap* O, int dtype, hipStream_t st, int64_t below_ns) {
@@ -449,7 +458,9 @@ int gemm_tile_launch(const GemmParams& P, const OutMap* O, int dtype, hipStream_
     if (span >= (1ll << 32)) return fail(VT_ERR_UNSUPPORTED, no);
   }
   int bm = 0, bn = 0;
-  const int64_t estimate_ns = choose_tile(P, &bm, &bn);
+  TileWork w = {P.N, P.K, 0, P.n_groups, P.c_f32 != 0, !P.g[0].b_kmajor && P.g[0].b_row.stride[2] * 2 % 4096 == 0};
+  for (int i = 0; i < P.n_groups; ++i) w.weights += i == 0 || P.g[i].b != P.g[i - 1].b;   // groups that are pieces of one A share their B
+  const int64_t estimate_ns = choose_tile(w, [&](int i) { return P.g[i].M; }, &bm, &bn);
   if (below_ns && estimate_ns >= below_ns) return fail(VT_ERR_UNSUPPORTED, no);
   if (!bm) return fail(VT_ERR_UNSUPPORTED, no);
   const NoMap none;

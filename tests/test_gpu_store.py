@@ -202,6 +202,27 @@ def test_a_few_row_blocks_of_a_wide_projection(gpu, B, T):
     compare_stored(tio, dw, wl, ref)
 
 
+# one slice stored at once, four waves and eight, K no whole tile; sixteen slices, fewer rows than a block, a ragged last column
+# block; small tiles for a block of 16 rows or fewer
+@pytest.mark.parametrize("B,hidden,Hq,Hkv,D", [(3, 72, 4, 2, 64), (16, 200, 6, 1, 64), (9, 4096, 4, 1, 128), (1, 4104, 3, 1, 64), (16, 2056, 5, 2, 64),
+                                               (5, 768, 2, 2, 64), (16, 1024, 32, 8, 128)])
+def test_store_routes_of_few_rows(gpu, B, hidden, Hq, Hkv, D):
+    vt, tio, pipelines, torch = gpu
+    wl = workloads.qkv_proj_store(seed=9, B=B, hidden=hidden, Hq=Hq, Hkv=Hkv, D=D, cap=16, pos=5)
+    ref = run_workload(wl)
+    dw = tio.DeviceWorkload(wl)
+    p = pipelines.GemmStore(dw)
+    p.run()
+    torch.cuda.synchronize()
+    compare_stored(tio, dw, wl, ref)
+    first = {n: dw.tensors[n].clone() for n in ref["stored"]}
+    for _ in range(5):
+        p.run()
+    torch.cuda.synchronize()
+    for n, t in first.items():
+        assert torch.equal(dw.tensors[n], t), n
+
+
 @pytest.mark.parametrize("tight", [False, True])
 def test_one_workspace_for_projections_of_different_widths(gpu, tight):
     """The arrival counters of the wider projection must not lie where the narrower one left partial sums.
