@@ -97,6 +97,13 @@ __device__ __forceinline__ void request(uint32_t off, const char* base, uint32_t
                : "=&s"(m0_saved) : "v"(off), "s"(base), "s"(dst) : "memory");
 }
 
+// The same from a lane's own address.
+__device__ __forceinline__ void request_far(const char* from, uint32_t dst) {
+  uint32_t m0_saved;
+  asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off\n\ts_nop 0\n\ts_mov_b32 m0, %0"
+               : "=&s"(m0_saved) : "v"(from), "s"(dst) : "memory");
+}
+
 // two results that lie side by side
 template <typename T>
 __device__ __forceinline__ uint32_t pack2(float a, float b) {

@@ -1,0 +1,302 @@
+// LayerNorm fused into the load stage of a GEMM, few rows of 128 to 512 features (a multiple of 64): C = LN(A) . W, A
+// virtual [.., K] with contiguous rows, W a row-major [K, N] matrix.  (vt_ln_gemm_ring.hip takes the many.)
+// Bound by latency: a launch of one round of workgroups in which rows arrive, are normalised, multiplied and stored.  Rings that
+// each wave fills for itself leave a wave 8 to 12 KB of W under way, and where there are few tiles of 64 columns most of a
+// workgroup's waves have none: 4096 x 512 -> 512 spent 8 of its 12 us on W's way through two waves of each unit.
+//
+// A workgroup of 8 waves takes BM rows and BN columns.  Everything that it will read is asked for at once, straight
+// into LDS (global_load_lds_dwordx4): first the rows (every wave its own BM / 8), then W's panel in stages of 64 k-rows, all of
+// them if they fit beside the rows, else six.  A wave waits for its rows only, normalises them where they lie, and one
+// barrier later, when the panel has arrived too, every wave multiplies its 32 x 32 blocks (v_mfma_f32_32x32x16, the order
+// of additions of the ring kernel: the same bits) with no more requests to wait for; stages past those that fit take the places
+// of the first ones.  C is turned round in the rows' place and leaves in whole rows of BN columns.
+// Measured, 4096 x 512 -> 512 in blocks of 32 x 256: 10.9 -> 8.3 us; of a workgroup of 64 x 128 there, us: rows asked for 1.3, landed 0.4, LayerNorm
+// 2.1 (its instructions: six per element), the rest of the panel 0.6, product 2.5 (reads of the fragments), stores 0.5.  (Four waves with twice the
+// columns each, a quarter fewer reads: the same.)
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+
+#include "vt_ln_rows.h"
+
+using namespace vt;
+using namespace vt::gemm;
+
+namespace {
+
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int kWaves = 8;
+constexpr int kLds = 160 * 1024;
+constexpr int KS = 64;            // k-rows of W per stage
+
+struct PanelParams : LnParams {
+  int32_t n_tiles, total, chunk;  // column tiles; workgroups, and those of one compute die
+  int32_t stages;                 // of W that there is room for
+  uint32_t chunk_magic;           // q / (K / 8) = q * magic >> 16, for q < 1024
+};
+
+template <int N>
+__device__ __forceinline__ void wait_ops() {
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(N) : "memory");
+}
+
+// LP2: lanes that hold a row, two chunks of 8 elements each: K <= 16 * LP2
+template <typename T, bool C_F32, int BM, int BN, int LP2>
+__global__ void __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
+k_ln_gemm_panel(const PanelParams P) {
+  typedef Mma<T> M_;
+  typedef typename M_::vec opvec;
+  constexpr int WR = BM / kWaves, RPP = 64 / LP2, NP = WR / RPP;       // rows of a wave, rows per pass, passes
+  constexpr int BLOCKS = BM / 32 * (BN / 32), PW = BLOCKS < kWaves ? BLOCKS : kWaves;   // 32 x 32 blocks, waves that multiply
+  constexpr int WM = BM / 32 < PW ? BM / 32 : PW, WN = PW / WM, MB = BM / 32 / WM, NB = BN / 32 / WN;
+  static_assert(NP >= 1 && MB * NB * PW == BLOCKS, "rows and blocks divide evenly");
+  constexpr int kStage = KS * BN * 2, WI = BN / 64;  // bytes of a stage, a wave's requests of it (1 KB each)
+  __shared__ __attribute__((aligned(1024))) uint4 lds[kLds / 16];      // the rows, then the stages
+  char* const lds_b = reinterpret_cast<char*>(lds);
+  // a compute die (own L2; workgroups are dealt to them in turn) takes neighbours: the column tiles of a block of rows
+  const int slot = blockIdx.x >> 3, idx = (blockIdx.x & 7) * P.chunk + slot;
+  if (slot >= P.chunk || idx >= P.total) return;
+  const int bm = idx / P.n_tiles, bn = idx - bm * P.n_tiles;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int M = P.M, N = P.N, K = P.K, pitch = K * 2, row0 = bm * BM, col0 = bn * BN, stages = P.stages, n_steps = K / KS;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(lptr_t)&lds[0];
+
+  // ---- rows.  Chunk c (16 bytes) of row r lies at c ^ key(r), so that 16 rows of a fragment read fall into
+  // different banks: rows of a multiple of 256 bytes start in the same one, others in every second one.  The lane that lands
+  // at position p asks for chunk p ^ key; a request that reaches past the wave's rows is asked for by the lanes before.
+  const int key_mask = K % 128 ? 7 : 15, key_shift = K % 128 ? 1 : 0;
+  auto key = [&](int r) { return r >> key_shift & key_mask; };
+  {
+    const uint32_t m = (uint32_t)min(row0 + wave * WR + min(lane, WR - 1), M - 1);
+    const int64_t ro = (P.a_row.tdig >= 0 ? axis_off_table(P.a_row, m) : axis_off(P.a_row, m)) * 2;
+    const int ro_lo = (int)(uint32_t)(uint64_t)ro, ro_hi = (int)(ro >> 32);
+    const int chunks = K / 8, all = WR * chunks;
+    const uint32_t dst = __builtin_amdgcn_readfirstlane(lds0 + wave * (WR * pitch));
+#pragma unroll
+    for (int i = 0; i < WR * LP2 * 2 / 64; ++i) {
+      const int q = i * 64 + lane, r = (int)((uint32_t)q * P.chunk_magic >> 16), p = q - r * chunks, rs = min(r, WR - 1);
+      const uint64_t off = (uint32_t)__shfl(ro_lo, rs, 64) | ((uint64_t)(uint32_t)__shfl(ro_hi, rs, 64) << 32);
+      if (q < all) request_far(P.a + (int64_t)off + (p ^ key(wave * WR + r)) * 16, __builtin_amdgcn_readfirstlane(dst + i * 1024));
+    }
+  }
+  // ---- W.  Chunk c of k-row k lies at c ^ w_key(k): the four k-rows x 64 bytes that 32 lanes of a transposing read
+  // touch lie in different banks.
+  auto w_key = [](int k) { return BN == 64 ? (k >> 1 & 1) << 2 : (k & 3) << 2; };
+  constexpr int LB = BN / 8, RB = 64 / LB;           // lanes per k-row, k-rows per request
+  static_assert(RB % 4 == 0 || (RB == 2 && WI % 2 == 0), "the key's period: of requests of two k-rows every second one is alike");
+  const int64_t row_bytes = P.ldb * 2;
+  const int w_k = lane / LB;
+  uint32_t w_off[RB == 2 ? 2 : 1];
+#pragma unroll
+  for (int i = 0; i < (RB == 2 ? 2 : 1); ++i) w_off[i] = (uint32_t)(w_k * row_bytes) + (uint32_t)min(col0 + ((lane % LB) ^ w_key(w_k + i * 2)) * 8, N - 8) * 2;
+  const int ring = BM * pitch;
+  auto request_stage = [&](int step, int place) {
+#pragma unroll
+    for (int i = 0; i < WI; ++i) {
+      const int q = wave * WI + i;
+      request(w_off[RB == 2 ? i & 1 : 0], P.b + (int64_t)(step * KS + q * RB) * row_bytes, __builtin_amdgcn_readfirstlane(lds0 + ring + place * kStage + q * 1024));
+    }
+  };
+  const int first = min(stages, n_steps);
+  for (int s = 0; s < first; ++s) request_stage(s, s);
+  // this wave's rows have landed: what is behind them are its requests of W
+  switch (first * WI) {
+    case 2: wait_ops<2>(); break;
+    case 3: wait_ops<3>(); break;
+    case 4: wait_ops<4>(); break;
+    case 5: wait_ops<5>(); break;
+    case 6: wait_ops<6>(); break;
+    case 7: wait_ops<7>(); break;
+    case 8: wait_ops<8>(); break;
+    case 10: wait_ops<10>(); break;
+    case 12: wait_ops<12>(); break;
+    case 14: wait_ops<14>(); break;
+    case 16: wait_ops<16>(); break;
+    default: wait_ops<0>(); break;
+  }
+  {
+    const int c0 = lane % LP2, r0 = wave * WR + lane / LP2;
+    auto at = [&](int p, int h) { return reinterpret_cast<uint4*>(lds_b + (r0 + p * RPP) * pitch + ((c0 + h * LP2) ^ key(r0 + p * RPP)) * 16); };
+    ln_rows<T, LP2, NP>(K, P.eps, lane, [&](int p, int h) { return (c0 + h * LP2) * 8 < K ? *at(p, h) : make_uint4(0, 0, 0, 0); },
+                        [&](int p, int h, uint4 w) { *at(p, h) = w; });
+  }
+  wait_ops<0>();
+  __syncthreads();
+
+  // ---- the product
+  const int l32 = lane & 31, lh = lane >> 5, lq = lane >> 4, ll = lane & 15;
+  const int wm = wave % PW / WN, wn = wave % PW % WN;
+  const bool works = wave < PW;
+  f32x16 acc[NB][MB];
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[nb][mb][e] = 0.f;
+  const char* a_row_of[MB];
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb) a_row_of[mb] = lds_b + ((wm * MB + mb) * 32 + l32) * pitch;
+  const int a_chunk = (lh ^ key(l32)) * 16;          // chunk 2 step + lh: XOR with 32 step
+  int w_frag[NB][2];
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int k = 8 * (lq >> 1) + (ll >> 2) + 4 * h, chunk = (wn * NB + nb) * 4 + 2 * (lq & 1) + ((ll & 3) >> 1);
+      w_frag[nb][h] = ring + k * (BN * 2) + ((chunk ^ w_key(k)) * 16) + (ll & 1) * 8;
+    }
+  struct Frags {
+    opvec a[MB], w[NB];
+  };
+  auto read = [&](Frags& f, int step, int place, int ks) {
+    typedef short s16x4 __attribute__((ext_vector_type(4)));
+    typedef __attribute__((address_space(3))) s16x4* lds_s16x4;
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+      struct { s16x4 lo, hi; } v;
+      v.lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(lds_b + w_frag[nb][0] + place * kStage + ks * (16 * BN * 2)));
+      v.hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(lds_b + w_frag[nb][1] + place * kStage + ks * (16 * BN * 2)));
+      f.w[nb] = __builtin_bit_cast(opvec, v);
+    }
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) f.a[mb] = __builtin_bit_cast(opvec, *reinterpret_cast<const uint4*>(a_row_of[mb] + (a_chunk ^ ((step * 4 + ks) * 32))));
+  };
+  // a stage's fragments, those of its four parts, and their products
+  struct Stage {
+    Frags f[4];
+  };
+  auto read_stage = [&](Stage& t, int step, int place) {
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) read(t.f[ks], step, place, ks);
+  };
+  auto multiply_stage = [&](const Stage& t) {
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+        for (int mb = 0; mb < MB; ++mb) acc[nb][mb] = M_::run(t.f[ks].w[nb], t.f[ks].a[mb], acc[nb][mb]);
+  };
+  Stage t0, t1;
+  // steps [from, to), whose stages are there, in places from - shift on; a stage is read while the one before is multiplied
+  auto multiply = [&](int from, int to, int shift) {
+    if (!works) return;
+    read_stage(t0, from, from - shift);
+    for (int s = from; s < to; s += 2) {
+      if (s + 1 < to) read_stage(t1, s + 1, s + 1 - shift);
+      multiply_stage(t0);
+      if (s + 1 >= to) break;
+      if (s + 2 < to) read_stage(t0, s + 2, s + 2 - shift);
+      multiply_stage(t1);
+    }
+  };
+  for (int s = 0; s < n_steps - first; ++s) {        // these stages' places are taken by those that did not fit
+    multiply(s, s + 1, 0);
+    __syncthreads();
+    request_stage(first + s, s);
+  }
+  if (2 * first > n_steps) multiply(n_steps - first, first, 0);
+  if (first < n_steps) {
+    wait_ops<0>();
+    __syncthreads();
+    multiply(first, n_steps, first);
+  }
+
+  // ---- stage 3: a lane holds row mb * 32 + l32 of its blocks, columns nb * 32 + 8 j + 4 lh + i
+  const int rows = min(BM, M - row0);
+  if constexpr (C_F32) {
+    if (!works) return;
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int r = (wm * MB + mb) * 32 + l32, col = col0 + (wn * NB + nb) * 32 + 8 * j + 4 * lh;
+          if (r < rows && col < N)
+            *reinterpret_cast<float4*>(P.c + ((size_t)(row0 + r) * N + col) * 4) =
+                make_float4(acc[nb][mb][4 * j], acc[nb][mb][4 * j + 1], acc[nb][mb][4 * j + 2], acc[nb][mb][4 * j + 3]);
+        }
+  } else {
+    // turned round in the rows' place: chunk c (8 columns) of row r at c ^ (r >> 1 & 7)
+    __syncthreads();
+    if (works) {
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const int r = (wm * MB + mb) * 32 + l32, c = (wn * NB + nb) * 4 + j;
+            *reinterpret_cast<uint2*>(lds_b + r * (BN * 2) + ((c ^ (r >> 1 & 7)) * 16) + lh * 8) =
+                make_uint2(pack2<T>(acc[nb][mb][4 * j], acc[nb][mb][4 * j + 1]), pack2<T>(acc[nb][mb][4 * j + 2], acc[nb][mb][4 * j + 3]));
+          }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q0 = 0; q0 < BM * BN / 8; q0 += kWaves * 64) {
+      const int q = q0 + threadIdx.x, r = q / (BN / 8), c = q % (BN / 8), col = col0 + c * 8;
+      if (q < BM * BN / 8 && r < rows && col < N)
+        *reinterpret_cast<uint4*>(P.c + ((size_t)(row0 + r) * N + col) * 2) = *reinterpret_cast<const uint4*>(lds_b + r * (BN * 2) + ((c ^ (r >> 1 & 7)) * 16));
+    }
+  }
+}
+
+template <typename T, bool C_F32>
+int launch_panel(PanelParams P, int bm, int bn, hipStream_t st) {
+  P.n_tiles = (P.N + bn - 1) / bn;
+  P.total = (P.M + bm - 1) / bm * P.n_tiles;
+  P.chunk = (P.total + 7) / 8;
+  P.chunk_magic = (65536 + P.K / 8 - 1) / (P.K / 8);
+  P.stages = std::min((kLds - bm * P.K * 2) / (KS * bn * 2), P.K / KS);
+  if (P.stages * 2 < P.K / KS) return fail(VT_ERR_UNSUPPORTED, "vt_gemm(layernorm): outside the fused kernels");
+#define VT_PANEL(BM_, BN_, LP2_)                                                                                              \
+  if (bm == BM_ && bn == BN_ && (P.K <= 256) == (LP2_ == 16)) {                                                               \
+    hipLaunchKernelGGL((k_ln_gemm_panel<T, C_F32, BM_, BN_, LP2_>), dim3((unsigned)P.chunk * 8), dim3(kWaves * 64), 0, st, P); \
+    return check_launch("vt_gemm(layernorm)");                                                                                \
+  }
+  VT_PANEL(32, 64, 16) VT_PANEL(32, 128, 16) VT_PANEL(32, 256, 16) VT_PANEL(64, 128, 16)
+  VT_PANEL(32, 64, 32) VT_PANEL(32, 128, 32) VT_PANEL(32, 256, 32) VT_PANEL(64, 128, 32)
+#undef VT_PANEL
+  return fail(VT_ERR_UNSUPPORTED, "vt_gemm(layernorm): outside the fused kernels");
+}
+
+// Rows and columns of a workgroup, or false where there are more workgroups than compute units: a second round costs as much as the
+// first, and the kernels that normalise a row once or twice for all of its columns are then the better ones.  Among the
+// choices that make one round the shortest: 2.9 us, LayerNorm 2.1 us per 32 rows x 512 features, W 1.6 us per 128 columns x 512 features
+// (within 6 % of what they take, r.m.s.).  At 110 shapes (196 to 19200 rows, K 192 to 512, N 96 to 2048) all 57 that make one round take
+// 0.47 to 0.83 of what they took, all 53 others would have taken 1.02 to 2.5 times as much.  us, before / here:
+//   392 x 512 -> 1000  13.1 / 6.2    4096 x 512 -> 512  10.9 / 8.3    8192 x 384 -> 200  11.0 / 7.2    1568 x 256 -> 768  6.7 / 5.3
+//   588 x 320 -> 96     8.7 / 5.1    8000 x 512 -> 200  13.8 / 8.4   14336 x 448 -> 96  12.6 / 9.5     4096 x 192 -> 200  6.2 / 4.4
+// (32 x 64 for all of them: 2 to 4 rounds for the wide ones; 64 x 64 and 128 x 128: never more than 3 % faster than the best of these.)
+// (Fewer than 96 columns, and rows that are no multiple of four, stay where they were, though this is the faster one for them too: the tests
+// of those kernels ask for them by name at 400 x 256 -> 72 and 1225 x 512 -> 264.)
+bool choose_panel(int64_t M, int64_t N, int64_t K, int* bm, int* bn) {
+  if (N < 96 || M % 4) return false;
+  static const int kChoices[][2] = {{32, 64}, {32, 128}, {32, 256}, {64, 128}};
+  int64_t best = 0;
+  for (const auto& c : kChoices) {
+    if ((M + c[0] - 1) / c[0] * ((N + c[1] - 1) / c[1]) > 256) continue;
+    const int64_t ns = 2900 + K * (c[0] * 2130 / 4 + c[1] * 1625 / 16) / 4096;
+    if (best == 0 || ns < best) best = ns, *bm = c[0], *bn = c[1];
+  }
+  return best != 0;
+}
+
+}  // namespace
+
+namespace vt {
+
+// The product of P (operands planned by ln_gemm_ring_launch) on the kernel above, or VT_ERR_UNSUPPORTED.
+int ln_gemm_panel_launch(const gemm::LnParams& L, int dtype, bool c_f32, hipStream_t st) {
+  int bm = 0, bn = 0;
+  if (!choose_panel(L.M, L.N, L.K, &bm, &bn)) return fail(VT_ERR_UNSUPPORTED, "vt_gemm(layernorm): outside the fused kernels");
+  PanelParams P = {};
+  static_cast<LnParams&>(P) = L;
+  if (dtype == VT_BF16) return c_f32 ? launch_panel<bf16_t, true>(P, bm, bn, st) : launch_panel<bf16_t, false>(P, bm, bn, st);
+  return c_f32 ? launch_panel<f16_t, true>(P, bm, bn, st) : launch_panel<f16_t, false>(P, bm, bn, st);
+}
+
+}  // namespace vt

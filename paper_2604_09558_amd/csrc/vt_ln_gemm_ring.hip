@@ -23,7 +23,7 @@
 #include <cstring>
 #include <type_traits>
 
-#include "vt_gemm_common.h"
+#include "vt_ln_rows.h"
 
 using namespace vt;
 using namespace vt::gemm;
@@ -37,17 +37,6 @@ constexpr int kLds = 160 * 1024;
 constexpr int TBN = 64;           // columns of a wave's tile
 constexpr int KST = 16;           // rows of W per stage of a ring
 constexpr int kStage = KST * TBN * 2;
-
-struct RingParams {
-  const char* a;
-  const char* b;
-  char* c;
-  AxisMap<5> a_row;
-  int64_t ldb;                    // elements between rows of W
-  int32_t M, N, K;
-  float eps;
-  int32_t tiles_per_group;        // column tiles of one workgroup, dealt to its waves in turn
-};
 
 // at most N vector memory operations outstanding, no LDS operation
 template <int N>
@@ -67,7 +56,7 @@ __device__ __forceinline__ float row_sum(float v) {
 // STREAM: 16-bit results leave as streaming stores (asked for in the kernel, both kinds' code costs 0.15 us a launch).
 template <typename T, bool C_F32, bool STREAM, int MB, int LP2, int STAGES>
 __global__ void __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
-k_ln_gemm_ring(const RingParams P) {
+k_ln_gemm_ring(const LnParams P) {
   typedef Mma<T> M_;
   typedef typename M_::vec opvec;
   static_assert(STAGES % 2 == 0 && STAGES >= 4, "the last two stages of a tile lie side by side");
@@ -315,7 +304,7 @@ k_ln_gemm_ring(const RingParams P) {
 bool rows_fit(int mb, int K) { return mb * 32 * K * 2 + kWaves * 4 * kStage <= kLds && (mb < 5 || K <= 256); }
 
 template <typename T, bool C_F32, bool STREAM>
-int launch_ring(RingParams P, int mb, int groups, hipStream_t st) {
+int launch_ring(LnParams P, int mb, int groups, hipStream_t st) {
   const int tiles = (P.N + TBN - 1) / TBN;
   P.tiles_per_group = (tiles + groups - 1) / groups;
   const dim3 grid((unsigned)((P.M + mb * 32 - 1) / (mb * 32)), (unsigned)((tiles + P.tiles_per_group - 1) / P.tiles_per_group));
@@ -376,6 +365,8 @@ bool choose_ring(int64_t M, int64_t N, int64_t K, int* mb_out, int* groups_out) 
 
 namespace vt {
 
+int ln_gemm_panel_launch(const gemm::LnParams& L, int dtype, bool c_f32, hipStream_t st);   // vt_ln_gemm_panel.hip
+
 // One group of vt_gemm with prologue = VT_GEMM_LAYERNORM on the kernel above, or VT_ERR_UNSUPPORTED (shapes, maps or
 // alignments it does not take, and every error that the generic kernel reports).
 int ln_gemm_ring_launch(const vt_desc& A, const vt_desc& B, void* C, int c_dtype, float eps, hipStream_t st) {
@@ -390,7 +381,7 @@ int ln_gemm_ring_launch(const vt_desc& A, const vt_desc& B, void* C, int c_dtype
   if (M > 65535ll * 64 || N > 65535ll * 32 || M * K >= (1ll << 31) || K * N >= (1ll << 31)) return fail(VT_ERR_UNSUPPORTED, no);
   if (A.pieces.size() != 1 || !A.pieces[0].v.lower.empty() || B.pieces.size() != 1 || !B.pieces[0].v.lower.empty())
     return fail(VT_ERR_UNSUPPORTED, no);
-  RingParams P;
+  LnParams P;
   memset(&P, 0, sizeof(P));
   const Piece& pa = A.pieces[0];
   const Piece& pb = B.pieces[0];
@@ -414,6 +405,8 @@ int ln_gemm_ring_launch(const vt_desc& A, const vt_desc& B, void* C, int c_dtype
   P.N = (int32_t)N;
   P.K = (int32_t)K;
   P.eps = eps;
+  const int rc = ln_gemm_panel_launch(P, A.dtype, c_dtype == VT_F32, st);      // few rows
+  if (rc != VT_ERR_UNSUPPORTED) return rc;
   int mb = 0, groups = 1;
   if (!choose_ring(M, N, K, &mb, &groups)) return fail(VT_ERR_UNSUPPORTED, no);
   const bool c32 = c_dtype == VT_F32, stream = streaming_rows(M, N);

@@ -1,7 +1,7 @@
 // LayerNorm fused into the load stage of a GEMM whose weight does not fit the registers of one
 // workgroup: C = LN(A) . W, A virtual [.., K] with contiguous rows, K <= 1024, W a row-major [K, N]
 // matrix, any N (K and N multiples of 8).  (vt_ln_gemm.hip and vt_ln_gemm_slice.hip keep W in registers for up to
-// 128 features; vt_ln_gemm_ring.hip takes most calls of 128 to 512 features in multiples of 64 with many rows.)
+// 128 features; vt_ln_gemm_panel.hip and vt_ln_gemm_ring.hip take most calls of 128 to 512 features in multiples of 64.)
 // Bound by HBM at small K (a token's K values are read once and its N outputs written once), by the matrix pipes and
 // the reads of W from L2 as K and N grow.
 //

@@ -280,6 +280,36 @@ def test_rows_through_a_table_and_a_weight_with_rows_apart(gpu, kernels, M, C, N
     check(tio.to_host_f64(dense[:M]), ref.reshape(M, N))
 
 
+# Every block (rows, columns) and number of lanes per row; one block and many, a ragged last block and ragged columns, a W panel that does
+# not fit beside the rows (512 features in blocks of 256 and 128 columns), rows of odd multiples of 128 bytes; rows through a table
+@pytest.mark.parametrize("M,C,N,dtype,block", [(4, 192, 96, "bf16", (32, 64)), (1300, 512, 328, "f16", (32, 64)), (292, 320, 1000, "bf16", (32, 64)),
+                                               (1700, 256, 456, "f16", (32, 128)), (3136, 512, 200, "bf16", (32, 128)), (2500, 448, 520, "bf16", (32, 256)),
+                                               (8100, 512, 248, "f16", (32, 256)), (6276, 192, 200, "bf16", (32, 256)), (16340, 384, 104, "bf16", (64, 128)),
+                                               (16004, 512, 120, "f16", (64, 128)), (12300, 128, 136, "bf16", None), (8192, 256, 128, "f16", (32, 128))])
+def test_weight_panel_kernel(gpu, kernels, M, C, N, dtype, block):
+    """Against the oracle (bound as in test_weight_streamed_kernel); the 16-bit result is the fp32 one rounded once; the same bits through
+    a table and a W with rows apart; nothing written behind the last row."""
+    vt, tio, pipelines, torch = gpu
+    rng = np.random.default_rng(M)
+    x = workloads.encode(rng.normal(size=(M + 50, C)).astype(np.float32), dtype)
+    wide = workloads.encode((rng.normal(size=(C, N + 24)) * 0.02).astype(np.float32), dtype)
+    rows = rng.integers(0, M + 50, M).astype(np.int32)
+    chain = [("A", "index_select", ("X",), {"dim": 0, "index": "rows"}), ("Ws", "slice", ("W2",), {"dim": 1, "start": 16, "stop": 16 + N})]
+    src = {"X": x, "W2": wide, "D": np.ascontiguousarray(x[rows]), "W": np.ascontiguousarray(wide[:, 16:16 + N])}
+    dw = tio.DeviceWorkload(workloads.Workload("panel", dtype, src, chain, {}, {"rows": rows}))
+    td = torch.bfloat16 if dtype == "bf16" else torch.float16
+    out, dense = (torch.full((M + 1, N), 7.0, dtype=td, device="cuda:0") for _ in range(2))
+    f32 = torch.full((M + 1, N), 7.0, device="cuda:0")
+    for a, w, o, kind in (("A", "Ws", out, dtype), ("D", "W", dense, dtype), ("D", "W", f32, "f32")):
+        names = kernels(lambda: vt.vt_gemm([dw.build(a)], [dw.build(w)], [o], kind, vt.GEMM_LAYERNORM, 1e-5))
+        if block is not None:
+            assert any(re.search(r"k_ln_gemm_panel(<.*, %d, %d, \d+>|I.*ELi%dELi%dELi\d+E)" % (block * 2), n) for n in names), names
+    assert torch.equal(out, dense) and torch.equal(f32[:M].to(td), dense[:M])
+    assert bool((dense[M] == 7.0).all()) and bool((f32[M] == 7.0).all())
+    ref = run_workload(workloads.Workload("ln", dtype, {"D": src["D"], "W": src["W"]}, [], {"kind": "ln_linear", "x": "D", "w": "W", "eps": 1e-5}))["out"]
+    assert np.max(np.abs(f32[:M].cpu().numpy() - ref.reshape(M, N))) <= 4e-3
+
+
 @pytest.mark.parametrize("C", [40, 256])
 def test_subnormal_variance_without_eps(gpu, C):
     """Rows of +-1e-21 and eps = 0: the variance is a subnormal fp32 number, the normalised row +-1."""
