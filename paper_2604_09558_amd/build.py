@@ -12,7 +12,7 @@ LIB = os.path.join(HERE, "libvt.so")
 LIB_PROFILE = os.path.join(HERE, "libvt_profile.so")   # same sources with -DVT_PROFILE: per-workgroup timestamps
 
 HOST_SOURCES = ["vt_build.cpp", "vt_device_host.cpp", "vt_vtog.cpp"]
-HIP_SOURCES = ["vt_kernels.hip", "vt_attn.hip", "vt_gemm.hip", "vt_gemm_tile.hip", "vt_ln_gemm.hip", "vt_ln_gemm_slice.hip", "vt_ln_gemm_ring.hip", "vt_ln_gemm_panel.hip", "vt_ln_gemm_wide.hip", "vt_gemm_store.hip"]
+HIP_SOURCES = ["vt_attn.hip", "vt_kernels.hip", "vt_gemm.hip", "vt_gemm_tile.hip", "vt_ln_gemm.hip", "vt_ln_gemm_slice.hip", "vt_ln_gemm_ring.hip", "vt_ln_gemm_panel.hip", "vt_ln_gemm_wide.hip", "vt_gemm_store.hip"]
 
 COMMON = ["-O3", "-std=c++17", "-fPIC", "-I", INCLUDE, "-I", CSRC, "-Wall", "-Wno-unused-function"]
 # gfx950 only; packed-fp32 instructions are switched off (they have given wrong results on
@@ -41,7 +41,7 @@ def hipcc() -> str:
     return os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 
-def build(verbose: bool = True, jobs: int = 4, profile: bool = False) -> str:
+def build(verbose: bool = True, jobs: int = 8, profile: bool = False) -> str:
     """Compile and link libvt.so, or with profile=True libvt_profile.so (the kernels record
     per-workgroup timestamps that profile_trace.py reads; load it through VT_LIB_PATH)."""
     objs = []

@@ -1142,8 +1142,8 @@ int most_splits(int units, int S, int n_splits) {
 //   96 to 128 units  one split of eight waves up to 65536 rows in all of 128-wide heads, else 512 / units, or 256 / units of them from 1537 keys on
 //   64-wide heads    two workgroups of four waves per compute unit, eight waves from 4096 keys of few units on
 //   128-wide heads   one workgroup per compute unit, and up to 16 splits or what leaves each 352 rows: every split costs its partial results and a
-//                    share of the merge.  From 33 units on 2049 to 4096 keys have two per compute unit (the two are within 2 % there).
-// Contexts of more than two segments have four waves only, and 512 / units or 256 / units splits; so have more than 256 units.
+//                    share of the merge.  Eight waves up to 16 units from 2560 keys on (32 x 8192: 25.6 us with four, 26.4 with eight).  From 33 units on 2049 to 4096 keys have two per compute unit (the two are within 2 % there).
+// Contexts of more than two segments, and 128-wide heads behind a table over the batch, have four waves only, and 512 / units or 256 / units splits; so have more than 256 units.
 //   units x keys, us with (waves x splits)
 //   8 x 200    7.4 (4 x 2)   6.9 (8 x 1)         1 x 8192   13.5 (4 x 24)  12.0 (8 x 24)     8 x 8192    13.6 (4 x 24)  12.5 (8 x 24)
 //   64 x 2048  16.3 (4 x 8)  15.7 (4 x 4)        64 x 8192  46.5 (4 x 8)   43.8 (4 x 4)      64 x 4096   26.1 (4 x 8)   25.2 (4 x 4)
@@ -1154,11 +1154,11 @@ int most_splits(int units, int S, int n_splits) {
 struct Splits {
   int n, waves;
 };
-Splits choose_splits(int units, int S, int n_splits, int64_t D, int n_seg) {
+Splits choose_splits(int units, int S, int n_splits, int64_t D, bool four_waves) {
   if (n_splits > 0) return {n_splits, 4};
   const int most = most_splits(units, S, 0), per_unit = std::max(1, 256 / units);
   const int few_rows = std::max(16, (S + 351) / 352);
-  if (n_seg > 2 || units > 256)
+  if (four_waves || units > 256)
     return {std::min(D == 128 && units < 64 && per_unit * units >= 230 ? std::min(most, per_unit) : most, few_rows), 4};
   if (S <= 128) return {1, 4};
   if (S <= 256) return {1, 8};
@@ -1172,13 +1172,14 @@ Splits choose_splits(int units, int S, int n_splits, int64_t D, int n_seg) {
   }
   Splits c = D == 64 ? Splits{std::min(S >= 4096 && units <= 32 ? per_unit : 512 / units, 24), S >= 4096 && units <= 32 ? 8 : 4}
              : units > 32 && S > 2048 && S <= 4096 ? Splits{std::min(most, few_rows), 4}
-                                                  : Splits{std::min(per_unit, few_rows), units <= 32 && S >= 2560 ? 8 : 4};
+                                                  : Splits{std::min(per_unit, few_rows), units <= 16 && S >= 2560 ? 8 : 4};
   c.n = std::min(c.n, most);
-  // a quarter more splits where that saves every wave a tile (46 units x 735 keys: 9.7 us with 5 splits of 160 rows, 9.1 with 6)
+  // a quarter more splits where that saves every wave a tile and they have places (46 units x 735 keys, 64-wide: 9.7 us with 5 splits of
+  // 160 rows, 9.1 with 6; but 32 x 1280, 128-wide: 11.1 with 8, 11.6 with 10, which are more than the compute units)
   const int tiles = ((S + c.n - 1) / c.n + 32 * c.waves - 1) / (32 * c.waves);
   if (tiles > 1) {
     const int more = (S + (tiles - 1) * 32 * c.waves - 1) / ((tiles - 1) * 32 * c.waves);
-    if (more <= most && more * 4 <= c.n * 5 && (c.waves == 4 || more <= per_unit)) c.n = more;
+    if (more <= most && more * 4 <= c.n * 5 && more * units <= (D == 64 && c.waves == 4 ? 512 : 256)) c.n = more;
   }
   return c;
 }
@@ -1324,7 +1325,8 @@ static int plan_attention(const vt_desc* Q, const vt_desc* K, const vt_desc* V, 
     if ((uintptr_t)P.q_ptr % 16 || P.q_sb % 16 || P.q_sh % 16) return fail(VT_ERR_UNSUPPORTED, "Q: rows are not 16-byte aligned");
   }
   const int Hkv = (int)(Hq / G);
-  const Splits chosen = B * Hkv > kCounters ? Splits{1, kWaves} : choose_splits((int)B * Hkv, (int)S, n_splits, D, P.n_seg);
+  P.batch_table = ko.batch_table || vo.batch_table;
+  const Splits chosen = B * Hkv > kCounters ? Splits{1, kWaves} : choose_splits((int)B * Hkv, (int)S, n_splits, D, P.n_seg > 2 || (D == 128 && P.batch_table));
   int ns = chosen.n;
   if (n_splits == 0 && D == 64) ns = std::min(ns, (int)(kWaves * kTile * D / 4 / G));   // what the merge below has room for
   int rows = (int)((S + ns - 1) / ns);
@@ -1337,7 +1339,6 @@ static int plan_attention(const vt_desc* Q, const vt_desc* K, const vt_desc* V, 
   P.G = (int)G;
   P.S = (int)S;
   P.D = (int)D;
-  P.batch_table = ko.batch_table || vo.batch_table;
   P.n_splits = ns_eff;
   P.waves = chosen.waves;
   P.rows_per_split = rows;
@@ -1435,7 +1436,8 @@ static int launch_attention(const vt_desc* Q, const vt_desc* K, const vt_desc* V
   // (eight waves: one workgroup on a compute unit, two waves per SIMD, whatever registers they need)
 #define VT_ATTN_NS(TT, DD, MM, RR, OCC)                                                                               \
   do {                                                                                                                \
-    if (few && P.waves == 8) hipLaunchKernelGGL((k_decode_attn<TT, DD, MM, RR, 2, 8, 2>), grid, dim3(8 * 64), 0, st, P2); \
+    constexpr int W8 = DD == 64 || RR == kRounded ? 8 : kWaves;   /* (the others are not asked for with eight) */     \
+    if (few && P.waves == 8) hipLaunchKernelGGL((k_decode_attn<TT, DD, MM, RR, 2, W8, W8 == 8 ? 2 : OCC>), grid, dim3(W8 * 64), 0, st, P2); \
     else if (few) hipLaunchKernelGGL((k_decode_attn<TT, DD, MM, RR, 2, kWaves, OCC>), grid, dim3(kWaves * 64), 0, st, P2); \
     else hipLaunchKernelGGL((k_decode_attn<TT, DD, MM, RR, kMaxSegs, kWaves, OCC>), grid, dim3(kWaves * 64), 0, st, P);   \
   } while (0)
