@@ -932,18 +932,19 @@ struct HeadMap {
 // A digit group that acts as ONE strided digit: a single plain digit, or several that nest
 // densely (each stride = the next stride x the next radix, as a reshape of a dense buffer
 // leaves them).
-bool single_plain(const std::vector<Digit>& g, int64_t* stride) {
-  if (g.empty()) {
+bool single_plain(const Digit* g, size_t n, int64_t* stride) {
+  if (n == 0) {
     *stride = 0;
     return true;
   }
-  for (size_t i = 0; i < g.size(); ++i) {
+  for (size_t i = 0; i < n; ++i) {
     if (g[i].table >= 0) return false;
-    if (i + 1 < g.size() && g[i].stride != g[i + 1].stride * g[i + 1].radix) return false;
+    if (i + 1 < n && g[i].stride != g[i + 1].stride * g[i + 1].radix) return false;
   }
-  *stride = g.back().stride;
+  *stride = g[n - 1].stride;
   return true;
 }
+bool single_plain(const std::vector<Digit>& g, int64_t* stride) { return single_plain(g.data(), g.size(), stride); }
 
 // Trailing zero-stride digits of the head group = heads that share rows.
 int64_t broadcast_factor(const std::vector<Digit>& g) {
@@ -967,16 +968,19 @@ struct AttnOperand {
   bool batch_table;
 };
 
+// (the page tables' form is looked at once for a descriptor and G: 48 rows through the evaluator, 1.9 us)
 int plan_operand(const vt_desc& d, const char* name, int64_t G, AttnOperand* out) {
   const int esz = 2;
   if (d.pieces.size() > (size_t)kMaxAttnPieces) return fail(VT_ERR_UNSUPPORTED, std::string(name) + ": more than 4 pieces along the context");
-  std::vector<const Piece*> ps;
-  for (const Piece& p : d.pieces) ps.push_back(&p);
-  std::sort(ps.begin(), ps.end(), [](const Piece* a, const Piece* b) { return a->lo[2] < b->lo[2]; });
+  const Piece* ps[kMaxAttnPieces];
+  const size_t n_ps = d.pieces.size();
+  for (size_t i = 0; i < n_ps; ++i) ps[i] = &d.pieces[i];
+  std::sort(ps, ps + n_ps, [](const Piece* a, const Piece* b) { return a->lo[2] < b->lo[2]; });
   int64_t expect = 0;
-  out->n = (int)ps.size();
+  out->n = (int)n_ps;
   out->batch_table = false;
-  for (size_t i = 0; i < ps.size(); ++i) {
+  const bool form_known = d.paged_form_of.load(std::memory_order_relaxed) == G;
+  for (size_t i = 0; i < n_ps; ++i) {
     const Piece& p = *ps[i];
     for (int dim : {0, 1, 3})
       if (p.lo[dim] != 0 || p.hi[dim] != d.shape[dim]) return fail(VT_ERR_UNSUPPORTED, std::string(name) + ": pieces must split the context dim only");
@@ -1010,31 +1014,34 @@ int plan_operand(const vt_desc& d, const char* name, int64_t G, AttnOperand* out
     }
     if (sd != 1) return fail(VT_ERR_UNSUPPORTED, std::string(name) + ": rows must be contiguous along the head dim");
     // head group: [kv heads (stride sh)] x [G broadcast]
-    std::vector<Digit> hg = p.v.groups[1];
+    Digit hg[kMaxDigits];
+    size_t nh = p.v.groups[1].size();
+    if (nh > (size_t)kMaxDigits) return fail(VT_ERR_UNSUPPORTED, std::string(name) + ": too many digits");
+    std::copy(p.v.groups[1].begin(), p.v.groups[1].end(), hg);
     int32_t a_hdiv = 1;
     int64_t left = G;
     while (left > 1) {
-      if (hg.empty() || hg.back().stride != 0 || hg.back().table >= 0 || (left % hg.back().radix != 0 && hg.back().radix % left != 0))
+      if (nh == 0 || hg[nh - 1].stride != 0 || hg[nh - 1].table >= 0 || (left % hg[nh - 1].radix != 0 && hg[nh - 1].radix % left != 0))
         return fail(VT_ERR_UNSUPPORTED, std::string(name) + ": head broadcast structure not recognised");
-      if (hg.back().radix <= left) {
-        left /= hg.back().radix;
-        hg.pop_back();
+      if (hg[nh - 1].radix <= left) {
+        left /= hg[nh - 1].radix;
+        --nh;
       } else {
-        hg.back().radix /= left;
+        hg[nh - 1].radix /= left;
         left = 1;
       }
     }
     // heads this operand still shares beyond G (the other operand is broadcast less, or not at
     // all: the group size is the factor common to both): consecutive groups read one stored head
     int64_t hdiv = 1;
-    while (!hg.empty() && hg.back().stride == 0 && hg.back().table < 0) {
-      hdiv *= hg.back().radix;
-      hg.pop_back();
+    while (nh > 0 && hg[nh - 1].stride == 0 && hg[nh - 1].table < 0) {
+      hdiv *= hg[nh - 1].radix;
+      --nh;
     }
     if (hdiv >= (1ll << 31)) return fail(VT_ERR_UNSUPPORTED, std::string(name) + ": head broadcast too wide");
     a_hdiv = (int32_t)hdiv;
     int64_t sh;
-    if (!single_plain(hg, &sh)) return fail(VT_ERR_UNSUPPORTED, std::string(name) + ": kv-head dim must be one strided digit");
+    if (!single_plain(hg, nh, &sh)) return fail(VT_ERR_UNSUPPORTED, std::string(name) + ": kv-head dim must be one strided digit");
     const vt_source& src = d.sources[p.src];
     if (!src.ptr) return fail(VT_ERR_INVALID_ARG, std::string(name) + ": source without a device pointer");
     PlanPiece& a = out->pc[i];
@@ -1091,8 +1098,8 @@ int plan_operand(const vt_desc& d, const char* name, int64_t G, AttnOperand* out
       a.pg.ps = T->stride;
       a.pg.W = make_fastdiv((uint32_t)W);
       a.pg.page = make_fastdiv((uint32_t)page_rows);
-      // the closed form above against the descriptor's own evaluator, on sampled rows
-      if (!tb.host.empty()) {
+      // the closed form above against the descriptor's own evaluator, on sampled rows (once for a descriptor)
+      if (!tb.host.empty() && !form_known) {
         const int64_t Hq = d.shape[1];
         uint64_t rng = 0x9E3779B97F4A7C15ull;
         for (int smp = 0; smp < 48; ++smp) {
@@ -1120,6 +1127,7 @@ int plan_operand(const vt_desc& d, const char* name, int64_t G, AttnOperand* out
       return fail(VT_ERR_UNSUPPORTED, std::string(name) + ": rows are not 16-byte aligned");
   }
   if (expect != d.shape[2]) return fail(VT_ERR_UNSUPPORTED, std::string(name) + ": pieces do not cover the context");
+  if (!form_known) d.paged_form_of.store(G, std::memory_order_relaxed);
   return VT_OK;
 }
 

@@ -16,6 +16,10 @@ int fail(int code, const std::string& msg) {
   g_err = msg;
   return code;
 }
+int fail(int code, const char* msg) {      // (without a string built for it: a call tries several kernels)
+  g_err = msg;
+  return code;
+}
 const char* last_error() { return g_err.c_str(); }
 
 struct Err {

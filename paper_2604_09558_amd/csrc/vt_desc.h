@@ -17,6 +17,7 @@
 // A stride of zero is a broadcast digit (Expand).
 #pragma once
 
+#include <atomic>
 #include <cstdint>
 #include <string>
 #include <vector>
@@ -71,12 +72,16 @@ struct vt_desc {
   std::vector<vt_source> sources;
   std::vector<vt::Table> tables;
   int64_t run = 1;
+  // The number of sharing heads for which vt_decode_attn has found that the pieces' page tables have its closed form
+  // (0: none yet).  A descriptor does not change once it is built, and neither does that.
+  mutable std::atomic<int64_t> paged_form_of{0};
 };
 
 namespace vt {
 
 void set_error(const std::string& msg);
 int fail(int code, const std::string& msg);
+int fail(int code, const char* msg);
 
 // Evaluate one piece's map at a local index (x - lo); tables are read from their host copy.
 int64_t eval_view(const vt_desc& d, const View& v, const int64_t* local);

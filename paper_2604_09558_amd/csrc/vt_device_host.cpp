@@ -151,29 +151,34 @@ int check_store_map(const vt_desc& d, const char* who) {
     int src;
     int64_t lo, hi;
   };
-  std::vector<Range> ranges;
+  Range ranges[kMaxPieces];
+  int n_ranges = 0;
+  if (d.pieces.size() > (size_t)kMaxPieces) return fail(VT_ERR_UNSUPPORTED, w + ": too many output pieces");
   for (const Piece& p : d.pieces) {
     if (!p.v.lower.empty()) return fail(VT_ERR_UNSUPPORTED, w + ": output with stacked index stages");
-    std::vector<std::pair<int64_t, int64_t>> dg;    // (|stride|, radix)
+    std::pair<int64_t, int64_t> dg[kMaxDigits];     // (|stride|, radix)
+    int n = 0;
     int64_t lo = p.v.base, hi = p.v.base;
     for (const auto& grp : p.v.groups)
       for (const Digit& g : grp) {
         if (g.radix <= 1) continue;
         if (g.table >= 0) return fail(VT_ERR_UNSUPPORTED, w + ": output through an index table");
         if (g.stride == 0) return fail(VT_ERR_NOT_ONE_TO_ONE, w + ": the output map sends several elements to one place (broadcast)");
-        dg.push_back({g.stride < 0 ? -g.stride : g.stride, g.radix});
+        if (n == kMaxDigits) return fail(VT_ERR_UNSUPPORTED, w + ": output with too many digits");
+        dg[n++] = {g.stride < 0 ? -g.stride : g.stride, g.radix};
         (g.stride < 0 ? lo : hi) += (g.radix - 1) * g.stride;
       }
-    std::sort(dg.begin(), dg.end());
+    std::sort(dg, dg + n);
     int64_t span = 1;
-    for (const auto& sr : dg) {
+    for (int i = 0; i < n; ++i) {
+      const auto& sr = dg[i];
       if (sr.first < span) return fail(VT_ERR_NOT_ONE_TO_ONE, w + ": the output map is not one to one (overlapping strides)");
       span = sr.first * (sr.second - 1) + span;
     }
-    for (const Range& r : ranges)
-      if (r.src == p.src && !(hi < r.lo || r.hi < lo))
+    for (int i = 0; i < n_ranges; ++i)
+      if (ranges[i].src == p.src && !(hi < ranges[i].lo || ranges[i].hi < lo))
         return fail(VT_ERR_NOT_ONE_TO_ONE, w + ": two pieces of the output may overlap in one tensor");
-    ranges.push_back({p.src, lo, hi});
+    ranges[n_ranges++] = {p.src, lo, hi};
   }
   return VT_OK;
 }

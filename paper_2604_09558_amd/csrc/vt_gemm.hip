@@ -653,6 +653,17 @@ extern "C" int vt_gemm(const vt_desc* const* A, const vt_desc* const* B, void* c
     }
     return VT_OK;
   }
+  // one unit of the launch per (group, piece of its A): a Concat along the rows of A is executed as
+  // a grouped launch, every piece writing its own range of rows of C
+  struct Unit {
+    int group;
+    size_t piece;
+    GemmGroup g;
+    int64_t M, Ka, Kb, Nb, row_begin;
+    int rc_a, rc_b;
+  };
+  std::vector<Unit> units;
+  units.reserve(n_groups);
   // Can the tiled kernel take every operand?  If a map lacks the separable form it needs (and only
   // then: wrong arguments are still errors), the whole call runs on the generic kernel, group by group.
   {
@@ -660,10 +671,16 @@ extern "C" int vt_gemm(const vt_desc* const* A, const vt_desc* const* B, void* c
     for (int i = 0; i < n_groups && !generic; ++i) {
       if (!A[i] || !B[i] || !C[i]) return fail(VT_ERR_INVALID_ARG, "vt_gemm: NULL descriptor or output");
       if (A[i]->dtype != dt || B[i]->dtype != dt) return fail(VT_ERR_INVALID_ARG, "vt_gemm: mixed operand dtypes");
-      GemmGroup probe;
-      int64_t m_, k_, n_, rb_;
-      for (size_t pi = 0; pi < A[i]->pieces.size() && !generic; ++pi) generic = plan_a(*A[i], &probe, &m_, &k_, pi, &rb_) == VT_ERR_UNSUPPORTED;
-      generic = generic || plan_b(*B[i], &probe, &k_, &n_) == VT_ERR_UNSUPPORTED;
+      for (size_t pi = 0; pi < A[i]->pieces.size() && !generic; ++pi) {
+        units.emplace_back();
+        Unit& u = units.back();
+        u.group = i;
+        u.piece = pi;
+        u.row_begin = 0;
+        u.rc_a = plan_a(*A[i], &u.g, &u.M, &u.Ka, pi, &u.row_begin);
+        u.rc_b = plan_b(*B[i], &u.g, &u.Kb, &u.Nb);
+        generic = u.rc_a == VT_ERR_UNSUPPORTED || u.rc_b == VT_ERR_UNSUPPORTED;
+      }
     }
     if (generic) {
       for (int i = 0; i < n_groups; ++i) {
@@ -674,31 +691,17 @@ extern "C" int vt_gemm(const vt_desc* const* A, const vt_desc* const* B, void* c
     }
   }
   int64_t N = -1, K = -1;
-  // one unit of the launch per (group, piece of its A): a Concat along the rows of A is executed as
-  // a grouped launch, every piece writing its own range of rows of C
-  struct Unit {
-    int group;
-    size_t piece;
-  };
-  std::vector<Unit> units;
-  for (int i = 0; i < n_groups; ++i) {
-    if (!A[i] || !B[i] || !C[i]) return fail(VT_ERR_INVALID_ARG, "vt_gemm: NULL descriptor or output");
-    for (size_t pi = 0; pi < A[i]->pieces.size(); ++pi) units.push_back({i, pi});
-  }
   for (size_t u0 = 0; u0 < units.size(); u0 += kMaxGroups) {
     GemmParams P;
     memset(&P, 0, sizeof(P));
     const int ng = (int)std::min<size_t>(kMaxGroups, units.size() - u0);
     for (int i = 0; i < ng; ++i) {
-      const vt_desc* a = A[units[u0 + i].group];
-      const vt_desc* b = B[units[u0 + i].group];
-      void* c = C[units[u0 + i].group];
-      if (a->dtype != dt || b->dtype != dt) return fail(VT_ERR_INVALID_ARG, "vt_gemm: mixed operand dtypes");
-      int64_t M, Ka, Kb, Nb, row_begin = 0;
-      int rc = plan_a(*a, &P.g[i], &M, &Ka, units[u0 + i].piece, &row_begin);
-      if (rc != VT_OK) return rc;
-      rc = plan_b(*b, &P.g[i], &Kb, &Nb);
-      if (rc != VT_OK) return rc;
+      Unit& u = units[u0 + i];
+      void* c = C[u.group];
+      if (u.rc_a != VT_OK) return plan_a(*A[u.group], &u.g, &u.M, &u.Ka, u.piece, &u.row_begin);      // (its message again)
+      if (u.rc_b != VT_OK) return plan_b(*B[u.group], &u.g, &u.Kb, &u.Nb);
+      P.g[i] = u.g;
+      const int64_t M = u.M, Ka = u.Ka, Kb = u.Kb, Nb = u.Nb, row_begin = u.row_begin;
       if (Ka != Kb) return fail(VT_ERR_SHAPE, "vt_gemm: inner dims of A and B differ");
       if (N < 0) {
         N = Nb;

@@ -156,30 +156,29 @@ template <int ND>
 int make_axis(const vt_desc& d, const Piece& p, int d0, int d1, AxisMap<ND>* out, const char* what, bool allow_table = false) {
   memset(out, 0, sizeof(*out));
   out->tdig = -1;
-  std::vector<Digit> dg;
+  // neighbours that form one dense digit are merged
+  Digit m[ND + 1];
+  int n = 0;
   for (int i = d0; i < d1; ++i)
-    for (const Digit& g : p.v.groups[i]) dg.push_back(g);
-  // merge neighbours that form one dense digit
-  std::vector<Digit> m;
-  for (const Digit& g : dg) {
-    if (!m.empty() && m.back().table < 0 && g.table < 0 && m.back().stride == g.stride * g.radix) {
-      m.back().radix *= g.radix;
-      m.back().stride = g.stride;
-    } else {
-      m.push_back(g);
+    for (const Digit& g : p.v.groups[i]) {
+      if (n > 0 && m[n - 1].table < 0 && g.table < 0 && m[n - 1].stride == g.stride * g.radix) {
+        m[n - 1].radix *= g.radix;
+        m[n - 1].stride = g.stride;
+      } else if (n <= ND) {
+        m[n++] = g;
+      }
     }
-  }
-  if ((int)m.size() > ND) return fail(VT_ERR_UNSUPPORTED, std::string(what) + ": too many index digits for the GEMM loader");
-  out->nd = (int)m.size();
+  if (n > ND) return fail(VT_ERR_UNSUPPORTED, std::string(what) + ": too many index digits for the GEMM loader");
+  out->nd = n;
   for (int i = 0; i < ND; ++i) {        // padding: digits that are always 0
     out->radix[i] = make_fastdiv(1);
     out->stride[i] = 0;
   }
   // real digits occupy the innermost slots so that slot 0 (which takes what is left of the
   // index without a division) is either the outermost real digit or padding over a zero
-  const int shift = ND - (int)m.size();
-  for (size_t i0 = 0; i0 < m.size(); ++i0) {
-    const int i = (int)i0 + shift;
+  const int shift = ND - n;
+  for (int i0 = 0; i0 < n; ++i0) {
+    const int i = i0 + shift;
     const Digit& mi = m[i0];
     if (mi.radix >= (1ll << 31)) return fail(VT_ERR_UNSUPPORTED, std::string(what) + ": extent too large");
     out->radix[i] = make_fastdiv((uint32_t)mi.radix);
