@@ -5,8 +5,8 @@
 // workgroup's waves have none: 4096 x 512 -> 512 spent 8 of its 12 us on W's way through two waves of each unit.
 //
 // A workgroup of 8 waves takes BM rows and BN columns.  Everything that it will read is asked for at once, straight
-// into LDS (global_load_lds_dwordx4): first the rows (every wave its own BM / 8), then W's panel in stages of 64 k-rows, all of
-// them if they fit beside the rows, else six.  A wave waits for its rows only, normalises them where they lie, and one
+// into LDS (global_load_lds_dwordx4): first the rows (every wave its own BM / 8), then W's panel in stages of 64 k-rows (32 in the
+// largest blocks), all of them if they fit beside the rows, else what does, half of them at least.  A wave waits for its rows only, normalises them where they lie, and one
 // barrier later, when the panel has arrived too, every wave multiplies its 32 x 32 blocks (v_mfma_f32_32x32x16, the order
 // of additions of the ring kernel: the same bits) with no more requests to wait for; stages past those that fit take the places
 // of the first ones.  C is turned round in the rows' place and leaves in whole rows of BN columns.
@@ -28,7 +28,6 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kWaves = 8;
 constexpr int kLds = 160 * 1024;
-constexpr int KS = 64;            // k-rows of W per stage
 
 struct PanelParams : LnParams {
   int32_t n_tiles, total, chunk;  // column tiles; workgroups, and those of one compute die
@@ -41,6 +40,9 @@ __device__ __forceinline__ void wait_ops() {
   asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(N) : "memory");
 }
 
+// k-rows of W per stage: half as many where a stage of 64 would take a third of the room beside the rows
+constexpr int k_rows_of(int bm, int bn) { return bm * bn >= 64 * 256 ? 32 : 64; }
+
 // LP2: lanes that hold a row, two chunks of 8 elements each: K <= 16 * LP2
 template <typename T, bool C_F32, int BM, int BN, int LP2>
 __global__ void __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
@@ -51,7 +53,7 @@ k_ln_gemm_panel(const PanelParams P) {
   constexpr int BLOCKS = BM / 32 * (BN / 32), PW = BLOCKS < kWaves ? BLOCKS : kWaves;   // 32 x 32 blocks, waves that multiply
   constexpr int WM = BM / 32 < PW ? BM / 32 : PW, WN = PW / WM, MB = BM / 32 / WM, NB = BN / 32 / WN;
   static_assert(NP >= 1 && MB * NB * PW == BLOCKS, "rows and blocks divide evenly");
-  constexpr int kStage = KS * BN * 2, WI = BN / 64;  // bytes of a stage, a wave's requests of it (1 KB each)
+  constexpr int KS = k_rows_of(BM, BN), kStage = KS * BN * 2, WI = kStage / 1024 / kWaves;  // of a stage: k-rows, bytes, a wave's requests (1 KB each)
   __shared__ __attribute__((aligned(1024))) uint4 lds[kLds / 16];      // the rows, then the stages
   char* const lds_b = reinterpret_cast<char*>(lds);
   // a compute die (own L2; workgroups are dealt to them in turn) takes neighbours: the column tiles of a block of rows
@@ -161,19 +163,20 @@ k_ln_gemm_panel(const PanelParams P) {
       f.w[nb] = __builtin_bit_cast(opvec, v);
     }
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb) f.a[mb] = __builtin_bit_cast(opvec, *reinterpret_cast<const uint4*>(a_row_of[mb] + (a_chunk ^ ((step * 4 + ks) * 32))));
+    for (int mb = 0; mb < MB; ++mb) f.a[mb] = __builtin_bit_cast(opvec, *reinterpret_cast<const uint4*>(a_row_of[mb] + (a_chunk ^ ((step * (KS / 16) + ks) * 32))));
   };
-  // a stage's fragments, those of its four parts, and their products
+  // a stage's fragments, those of its parts of 16 k, and their products
+  constexpr int PARTS = KS / 16;
   struct Stage {
-    Frags f[4];
+    Frags f[PARTS];
   };
   auto read_stage = [&](Stage& t, int step, int place) {
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) read(t.f[ks], step, place, ks);
+    for (int ks = 0; ks < PARTS; ++ks) read(t.f[ks], step, place, ks);
   };
   auto multiply_stage = [&](const Stage& t) {
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks)
+    for (int ks = 0; ks < PARTS; ++ks)
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
@@ -250,15 +253,16 @@ int launch_panel(PanelParams P, int bm, int bn, hipStream_t st) {
   P.total = (P.M + bm - 1) / bm * P.n_tiles;
   P.chunk = (P.total + 7) / 8;
   P.chunk_magic = (65536 + P.K / 8 - 1) / (P.K / 8);
-  P.stages = std::min((kLds - bm * P.K * 2) / (KS * bn * 2), P.K / KS);
-  if (P.stages * 2 < P.K / KS) return fail(VT_ERR_UNSUPPORTED, "vt_gemm(layernorm): outside the fused kernels");
+  const int ks = k_rows_of(bm, bn);
+  P.stages = std::min((kLds - bm * P.K * 2) / (ks * bn * 2), P.K / ks);
+  if (P.stages * 2 < P.K / ks) return fail(VT_ERR_UNSUPPORTED, "vt_gemm(layernorm): outside the fused kernels");
 #define VT_PANEL(BM_, BN_, LP2_)                                                                                              \
   if (bm == BM_ && bn == BN_ && (P.K <= 256) == (LP2_ == 16)) {                                                               \
     hipLaunchKernelGGL((k_ln_gemm_panel<T, C_F32, BM_, BN_, LP2_>), dim3((unsigned)P.chunk * 8), dim3(kWaves * 64), 0, st, P); \
     return check_launch("vt_gemm(layernorm)");                                                                                \
   }
-  VT_PANEL(32, 64, 16) VT_PANEL(32, 128, 16) VT_PANEL(32, 256, 16) VT_PANEL(64, 128, 16)
-  VT_PANEL(32, 64, 32) VT_PANEL(32, 128, 32) VT_PANEL(32, 256, 32) VT_PANEL(64, 128, 32)
+  VT_PANEL(32, 64, 16) VT_PANEL(32, 128, 16) VT_PANEL(32, 256, 16) VT_PANEL(64, 128, 16) VT_PANEL(64, 256, 16)
+  VT_PANEL(32, 64, 32) VT_PANEL(32, 128, 32) VT_PANEL(32, 256, 32) VT_PANEL(64, 128, 32) VT_PANEL(64, 256, 32)
 #undef VT_PANEL
   return fail(VT_ERR_UNSUPPORTED, "vt_gemm(layernorm): outside the fused kernels");
 }
@@ -270,15 +274,19 @@ int launch_panel(PanelParams P, int bm, int bn, hipStream_t st) {
 // 0.47 to 0.83 of what they took, all 53 others would have taken 1.02 to 2.5 times as much.  us, before / here:
 //   392 x 512 -> 1000  13.1 / 6.2    4096 x 512 -> 512  10.9 / 8.3    8192 x 384 -> 200  11.0 / 7.2    1568 x 256 -> 768  6.7 / 5.3
 //   588 x 320 -> 96     8.7 / 5.1    8000 x 512 -> 200  13.8 / 8.4   14336 x 448 -> 96  12.6 / 9.5     4096 x 192 -> 200  6.2 / 4.4
+// Blocks of 64 x 256 (for what none of the others takes in one round) from 256 features to 384, the last with room for half of the panel
+// beside the rows: 0.82 to 0.99 of the ring kernel's time at 13 shapes.  Not with 192 features, 0.93 to 1.05 at seven shapes, nor with 128:
+//   9408 x 256 -> 256   7.9 / 7.1    2156 x 384 -> 1536 13.0 / 11.1   3072 x 192 -> 768  6.4 / 6.8    5120 x 128 -> 512  5.7 / 6.1
 // (32 x 64 for all of them: 2 to 4 rounds for the wide ones; 64 x 64 and 128 x 128: never more than 3 % faster than the best of these.)
 // (Fewer than 96 columns, and rows that are no multiple of four, stay where they were, though this is the faster one for them too: the tests
 // of those kernels ask for them by name at 400 x 256 -> 72 and 1225 x 512 -> 264.)
 bool choose_panel(int64_t M, int64_t N, int64_t K, int* bm, int* bn) {
   if (N < 96 || M % 4) return false;
-  static const int kChoices[][2] = {{32, 64}, {32, 128}, {32, 256}, {64, 128}};
+  static const int kChoices[][2] = {{32, 64}, {32, 128}, {32, 256}, {64, 128}, {64, 256}};
   int64_t best = 0;
   for (const auto& c : kChoices) {
     if ((M + c[0] - 1) / c[0] * ((N + c[1] - 1) / c[1]) > 256) continue;
+    if (c[0] * c[1] == 64 * 256 && (K < 256 || K > 384)) continue;
     const int64_t ns = 2900 + K * (c[0] * 2130 / 4 + c[1] * 1625 / 16) / 4096;
     if (best == 0 || ns < best) best = ns, *bm = c[0], *bn = c[1];
   }

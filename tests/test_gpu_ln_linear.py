@@ -285,7 +285,7 @@ def test_rows_through_a_table_and_a_weight_with_rows_apart(gpu, kernels, M, C, N
 @pytest.mark.parametrize("M,C,N,dtype,block", [(4, 192, 96, "bf16", (32, 64)), (1300, 512, 328, "f16", (32, 64)), (292, 320, 1000, "bf16", (32, 64)),
                                                (1700, 256, 456, "f16", (32, 128)), (3136, 512, 200, "bf16", (32, 128)), (2500, 448, 520, "bf16", (32, 256)),
                                                (8100, 512, 248, "f16", (32, 256)), (6276, 192, 200, "bf16", (32, 256)), (16340, 384, 104, "bf16", (64, 128)),
-                                               (16004, 512, 120, "f16", (64, 128)), (12300, 128, 136, "bf16", None), (8192, 256, 128, "f16", (32, 128))])
+                                               (16004, 512, 120, "f16", (64, 128)), (12300, 128, 136, "bf16", None), (12300, 256, 136, "bf16", (64, 256)), (12300, 192, 136, "bf16", None), (2148, 384, 1544, "f16", (64, 256)), (8192, 256, 128, "f16", (32, 128))])
 def test_weight_panel_kernel(gpu, kernels, M, C, N, dtype, block):
     """Against the oracle (bound as in test_weight_streamed_kernel); the 16-bit result is the fp32 one rounded once; the same bits through
     a table and a W with rows apart; nothing written behind the last row."""
