@@ -244,20 +244,25 @@ __global__ void __launch_bounds__(kWaves * 64) __attribute__((amdgpu_waves_per_e
     VT_PROF_FLUSH(gemm_store, STORE_WG);
     return;
   }
-  // every slice of four columns in one round trip: sixteen requests at a time, past the last slice out of the buffer
-  // descriptor's range (no access, zero); the slices are added in order, so that the sum is reproducible
+  // every slice of four columns in one round trip: four requests (up to four slices) or sixteen at a time, past the last slice out of the
+  // buffer descriptor's range (no access, zero); the slices are added in order, so that the sum is reproducible
   const __amdgpu_buffer_rsrc_t all = __builtin_amdgcn_make_buffer_rsrc(a_partial + blk * a_ns * (kBM * kBN), 0, a_ns * (kBM * kBN * 4), 0x00020000);
-  for (int idx = threadIdx.x * 4; idx < n_valid; idx += kWaves * 64 * 4) {
-    float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int sp0 = 0; sp0 < a_ns; sp0 += 16) {
-      float4 t[16];
+  auto merge = [&](auto width) {
+    constexpr int W = decltype(width)::value;
+    for (int idx = threadIdx.x * 4; idx < n_valid; idx += kWaves * 64 * 4) {
+      float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+      for (int sp0 = 0; sp0 < a_ns; sp0 += W) {
+        float4 t[W];
 #pragma unroll
-      for (int u = 0; u < 16; ++u) t[u] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(all, ((sp0 + u) * (kBM * kBN) + idx) * 4, 0, 16));   // sc1
+        for (int u = 0; u < W; ++u) t[u] = __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(all, ((sp0 + u) * (kBM * kBN) + idx) * 4, 0, 16));   // sc1
 #pragma unroll
-      for (int u = 0; u < 16; ++u) s.x += t[u].x, s.y += t[u].y, s.z += t[u].z, s.w += t[u].w;
+        for (int u = 0; u < W; ++u) s.x += t[u].x, s.y += t[u].y, s.z += t[u].z, s.w += t[u].w;
+      }
+      store(idx, s);
     }
-    store(idx, s);
-  }
+  };
+  if (a_ns <= 4) merge(std::integral_constant<int, 4>());
+  else merge(std::integral_constant<int, 16>());
 #ifdef VT_PROFILE
   __builtin_amdgcn_s_waitcnt(0);
   VT_PROF(5);
@@ -289,12 +294,13 @@ int compute_units() {
 // second workgroup on a unit would finish last; measured on the 4096 x 6144 projection, 48 column
 // blocks: 4 slices 14.75 us, 5: 14.5, 6: 16.7, 7: 16.6, 8: 15.9), at least 128 rows of B each, and at
 // most 16, which the merge reads in one round trip (8 x 4096 x 768: 16 slices 7.1 us, 24 7.5, 32 7.9).  The slices are whole tiles and need not be equal.
-// (The size of the workspace follows from most_k_splits.)
+// Fewer than 384 rows are one slice, with no tickets and no merge (from memory, us: 12 x 256 x 3072 8.8 -> 6.6, 1 x 256 x 768 6.3 -> 5.7; three
+// slices or one: 1 x 384 x 2048 6.3 / 6.5; four, two, one: 1 x 512 x 2048 6.5, 7.1, 7.6).  (The size of the workspace follows from most_k_splits.)
 int most_k_splits(int64_t blocks, int64_t K) {
   if (blocks > kCounters) return 1;
   return (int)std::min<int64_t>(std::min(std::max<int64_t>(1, compute_units() / blocks), std::max<int64_t>(1, K / 128)), 64);
 }
-int choose_k_splits(int64_t blocks, int64_t K) { return std::min(most_k_splits(blocks, K), 16); }
+int choose_k_splits(int64_t blocks, int64_t K) { return K < 384 ? 1 : std::min(most_k_splits(blocks, K), 16); }
 
 // A workspace that does not hold the whole counter area: the partial sums follow the problem's own counters.
 size_t counters_used(int64_t blocks) { return (size_t)((blocks * 4 + 255) / 256 * 256); }
@@ -424,18 +430,20 @@ int vt_gemm_store(const vt_desc* A, const vt_desc* B, const vt_desc* C, void* wo
   // merged: within 10 % of what 236 shapes take, r.m.s.).  At 120 other shapes of 17 to 128 rows what runs takes 0.8 % longer than the better
   // of the two on average, 19 % at most (us here / there: 4096 x 6144 with 32 rows 22.7 / 25.4, 48 rows 33.7 / 26.8, 90 rows 62.4 / 25.1;
   // 2048 x 768 with 33 rows 12.3 / 9.1; 768 x 1024 with 25 rows 9.5 / 6.8).
-  // One block: launch and merge, the rows of a slice, B, 3 us for workgroups that have to wait for others' places, the rows merged; within 3 %
-  // (four waves) and 5 % (eight) of what 165 shapes take, r.m.s., K 512 to 8192, N 192 to 10240; the tiles' estimate is 10 to 15 % low for so
-  // few rows, and by more beyond that width (6 x 64 x 63488: 6.6 us here, 11.3 there).  What runs is 0.5 % above the better of the two on average, 12 % at most (us here / there: 16 x 2048 x 6144 10.6 / 9.8,
-  // 13 x 1024 x 6144 8.5 / 7.7, 8 x 768 x 384 6.1 / 5.4, 4 x 4096 x 2304 8.1 / 13.0, 8 x 4096 x 6144 13.9 / 14.5).
-  const int64_t wgs = rbs * cbs * ns_eff, rounds = (wgs + compute_units() - 1) / compute_units(), draw_mb = N * K * 2 / 1000;
-  const int64_t waiting_ns = (wgs - 1) / (compute_units() * (waves == 4 ? 2 : 1)) * 3000;
-  const int64_t here_ns = rbs > 1      ? 6400 + ns_eff * 267 + rounds * kps * (kBN * 2) / 33
-                          : waves == 4 ? 4960 + waiting_ns + rounds * kps * 4617 / 1000 + draw_mb * 80 / 1000 + M * 113
-                                       : 6240 + waiting_ns + rounds * kps * 5078 / 1000 + draw_mb * 46 / 1000 + M * 51;
-  const int64_t below_ns = rbs > 1 ? here_ns : here_ns * 100 / 115;
-  const int64_t there_ns = rbs > 1 || N <= 12288 ? gemm_tile_estimate_ns(M, N, K, P.ldb) : 0;
-  if (there_ns && there_ns < below_ns) {
+  // One block: a weight is read once per step and comes from memory then.  Here the requests of a whole slice are under way at once; a
+  // tile waits for each stage of all K, one behind the other: 1.4 us per 1024 of K more than from a cache (8 x 4096 x 6144: 15.0 here,
+  // 22.4 there; from a cache 14.3 and 15.0).  From 9 rows on the tiles (one round of them, short K) are the faster ones either way: us from
+  // memory, here / there: 15 x 64 x 384 5.7 / 4.5, 12 x 512 x 192 8.6 / 6.4, 14 x 768 x 6144 10.2 / 8.5, 12 x 1024 x 8192 10.0 / 9.4, 14 x 1024 x 768
+  // 9.0 / 9.1, 16 x 1536 x 384 9.1 / 10.6, 11 x 1024 x 10240 10.7 / 14.2; 3 x 64 x 1280 4.3 / 5.4, 8 x 192 x 1536 5.4 / 5.6, 6 x 512 x 2560 7.0 / 7.5.
+  bool tiles = M > 8 && K <= 1024 && N <= 32 * compute_units();
+  int64_t below_ns = INT64_MAX;
+  if (rbs > 1) {
+    const int64_t rounds = (rbs * cbs * ns_eff + compute_units() - 1) / compute_units();
+    below_ns = 6400 + ns_eff * 267 + rounds * kps * (kBN * 2) / 33;
+    const int64_t there_ns = gemm_tile_estimate_ns(M, N, K, P.ldb);
+    tiles = there_ns && there_ns < below_ns;
+  }
+  if (tiles) {
     rc = gemm_store_launch(*A, *B, *C, below_ns, (hipStream_t)stream);
     if (rc != VT_ERR_UNSUPPORTED) return rc;
   }

@@ -202,10 +202,11 @@ def test_a_few_row_blocks_of_a_wide_projection(gpu, B, T):
     compare_stored(tio, dw, wl, ref)
 
 
-# one slice stored at once, four waves and eight, K no whole tile; sixteen slices, fewer rows than a block, a ragged last column
-# block; small tiles for a block of 16 rows or fewer
+# one slice stored at once, four waves and eight, K no whole tile; sixteen slices, four, fewer rows than a block, a ragged last column
+# block; small tiles for a block of 9 to 16 rows, and not one column block or K step more than they take
 @pytest.mark.parametrize("B,hidden,Hq,Hkv,D", [(3, 72, 4, 2, 64), (16, 200, 6, 1, 64), (9, 4096, 4, 1, 128), (1, 4104, 3, 1, 64), (16, 2056, 5, 2, 64),
-                                               (5, 768, 2, 2, 64), (16, 1024, 32, 8, 128)])
+                                               (5, 768, 2, 2, 64), (16, 1024, 32, 8, 128), (9, 376, 3, 1, 64), (2, 512, 3, 1, 64),
+                                               (9, 1024, 62, 1, 128), (9, 1024, 63, 1, 128), (10, 1088, 4, 1, 64), (8, 1024, 4, 1, 64)])
 def test_store_routes_of_few_rows(gpu, B, hidden, Hq, Hkv, D):
     vt, tio, pipelines, torch = gpu
     wl = workloads.qkv_proj_store(seed=9, B=B, hidden=hidden, Hq=Hq, Hkv=Hkv, D=D, cap=16, pos=5)
