@@ -292,9 +292,9 @@ int vt_scatter(const vt_desc* src, const vt_desc* dst, void* stream);
  *      one tensor may overlap give VT_ERR_NOT_ONE_TO_ONE; index tables and stacked stages on
  *      the output give VT_ERR_UNSUPPORTED.
  * N and K are multiples of 8.  Up to 16 rows (a decode step: M = batch) run on a kernel built for a
- * handful of rows: they are processed 16 at a time and B is read once per 16 rows.  17 to 128 rows run
- * there or, where that is expected to be faster and A and B obey vt_gemm's layout rules, on the small
- * tiles of vt_gemm with the map applied in their store stage; more rows always run on vt_gemm's tiled
+ * handful of rows: they are processed 16 at a time and B is read once per 16 rows.  9 to 16 rows with a short K,
+ * and 17 to 128 rows, run there or, where that is expected to be faster and A and B obey vt_gemm's layout
+ * rules, on the small tiles of vt_gemm with the map applied in their store stage; more rows always run on vt_gemm's tiled
  * kernels.  The workspace has to be there up to 128 rows, used or not.
  * workspace: device pointer (16-byte aligned), at least vt_gemm_store_workspace(M, N, K) bytes,
  * cleared once with vt_gemm_store_workspace_init (arrival counters in its first 4 KiB, left at zero by
